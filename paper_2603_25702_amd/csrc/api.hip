@@ -94,7 +94,7 @@ struct s2d2_ctx {
 
 namespace {
 
-constexpr int TILE_PARTIAL_CAP = 4096, TILE_COUNTER_CAP = 4096, PAIR_CAP = 512;
+constexpr int TILE_PARTIAL_CAP = 4096, TILE_COUNTER_CAP = 4096, PAIR_CAP = 16384;
 
 struct Carver {
   uint8_t* base;
@@ -174,11 +174,13 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   c->plan.seq_L = cv.take<int32_t>(NB);
   c->h = cv.take<float>(R * d.d_model);
   const size_t P = act_planes(d);
-  c->a = cv.take<uint8_t>(R * d.d_model * es * P);
+  // GEMM inputs: two bf16 planes, or whole blocks of 16 rows of half values (fragment order)
+  auto act_rows = [&](size_t rows) { return std::max(rows * P, (rows + 15) / 16 * 16); };
+  c->a = cv.take<uint8_t>(act_rows(R) * d.d_model * es);
   c->qkv = cv.take<float>(R * (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim);
   c->qbuf = cv.take<uint8_t>(R * (size_t)d.n_q_heads * d.head_dim * es * act_planes(d));
-  c->obuf = cv.take<uint8_t>(R * (size_t)d.n_q_heads * d.head_dim * es * P);
-  c->ffn = cv.take<uint8_t>(R * (size_t)d.d_ffn * es * P);
+  c->obuf = cv.take<uint8_t>(act_rows(R) * (size_t)d.n_q_heads * d.head_dim * es);
+  c->ffn = cv.take<uint8_t>(act_rows(R) * (size_t)d.d_ffn * es);
   c->af = cv.take<uint8_t>(LR * (size_t)d.d_model * es);
   c->kwin = cv.take<uint8_t>(R * (size_t)d.n_kv_heads * d.head_dim * es);
   c->vwin = cv.take<uint8_t>(R * (size_t)d.n_kv_heads * d.head_dim * es);
@@ -208,7 +210,7 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
     c->moe_tile_row0 = cv.take<int32_t>(c->moe_tile_cap);
     c->moe_tile_rows = cv.take<int32_t>(c->moe_tile_cap);
     c->moe_n_tiles = cv.take<int32_t>(8);
-    c->moe_act = cv.take<uint8_t>(RK * (size_t)d.d_expert * es * P);
+    c->moe_act = cv.take<uint8_t>(act_rows(RK) * (size_t)d.d_expert * es);
     c->moe_y = cv.take<float>(RK * (size_t)d.d_model);
   }
   if (d.dtype == S2D2_BF16) {
@@ -322,17 +324,19 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
     x.tile_partial_cap = TILE_PARTIAL_CAP; x.tile_counter_cap = TILE_COUNTER_CAP; x.coop_wgs = c->n_cus;
     x.pair_buf = c->pair_buf; x.pair_status = c->dev_status + 1; x.pair_cap = PAIR_CAP;
   };
-  // GEMM inputs: one plane of half values, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which
-  // (0: one bf16 plane; LO_F16: half).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
+  // GEMM inputs: one plane of half values, in fragment order where the streaming and the mid-size kernel have most of
+  // the work, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which (0: one bf16 plane).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
   // (the generic attention kernel reads and writes single planes: two-plane models then run on their high plane)
   const int mode = operand_mode_of(d);
   const int opm = !fused ? OPM_BF16 : (flash || mode == OPM_F16 ? mode : OPM_BF16);
   const int P = opm == OPM_BF16X2 ? 2 : 1;
-  auto lo_of = [&](int width) { return opm == OPM_F16 ? LO_F16 : (P == 2 ? width : 0); };
+  const bool frag = opm == OPM_F16 && m_hint <= gemm_mid_most_rows(qkv_n / 16, d.d_model / 32);
+  auto lo_row = [&](int width) { return opm == OPM_F16 ? LO_F16 : (P == 2 ? width : 0); };   // rows of the MoE FFN
+  auto lo_of = [&](int width) { return opm == OPM_F16 ? (frag ? LO_F16P : LO_F16) : (P == 2 ? width : 0); };
   const int ld_a = P * d.d_model, lo_a = lo_of(d.d_model);
   const int ld_o = P * HqD, lo_o = lo_of(HqD);
   const int ld_f = P * d.d_ffn, lo_f = lo_of(d.d_ffn);
-  const int ld_e = P * d.d_expert, lo_e = lo_of(d.d_expert);
+  const int ld_e = P * d.d_expert;
   // queries stay bf16 (the attention kernels multiply them with the cache's bf16 keys): hi + lo planes unless the
   // model asked for single bf16 planes
   // model asked for single bf16 planes; the kernel for wide windows takes them as half values in the half mode
@@ -381,14 +385,14 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
       }
     } else {
       ProfScope ps(c, 1, 0.0);
-      launch_attention_generic(st, dt, c->qbuf, kw, vw, kp, vp, g, c->plan, R, d.n_q_heads, c->obuf, lds, opm == OPM_F16);
+      launch_attention_generic(st, dt, c->qbuf, kw, vw, kp, vp, g, c->plan, R, d.n_q_heads, c->obuf, lds, lo_o);
     }
     if (fused) {
       GemmStreamArgs a{};
       a.m_count = n_rows;
       a.Wp = c->pk[l].wo; a.NT = d.d_model / 16; a.KT = HqD / 32; a.N = d.d_model; a.K = HqD;
       a.X = (const bf16_t*)c->obuf; a.ldx = ld_o; a.x_lo = lo_o; a.out = c->h; a.ldo = d.d_model;
-      a.xg_out = (bf16_t*)c->a; a.xg_ld = ld_a; a.xg_lo = lo_a; a.gain_next = L.norm2; a.ss_out = c->ss; a.ss_stride = ss_stride;
+      a.xg_out = (bf16_t*)c->a; a.xg_ld = ld_a; a.xg_lo = d.n_experts ? lo_row(d.d_model) : lo_a; a.gain_next = L.norm2; a.ss_out = c->ss; a.ss_stride = ss_stride;
       { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); sk(a); launch_gemm_stream(st, SEPI_ADD_F32, a, R); }
       const float* gain_after = l + 1 < d.n_layers ? c->layers[l + 1].norm1 : c->w.norm_f;
       if (d.n_experts == 0) {
@@ -411,7 +415,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
         GemmStreamArgs r{};
         r.m_count = n_rows;
         r.Wp = c->pk[l].router; r.NT = (E + 15) / 16; r.KT = d.d_model / 32; r.N = E; r.K = d.d_model;
-        r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_a; r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_stride;
+        r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_row(d.d_model); r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_stride;
         r.eps = d.rms_eps; r.out = c->router_logits; r.ldo = E;
         { ProfScope ps(c, 0, (double)E * d.d_model * es, fr * E * d.d_model); sk(r); launch_gemm_stream(st, SEPI_STORE_F32, r, R); }
         { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w); }
@@ -423,15 +427,15 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
         b.tile_row0 = c->moe_tile_row0; b.tile_rows = c->moe_tile_rows; b.sorted = c->moe_sorted; b.route_w = c->moe_w;
         b.expert_stride = packed_weight_bytes(Fe, d.d_model) / 16;
         b.Wp = c->pk[l].eg; b.Wp2 = c->pk[l].eu; b.NT = Fe / 16; b.KT = d.d_model / 32; b.N = Fe; b.K = d.d_model;
-        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_a; b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_stride;
-        b.eps = d.rms_eps; b.out = c->moe_act; b.ldo = ld_e; b.out_lo = lo_e;
+        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_row(d.d_model); b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_stride;
+        b.eps = d.rms_eps; b.out = c->moe_act; b.ldo = ld_e; b.out_lo = lo_row(d.d_expert);
         { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); launch_gemm_tile(st, SEPI_SWIGLU, SPRO_BF16S, b, tile_cap); }
         GemmStreamArgs e{};
         e.grouped = GROUP_SCATTER; e.top_k = tk; e.n_tiles = c->moe_n_tiles; e.tile_expert = c->moe_tile_expert;
         e.tile_row0 = c->moe_tile_row0; e.tile_rows = c->moe_tile_rows; e.sorted = c->moe_sorted; e.route_w = c->moe_w;
         e.expert_stride = packed_weight_bytes(d.d_model, Fe) / 16;
         e.Wp = c->pk[l].ed; e.NT = d.d_model / 16; e.KT = Fe / 32; e.N = d.d_model; e.K = Fe;
-        e.X = (const bf16_t*)c->moe_act; e.ldx = ld_e; e.x_lo = lo_e; e.out = c->moe_y; e.ldo = d.d_model;
+        e.X = (const bf16_t*)c->moe_act; e.ldx = ld_e; e.x_lo = lo_row(d.d_expert); e.out = c->moe_y; e.ldo = d.d_model;
         { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); launch_gemm_tile(st, SEPI_STORE_F32, SPRO_BF16, e, tile_cap); }
         { ProfScope ps(c, 3, 0.0); launch_moe_combine(st, c->moe_y, d.d_model, tk, n_rows, R, c->h, c->a, ld_a, lo_a, gain_after, c->ss, ss_stride); }
       }

@@ -75,7 +75,8 @@ __device__ __forceinline__ void fa_merge(FaState& a, float m2, float l2, const f
 
 // Four consecutive output elements in the storage the low-plane offset o_lo names (bf16, bf16 hi + lo planes, or half).
 template <bool COH>
-__device__ __forceinline__ void fa_store4(bf16_t* p, int o_lo, float a, float b, float c, float d) {
+__device__ __forceinline__ void fa_store4(bf16_t* o, int o_lo, int row, int col, int o_ld, float a, float b, float c, float d) {
+  bf16_t* p = o + act_offset(o_lo, row, col, o_ld);
   uint2 first, second;
   act_pack4(o_lo, a, b, c, d, first, second);
   if (COH) st8_coh(p, first); else *(uint2*)p = first;
@@ -136,7 +137,7 @@ __device__ __forceinline__ void fa_combine(const float* part_o, const float* par
     if (qi >= nq) continue;
     const float inv = l[it] > 0.f ? 1.0f / l[it] : 0.f;
     const int r = row0 + qi / grp, head = kvh * grp + qi % grp;
-    fa_store4<COH>(o + (size_t)r * o_ld + head * D + d0, o_lo, acc[it].x * inv, acc[it].y * inv, acc[it].z * inv, acc[it].w * inv);
+    fa_store4<COH>(o, o_lo, r, head * D + d0, o_ld, acc[it].x * inv, acc[it].y * inv, acc[it].z * inv, acc[it].w * inv);
   }
 }
 
@@ -369,7 +370,7 @@ __device__ __forceinline__ void attn_flash_body(
         const float L = s_ML[32 + cc], inv = L > 0.f ? 1.0f / L : 0.f;
         const int r2 = row0 + qi2 / grp, head2 = kvh * grp + qi2 % grp;
         const int d0 = (g16 >> 2) * 32 + 8 * (g16 & 3) + 4 * hh;
-        fa_store4<COH>(o + (size_t)r2 * o_ld + head2 * D + d0, o_lo, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+        fa_store4<COH>(o, o_lo, r2, head2 * D + d0, o_ld, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
       }
     } else {
       st16f_coh(part_o + (item0 + z) * 32 * D + (size_t)idx * 4, acc.x, acc.y, acc.z, acc.w);

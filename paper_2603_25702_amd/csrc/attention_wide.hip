@@ -410,12 +410,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   if (Z == 1) {
     if (active && q0 + c < nq) {
       const float inv = st.l > 0.f ? 1.0f / st.l : 0.f;
-      bf16_t* op = o + (size_t)r * o_ld + head * D + 4 * h;
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4)
-          fa_store4<false>(op + dt * 32 + 8 * i4, o_lo, st.o[dt][4 * i4] * inv, st.o[dt][4 * i4 + 1] * inv,
+          fa_store4<false>(o, o_lo, r, head * D + 4 * h + dt * 32 + 8 * i4, o_ld, st.o[dt][4 * i4] * inv, st.o[dt][4 * i4 + 1] * inv,
                            st.o[dt][4 * i4 + 2] * inv, st.o[dt][4 * i4 + 3] * inv);
     }
     return;

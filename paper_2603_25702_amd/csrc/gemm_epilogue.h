@@ -1,0 +1,97 @@
+// Epilogue of the packed-weight GEMMs on one 16 x 16 accumulator in MFMA register order, shared by the tiled and the
+// mid-size kernel.
+#pragma once
+#include "s2d2_internal.h"
+
+namespace s2d2 {
+
+// v0 (and v1, the up projection, for SwiGLU): v[i] = sum of output row orow (this lane's row; live: it exists), feature
+// nt * 16 + 4 g + i, g = lane / 16; rs scales it.  The whole wavefront calls it with one nt (the norm's partial sums and
+// the rotation pairs travel between lanes); nt >= NT does nothing.  h0: the residual's four values at that place,
+// requested by the caller ahead of time (SEPI_ADD_F32).
+template <int EPI>
+__device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const bool live, const int orow, const float rs,
+                                              const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4& h0) {
+  if (nt >= a.NT) return;   // uniform over the wavefront
+  const int n = nt * 16 + 4 * g;
+  if (EPI == SEPI_STORE_F32) {
+    if (live) {
+      float* op = (float*)a.out + (size_t)orow * a.ldo + n;
+      const f32x4_t v = v0 * rs;
+      if (n + 3 < a.N) *(float4*)op = make_float4(v[0], v[1], v[2], v[3]);
+      else
+        for (int i = 0; i < 4; ++i)
+          if (n + i < a.N) op[i] = v[i];
+    }
+  } else if (EPI == SEPI_ADD_F32) {   // N is a multiple of 16 here: four features per lane as one 16-byte access
+    float hv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (live) {
+      hv[0] = h0.x + v0[0] * rs;
+      hv[1] = h0.y + v0[1] * rs;
+      hv[2] = h0.z + v0[2] * rs;
+      hv[3] = h0.w + v0[3] * rs;
+      *(float4*)((float*)a.out + (size_t)orow * a.ldo + n) = make_float4(hv[0], hv[1], hv[2], hv[3]);
+      if (a.xg_out) {
+        const float4 gn = *(const float4*)(a.gain_next + n);
+        act_put4(a.xg_out, a.xg_lo, orow, n, a.xg_ld, hv[0] * gn.x, hv[1] * gn.y, hv[2] * gn.z, hv[3] * gn.w);
+      }
+    }
+    if (a.ss_out) {
+      float sq = (hv[0] * hv[0] + hv[1] * hv[1]) + (hv[2] * hv[2] + hv[3] * hv[3]);
+      sq += __shfl_xor(sq, 16, 64);
+      sq += __shfl_xor(sq, 32, 64);
+      if (live && g == 0) a.ss_out[(size_t)orow * a.ss_stride + nt] = sq;
+    }
+  } else if (EPI == SEPI_SWIGLU) {
+    if (live) {
+      float sv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float gate = v0[i] * rs, up = v1[i] * rs;
+        sv[i] = gate / (1.0f + __expf(-gate)) * up;
+      }
+      act_put4((bf16_t*)a.out, a.out_lo, orow, n, a.ldo, sv[0], sv[1], sv[2], sv[3]);
+    }
+  } else {  // SEPI_QKV_ROPE: features 0-7 of a tile pair with features 8-15 (lanes 32 apart)
+    const int D = a.D, half = D >> 1, tiles_per_head = D / 16;
+    const int head = nt / tiles_per_head, i0 = 8 * (nt % tiles_per_head) + 4 * (g & 1);
+    float own[4], oth[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      own[i] = v0[i] * rs;
+      oth[i] = __shfl_xor(own[i], 32, 64);
+    }
+    if (live) {
+      const bool second = g >= 2;   // this lane holds x2 (element i + D/2) of the pair
+      if (head < a.Hq + a.Hkv) {
+        const bool is_q = head < a.Hq;
+        bf16_t* dst = is_q ? a.q_out + (size_t)orow * a.q_ld + head * D
+                           : a.k_out + ((size_t)orow * a.Hkv + (head - a.Hq)) * D;
+        const float4 c01 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0), c23 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0 + 2);
+        const float cs_c[4] = {c01.x, c01.z, c23.x, c23.z}, cs_s[4] = {c01.y, c01.w, c23.y, c23.w};
+        float y[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = second ? own[i] * cs_c[i] + oth[i] * cs_s[i] : own[i] * cs_c[i] - oth[i] * cs_s[i];
+        // queries in the storage the attention kernel reads (q_lo); keys always as one bf16 plane (the cache's type)
+        act_store4(dst + i0 + (second ? half : 0), is_q ? a.q_lo : 0, y[0], y[1], y[2], y[3]);
+        if (!is_q && a.k16_out)   // the window's keys once more as half values (the attention kernel's copy)
+          act_store4(a.k16_out + ((size_t)orow * a.Hkv + (head - a.Hq)) * D + i0 + (second ? half : 0), LO_F16, y[0], y[1], y[2], y[3]);
+      } else {
+        const int vh = head - a.Hq - a.Hkv;
+        bf16_t* dst = a.v_out + ((size_t)orow * a.Hkv + vh) * D + (second ? half : 0);
+        const int sq = a.row_seq[orow], tw = orow - a.seq_row0[sq];
+        bf16_t b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = f32_to_bf16(own[i]);
+        *(uint2*)(dst + i0) = make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
+        if (a.vT_out) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            a.vT_out[((size_t)(sq * a.Hkv + vh) * D + i0 + i + (second ? half : 0)) * a.wpad + tw] = a.win_f16 ? f32_to_f16_bits(own[i]) : b[i];
+        }
+      }
+    }
+  }
+}
+
+}  // namespace s2d2

@@ -176,12 +176,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(const GemmStreamAr
   const int32_t* gather = CAN_GATHER ? a.gather : nullptr;
   const int xrow_i = m0 + (row_ok ? f : 0);
   const int xrow = gather ? gather[xrow_i] : xrow_i;
-  const bf16_t* xg = a.X + (size_t)xrow * a.ldx + g * 8;
+  // half mode: fragment order, 512 elements per K tile (the MoE router reads rows: its input is gathered row by row too)
+  const bool frag = OPM == OPM_F16 && (EPI != SEPI_STORE_F32 || a.x_lo == LO_F16P);
+  const int XK = frag ? 512 : 32;
+  const bf16_t* xg = a.X + (frag ? frag_offset(xrow, g * 8, a.K) : (size_t)xrow * a.ldx + g * 8);
   u32x4_t xb[U], xl[SPLIT ? U : 1];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int kc = max(0, min(kt_begin + u, kt_end - 1));   // (an empty share reads tile 0 and multiplies nothing)
-    xb[u] = *(const u32x4_t*)(xg + kc * 32);
+    xb[u] = *(const u32x4_t*)(xg + kc * XK);
     if (SPLIT) xl[u] = *(const u32x4_t*)(xg + a.x_lo + kc * 32);
   }
 
@@ -237,7 +240,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(const GemmStreamAr
         const int kc = max(0, min(kt0 + U + u, kt_end - 1));
 #pragma unroll
         for (int t = 0; t < TA; ++t) w[t][u] = ld_stream(&wp[t][(size_t)kc * 64]);
-        xb[u] = *(const u32x4_t*)(xg + kc * 32);
+        xb[u] = *(const u32x4_t*)(xg + kc * XK);
         if (SPLIT) xl[u] = *(const u32x4_t*)(xg + a.x_lo + kc * 32);
       }
     } else {
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(const GemmStreamAr
           float* hp = (float*)a.out + (size_t)m * a.ldo + n;
           hv = *hp + total;
           *hp = hv;
-          if (a.xg_out) act_store1(a.xg_out + (size_t)m * a.xg_ld + n, a.xg_lo, hv * a.gain_next[n]);
+          if (a.xg_out) act_put1(a.xg_out, a.xg_lo, m, n, a.xg_ld, hv * a.gain_next[n]);
         }
         if (a.ss_out) {
           float sq = hv * hv;
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(const GemmStreamAr
       } else if (EPI == SEPI_SWIGLU) {
         const int n = nt * 16 + fe;
         const float gate = S2D2_TOTAL(2 * t, fe), up = S2D2_TOTAL(2 * t + 1, fe);
-        if (live && n < a.N) act_store1((bf16_t*)a.out + (size_t)m * a.ldo + n, a.out_lo, gate / (1.0f + __expf(-gate)) * up);
+        if (live && n < a.N) act_put1((bf16_t*)a.out, a.out_lo, m, n, a.ldo, gate / (1.0f + __expf(-gate)) * up);
       } else if (live && fe < 8) {  // SEPI_QKV_ROPE: lanes fe < 8 own the pair (i, i + D/2) of one head
         const int D = a.D, half = D >> 1, tiles_per_head = D / 16;
         const int head = nt / tiles_per_head, i = 8 * (nt % tiles_per_head) + fe;
@@ -401,6 +404,10 @@ void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m
   // wide windows: the LDS-tiled kernel reads the weights once per 128 rows instead of once per 16.  Not for a matrix
   // of a few feature tiles (the MoE router, 64 experts): its weights stay in L2, a 256-column tile would be mostly
   // empty, and a row tile of 16 per workgroup spreads the rows over the whole chip.
+  if (gemm_mid_takes(kind, a)) {
+    launch_gemm_mid(st, kind, a, m_cap);
+    return;
+  }
   if (m_cap > 32 && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) {
     launch_gemm_tile(st, kind, kind == SEPI_ADD_F32 ? SPRO_BF16 : SPRO_BF16S, a, (m_cap + 127) / 128);
     return;
@@ -464,7 +471,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const bf16_t* __restric
   for (int i = threadIdx.x; i < d; i += 256) {
     const float v = bf16_to_f32(src[i]);
     h[(size_t)r * d + i] = v;
-    act_store1(xg + (size_t)r * xg_ld + i, xg_lo, v * gain[i]);
+    act_put1(xg, xg_lo, r, i, xg_ld, v * gain[i]);
     acc += v * v;
   }
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);

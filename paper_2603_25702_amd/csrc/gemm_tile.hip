@@ -14,8 +14,7 @@
 // 64 bytes per clock.)  The activation tile is loaded once per compute unit and goes through LDS (three buffers,
 // rows padded to 144 bytes per plane so that the 16-byte operand reads of a wavefront hit 64 distinct banks);
 // all eight wavefronts read all of it, four operand reads ahead of the MFMA pair that uses them.  All memory
-// requests of a step are issued one at a time between its MFMA pairs.  (A four-wavefront variant on 128 x 128
-// tiles, two workgroups per compute unit, is kept as a tuning aid.)
+// requests of a step are issued one at a time between its MFMA pairs.
 //
 // K can be split over blockIdx.z when the tiles alone would leave compute units idle (few rows, narrow
 // outputs): every split writes its accumulators as an fp32 partial in register order (write-through
@@ -40,7 +39,7 @@
 // sums of the next norm, SwiGLU, RoPE + q/k/v split.  In grouped mode a row tile belongs to one
 // expert: rows are gathered through the expert-sorted slot list and the down projection scatters
 // its result, scaled by the routing weight, to the (token, slot) row it came from.
-#include "s2d2_internal.h"
+#include "gemm_epilogue.h"
 #include "../../include/s2d2.h"
 
 #include <algorithm>
@@ -49,7 +48,7 @@
 
 namespace s2d2 {
 
-static constexpr int TM = 128, TK = 64;
+static constexpr int TM = 128, TK = 64, WC = 4;   // 2 WC wavefronts per workgroup
 // Tuning constants of the K loop (measured on the batched configurations: 3 to 6 weight stages and 2 to 8 operand
 // reads in flight gave the same times within the run-to-run spread)
 #ifndef S2D2_TILE_WS
@@ -85,7 +84,7 @@ __device__ unsigned long long g_tile_ts[1024];   // [128 + 3 id + k]: start, loo
 // SPLIT: the activations come as a high- and a low-order bf16 plane (16 significant bits); both planes
 // of a row sit side by side in LDS and every weight operand is multiplied with both.
 // One row tile (index ty) of the workgroup's column tile and K split; false: there is no such row tile.
-template <int EPI, int PRO, int OPM, int WC>
+template <int EPI, int PRO, int OPM, bool FRAG>
 // z of KS: this workgroup's share of K; ncol: column tiles of the launch (numbering of the tiles' counters and
 // partials); wait_ok: every workgroup of the launch is resident at once, so the splits of a tile may wait for each other;
 // same_rows: the row maps in LDS are already those of row tile ty (the workgroup's previous item had the same rows).
@@ -203,7 +202,9 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
 
   S2D2_TTS(1);
   // ---- operand addressing ----
-  const int c16 = tid & 7, rbase = tid >> 3;   // this thread stages rows rbase + (NTH / 8) i, bytes [16 c16, +16) of the 128
+  // This thread stages rows rbase + (NTH / 8) i, bytes [16 c16, +16) of the 128.  Row-major activations: 8 threads
+  // take the 128 bytes of a row; fragment order: 16 threads take the 256 bytes that 16 rows share.
+  const int c16 = FRAG ? (tid >> 4) & 7 : tid & 7, rbase = FRAG ? ((tid >> 7) << 4) | (tid & 15) : tid >> 3;
   // Loads in the K loop are unconditional (clamped addresses, values of invalid rows / columns replaced when
   // they are stored to LDS): a load under a branch would make the compiler wait for every outstanding load
   // before the MFMA block and so undo the weight pipeline.
@@ -213,7 +214,7 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
   for (int i = 0; i < XI; ++i) {
     const int xr_ = s_xrow[rbase + (NTH / 8) * i];
     xok[i] = xr_ >= 0;
-    xsrc[i] = a.X + (size_t)(xok[i] ? xr_ : 0) * a.ldx + c16 * 8;
+    xsrc[i] = a.X + (FRAG ? frag_offset(xok[i] ? xr_ : 0, c16 * 8, a.K) : (size_t)(xok[i] ? xr_ : 0) * a.ldx + c16 * 8);
   }
   const u32x4_t zero = {0u, 0u, 0u, 0u};
 
@@ -229,7 +230,9 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
   // step the loads re-read an earlier tile into a register set nobody stores any more.
   // (plain: K is a multiple of the step, so the step's offset is the same for every lane)
   auto load_x1 = [&](u32x4_t (&r)[XI], u32x4_t (&l)[SPLIT ? XI : 1], int kb, int j, bool plain = false) __attribute__((always_inline)) {
-    const int ko = plain ? min(kb, nk - 1) * TK
+    // (a step is 64 columns: two tiles of 512 elements in fragment order)
+    const int ko = FRAG  ? (plain ? min(kb, nk - 1) * 1024 : min(min(kb, nk - 1) * 2 + (c16 >> 2), KT - 1) * 512 - (c16 >> 2) * 512)
+                   : plain ? min(kb, nk - 1) * TK
                          : min(min(kb, nk - 1) * TK + c16 * 8, a.K - 8) - c16 * 8;   // in bounds; columns at or past K are zeroed in store_x
     if (j < XI) r[j] = *(const u32x4_t*)(xsrc[j] + ko);
     else l[j - XI] = *(const u32x4_t*)(xsrc[j - XI] + a.x_lo + ko);
@@ -371,88 +374,9 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
     const int orow = live ? s_orow[r] : 0;
     const float rs = s_rs[r];
     const int nt = nt0 + t;
-    if (nt >= a.NT) return;   // uniform over the wavefront
-    const int n = nt * 16 + 4 * g;
-    if (EPI == SEPI_STORE_F32) {
-      if (live) {
-        float* op = (float*)a.out + (size_t)orow * a.ldo + n;
-        const f32x4_t v = v0 * rs;
-        if (n + 3 < a.N) *(float4*)op = make_float4(v[0], v[1], v[2], v[3]);
-        else
-          for (int i = 0; i < 4; ++i)
-            if (n + i < a.N) op[i] = v[i];
-      }
-    } else if (EPI == SEPI_ADD_F32) {   // N is a multiple of 16 here: four features per lane as one 16-byte access
-      float hv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (live) {
-        float4* hp = (float4*)((float*)a.out + (size_t)orow * a.ldo + n);
-        const float4 h0 = *hp;
-        hv[0] = h0.x + v0[0] * rs;
-        hv[1] = h0.y + v0[1] * rs;
-        hv[2] = h0.z + v0[2] * rs;
-        hv[3] = h0.w + v0[3] * rs;
-        *hp = make_float4(hv[0], hv[1], hv[2], hv[3]);
-        if (a.xg_out) {
-          const float4 gn = *(const float4*)(a.gain_next + n);
-          act_store4(a.xg_out + (size_t)orow * a.xg_ld + n, a.xg_lo, hv[0] * gn.x, hv[1] * gn.y, hv[2] * gn.z, hv[3] * gn.w);
-        }
-      }
-      if (a.ss_out) {
-        float sq = (hv[0] * hv[0] + hv[1] * hv[1]) + (hv[2] * hv[2] + hv[3] * hv[3]);
-        sq += __shfl_xor(sq, 16, 64);
-        sq += __shfl_xor(sq, 32, 64);
-        if (live && g == 0) a.ss_out[(size_t)orow * a.ss_stride + nt] = sq;
-      }
-    } else if (EPI == SEPI_SWIGLU) {
-      if (live) {
-        float sv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float gate = v0[i] * rs, up = v1[i] * rs;
-          sv[i] = gate / (1.0f + __expf(-gate)) * up;
-        }
-        act_store4((bf16_t*)a.out + (size_t)orow * a.ldo + n, a.out_lo, sv[0], sv[1], sv[2], sv[3]);
-      }
-    } else {  // SEPI_QKV_ROPE: features 0-7 of a tile pair with features 8-15 (lanes 32 apart)
-      const int D = a.D, half = D >> 1, tiles_per_head = D / 16;
-      const int head = nt / tiles_per_head, i0 = 8 * (nt % tiles_per_head) + 4 * (g & 1);
-      float own[4], oth[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        own[i] = v0[i] * rs;
-        oth[i] = __shfl_xor(own[i], 32, 64);
-      }
-      if (live) {
-        const bool second = g >= 2;   // this lane holds x2 (element i + D/2) of the pair
-        if (head < a.Hq + a.Hkv) {
-          const bool is_q = head < a.Hq;
-          bf16_t* dst = is_q ? a.q_out + (size_t)orow * a.q_ld + head * D
-                             : a.k_out + ((size_t)orow * a.Hkv + (head - a.Hq)) * D;
-          const float4 c01 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0), c23 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0 + 2);
-          const float cs_c[4] = {c01.x, c01.z, c23.x, c23.z}, cs_s[4] = {c01.y, c01.w, c23.y, c23.w};
-          float y[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) y[i] = second ? own[i] * cs_c[i] + oth[i] * cs_s[i] : own[i] * cs_c[i] - oth[i] * cs_s[i];
-          // queries in the storage the attention kernel reads (q_lo); keys always as one bf16 plane (the cache's type)
-          act_store4(dst + i0 + (second ? half : 0), is_q ? a.q_lo : 0, y[0], y[1], y[2], y[3]);
-          if (!is_q && a.k16_out)   // the window's keys once more as half values (the attention kernel's copy)
-            act_store4(a.k16_out + ((size_t)orow * a.Hkv + (head - a.Hq)) * D + i0 + (second ? half : 0), LO_F16, y[0], y[1], y[2], y[3]);
-        } else {
-          const int vh = head - a.Hq - a.Hkv;
-          bf16_t* dst = a.v_out + ((size_t)orow * a.Hkv + vh) * D + (second ? half : 0);
-          const int sq = a.row_seq[orow], tw = orow - a.seq_row0[sq];
-          bf16_t b[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) b[i] = f32_to_bf16(own[i]);
-          *(uint2*)(dst + i0) = make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
-          if (a.vT_out) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              a.vT_out[((size_t)(sq * a.Hkv + vh) * D + i0 + i + (second ? half : 0)) * a.wpad + tw] = a.win_f16 ? f32_to_f16_bits(own[i]) : b[i];
-          }
-        }
-      }
-    }
+    float4 h0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (EPI == SEPI_ADD_F32 && live && nt < a.NT) h0 = *(const float4*)((const float*)a.out + (size_t)orow * a.ldo + nt * 16 + 4 * g);
+    gemm_epi_unit<EPI>(a, live, orow, rs, nt, g, v0, v1, h0);
   };
 
   if (KS == 1) {
@@ -620,7 +544,7 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
 // memory once per row tile (measured: 2.2x the weight bytes for the verifier's gate / up projection of the 8 B
 // model, 7.8x for the unembedding of 8 row tiles).  Here XCD i % 8 owns the column tiles c with c % 8 == i % 8 and
 // takes them one after the other, all row tiles of a column next to each other in launch order.
-template <int EPI, int PRO, int OPM, int WC>
+template <int EPI, int PRO, int OPM, bool FRAG>
 __global__ __launch_bounds__(128 * WC, 2) void gemm_tile_kernel(const GemmStreamArgs a) {
   constexpr int COLS = (EPI == SEPI_SWIGLU ? 2 : 4) * WC;   // 16-feature tiles per workgroup
   // Three forms of the launch.  (1) plain: blockIdx = (column tile, first row tile, K split).  (2) xcd_order, see
@@ -676,7 +600,7 @@ __global__ __launch_bounds__(128 * WC, 2) void gemm_tile_kernel(const GemmStream
         tx = t % sk_cols; ty = sk_rows + t / sk_cols;
       }
     }
-    const bool did = gemm_tile_body<EPI, PRO, OPM, WC>(a, tx, ty, z, ks, ncol, wait_ok, sk_rows > 0 && it == 1 && did_prev);
+    const bool did = gemm_tile_body<EPI, PRO, OPM, FRAG>(a, tx, ty, z, ks, ncol, wait_ok, sk_rows > 0 && it == 1 && did_prev);
     did_prev = did;
     if (did) __syncthreads();   // the next tile reuses the LDS arrays
     else if (open_end) break;
@@ -690,10 +614,10 @@ void launch_tile_ts_copy(hipStream_t st, void* out) { S2D2_LAUNCH(tile_ts_copy_k
 void launch_tile_ts_copy(hipStream_t, void*) {}
 #endif
 
-template <int EPI, int PRO, int WC>
+template <int EPI, int PRO>
 static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) {
   constexpr int COLS = (EPI == SEPI_SWIGLU ? 2 : 4) * WC;   // 16-feature tiles per workgroup
-  constexpr int RESIDENT = WC == 2 ? 512 : 256;             // workgroups of one round over the chip
+  constexpr int RESIDENT = 256;                              // workgroups of one round over the chip
   constexpr double PART_BYTES = 32768.0 * WC;                // fp32 partial of one tile and split
   const int col_tiles = (a.NT + COLS - 1) / COLS;
   // K is split over blockIdx.z when that shortens the launch.  The choice minimises a small cost model fitted to
@@ -732,7 +656,7 @@ static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) 
   // K splits dealt to XCDs (see the kernel): splits that divide the 8 XCDs, whole columns of tiles per XCD
   b.split_xcd = a.grouped == GROUP_NONE && KS > 1 && 8 % KS == 0 && col_tiles % (8 / KS) == 0 &&
                 ((long long)col_tiles * hint_tiles * KS) % 8 == 0;
-  if (b.xcd_order && WC == 4 && a.tile_partials && a.coop_wgs > 0 && 2 * live == 3LL * a.coop_wgs && (a.coop_wgs & 15) == 0 && (col_tiles & 7) == 0 && (a.coop_wgs / 16) % hint_tiles == 0 &&
+  if (b.xcd_order && a.tile_partials && a.coop_wgs > 0 && 2 * live == 3LL * a.coop_wgs && (a.coop_wgs & 15) == 0 && (col_tiles & 7) == 0 && (a.coop_wgs / 16) % hint_tiles == 0 &&
       live <= a.tile_counter_cap && live * 2 * (WC / 2) <= a.tile_partial_cap && nk >= 8) {
     b.stream_k = hint_tiles;   // see the kernel: 3/2 tiles per workgroup, one workgroup per compute unit
     b.xcd_order = 0;
@@ -743,28 +667,23 @@ static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) 
   // three activation tiles in LDS (54 KB; 102 KB with two planes, above the 64 KB a kernel gets without asking)
   // (one plane: plus 8 KB per wavefront in which a K split parks its own share of the accumulators)
   const unsigned lds = 3u * TM * ((opm == OPM_BF16X2 ? 256 : 128) + 16) + (opm == OPM_BF16X2 ? 0u : 2u * WC * 8192u);
-  static bool lds_set[3][64];
-  const int oi = opm == OPM_F16 ? 0 : opm == OPM_BF16X2 ? 1 : 2;
+  static bool lds_set[4][64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-  if (dev >= 0 && dev < 64 && !lds_set[oi][dev]) {
-    const void* fn = opm == OPM_F16      ? (const void*)gemm_tile_kernel<EPI, PRO, OPM_F16, WC>
-                     : opm == OPM_BF16X2 ? (const void*)gemm_tile_kernel<EPI, PRO, OPM_BF16X2, WC>
-                                         : (const void*)gemm_tile_kernel<EPI, PRO, OPM_BF16, WC>;
+  auto go = [&](auto opm_tag, auto frag_tag) {
+    constexpr int M_ = decltype(opm_tag)::value;
+    constexpr bool FRAG = decltype(frag_tag)::value;
+    bool* set = lds_set[FRAG ? 3 : M_];
     // on failure the launch below fails too, and the entry point reports that error
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) lds_set[oi][dev] = true;
-  }
-  if (opm == OPM_F16) S2D2_LAUNCH((gemm_tile_kernel<EPI, PRO, OPM_F16, WC>), grid, block, lds, st, b);
-  else if (opm == OPM_BF16X2) S2D2_LAUNCH((gemm_tile_kernel<EPI, PRO, OPM_BF16X2, WC>), grid, block, lds, st, b);
-  else S2D2_LAUNCH((gemm_tile_kernel<EPI, PRO, OPM_BF16, WC>), grid, block, lds, st, b);
-}
-
-template <int EPI, int PRO>
-static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) {
-  const char* e = getenv("S2D2_TILE_WC");   // tuning aid, read per launch so that a test can cover both shapes
-  const int wc = e ? atoi(e) : 4;
-  if (wc == 4) launch_tile<EPI, PRO, 4>(st, a, row_tiles);
-  else launch_tile<EPI, PRO, 2>(st, a, row_tiles);
+    if (dev >= 0 && dev < 64 && !set[dev] &&
+        hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI, PRO, M_, FRAG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)
+      set[dev] = true;
+    S2D2_LAUNCH((gemm_tile_kernel<EPI, PRO, M_, FRAG>), grid, block, lds, st, b);
+  };
+  if (a.x_lo == LO_F16P) go(std::integral_constant<int, OPM_F16>{}, std::true_type{});
+  else if (opm == OPM_F16) go(std::integral_constant<int, OPM_F16>{}, std::false_type{});
+  else if (opm == OPM_BF16X2) go(std::integral_constant<int, OPM_BF16X2>{}, std::false_type{});
+  else go(std::integral_constant<int, OPM_BF16>{}, std::false_type{});
 }
 
 // row_tiles: upper bound of 128-row tiles (ungrouped: ceil(m_cap / 128); grouped: capacity of the tile list)

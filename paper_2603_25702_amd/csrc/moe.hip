@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const float* __restric
     *(float4*)(h + (size_t)row * d + c) = acc;
     const float4 gn = *(const float4*)(gain_next + c);
     const float xv[4] = {acc.x * gn.x, acc.y * gn.y, acc.z * gn.z, acc.w * gn.w};
-    act_store4(xg + (size_t)row * xg_ld + c, xg_lo, xv[0], xv[1], xv[2], xv[3]);
+    act_put4(xg, xg_lo, row, c, xg_ld, xv[0], xv[1], xv[2], xv[3]);
     float sq = (acc.x * acc.x + acc.y * acc.y) + (acc.z * acc.z + acc.w * acc.w);
     sq += __shfl_xor(sq, 1, 64);
     sq += __shfl_xor(sq, 2, 64);

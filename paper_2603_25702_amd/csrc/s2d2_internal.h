@@ -56,23 +56,31 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
 //   LO_F16   one plane of IEEE half values (11 significant bits); the GEMMs then run the f16 MFMA against weights
 //            whose packed copy was converted from bf16 to half (exact for |w| >= 2^-17; below that the absolute
 //            error is at most 2^-25), at the same matrix rate as bf16 and half the instructions of two planes.
-constexpr int LO_F16 = -1;
+//   LO_F16P  the same values in fragment order, for the streaming and the mid-size kernel: the rows are cut
+//            into tiles of 16 rows x 32 columns, a tile is stored as 64 lanes x 16 bytes in the register order of the
+//            MFMA's B operand (lane l: row l % 16, columns 8 (l / 16) .. +7), tiles of a row block one behind the
+//            other.  A wavefront's operand load is then 1 KB of contiguous memory.  (Row-major, the same load touches
+//            16 rows 64 bytes each, and consecutive lanes lie in different rows.)  Buffers are padded to 16 rows.
+//            A forward of more rows, where the tiled kernel has most matrices, and the MoE FFN, which gathers single
+//            rows, keep rows: there the order costs more than it gives (tiled gate / up 34.7 -> 37.1 us per launch at
+//            256 rows of the 1.7B shape, MoE combine 16.2 -> 19.2 us at 1024 rows).
+constexpr int LO_F16 = -1, LO_F16P = -2;
 enum OperandMode { OPM_BF16 = 0, OPM_BF16X2 = 1, OPM_F16 = 2 };
-__host__ __device__ inline int operand_mode(int lo) { return lo == LO_F16 ? OPM_F16 : (lo > 0 ? OPM_BF16X2 : OPM_BF16); }
+__host__ __device__ inline int operand_mode(int lo) { return lo < 0 ? OPM_F16 : (lo > 0 ? OPM_BF16X2 : OPM_BF16); }
 __device__ __forceinline__ bf16_t f32_to_f16_bits(float f) {   // round to nearest even, as 16 raw bits
   const _Float16 h = (_Float16)f;
   return __builtin_bit_cast(bf16_t, h);
 }
 // Stores one value / four consecutive values of such a row at p (the lo plane, if there is one, at p + lo).
 __device__ __forceinline__ void act_store1(bf16_t* p, int lo, float v) {
-  if (lo == LO_F16) { *p = f32_to_f16_bits(v); return; }
+  if (lo < 0) { *p = f32_to_f16_bits(v); return; }
   bf16_t hi, l;
   split_bf16(v, hi, l);
   *p = hi;
   if (lo > 0) p[lo] = l;
 }
 __device__ __forceinline__ void act_pack4(int lo, float a, float b, float c, float d, uint2& first, uint2& second) {
-  if (lo == LO_F16) {
+  if (lo < 0) {
     first = make_uint2((uint32_t)f32_to_f16_bits(a) | ((uint32_t)f32_to_f16_bits(b) << 16),
                        (uint32_t)f32_to_f16_bits(c) | ((uint32_t)f32_to_f16_bits(d) << 16));
     second = first;
@@ -91,6 +99,18 @@ __device__ __forceinline__ void act_store4(bf16_t* p, int lo, float a, float b, 
   act_pack4(lo, a, b, c, d, f, s2);
   *(uint2*)p = f;
   if (lo > 0) *(uint2*)(p + lo) = s2;
+}
+// Element offset of (row, col) in fragment order; width: columns of the matrix (a multiple of 32).
+__host__ __device__ inline size_t frag_offset(int row, int col, int width) {
+  return ((size_t)(row >> 4) * (width >> 5) + (col >> 5)) * 512 + ((col >> 3) & 3) * 128 + (row & 15) * 8 + (col & 7);
+}
+// The same by row and column, in any of the layouts (ld: elements per row, in fragment order the matrix' width).
+__device__ __forceinline__ size_t act_offset(int lo, int row, int col, int ld) {
+  return lo == LO_F16P ? frag_offset(row, col, ld) : (size_t)row * ld + col;
+}
+__device__ __forceinline__ void act_put1(bf16_t* base, int lo, int row, int col, int ld, float v) { act_store1(base + act_offset(lo, row, col, ld), lo, v); }
+__device__ __forceinline__ void act_put4(bf16_t* base, int lo, int row, int col, int ld, float a, float b, float c, float d) {
+  act_store4(base + act_offset(lo, row, col, ld), lo, a, b, c, d);   // col is a multiple of 4
 }
 // One MFMA 16x16x32 on 16-byte operand fragments in either operand type.
 template <int OPM>
@@ -202,7 +222,7 @@ struct GemmStreamArgs {
   int32_t m_hint;           // host: rows the caller expects (0 = unknown); only steers the choice of launch shape
   const bf16_t* X;          // activations [*, ldx] (for SPRO_BF16S: h * gain, not yet divided by the rms)
   int32_t ldx;
-  int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16: half values)
+  int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16P: half values in fragment order)
   const int32_t* gather;    // optional row indices into X / ss_part
   const float* ss_part;     // SPRO_BF16S: [*, ss_stride] partial sums of squares of the residual rows
   int32_t ss_stride, ss_count;
@@ -248,7 +268,7 @@ struct GemmStreamArgs {
   int32_t xcd_order;        // set by the tile kernel's launcher: tiles are re-dealt so that the row tiles of a column share an XCD
   int32_t split_xcd;        // set by the tile kernel's launcher: K split z runs on the XCDs x with x % splits == z
   int32_t coop_wgs;         // compute units: a launch of at most that many workgroups of the tile kernel is resident at once (0: unknown)
-  // streaming kernel, paired K split of the residual-add GEMM: pair_cap x 256 (value, tag) words, zero between
+  // streaming and mid-size kernel, K split of the residual-add GEMM: pair_cap x 256 (value, tag) words, zero between
   // launches; *pair_status is set when a bounded wait ran out
   unsigned long long* pair_buf;
   int32_t* pair_status;
@@ -261,6 +281,10 @@ void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, 
                        float* h, void* xg, int xg_ld, int xg_lo, float* ss, int ss_stride,
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
 void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+// gemm_mid.hip : windows of 17 to about 128 rows, half operands in fragment order
+int gemm_mid_most_rows(int NT, int KT);
+bool gemm_mid_takes(int kind, const GemmStreamArgs& a);
+void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
 // gemm_tile.hip : 128 x 256 LDS-tiled kernel on the same packed weights and argument block
 void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a, int row_tiles);
 
@@ -278,7 +302,7 @@ void launch_moe_copy_choices(hipStream_t st, const int32_t* src, int32_t* dst, i
 // attention.hip
 void launch_attention_generic(hipStream_t st, int dtype, const void* q, const void* k_win, const void* v_win,
                               const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g,
-                              const Plan& p, int rows_cap, int Hq, void* o, size_t lds_bytes, int o_f16 /* bf16 models: write o as half values */);
+                              const Plan& p, int rows_cap, int Hq, void* o, size_t lds_bytes, int o_lo /* storage of o in bf16 models: half values if negative, else one bf16 plane */);
 int attention_init();
 size_t attention_flash_partial_floats(size_t entries);
 void launch_attention_flash(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
