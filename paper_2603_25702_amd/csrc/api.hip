@@ -172,6 +172,8 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   c->plan.seq_lead = cv.take<int32_t>(NB);
   c->plan.seq_j = cv.take<int32_t>(NB);
   c->plan.seq_L = cv.take<int32_t>(NB);
+  c->plan.seq_splits = cv.take<int32_t>(NB);
+  c->plan.split_of = cv.take<int32_t>(NB + WIDE_MAX_TARGET);
   c->h = cv.take<float>(R * d.d_model);
   const size_t P = act_planes(d);
   // GEMM inputs: two bf16 planes, or whole blocks of 16 rows of half values (fragment order)
@@ -278,17 +280,37 @@ KvGeom geom(const s2d2_ctx* c, const s2d2_kv_view* kv) {
                 c->desc.n_kv_heads, c->desc.head_dim};
 }
 
+// Shape of the wide attention launch: q_tiles 32-row query tiles per window; target key splits of all sequences together,
+// per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence.
+struct WideShape { int q_tiles, target, Z; };
+WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) {
+  WideShape w;
+  w.q_tiles = (win * (c->desc.n_q_heads / c->desc.n_kv_heads) + 31) / 32;
+  const int wg = c->desc.n_kv_heads * ((w.q_tiles + 7) / 8);
+  w.target = std::max(1, std::min((c->wide_wgs + wg - 1) / wg, WIDE_MAX_TARGET));
+  w.Z = attention_wide_splits(geom(c, kv), N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
+  return w;
+}
+
 // One forward over the planned window rows; K/V of every window row go to k_stage/v_stage
 // ([n_layers, rows_cap, Hkv, D]) if given, else to a one-layer scratch.
-int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void* k_stage, void* v_stage, float* logits) {
+// Bounds of a forward: rows of one window, rows, logit rows of all windows, and the rows the caller expects.
+struct FwdSize { int win, R, LR, hint; };
+FwdSize draft_size(int N, int B) { return {2 * B, 2 * N * B, N * B, N * B}; }        // carry + block; a fresh block has B rows
+FwdSize verify_size(int N, int B) { return {3 * B, 3 * N * B, N * B, 2 * N * B}; }   // carry + 2L; a fresh block has 2 B (more only with carried or pending committed tokens)
+FwdSize prefill_size(int N, int T) { return {T, N * T, 0, N * T}; }
+
+// Without logit rows (LR = 0) the forward ends with the K/V of the last layer.
+int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& sz, void* k_stage, void* v_stage, float* logits) {
   const s2d2_model_desc& d = c->desc;
-  const int dt = d.dtype, R = (k_stage ? 3 : 2) * N * B, LR = N * B, es = elt_size(dt);  // row bounds of this call (draft: carry + block)
+  const int dt = d.dtype, R = sz.R, LR = sz.LR, es = elt_size(dt);
   const int HqD = d.n_q_heads * d.head_dim, qkv_n = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
   hipStream_t st = c->stream;
   const KvGeom g = geom(c, kv);
   // MFMA flash attention for bf16 / head_dim 128 / pages that hold whole 8-key groups; else the generic kernel
   const bool flash = dt == S2D2_BF16 && d.head_dim == 128 && kv->page_size % 8 == 0;
-  const int q_tiles = ((k_stage ? 3 : 2) * B * (d.n_q_heads / d.n_kv_heads) + 31) / 32;   // 32-row query tiles of this call's windows
+  const WideShape ws = wide_shape(c, kv, N, sz.win);
+  const int q_tiles = ws.q_tiles;   // 32-row query tiles of this call's windows
   int Z = 1;
   // several query tiles per (sequence, KV head): the kernel that shares K / V tiles among them
   bool wide = flash && q_tiles >= 2 && (kv->page_size & (kv->page_size - 1)) == 0;
@@ -300,26 +322,21 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
     const int want = (512 + groups - 1) / groups;
     Z = std::max(1, std::min(std::min(want, (cap_tiles + 7) / 8), c->attn_zmax));
     if (wide) {
-      // one workgroup per (sequence, KV head, group of query tiles, split); a split keeps at least 4 key tiles
-      const int wg = N * d.n_kv_heads * ((q_tiles + 7) / 8);
-      Z = std::max(1, std::min((c->wide_wgs + wg - 1) / wg, std::min((cap_tiles + 3) / 4, c->attn_zmax)));
-      while (Z > 1 && ((size_t)Z * N * d.n_kv_heads * q_tiles > c->attn_part_entries ||
-                       attention_wide_lds_bytes(attention_wide_pt_cap(g, Z)) > 160 * 1024)) --Z;
-      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, Z)) > 160 * 1024) wide = false, Z = 1;
+      Z = ws.Z;
+      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, Z, ws.target)) > 160 * 1024) wide = false, Z = 1;
     }
   }
-  const size_t lds = flash ? 0 : attention_generic_lds_bytes(g, 3 * B);
+  const size_t lds = flash ? 0 : attention_generic_lds_bytes(g, sz.win);
   if (lds > 160 * 1024) return fail(S2D2_ENOSPC, "attention needs %zu bytes of LDS for max_pages_per_seq*page_size=%d keys (limit 163840)", lds, kv->max_pages_per_seq * kv->page_size);
   const size_t stage_layer = (size_t)c->rows_cap * d.n_kv_heads * d.head_dim * es;
   const size_t page_layer = (size_t)kv->n_pages * d.n_kv_heads * kv->page_size * d.head_dim * es;
   const int32_t* n_rows = c->plan.counts;
   const bool fused = c->pk != nullptr;
   const int ss_stride = (d.d_model + 15) / 16;
-  // rows a fresh block gives: N*B draft rows, 2*N*B verifier rows (more only with carried or pending committed tokens)
-  const int m_hint = (k_stage ? 2 : 1) * N * B;
-  const double fr = 2.0 * m_hint, fl = 2.0 * N * B;   // flops per weight element: layer GEMMs, unembedding (method's flops, one plane)
+  const int m_hint = sz.hint;
+  const double fr = 2.0 * m_hint, fl = 2.0 * LR;   // flops per weight element: layer GEMMs, unembedding (method's flops, one plane)
   auto sk = [&](GemmStreamArgs& x) {   // split-K buffers of the tiled GEMM, expected rows
-    x.m_hint = x.m_count == c->plan.counts + 1 ? N * B : m_hint;   // (logit rows: one per masked position)
+    x.m_hint = x.m_count == c->plan.counts + 1 ? LR : m_hint;   // (logit rows: one per masked position)
     x.tile_partials = c->tile_partials; x.tile_counters = c->tile_counters;
     x.tile_partial_cap = TILE_PARTIAL_CAP; x.tile_counter_cap = TILE_COUNTER_CAP; x.coop_wgs = c->n_cus;
     x.pair_buf = c->pair_buf; x.pair_status = c->dev_status + 1; x.pair_cap = PAIR_CAP;
@@ -366,12 +383,13 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t B, void*
       { ProfScope ps(c, 0, (double)qkv_n * d.d_model * es, fr * qkv_n * d.d_model, 4); launch_gemm(st, dt, EPI_STORE_F32, c->a, d.d_model, L.wqkv, d.d_model, qkv_n, n_rows, R, c->qkv, qkv_n); }
       { ProfScope ps(c, 3, 0.0); launch_rope_split(st, dt, c->qkv, c->plan, R, d.n_q_heads, d.n_kv_heads, d.head_dim, d.rope_theta, c->qbuf, kw, vw, flash ? c->vT_win : nullptr, c->wpad); }
     }
+    if (LR == 0 && l == d.n_layers - 1) return check_launch("forward");
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;
     const void* vp = (const uint8_t*)kv->v_pages + l * page_layer;
     if (flash) {
       ProfScope ps(c, 1, 0.0);
       if (wide)
-        launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries, c->attn_counters);
+        launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries);
       else
       {
         // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the
@@ -656,9 +674,11 @@ int32_t s2d2_draft(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state* 
   int32_t rc;
   if ((rc = check_state(c, st, N, B)) || (rc = check_kv(c, kv)) || (rc = check_params(prm)) || (rc = check_draft_out(out))) return rc;
   const s2d2_model_desc& d = c->desc;
+  const WideShape ws = wide_shape(c, kv, N, draft_size(N, B).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 0, d.right_shifted, N, B, d.mask_id, prm->ar_mask, kv->seq_len, st->block_pos0, st->block_tokens,
-              st->carry_tokens, nullptr, c->plan, out->logit_row_of, out->span_start, out->span_len, nullptr, nullptr, nullptr, kv->status); }
-  if ((rc = forward(c, kv, N, B, nullptr, nullptr, out->logits))) return rc;
+              st->carry_tokens, nullptr, c->plan, out->logit_row_of, out->span_start, out->span_len, nullptr, nullptr, nullptr, kv->status,
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+  if ((rc = forward(c, kv, N, draft_size(N, B), nullptr, nullptr, out->logits))) return rc;
   { ProfScope ps(c, 2, 0.0); launch_vocab_draft(c->stream, out->logits, d.vocab, c->plan.counts + 1, N * B, c->vws, c->plan.logit_seq,
                      c->plan.logit_idx, B, out->xhat, out->p, out->lse, out->margin, out->entropy_n,
                      VocabSample{prm->mode == S2D2_SAMPLE, prm->temperature, prm->seed, prm->step, prm->step_dev}); }
@@ -674,10 +694,11 @@ int32_t s2d2_verify(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state*
       (rc = check_draft_out(draft)) || (rc = check_verify_out(out)))
     return rc;
   const s2d2_model_desc& d = c->desc;
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 1, d.right_shifted, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               draft->xhat, c->plan, out->logit_row_of, nullptr, nullptr, out->stage_row0, out->stage_lead, prm->active, kv->status,
-              out->q, out->lse_ver); }
-  if ((rc = forward(c, kv, N, B, out->k_stage, out->v_stage, out->logits_ver))) return rc;
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, out->q, out->lse_ver); }
+  if ((rc = forward(c, kv, N, verify_size(N, B), out->k_stage, out->v_stage, out->logits_ver))) return rc;
   { ProfScope ps(c, 2, 0.0); launch_vocab_score(c->stream, out->logits_ver, d.vocab, c->plan.counts + 1, N * B, c->vws, c->plan.logit_seq,
                      c->plan.logit_idx, B, draft->xhat, out->q, out->lse_ver, inv_temperature(prm)); }
   return check_launch("s2d2_verify");
@@ -741,15 +762,38 @@ int32_t s2d2_block_complete(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_bloc
   const s2d2_model_desc& d = c->desc;
   if (d.right_shifted) return fail(S2D2_EINVAL, "s2d2_block_complete is not defined for right-shifted models (their cache lags one token)");
   if (causal != 0 && causal != 1) return fail(S2D2_EINVAL, "causal must be 0 or 1");
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, causal ? 3 : 2, 0, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
-              nullptr, c->plan, scratch->logit_row_of, nullptr, nullptr, scratch->stage_row0, scratch->stage_lead, nullptr, nullptr); }
-  if ((rc = forward(c, kv, N, B, scratch->k_stage, scratch->v_stage, scratch->logits_ver))) return rc;
+              nullptr, c->plan, scratch->logit_row_of, nullptr, nullptr, scratch->stage_row0, scratch->stage_lead, nullptr, nullptr,
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+  if ((rc = forward(c, kv, N, verify_size(N, B), scratch->k_stage, scratch->v_stage, scratch->logits_ver))) return rc;
   const KvGeom g = geom(c, kv);
   // every staged row is appended: lead = rows, accepted = 0 (the zero array stands in for n_accept and span_len)
   { ProfScope ps(c, 3, 0.0); launch_kv_append(c->stream, d.dtype, d.n_layers, N, c->rows_cap, g, kv->k_pages, kv->v_pages,
                    scratch->k_stage, scratch->v_stage, scratch->stage_row0, scratch->stage_lead, c->zeros_i32, c->zeros_i32,
                    kv->seq_len, kv->status, B, 0); }
   return check_launch("s2d2_block_complete");
+}
+
+int32_t s2d2_prefill(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t T, const int32_t* tokens, int32_t ld,
+                     const int32_t* n_tokens, void* k_stage, void* v_stage) {
+  int32_t rc;
+  if (!c) return fail(S2D2_EINVAL, "ctx is NULL");
+  if (N < 1 || N > c->max_batch) return fail(S2D2_EINVAL, "N=%d outside [1, max_batch=%d]", N, c->max_batch);
+  if (T < 1 || T > 3 * c->max_block) return fail(S2D2_EINVAL, "T=%d outside [1, 3 * max_block=%d]", T, 3 * c->max_block);
+  if (!tokens || !n_tokens || ld < T) return fail(S2D2_EINVAL, "tokens or n_tokens is NULL, or ld=%d is below T=%d", ld, T);
+  if (!k_stage || !v_stage || (((uintptr_t)k_stage | (uintptr_t)v_stage) & 15)) return fail(S2D2_EINVAL, "the K/V stage is NULL or not 16-byte aligned");
+  if ((rc = check_kv(c, kv))) return rc;
+  const s2d2_model_desc& d = c->desc;
+  const FwdSize sz = prefill_size(N, T);
+  const WideShape ws = wide_shape(c, kv, N, sz.win);
+  { ProfScope ps(c, 3, 0.0); launch_plan_prefill(c->stream, N, T, d.mask_id, kv->seq_len, tokens, ld, n_tokens, c->plan,
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+  if ((rc = forward(c, kv, N, sz, k_stage, v_stage, nullptr))) return rc;
+  const KvGeom g = geom(c, kv);
+  { ProfScope ps(c, 3, 0.0); launch_kv_append(c->stream, d.dtype, d.n_layers, N, c->rows_cap, g, kv->k_pages, kv->v_pages,
+                   k_stage, v_stage, c->plan.seq_row0, c->plan.seq_lead, c->zeros_i32, c->zeros_i32, kv->seq_len, kv->status, (T + 1) / 2, 0); }
+  return check_launch("s2d2_prefill");
 }
 
 int32_t s2d2_block_advance(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state* st, int32_t N, int32_t B,

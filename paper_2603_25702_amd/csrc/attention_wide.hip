@@ -5,8 +5,8 @@
 // ONE query tile of the same (sequence, KV head, key split) and walk the keys together: a 32-key tile of K
 // and of V^T is fetched from global memory once per workgroup (every thread one or a few 16-byte pieces),
 // parked in LDS, and read from there as MFMA operands by all wavefronts.  A wavefront never shares its
-// softmax state, so there is no merge inside the workgroup; key splits merge through the same
-// last-arriver scheme as the narrow kernel, in split order.
+// softmax state, so there is no merge inside the workgroup; key splits are added up by a second
+// launch, in split order.
 //
 // Pipeline: two tiles are in flight in registers (sets R0 / R1) while a third is being consumed from one of two
 // LDS buffers; a wavefront parks tile i + 1 in the other buffer after its own math on tile i, and one barrier
@@ -35,7 +35,7 @@ static constexpr int FW_KBUF = 32 * FW_KROW;
 static constexpr int FW_BUF = FW_KBUF + 128 * FW_VROW;
 static constexpr int FW_RING = 2;
 
-size_t attention_wide_lds_bytes(int pt_cap) { return (size_t)FW_RING * FW_BUF + (size_t)pt_cap * 4 + 16; }
+size_t attention_wide_lds_bytes(int pt_cap) { return (size_t)FW_RING * FW_BUF + (size_t)pt_cap * 4; }
 
 struct FwTile { bool win; int kbase, limit; };
 
@@ -70,16 +70,20 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int32_t* __restrict__ counters, int q_tiles, int per, int pt_cap, int ps_shift) {
+    float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift) {
   constexpr int D = FA_D, T = NW * 64, U = 512 / T;
   constexpr bool SPLIT = QM == OPM_BF16X2, F16 = QM == OPM_F16;
   static_assert(U == 1 || U == 2, "8 or 4 wavefronts");
   extern __shared__ __align__(16) unsigned char lds[];
   int32_t* s_pt = (int32_t*)(lds + FW_RING * FW_BUF);
-  int* s_last = (int*)(s_pt + pt_cap);
-  const int z = blockIdx.x, qgrp = blockIdx.y, item = blockIdx.z;
+  // Splits are numbered through over the sequences (Plan.split_of), so the workgroups without one are the last of the
+  // grid.  Between the others they leave compute units empty that hold two workgroups elsewhere, one after the
+  // other (the hardware deals workgroups out in turn, whether they leave at once or not): 125 -> 167 us.
+  const int qgrp = blockIdx.y;
+  if ((int)blockIdx.z >= p.counts[2]) return;
+  const int so = p.split_of[blockIdx.z], z = so >> 16;
   const int Hkv = g.n_kv_heads, ps = g.page_size;
-  const int n = item / Hkv, kvh = item % Hkv;
+  const int n = so & 0xffff, kvh = blockIdx.x, item = n * Hkv + kvh;
   const int grp = Hq / Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, h = lane >> 5;
@@ -96,8 +100,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   const int lo = p.row_lo[r], hi = p.row_hi[r];
 
   const int Tc = (S + 31) >> 5, Tw = (nw + 31) >> 5;
-  const int t0 = (int)((long long)Tc * z / Z), t1 = (int)((long long)Tc * (z + 1) / Z);
-  const int n_c = t1 - t0, n_w = z == Z - 1 ? Tw : 0, n_it = n_c + n_w;
+  const int Zn = p.seq_splits[n];
+  const int t0 = (int)((long long)Tc * z / Zn), t1 = (int)((long long)Tc * (z + 1) / Zn);
+  const int n_c = t1 - t0, n_w = z == Zn - 1 ? Tw : 0, n_it = n_c + n_w;
 
   // page-table slice of this split's keys
   const int pb0 = (t0 * 32) >> ps_shift;   // page_size = 1 << ps_shift
@@ -381,7 +386,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
       for (; i + 4 < n_fast; i += 2) pass(FT_, i);
       for (; i < n_it; i += 2) pass(GT_, i);
     } else {
-      // smaller workgroups hold several pieces per thread: one tile in flight (two workgroups share a CU)
+      // smaller workgroups hold several pieces per thread: one tile in flight (two workgroups share a CU; with two, as above,
+      // launches of short splits took 2 us longer and long ones the same)
       uint4 k0, v0, k1, v1;
       fetch1(GT_, 0, 0, k0, v0);
       fetch1(GT_, 1, 0, k1, v1);
@@ -407,7 +413,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
 
   // ---- output: lane (c, h) holds head-dim positions dt*32 + 8*i4 + 4*h .. + 4 of query row c ----
   const size_t item0 = ((size_t)item * q_tiles + qt) * Z;
-  if (Z == 1) {
+  if (Zn == 1) {
     if (active && q0 + c < nq) {
       const float inv = st.l > 0.f ? 1.0f / st.l : 0.f;
 #pragma unroll
@@ -419,47 +425,76 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     }
     return;
   }
+  // the splits' partials, in register order; attn_wide_merge_kernel, launched next, adds them up
   if (active) {
     float* po = part_o + (item0 + z) * 32 * D + (size_t)lane * 4;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4)
-        st16f_coh(po + (dt * 4 + i4) * 256, st.o[dt][4 * i4], st.o[dt][4 * i4 + 1], st.o[dt][4 * i4 + 2], st.o[dt][4 * i4 + 3]);
+        *(float4*)(po + (dt * 4 + i4) * 256) = make_float4(st.o[dt][4 * i4], st.o[dt][4 * i4 + 1], st.o[dt][4 * i4 + 2], st.o[dt][4 * i4 + 3]);
     if (h == 0) {
-      st4f_coh(&part_ml[(item0 + z) * 64 + c], st.m);
-      st4f_coh(&part_ml[(item0 + z) * 64 + 32 + c], st.l);
+      part_ml[(item0 + z) * 64 + c] = st.m;
+      part_ml[(item0 + z) * 64 + 32 + c] = st.l;
     }
   }
-  __builtin_amdgcn_s_waitcnt(0);  // the write-through stores of the partials have completed before the arrival is counted
-  __syncthreads();
-  const int cidx = item * q_tiles + qgrp * per;
-  if (tid == 0) {
-    const int prev = __hip_atomic_fetch_add(&counters[cidx], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *s_last = prev == Z - 1;
-    if (prev == Z - 1) __hip_atomic_store(&counters[cidx], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sums of the key splits, in split order: one wavefront per 32 query rows x 8 output columns (the 64 x 16 bytes its
+// accumulator group has in every split), the partials of 12 splits requested at once.  A launch of its own costs 4-5 us, all
+// of it latency; when the split that arrived last added up its workgroup's tiles by itself, that was one memory round
+// trip per query tile, pass and four splits behind each other, on one compute unit, 6 to 27 us of the launch.
+__global__ __launch_bounds__(256) void attn_wide_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml, KvGeom g,
+                                                              Plan p, int Hq, int Z, bf16_t* __restrict__ o, int o_ld, int o_lo) {
+  constexpr int D = FA_D, ZB = 12;
+  const int lane = threadIdx.x & 63, g16 = blockIdx.x * 4 + (threadIdx.x >> 6), qt = blockIdx.y, item = blockIdx.z;
+  const int Hkv = g.n_kv_heads, grp = Hq / Hkv, n = item / Hkv, kvh = item % Hkv, c = lane & 31;
+  const int row0 = p.seq_row0[n], nq = p.seq_rows[n] * grp, Zn = p.seq_splits[n];
+  if (Zn == 1 || qt * 32 >= nq) return;
+  const size_t item0 = ((size_t)item * gridDim.y + qt) * Z;
+  float M = -INFINITY, L = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z0 = 0; z0 < Zn; z0 += ZB) {
+    float m[ZB], l[ZB];
+    float4 v[ZB];
+#pragma unroll
+    for (int k = 0; k < ZB; ++k) {
+      const size_t e = item0 + min(z0 + k, Zn - 1);   // clamped duplicates get no weight below
+      m[k] = part_ml[e * 64 + c];
+      l[k] = part_ml[e * 64 + 32 + c];
+      v[k] = *(const float4*)(part_o + e * 32 * D + (g16 * 64 + lane) * 4);
+    }
+    float Mn = M;
+#pragma unroll
+    for (int k = 0; k < ZB; ++k) {
+      if (z0 + k >= Zn) m[k] = -INFINITY;
+      Mn = fmaxf(Mn, m[k]);
+    }
+    const float ref = Mn == -INFINITY ? 0.f : Mn;   // (nothing seen yet: all weights are exp2(-inf) = 0)
+    const float fo = __builtin_amdgcn_exp2f(M - ref);
+    L *= fo; acc.x *= fo; acc.y *= fo; acc.z *= fo; acc.w *= fo;
+#pragma unroll
+    for (int k = 0; k < ZB; ++k) {
+      const float f = __builtin_amdgcn_exp2f(m[k] - ref);
+      L += f * l[k];
+      acc.x += f * v[k].x; acc.y += f * v[k].y; acc.z += f * v[k].z; acc.w += f * v[k].w;
+    }
+    M = Mn;
   }
-  __syncthreads();
-  if (!*s_last) return;
-  // the last split to arrive merges every query tile of the workgroup, all threads on one tile at a time
-  for (int w = 0; w < per; ++w) {
-    const int qt2 = qgrp * per + w;
-    if (qt2 * 32 >= nq) break;
-    // in passes of 512 pieces, so that a thread never holds more than two pieces per split in registers
-#pragma unroll 1
-    for (int pass = 0; pass < 512 / T; ++pass)
-      fa_combine<false, 512>(part_o, part_ml, ((size_t)item * q_tiles + qt2) * Z, Z, tid + pass * T, qt2, nq, grp, row0, kvh, Hq, o, o_ld, o_lo);
-  }
+  const int qi = qt * 32 + c, d0 = (g16 >> 2) * 32 + 8 * (g16 & 3) + 4 * (lane >> 5);
+  if (qi >= nq) return;
+  const float inv = L > 0.f ? 1.0f / L : 0.f;
+  fa_store4<false>(o, o_lo, row0 + qi / grp, (kvh * grp + qi % grp) * D + d0, o_ld, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
 }
 
 template <int NW>
 static void launch_wide(hipStream_t st, int qm, dim3 grid, size_t lds, const bf16_t* q, int q_ld, int q_lo,
                         const bf16_t* k_win, const bf16_t* vT_win, const bf16_t* kp, const bf16_t* vp, const KvGeom& g,
                         const Plan& p, int Hq, int Z, int wpad, float scale_log2e, bf16_t* o, int o_ld, int o_lo,
-                        float* part_o, float* part_ml, int32_t* counters, int q_tiles, int per, int pt_cap, int ps_shift) {
+                        float* part_o, float* part_ml, int q_tiles, int per, int pt_cap, int ps_shift) {
 #define S2D2_WIDE_QM(QMV)                                                                                                    \
   S2D2_LAUNCH((attn_flash_wide_kernel<NW, QMV>), grid, dim3(NW * 64), lds, st, q, q_ld, q_lo, k_win, vT_win, kp, vp, g, p, \
-              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, counters, q_tiles, per, pt_cap, ps_shift)
+              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift)
   if (qm == OPM_F16) S2D2_WIDE_QM(OPM_F16);
   else if (qm == OPM_BF16X2) S2D2_WIDE_QM(OPM_BF16X2);
   else S2D2_WIDE_QM(OPM_BF16);
@@ -473,35 +508,45 @@ int attention_wide_nw(int q_tiles) {
   return need <= 4 ? 4 : 8;   // (two wavefronts for two tiles measured slower: four share the fetch work, 3.76 -> 3.27 ms of attention per step on the 4B shape)
 }
 
-// Page-table entries a split can touch (plus slack for the ragged ends).
-int attention_wide_pt_cap(const KvGeom& g, int Z) {
+// Most splits of a sequence: a split keeps at least four key tiles, the partials fit their buffer.
+int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target) {
   const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32;
-  const int per_split = (cap_tiles + Z - 1) / Z + 1;
-  return std::min(g.max_pages_per_seq, per_split * 32 / g.page_size + 2);
+  int Z = std::max(1, std::min(std::min((cap_tiles + WIDE_MIN_TILES - 1) / WIDE_MIN_TILES, 64), target + 1));
+  while (Z > 1 && (size_t)Z * items * q_tiles > part_entries) --Z;
+  return Z;
+}
+
+// Page-table entries a split can touch (plus slack for the ragged ends): N sequences of the cache's capacity share the
+// target's splits, a single one has at most Z.
+int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
+  const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32;
+  const long long per_split = std::max((long long)std::max((cap_tiles + Z - 1) / Z, WIDE_MIN_TILES), ((long long)N * cap_tiles + target - 1) / target) + 1;
+  return (int)std::min((long long)g.max_pages_per_seq, per_split * 32 / g.page_size + 2);
 }
 
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int wpad, void* o, int o_ld, int o_lo, float* part,
-                           size_t part_entries, int32_t* counters) {
+                           int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           size_t part_entries) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)g.head_dim);
   const int items = N * g.n_kv_heads;
   const int qgroups = (q_tiles + 7) / 8, per = (q_tiles + qgroups - 1) / qgroups;   // tiles per workgroup, balanced
   const int nw = attention_wide_nw(q_tiles);
-  const int pt_cap = attention_wide_pt_cap(g, Z);
+  const int pt_cap = attention_wide_pt_cap(g, N, Z, target);
   float* part_o = part;
   float* part_ml = part + part_entries * 32 * FA_D;
-  const dim3 grid(Z, qgroups, items);
+  const dim3 grid(g.n_kv_heads, qgroups, std::min(N * Z, N + target));   // (N + target: a run more than the target per sequence at most)
   const size_t lds = attention_wide_lds_bytes(pt_cap);
   int ps_shift = 0;
   while ((1 << ps_shift) < g.page_size) ++ps_shift;   // the caller has checked that page_size is a power of two
 #define S2D2_WIDE(NWV)                                                                                                  \
   launch_wide<NWV>(st, operand_mode(q_lo), grid, lds, (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win, \
                    (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,          \
-                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, q_tiles, per, pt_cap, ps_shift)
+                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift)
   if (nw == 4) S2D2_WIDE(4);
   else S2D2_WIDE(8);
 #undef S2D2_WIDE
+  if (Z > 1) S2D2_LAUNCH(attn_wide_merge_kernel, dim3(4, q_tiles, items), dim3(256), 0, st, part_o, part_ml, g, p, Hq, Z, (bf16_t*)o, o_ld, o_lo);
 }
 
 template <int NW, int QM>

@@ -21,8 +21,9 @@ __global__ __launch_bounds__(1024) void plan_kernel(
     const int32_t* __restrict__ carry, const int32_t* __restrict__ xhat, Plan p,
     int32_t* __restrict__ logit_row_of, int32_t* __restrict__ span_start,
     int32_t* __restrict__ span_len, int32_t* __restrict__ stage_row0, int32_t* __restrict__ stage_lead,
-    const int32_t* __restrict__ active, int32_t* __restrict__ status, float* __restrict__ clear_a,
+    const int32_t* __restrict__ active, int32_t* __restrict__ status, int seq_cap, int split_target, int split_most, float* __restrict__ clear_a,
     float* __restrict__ clear_b) {
+  __shared__ int32_t s_tiles, s_splits[1024];
   __shared__ int32_t s_rows[1024];
   __shared__ int32_t s_lrows[1024];
   const int n = threadIdx.x;
@@ -56,19 +57,29 @@ __global__ __launch_bounds__(1024) void plan_kernel(
     } else if (verify) { rows = shifted ? lead + max(L - 1, 0) : lead + 2 * L; lrows = L; }
     else        { rows = nc + (B - c); lrows = bad ? 0 : n_masked; }
   }
+  if (n == 0) s_tiles = 0;
   s_rows[n] = rows;
   s_lrows[n] = lrows;
   __syncthreads();
+  // key splits: the cached key tiles of the sequences that have a window, in runs that give split_target of them
+  const int tiles = rows > 0 ? (max(0, min(S, seq_cap)) + 31) >> 5 : 0;
+  if (tiles) atomicAdd(&s_tiles, tiles);
+  __syncthreads();
+  const int run = max(WIDE_MIN_TILES, (s_tiles + split_target - 1) / split_target);
+  const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
+  s_splits[n] = splits;
+  __syncthreads();
   // inclusive Hillis-Steele scan over the 1024 slots
   for (int off = 1; off < 1024; off <<= 1) {
-    int a = 0, b = 0;
-    if (n >= off) { a = s_rows[n - off]; b = s_lrows[n - off]; }
+    int a = 0, b = 0, d = 0;
+    if (n >= off) { a = s_rows[n - off]; b = s_lrows[n - off]; d = s_splits[n - off]; }
     __syncthreads();
     s_rows[n] += a;
     s_lrows[n] += b;
+    s_splits[n] += d;
     __syncthreads();
   }
-  if (n == 1023) { p.counts[0] = s_rows[1023]; p.counts[1] = s_lrows[1023]; }
+  if (n == 1023) { p.counts[0] = s_rows[1023]; p.counts[1] = s_lrows[1023]; p.counts[2] = s_splits[1023]; }
   if (n >= N) return;
   const int row0 = s_rows[n] - rows;
   int k = s_lrows[n] - lrows;
@@ -77,6 +88,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(
   p.seq_lead[n] = lead;
   p.seq_j[n] = j;
   p.seq_L[n] = L;
+  p.seq_splits[n] = splits;
+  for (int z = 0; z < splits; ++z) p.split_of[s_splits[n] - splits + z] = n | (z << 16);
   const int32_t* blk = block + (size_t)n * B;
   const int32_t* car = carry + (size_t)n * B;
   if (!verify) {
@@ -168,10 +181,63 @@ void launch_plan(hipStream_t st, int verify, int shifted, int N, int B, int mask
                  const int32_t* seq_len, const int32_t* pos0, const int32_t* block,
                  const int32_t* carry, const int32_t* xhat, const Plan& p, int32_t* logit_row_of,
                  int32_t* span_start, int32_t* span_len, int32_t* stage_row0, int32_t* stage_lead,
-                 const int32_t* active, int32_t* status, float* clear_a, float* clear_b) {
+                 const int32_t* active, int32_t* status, int seq_cap, int split_target, int split_most, float* clear_a, float* clear_b) {
   S2D2_LAUNCH(plan_kernel, dim3(1), dim3(1024), 0, st, verify, shifted, N, B, mask_id, ar_mask,
                      seq_len, pos0, block, carry, xhat, p, logit_row_of, span_start, span_len,
-                     stage_row0, stage_lead, active, status, clear_a, clear_b);
+                     stage_row0, stage_lead, active, status, seq_cap, split_target, split_most, clear_a, clear_b);
+}
+
+// Prompt tokens pushed into the cache: n_tokens[n] causal rows of sequence n behind its cached ones, no logits.  A
+// wavefront fills the rows of a sequence (in plan_kernel one thread does, a few rows there, up to 192 here).
+__global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int mask_id, const int32_t* __restrict__ seq_len,
+                                                            const int32_t* __restrict__ tokens, int ld,
+                                                            const int32_t* __restrict__ n_tokens, Plan p, int seq_cap,
+                                                            int split_target, int split_most) {
+  __shared__ int32_t s_tiles, s_rows[1024], s_splits[1024];
+  const int n = threadIdx.x;
+  const int S = n < N ? seq_len[n] : 0, rows = n < N ? max(0, min(T, n_tokens[n])) : 0;
+  if (n == 0) s_tiles = 0;
+  s_rows[n] = rows;
+  __syncthreads();
+  const int tiles = rows > 0 ? (max(0, min(S, seq_cap)) + 31) >> 5 : 0;
+  if (tiles) atomicAdd(&s_tiles, tiles);
+  __syncthreads();
+  const int run = max(WIDE_MIN_TILES, (s_tiles + split_target - 1) / split_target);
+  const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
+  s_splits[n] = splits;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    int a = 0, d = 0;
+    if (n >= off) { a = s_rows[n - off]; d = s_splits[n - off]; }
+    __syncthreads();
+    s_rows[n] += a;
+    s_splits[n] += d;
+    __syncthreads();
+  }
+  if (n == 1023) { p.counts[0] = s_rows[1023]; p.counts[1] = 0; p.counts[2] = s_splits[1023]; }
+  if (n < N) {
+    p.seq_row0[n] = s_rows[n] - rows;
+    p.seq_rows[n] = rows;
+    p.seq_lead[n] = rows;
+    p.seq_splits[n] = splits;
+    for (int z = 0; z < splits; ++z) p.split_of[s_splits[n] - splits + z] = n | (z << 16);
+  }
+  for (int m = n >> 6; m < N; m += 16) {
+    const int end = s_rows[m], row0 = m ? s_rows[m - 1] : 0, S0 = seq_len[m];
+    for (int r = row0 + (n & 63); r < end; r += 64) {
+      p.row_token[r] = in_vocab(tokens[(size_t)m * ld + (r - row0)], p.vocab, mask_id);
+      p.row_pos[r] = S0 + (r - row0);
+      p.row_seq[r] = m;
+      p.row_lo[r] = row0;
+      p.row_hi[r] = r + 1;
+    }
+  }
+}
+
+void launch_plan_prefill(hipStream_t st, int N, int T, int mask_id, const int32_t* seq_len, const int32_t* tokens, int ld,
+                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most) {
+  S2D2_LAUNCH(plan_prefill_kernel, dim3(1), dim3(1024), 0, st, N, T, mask_id, seq_len, tokens, ld, n_tokens, p, seq_cap,
+              split_target, split_most);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -145,12 +145,13 @@ template <typename T> __device__ __forceinline__ T from_f32(float x);
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return f32_to_bf16(x); }
 
+constexpr int WIDE_MAX_TARGET = 1024;   // most splits the wide attention kernel aims for
 // ---- device-resident description of one forward's window rows (built by the plan kernel) ----
 // Rows of all sequences are packed back to back; the rows of sequence n are
 // [seq_row0[n], seq_row0[n] + seq_rows[n]).  Row r attends to every cached position of its
 // sequence, to the window rows [row_lo[r], row_hi[r]) and to itself.
 struct Plan {
-  int32_t* counts;      // [0] = number of window rows, [1] = number of logit rows
+  int32_t* counts;      // [0] = number of window rows, [1] = number of logit rows, [2] = key splits (wide attention)
   int32_t* row_token;   // [rows_cap]
   int32_t* row_pos;     // [rows_cap] absolute position (RoPE phase)
   int32_t* row_seq;     // [rows_cap]
@@ -164,6 +165,9 @@ struct Plan {
   int32_t* seq_lead;    // [max_batch] leading causal rows before C_t (carry + pending)
   int32_t* seq_j;       // [max_batch] first masked block index (B if none)
   int32_t* seq_L;       // [max_batch] |C_t|
+  // key splits of the wide attention kernel: the cached 32-key tiles of the batch in equal runs, none across sequences
+  int32_t* seq_splits;  // [max_batch] splits of a sequence
+  int32_t* split_of;    // [max_batch + WIDE_MAX_TARGET] sequence | split << 16
   int32_t vocab;        // token ids outside [0, vocab) in the caller's state are read as [MASK]
 };
 
@@ -187,7 +191,11 @@ void launch_plan(hipStream_t st, int verify /* 0 draft, 1 verifier, 2 block comp
                  const int32_t* carry, const int32_t* xhat, const Plan& p, int32_t* logit_row_of,
                  int32_t* span_start, int32_t* span_len, int32_t* stage_row0, int32_t* stage_lead,
                  const int32_t* active, int32_t* status,
+                 int seq_cap, int split_target /* wide attention: key splits of all sequences together, per KV head */,
+                 int split_most /* and of one sequence */,
                  float* clear_a = nullptr, float* clear_b = nullptr /* verifier: [N, B] outputs zeroed for every position */);
+void launch_plan_prefill(hipStream_t st, int N, int T, int mask_id, const int32_t* seq_len, const int32_t* tokens, int ld,
+                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most);
 void launch_kv_append(hipStream_t st, int dtype, int n_layers, int N, int rows_cap, const KvGeom& g,
                       void* k_pages, void* v_pages, const void* k_stage, const void* v_stage,
                       const int32_t* stage_row0, const int32_t* stage_lead, const int32_t* span_len,
@@ -312,12 +320,14 @@ void launch_attention_flash(hipStream_t st, const void* q, int q_ld, int q_lo, c
 // Several query tiles per (sequence, KV head): one workgroup shares each K / V tile among them.
 int attention_wide_init();
 int attention_wide_nw(int q_tiles);
-int attention_wide_pt_cap(const KvGeom& g, int Z);
+constexpr int WIDE_MIN_TILES = 4;   // key tiles (of 32) a split of the wide kernel keeps at least
+int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target);
+int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target);
 size_t attention_wide_lds_bytes(int pt_cap);
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int wpad, void* o, int o_ld, int o_lo, float* part,
-                           size_t part_entries, int32_t* counters);
+                           int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           size_t part_entries);
 void launch_fill_i32(hipStream_t st, int32_t* p, int n, int32_t v);
 void launch_attn_ts_copy(hipStream_t st, void* out);   // timing build only
 void launch_wide_ts_copy(hipStream_t st, void* out);   // timing build only
