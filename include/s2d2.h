@@ -287,6 +287,15 @@ int32_t s2d2_kv_append(s2d2_ctx* ctx, const s2d2_kv_view* kv, int32_t N, int32_t
                        const s2d2_draft_out* draft, const s2d2_verify_out* ver,
                        const int32_t* n_accept /* device [N] */);
 
+/* Prompt tokens into the cache: up to T tokens of every sequence (row n of `tokens`, stride ld; n_tokens[n] of them, values
+ * outside [0, T] are cut) go through one causal forward behind the cached ones, their K/V are appended and seq_len
+ * advances.  No logits: the last layer ends with its K/V.  T <= 3 * max_block.  k_stage / v_stage: device scratch of
+ * n_layers x s2d2_stage_rows(max_batch, max_block) rows, as in s2d2_verify_out.  kv->status reports S2D2_ENOSPC as in
+ * s2d2_kv_append.  The cache gets what s2d2_verify + s2d2_kv_append (n_accept 0) of the same tokens in front of a
+ * [MASK] give, to rounding. */
+int32_t s2d2_prefill(s2d2_ctx* ctx, const s2d2_kv_view* kv, int32_t N, int32_t T, const int32_t* tokens /* device */,
+                     int32_t ld, const int32_t* n_tokens /* device [N] */, void* k_stage, void* v_stage);
+
 /* Alg. 1: a block without [MASK] is replaced by a fresh [MASK]^B block at block_pos0 + B; its
  * uncached committed tokens move to carry_tokens (capacity B).  A finished block whose uncached tokens, together
  * with the tokens already carried, exceed that capacity is left as it is and kv->status[n] is set to S2D2_ENOSPC:

@@ -22,7 +22,7 @@ S2D2_GREEDY, S2D2_SAMPLE = 0, 1
 EXPORTS = [
     "s2d2_last_error", "s2d2_version", "s2d2_stage_rows", "s2d2_workspace_bytes", "s2d2_packed_bytes", "s2d2_create", "s2d2_destroy",
     "s2d2_set_stream", "s2d2_draft", "s2d2_verify", "s2d2_accept", "s2d2_accept_static", "s2d2_kv_append", "s2d2_block_advance",
-    "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score", "s2d2_profile_start", "s2d2_profile_stop",
+    "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_prefill", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score", "s2d2_profile_start", "s2d2_profile_stop",
 ]
 PROFILE_CLASSES = ("gemm", "attention", "vocab", "other", "gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "gemm_unembed")
 
@@ -136,6 +136,8 @@ def load_library():
     lib.s2d2_commit_threshold.argtypes = [C.c_void_p, C.POINTER(BlockStateC), C.c_int32, C.c_int32, C.POINTER(DraftOutC)]
     lib.s2d2_block_complete.argtypes = [C.c_void_p, C.POINTER(KvView), C.POINTER(BlockStateC), C.c_int32, C.c_int32,
                                         C.POINTER(VerifyOutC), C.c_int32]
+    lib.s2d2_prefill.argtypes = [C.c_void_p, C.POINTER(KvView), C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p,
+                                 C.c_void_p, C.c_void_p]
     lib.s2d2_route.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(RouteParamsC), C.POINTER(DraftOutC), C.c_void_p,
                                C.POINTER(RouteOutC)]
     lib.s2d2_status.argtypes = [C.c_void_p]
@@ -149,7 +151,7 @@ def load_library():
     lib.s2d2_profile_start.argtypes = [C.c_void_p, C.c_int32]
     lib.s2d2_profile_stop.argtypes = [C.c_void_p, C.POINTER(ProfileC)]
     for name in ("s2d2_profile_start", "s2d2_profile_stop", "s2d2_destroy", "s2d2_set_stream", "s2d2_draft", "s2d2_verify", "s2d2_accept", "s2d2_kv_append",
-                 "s2d2_block_advance", "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score"):
+                 "s2d2_block_advance", "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_prefill", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score"):
         getattr(lib, name).restype = C.c_int32
     _LIB = lib
     return lib
@@ -418,6 +420,13 @@ class Engine:
     def s2d2_block_complete(self, kv: KvCache, st: BlockState, N, B, scratch: VerifyOut, causal: int = 0):
         _check(self.lib, self.lib.s2d2_block_complete(self.ctx, C.byref(kv.c()), C.byref(st.c()), N, B, C.byref(scratch.c()),
                                                       int(causal)))
+
+    def s2d2_prefill(self, kv: KvCache, N, T, tokens: torch.Tensor, offset: int, n_tokens: torch.Tensor,
+                     k_stage: torch.Tensor, v_stage: torch.Tensor):
+        """tokens: int32 [N, ld]; the columns from `offset` on are the next ones."""
+        assert tokens.stride(1) == 1 and offset + T <= tokens.shape[1] and n_tokens.is_contiguous()
+        _check(self.lib, self.lib.s2d2_prefill(self.ctx, C.byref(kv.c()), N, T, tokens.data_ptr() + 4 * offset, tokens.stride(0),
+                                               n_tokens.data_ptr(), k_stage.data_ptr(), v_stage.data_ptr()))
 
     def s2d2_route(self, N, B, rp: RouteParams, draft: DraftOut, hysteresis: Optional[torch.Tensor], out: RouteOut):
         _check(self.lib, self.lib.s2d2_route(self.ctx, N, B, C.byref(rp.c_struct()), C.byref(draft.c()), _ptr(hysteresis),

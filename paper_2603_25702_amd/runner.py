@@ -50,29 +50,22 @@ class Session:
         return BlockState(self._blk.view(-1)[:n].view(self.N, B), self.pos0, self._car.view(-1)[:n].view(self.N, B))
 
     def prefill(self, ids: Sequence[np.ndarray]):
-        """Fills the cache with the causal K/V of the prompts by pushing them through the verifier's
-        causal rows (committed tokens left of a [MASK]) and appending with n_accept = 0."""
-        N, mb, mask = self.N, self.eng.max_block, self.cfg.mask_id
+        """Fills the cache with the causal K/V of the prompts: one upload, then one forward per chunk of up to
+        3 * max_block tokens of every sequence (equal chunks), all enqueued without a wait in between."""
+        N, most = self.N, 3 * self.eng.max_block
         lens = [len(x) for x in ids]
-        done = [0] * N
-        zeros = torch.zeros(N, dtype=torch.int32, device=self.dev)
-        prm = Params()
-        pd, pv = self.eng.alloc_draft_out(N, mb), self.eng.alloc_verify_out(N, mb)  # released after the prefill
-        while any(done[n] < lens[n] for n in range(N)):
-            T = [min(mb - 1, lens[n] - done[n]) for n in range(N)]
-            Bc = max(T) + 1
-            st = self._state(Bc)
-            blk = np.full((N, Bc), mask, dtype=np.int32)
+        longest = max(lens)
+        self.kv.seq_len.zero_()
+        if longest:
+            chunks = (longest + most - 1) // most
+            T = (longest + chunks - 1) // chunks
+            host = np.zeros((N, chunks * T), dtype=np.int32)
             for n in range(N):
-                blk[n, :T[n]] = ids[n][done[n]:done[n] + T[n]]
-            st.block_tokens.copy_(torch.from_numpy(blk))
-            st.block_pos0.copy_(torch.as_tensor(done, dtype=torch.int32))
-            self.kv.seq_len.copy_(torch.as_tensor(done, dtype=torch.int32))
-            pd.xhat.zero_()
-            pd.span_len.zero_()
-            self.eng.s2d2_verify(self.kv, st, N, Bc, prm, pd, pv)
-            self.eng.s2d2_kv_append(self.kv, N, Bc, pd, pv, zeros)
-            done = [done[n] + T[n] for n in range(N)]
+                host[n, :lens[n]] = ids[n]
+            left = np.clip(np.asarray(lens)[None, :] - T * np.arange(chunks)[:, None], 0, T).astype(np.int32)
+            tok, n_tok = torch.from_numpy(host).to(self.dev), torch.from_numpy(left).to(self.dev)
+            for c in range(chunks):
+                self.eng.s2d2_prefill(self.kv, N, T, tok, c * T, n_tok[c], self.v.k_stage, self.v.v_stage)
         torch.cuda.synchronize(self.dev)
         self.reset_blocks(lens, [int(x[-1]) for x in ids])
 
