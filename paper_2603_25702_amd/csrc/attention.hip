@@ -20,13 +20,16 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// The launch is a chain of round trips to memory, so each of its steps requests what it can at once: a quarter-row of K
+// per lane (four lanes a key), eight V values per thread, and 1024 threads where their sums fit into LDS (with 256
+// threads, a key per thread and one V value per iteration: 16.8 us per launch at 136 keys of 64 floats).
 template <typename T>
-__global__ __launch_bounds__(256) void attn_generic_kernel(
+__global__ __launch_bounds__(1024) void attn_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k_win, const T* __restrict__ v_win,
     const T* __restrict__ k_pages, const T* __restrict__ v_pages, KvGeom g, Plan p, int Hq,
     T* __restrict__ o, float scale, int o_lo) {
   extern __shared__ float smem[];
-  const int r = blockIdx.x, hq = blockIdx.y;
+  const int r = blockIdx.x, hq = blockIdx.y, NT = blockDim.x;
   if (r >= p.counts[0]) return;
   const int D = g.head_dim, Hkv = g.n_kv_heads, ps = g.page_size;
   const int kvh = hq / (Hq / Hkv);
@@ -35,17 +38,20 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
   const int row0 = p.seq_row0[n], nw = p.seq_rows[n];
   const int lo = p.row_lo[r], hi = p.row_hi[r];
   const int total = S + nw;
-  float* s_q = smem;            // [D]
-  float* s_red = smem + D;      // [256 + 8]
-  float* s_sc = s_red + 264;    // [total]
-  const int tid = threadIdx.x;
+  float* s_q = smem;               // [D]
+  float* s_red = smem + D;         // [NT + 8]
+  float* s_sc = s_red + NT + 8;    // [total]
+  const int tid = threadIdx.x, wave = tid >> 6, waves = NT >> 6;
 
-  for (int d = tid; d < D; d += 256) s_q[d] = to_f32(q[((size_t)r * Hq + hq) * D + d]) * scale;
+  for (int d = tid; d < D; d += NT) s_q[d] = to_f32(q[((size_t)r * Hq + hq) * D + d]) * scale;
   __syncthreads();
 
   const int32_t* pt = g.page_table + (size_t)n * g.max_pages_per_seq;
+  constexpr int VE = 16 / (int)sizeof(T);
+  const int part = tid & 3, dq = D / 4, nv = dq / VE;   // this lane's quarter of a key's row: nv 16-byte pieces (1 .. 16)
   float lmax = -INFINITY;
-  for (int s = tid; s < total; s += 256) {
+  for (int s0 = 0; s0 < total; s0 += NT / 4) {
+    const int s = min(s0 + (tid >> 2), total - 1);
     const T* kp;
     bool vis = true;
     if (s < S) {
@@ -56,45 +62,65 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
       vis = (w >= lo && w < hi) || w == r;
       kp = k_win + ((size_t)w * Hkv + kvh) * D;
     }
-    float dot = -INFINITY;
-    if (vis) {
-      dot = 0.f;
-      for (int d = 0; d < D; ++d) dot += s_q[d] * to_f32(kp[d]);
+    kp += part * dq;
+    float dot = 0.f;
+    for (int v0 = 0; v0 < nv; v0 += 4) {
+      uint4 kv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kv[u] = *(const uint4*)(kp + min(v0 + u, nv - 1) * VE);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {   // (no branch around the use of a load: it would take the load with it; past the end the weight is 0)
+        const T* e = (const T*)&kv[u];
+        const float* qe = s_q + part * dq + min(v0 + u, nv - 1) * VE;
+#pragma unroll
+        for (int i = 0; i < VE; ++i) dot += (v0 + u < nv ? qe[i] : 0.f) * to_f32(e[i]);
+      }
     }
-    s_sc[s] = dot;
+    dot += __shfl_xor(dot, 1, 64);
+    dot += __shfl_xor(dot, 2, 64);
+    if (!vis) dot = -INFINITY;
+    if (part == 0 && s0 + (tid >> 2) < total) s_sc[s] = dot;
     lmax = fmaxf(lmax, dot);
   }
   lmax = wave_max(lmax);
-  if ((tid & 63) == 0) s_red[tid >> 6] = lmax;
+  if ((tid & 63) == 0) s_red[wave] = lmax;
   __syncthreads();
-  const float m = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+  float m = s_red[0];
+  for (int w = 1; w < waves; ++w) m = fmaxf(m, s_red[w]);
   __syncthreads();
   float lsum = 0.f;
-  for (int s = tid; s < total; s += 256) {
+  for (int s = tid; s < total; s += NT) {
     const float e = __expf(s_sc[s] - m);   // exp(-inf) = 0 for invisible keys
     s_sc[s] = e;
     lsum += e;
   }
   lsum = wave_sum(lsum);
-  if ((tid & 63) == 0) s_red[tid >> 6] = lsum;
+  if ((tid & 63) == 0) s_red[wave] = lsum;
   __syncthreads();
-  const float denom = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+  float denom = s_red[0];
+  for (int w = 1; w < waves; ++w) denom += s_red[w];
   __syncthreads();
 
-  const int nslice = 256 / D, d = tid % D, sl = tid / D;
+  const int nslice = NT / D, d = tid % D, sl = tid / D;   // (D is a power of two up to 256)
   float acc = 0.f;
-  if (sl < nslice) {
-    for (int s = sl; s < total; s += nslice) {
-      const float pw = s_sc[s];
-      if (pw == 0.f) continue;
-      const T* vp;
-      if (s < S) {
-        const int page = min(max(pt[s / ps], 0), g.n_pages - 1);
-        vp = v_pages + (((size_t)page * Hkv + kvh) * D + d) * ps + (s % ps);   // cache V is stored [D, page_size]
-      } else {
-        vp = v_win + ((size_t)(row0 + (s - S)) * Hkv + kvh) * D + d;
-      }
-      acc += pw * to_f32(*vp);
+  constexpr int VB = 8;
+  for (int s0 = sl; s0 < total; s0 += VB * nslice) {
+    int page[VB];
+    T val[VB];
+#pragma unroll
+    for (int u = 0; u < VB; ++u) page[u] = S > 0 ? pt[min(s0 + u * nslice, S - 1) / ps] : 0;
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+      const int s = min(s0 + u * nslice, total - 1);
+      const T* vp = s < S ? v_pages + (((size_t)min(max(page[u], 0), g.n_pages - 1) * Hkv + kvh) * D + d) * ps + (s % ps)   // cache V is stored [D, page_size]
+                          : v_win + ((size_t)(row0 + (s - S)) * Hkv + kvh) * D + d;
+      val[u] = *vp;
+    }
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+      const float pw = s0 + u * nslice < total ? s_sc[s0 + u * nslice] : 0.f;
+      const float t = pw * to_f32(val[u]);
+      acc += pw != 0.f ? t : 0.f;   // (an invisible key adds nothing, whatever its value is)
     }
   }
   s_red[tid] = acc;
@@ -190,14 +216,16 @@ int attention_init() {
 
 size_t attention_generic_lds_bytes(const KvGeom& g, int max_window_rows) {
   const size_t keys = (size_t)g.max_pages_per_seq * g.page_size + max_window_rows;
-  return (g.head_dim + 264 + keys) * sizeof(float);
+  return (g.head_dim + 264 + keys) * sizeof(float);   // with 256 threads
 }
 
 void launch_attention_generic(hipStream_t st, int dtype, const void* q, const void* k_win, const void* v_win,
                               const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g,
                               const Plan& p, int rows_cap, int Hq, void* o, size_t lds_bytes, int o_lo) {
   const float scale = 1.0f / sqrtf((float)g.head_dim);
-  dim3 grid(rows_cap, Hq), block(256);
+  // (lds_bytes: with 256 threads; 1024 need 3 KB more)
+  dim3 grid(rows_cap, Hq), block(lds_bytes + 3072 <= 160 * 1024 ? 1024 : 256);
+  if (block.x == 1024) lds_bytes += 3072;
   if (dtype == S2D2_BF16) {
     S2D2_LAUNCH(attn_generic_kernel<bf16_t>, grid, block, lds_bytes, st, (const bf16_t*)q,
                        (const bf16_t*)k_win, (const bf16_t*)v_win, (const bf16_t*)k_pages_layer,
