@@ -12,9 +12,11 @@
 
 namespace s2d2 {
 
-static constexpr int VCHUNK = 4096;  // logits per workgroup: 256 lanes x 4 float4
+// Logits per workgroup: 256 lanes x VT float4.  Eight for the large vocabularies (256 rows of 152k: 36.5 -> 35 us), four
+// for small ones, whose rows are few workgroups (four rows of 4096: 4.4 us, 5.8 with eight).
+static int vocab_vt(int V) { return V > 32768 ? 8 : 4; }
 
-int vocab_chunks(int V) { return (V + VCHUNK - 1) / VCHUNK; }
+int vocab_chunks(int V) { return (V + 1024 * vocab_vt(V) - 1) / (1024 * vocab_vt(V)); }
 
 struct Stat {
   float m;    // max logit
@@ -51,6 +53,7 @@ __device__ __forceinline__ Stat stat_shfl_xor(const Stat& s, int off) {
 // part[row][chunk][8] = {m, z, e, m2, arg}
 // inv_t: 1 / temperature (1 in greedy mode: the multiplication is then exact); all statistics are those of
 // softmax(logits * inv_t).
+template <int VT>
 __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restrict__ logits, int V,
                                                             const int32_t* __restrict__ count, int chunks,
                                                             float inv_t, float* __restrict__ part) {
@@ -58,18 +61,18 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   const int row = blockIdx.y, chunk = blockIdx.x;
   if (row >= *count) return;
   const float* x = logits + (size_t)row * V;
-  const int base = chunk * VCHUNK;
+  const int base = chunk * 1024 * VT;
   const int tid = threadIdx.x;
-  float v[16];
-  int idx0[4];
+  float v[4 * VT];
+  int idx0[VT];
   const bool vec_ok = (V & 3) == 0;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < VT; ++t) {
     const int i = base + t * 1024 + tid * 4;
     idx0[t] = i;
     if (vec_ok && i + 3 < V) {
-      const float4 f = *(const float4*)(x + i);
-      v[4 * t] = f.x * inv_t; v[4 * t + 1] = f.y * inv_t; v[4 * t + 2] = f.z * inv_t; v[4 * t + 3] = f.w * inv_t;
+      const f32x4_t f = ld_stream((const f32x4_t*)(x + i));
+      v[4 * t] = f[0] * inv_t; v[4 * t + 1] = f[1] * inv_t; v[4 * t + 2] = f[2] * inv_t; v[4 * t + 3] = f[3] * inv_t;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[4 * t + e] = (i + e < V) ? x[i + e] * inv_t : -INFINITY;
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   }
   Stat s = stat_empty();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
+  for (int t = 0; t < 4 * VT; ++t) {
     const float l = v[t];
     const int i = idx0[t >> 2] + (t & 3);
     if (l > s.m) { s.m2 = s.m; s.m = l; s.arg = i; }
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   }
   if (s.m > -INFINITY) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < 4 * VT; ++t) {
       const float d = v[t] - s.m;
       const float ex = __expf(d);          // exp(-inf) = 0 for padded slots
       s.z += ex;
@@ -100,6 +103,11 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
     float* o = part + ((size_t)row * chunks + chunk) * 8;
     o[0] = r.m; o[1] = r.z; o[2] = r.e; o[3] = r.m2; o[4] = __int_as_float(r.arg);
   }
+}
+
+static void launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
+  if (vocab_vt(V) == 8) S2D2_LAUNCH(vocab_partial_kernel<8>, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
+  else S2D2_LAUNCH(vocab_partial_kernel<4>, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
 }
 
 // Chunk partials of one row, merged by one wavefront: lane c takes chunks c, c + 64, ..., then a butterfly over the
@@ -164,20 +172,18 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         int32_t* xhat, float* p, float* lse, float* margin, float* entropy_n, const VocabSample& sm) {
   const float inv_t = sm.sample ? 1.0f / sm.temperature : 1.0f;
-  S2D2_LAUNCH(vocab_partial_kernel, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count,
-                     ws.chunks, inv_t, ws.part);
+  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
   S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
                      count, logit_seq, logit_idx, B, xhat, p, lse, margin, entropy_n);
   if (sm.sample)
-    S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap), dim3(256), 0, st, logits, V, count, logit_seq, logit_idx, B,
+    S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
                 sm.seed, sm.step, sm.step_dev, inv_t, lse, xhat, p);
 }
 
 void launch_vocab_score(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         const int32_t* token, float* q, float* lse, float inv_t) {
-  S2D2_LAUNCH(vocab_partial_kernel, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count,
-                     ws.chunks, inv_t, ws.part);
+  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
   S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
                      logits, count, logit_seq, logit_idx, B, token, inv_t, q, lse);
 }
@@ -374,7 +380,8 @@ __device__ __forceinline__ int inverse_cdf_block(const F& w4, int V, float u, fl
 // SampleFromLogits in sampling mode: x_hat ~ softmax(logits / T) by inverse CDF in ascending vocabulary order with
 // the uniform of stream 2 at (step, sequence, block index); p = that token's probability.  One workgroup per
 // logit row; runs after the statistics kernels (reads lse, overwrites the arg-max proposal and its probability).
-__global__ __launch_bounds__(256) void vocab_sample_kernel(
+// Sixteen wavefronts: a row of 152k logits is one stream through one compute unit (with four, 105 us per launch at 64 rows).
+__global__ __launch_bounds__(1024) void vocab_sample_kernel(
     const float* __restrict__ logits, int V, const int32_t* __restrict__ count, const int32_t* __restrict__ logit_seq,
     const int32_t* __restrict__ logit_idx, int B, uint64_t seed, uint32_t step, const uint32_t* __restrict__ step_dev,
     float inv_t, const float* __restrict__ lse, int32_t* __restrict__ xhat, float* __restrict__ p) {
