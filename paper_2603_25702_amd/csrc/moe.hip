@@ -31,31 +31,33 @@ __global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict_
     m = fmaxf(m, v[j]);
   }
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  float p[4];
+  // top-k of the logits (softmax is monotone), lowest index on ties: a maximum over (value, index) keys of 64 bits, so that
+  // a choice is one chain of six exchanges (value, index and probability one after the other were eighteen)
+  unsigned long long key[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) p[j] = v[j] > -INFINITY ? __expf(v[j] - m) : 0.f;   // common factor 1/Z cancels in the renormalisation
-  // top-k of the logits (softmax is monotone), lowest index on ties
-  float wsel = 0.f;      // lane k keeps the k-th selected probability
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t b = __float_as_uint(v[j]);
+    const uint32_t ord = v[j] > -INFINITY ? (b & 0x80000000u ? ~b : b | 0x80000000u) : 0u;   // order of the floats as unsigned; 0: not a choice
+    key[j] = ((unsigned long long)ord << 32) | (uint32_t)~(lane + 64 * j);
+  }
+  float wsel = 0.f;      // lane k keeps the k-th selected probability (the common factor 1/Z cancels in the renormalisation)
   int esel = -1;
   float wsum = 0.f;
   for (int k = 0; k < top_k; ++k) {
-    float best = -INFINITY;
+    unsigned long long best = key[0];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) best = fmaxf(best, v[j]);
-    float bw = best;
-    for (int off = 32; off > 0; off >>= 1) bw = fmaxf(bw, __shfl_xor(bw, off, 64));
-    int cand = 0x7fffffff;
-#pragma unroll
-    for (int j = 3; j >= 0; --j)
-      if (v[j] == bw) cand = lane + 64 * j;
-    int ce = cand;
-    for (int off = 32; off > 0; off >>= 1) ce = min(ce, __shfl_xor(ce, off, 64));
-    // the owner removes it and publishes its probability
-    float pw = 0.f;
+    for (int j = 1; j < 4; ++j) best = max(best, key[j]);
+    for (int off = 32; off > 0; off >>= 1) {
+      const unsigned long long o = ((unsigned long long)(uint32_t)__shfl_xor((int)(best >> 32), off, 64) << 32) | (uint32_t)__shfl_xor((int)(uint32_t)best, off, 64);
+      best = max(best, o);
+    }
+    const uint32_t ord = (uint32_t)(best >> 32);
+    const int ce = (int)~(uint32_t)best;
+    const float bv = ord & 0x80000000u ? __uint_as_float(ord & 0x7fffffffu) : __uint_as_float(~ord);
+    const float pw = ord ? __expf(bv - m) : 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (lane + 64 * j == ce) { pw = p[j]; v[j] = -INFINITY; }
-    for (int off = 32; off > 0; off >>= 1) pw += __shfl_xor(pw, off, 64);
+      if (lane + 64 * j == ce) key[j] = (uint32_t)~ce;   // taken
     wsum += pw;
     if (lane == k) { wsel = pw; esel = ce; }
   }
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
                                                          int32_t* __restrict__ sorted, int32_t* __restrict__ tile_expert,
                                                          int32_t* __restrict__ tile_row0, int32_t* __restrict__ tile_rows,
                                                          int32_t* __restrict__ n_tiles, int tile_cap) {
-  __shared__ int s_off[MOE_MAX_E + 1], s_tile0[MOE_MAX_E + 1];
+  __shared__ int s_off[MOE_MAX_E], s_tile0[MOE_MAX_E];
   __shared__ int s_cnt[MOE_MAX_E], s_fill[MOE_MAX_E];
   const int tid = threadIdx.x;
   const int total = *m_count * top_k;
@@ -93,18 +95,30 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
     if (mine[j] >= 0) atomicAdd(&s_cnt[mine[j]], 1);
   for (int i = tid + KEEP * 1024; i < total; i += 1024) atomicAdd(&s_cnt[choice[i]], 1);
   __syncthreads();
-  if (tid == 0) {   // offsets of the groups and of their tiles
-    int run = 0, t = 0;
-    for (int e = 0; e < E; ++e) {
-      const int c = s_cnt[e];
-      s_off[e] = run;
-      s_tile0[e] = t;
-      run += c;
-      t += (c + 127) >> 7;
+  if (tid < 64) {   // offsets of the groups and of their tiles: a scan by one wavefront, four experts per lane
+    int c[4], run = 0, t = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      c[j] = 4 * tid + j < E ? s_cnt[4 * tid + j] : 0;
+      run += c[j];
+      t += (c[j] + 127) >> 7;
     }
-    s_off[E] = run;
-    s_tile0[E] = t;
-    *n_tiles = min(t, tile_cap);
+    int ri = run, ti = t;   // inclusive over the lanes
+    for (int off = 1; off < 64; off <<= 1) {
+      const int a = __shfl_up(ri, off, 64), b = __shfl_up(ti, off, 64);
+      if (tid >= off) { ri += a; ti += b; }
+    }
+    run = ri - run;
+    t = ti - t;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (4 * tid + j < E) {
+        s_off[4 * tid + j] = run;
+        s_tile0[4 * tid + j] = t;
+        run += c[j];
+        t += (c[j] + 127) >> 7;
+      }
+    if (tid == 63) *n_tiles = min(ti, tile_cap);
   }
   __syncthreads();
   for (int e = tid; e < E; e += 1024) {
