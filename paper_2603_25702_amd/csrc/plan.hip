@@ -69,8 +69,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(
   const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
   s_splits[n] = splits;
   __syncthreads();
-  // inclusive Hillis-Steele scan over the 1024 slots
-  for (int off = 1; off < 1024; off <<= 1) {
+  // inclusive Hillis-Steele scan over the sequences
+  for (int off = 1; off < N; off <<= 1) {
     int a = 0, b = 0, d = 0;
     if (n >= off) { a = s_rows[n - off]; b = s_lrows[n - off]; d = s_splits[n - off]; }
     __syncthreads();
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(
     s_splits[n] += d;
     __syncthreads();
   }
-  if (n == 1023) { p.counts[0] = s_rows[1023]; p.counts[1] = s_lrows[1023]; p.counts[2] = s_splits[1023]; }
+  if (n == N - 1) { p.counts[0] = s_rows[n]; p.counts[1] = s_lrows[n]; p.counts[2] = s_splits[n]; }
   if (n >= N) return;
   const int row0 = s_rows[n] - rows;
   int k = s_lrows[n] - lrows;
@@ -182,7 +182,7 @@ void launch_plan(hipStream_t st, int verify, int shifted, int N, int B, int mask
                  const int32_t* carry, const int32_t* xhat, const Plan& p, int32_t* logit_row_of,
                  int32_t* span_start, int32_t* span_len, int32_t* stage_row0, int32_t* stage_lead,
                  const int32_t* active, int32_t* status, int seq_cap, int split_target, int split_most, float* clear_a, float* clear_b) {
-  S2D2_LAUNCH(plan_kernel, dim3(1), dim3(1024), 0, st, verify, shifted, N, B, mask_id, ar_mask,
+  S2D2_LAUNCH(plan_kernel, dim3(1), dim3((N + 63) / 64 * 64), 0, st, verify, shifted, N, B, mask_id, ar_mask,
                      seq_len, pos0, block, carry, xhat, p, logit_row_of, span_start, span_len,
                      stage_row0, stage_lead, active, status, seq_cap, split_target, split_most, clear_a, clear_b);
 }
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int ma
   const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
   s_splits[n] = splits;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
+  for (int off = 1; off < N; off <<= 1) {
     int a = 0, d = 0;
     if (n >= off) { a = s_rows[n - off]; d = s_splits[n - off]; }
     __syncthreads();
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int ma
     s_splits[n] += d;
     __syncthreads();
   }
-  if (n == 1023) { p.counts[0] = s_rows[1023]; p.counts[1] = 0; p.counts[2] = s_splits[1023]; }
+  if (n == N - 1) { p.counts[0] = s_rows[n]; p.counts[1] = 0; p.counts[2] = s_splits[n]; }
   if (n < N) {
     p.seq_row0[n] = s_rows[n] - rows;
     p.seq_rows[n] = rows;
