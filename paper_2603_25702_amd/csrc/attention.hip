@@ -11,6 +11,8 @@
 
 namespace s2d2 {
 
+template <int I> struct Lane { static constexpr int value = I; };
+
 __device__ __forceinline__ float wave_max(float v) {
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
   return v;
@@ -20,35 +22,59 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// The launch is a chain of round trips to memory, so each of its steps requests what it can at once: a quarter-row of K
-// per lane (four lanes a key), eight V values per thread, and 1024 threads where their sums fit into LDS (with 256
-// threads, a key per thread and one V value per iteration: 16.8 us per launch at 136 keys of 64 floats).
-template <typename T>
+// Every sum has one association, whatever the batch and the cache size are: a score is one chain over the head dimension,
+// the softmax denominator the sum of 256 strided ones, P V 256 / D chains of every (256 / D)-th key.  (With four partial
+// scores a key, 1024 / D chains and 1024 strided sums where LDS had room for that many threads, the results were as close
+// to 64 bits, but a sequence's own depended on the capacity of the cache it sat in: its logits by 5e-7 of their norm, its
+// margins, differences of two nearly equal probabilities, by up to 8e-5.)
+//
+// The launch is a chain of round trips to memory, so its 1024 threads request what they can at once and hand the chains
+// on: four lanes take 16 bytes of a key's row each, in turn; P V runs through four quarters of the workgroup, VB keys of
+// a chain each, whose V values are requested ahead of the scores.  8 and 12 rows over 136 keys of 64 floats: 12.9 and
+// 13.4 us per launch; 256 threads with a key each and one V value per iteration took 16.8.
+template <typename T, int D>
 __global__ __launch_bounds__(1024) void attn_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k_win, const T* __restrict__ v_win,
     const T* __restrict__ k_pages, const T* __restrict__ v_pages, KvGeom g, Plan p, int Hq,
     T* __restrict__ o, float scale, int o_lo) {
+  constexpr int NT = 1024, VE = 16 / (int)sizeof(T), NCH = D / (4 * VE), CB = NCH < 4 ? NCH : 4;   // NCH: 16-byte pieces of a row per lane, CB: requested at once
+  constexpr int NS = 256 / D, VB = 12;
   extern __shared__ float smem[];
-  const int r = blockIdx.x, hq = blockIdx.y, NT = blockDim.x;
+  const int r = blockIdx.x, hq = blockIdx.y;
   if (r >= p.counts[0]) return;
-  const int D = g.head_dim, Hkv = g.n_kv_heads, ps = g.page_size;
+  const int Hkv = g.n_kv_heads, ps = g.page_size;
   const int kvh = hq / (Hq / Hkv);
   const int n = p.row_seq[r];
   const int S = max(0, min(g.seq_len[n], g.max_pages_per_seq * ps));
   const int row0 = p.seq_row0[n], nw = p.seq_rows[n];
   const int lo = p.row_lo[r], hi = p.row_hi[r];
   const int total = S + nw;
-  float* s_q = smem;               // [D]
-  float* s_red = smem + D;         // [NT + 8]
-  float* s_sc = s_red + NT + 8;    // [total]
-  const int tid = threadIdx.x, wave = tid >> 6, waves = NT >> 6;
+  float* s_q = smem;             // [D]
+  float* s_red = smem + D;       // [256 + 8]
+  float* s_sc = s_red + 264;     // [total]
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int32_t* pt = g.page_table + (size_t)n * g.max_pages_per_seq;
 
-  for (int d = tid; d < D; d += NT) s_q[d] = to_f32(q[((size_t)r * Hq + hq) * D + d]) * scale;
+  // V values of the keys at places e0 + VB (tid / 256) .. of this thread's chain (key = slice + NS place; past the end the last key)
+  const int quarter = tid >> 8, t8 = tid & 255, d = t8 % D, sl = t8 / D;
+  T val[VB];
+  auto load_v = [&](int e0) __attribute__((always_inline)) {
+    int page[VB];
+#pragma unroll
+    for (int u = 0; u < VB; ++u) page[u] = S > 0 ? pt[min(sl + (e0 + quarter * VB + u) * NS, S - 1) / ps] : 0;
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+      const int s = min(sl + (e0 + quarter * VB + u) * NS, total - 1);
+      const T* vp = s < S ? v_pages + (((size_t)min(max(page[u], 0), g.n_pages - 1) * Hkv + kvh) * D + d) * ps + (s % ps)   // cache V is stored [D, page_size]
+                          : v_win + ((size_t)(row0 + (s - S)) * Hkv + kvh) * D + d;
+      val[u] = *vp;
+    }
+  };
+  load_v(0);
+  for (int i = tid; i < D; i += NT) s_q[i] = to_f32(q[((size_t)r * Hq + hq) * D + i]) * scale;
   __syncthreads();
 
-  const int32_t* pt = g.page_table + (size_t)n * g.max_pages_per_seq;
-  constexpr int VE = 16 / (int)sizeof(T);
-  const int part = tid & 3, dq = D / 4, nv = dq / VE;   // this lane's quarter of a key's row: nv 16-byte pieces (1 .. 16)
+  const int part = tid & 3;
   float lmax = -INFINITY;
   for (int s0 = 0; s0 < total; s0 += NT / 4) {
     const int s = min(s0 + (tid >> 2), total - 1);
@@ -62,22 +88,28 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
       vis = (w >= lo && w < hi) || w == r;
       kp = k_win + ((size_t)w * Hkv + kvh) * D;
     }
-    kp += part * dq;
-    float dot = 0.f;
-    for (int v0 = 0; v0 < nv; v0 += 4) {
-      uint4 kv[4];
+    float dot = 0.f;   // the same in all four lanes of the key
 #pragma unroll
-      for (int u = 0; u < 4; ++u) kv[u] = *(const uint4*)(kp + min(v0 + u, nv - 1) * VE);
+    for (int c0 = 0; c0 < NCH; c0 += CB) {
+      uint4 kv[CB];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {   // (no branch around the use of a load: it would take the load with it; past the end the weight is 0)
-        const T* e = (const T*)&kv[u];
-        const float* qe = s_q + part * dq + min(v0 + u, nv - 1) * VE;
+      for (int c = 0; c < CB; ++c) kv[c] = *(const uint4*)(kp + ((c0 + c) * 4 + part) * VE);
 #pragma unroll
-        for (int i = 0; i < VE; ++i) dot += (v0 + u < nv ? qe[i] : 0.f) * to_f32(e[i]);
+      for (int c = 0; c < CB; ++c) {
+        const T* e = (const T*)&kv[c];
+        const float* qe = s_q + ((c0 + c) * 4 + part) * VE;
+        float qv[VE];
+#pragma unroll
+        for (int i = 0; i < VE; ++i) qv[i] = qe[i];
+        auto turn = [&](auto P) __attribute__((always_inline)) {   // lane P of the four adds its piece and passes the sum on
+          float t = dot;
+#pragma unroll
+          for (int i = 0; i < VE; ++i) t = __builtin_fmaf(qv[i], to_f32(e[i]), t);
+          dot = __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(t), decltype(P)::value * 0x55, 0xf, 0xf, true));
+        };
+        turn(Lane<0>{}); turn(Lane<1>{}); turn(Lane<2>{}); turn(Lane<3>{});
       }
     }
-    dot += __shfl_xor(dot, 1, 64);
-    dot += __shfl_xor(dot, 2, 64);
     if (!vis) dot = -INFINITY;
     if (part == 0 && s0 + (tid >> 2) < total) s_sc[s] = dot;
     lmax = fmaxf(lmax, dot);
@@ -86,48 +118,46 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   if ((tid & 63) == 0) s_red[wave] = lmax;
   __syncthreads();
   float m = s_red[0];
-  for (int w = 1; w < waves; ++w) m = fmaxf(m, s_red[w]);
+  for (int w = 1; w < NT / 64; ++w) m = fmaxf(m, s_red[w]);
   __syncthreads();
-  float lsum = 0.f;
-  for (int s = tid; s < total; s += NT) {
-    const float e = __expf(s_sc[s] - m);   // exp(-inf) = 0 for invisible keys
-    s_sc[s] = e;
-    lsum += e;
+  if (tid < 256) {
+    float lsum = 0.f;
+    for (int s = tid; s < total; s += 256) {
+      const float e = __expf(s_sc[s] - m);   // exp(-inf) = 0 for invisible keys
+      s_sc[s] = e;
+      lsum += e;
+    }
+    lsum = wave_sum(lsum);
+    if ((tid & 63) == 0) s_red[wave] = lsum;
   }
-  lsum = wave_sum(lsum);
-  if ((tid & 63) == 0) s_red[wave] = lsum;
   __syncthreads();
-  float denom = s_red[0];
-  for (int w = 1; w < waves; ++w) denom += s_red[w];
+  const float denom = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
   __syncthreads();
 
-  const int nslice = NT / D, d = tid % D, sl = tid / D;   // (D is a power of two up to 256)
-  float acc = 0.f;
-  constexpr int VB = 8;
-  for (int s0 = sl; s0 < total; s0 += VB * nslice) {
-    int page[VB];
-    T val[VB];
-#pragma unroll
-    for (int u = 0; u < VB; ++u) page[u] = S > 0 ? pt[min(s0 + u * nslice, S - 1) / ps] : 0;
+  for (int e0 = 0; e0 * NS < total; e0 += 4 * VB) {
+    if (e0) load_v(e0);
+    float pw[VB];
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
-      const int s = min(s0 + u * nslice, total - 1);
-      const T* vp = s < S ? v_pages + (((size_t)min(max(page[u], 0), g.n_pages - 1) * Hkv + kvh) * D + d) * ps + (s % ps)   // cache V is stored [D, page_size]
-                          : v_win + ((size_t)(row0 + (s - S)) * Hkv + kvh) * D + d;
-      val[u] = *vp;
+      const int s = sl + (e0 + quarter * VB + u) * NS;
+      pw[u] = s < total ? s_sc[s] : 0.f;
     }
+    for (int w = 0; w < 4; ++w) {
+      if (quarter == w) {
+        float acc = e0 + w ? s_red[t8] : 0.f;
 #pragma unroll
-    for (int u = 0; u < VB; ++u) {
-      const float pw = s0 + u * nslice < total ? s_sc[s0 + u * nslice] : 0.f;
-      const float t = pw * to_f32(val[u]);
-      acc += pw != 0.f ? t : 0.f;   // (an invisible key adds nothing, whatever its value is)
+        for (int u = 0; u < VB; ++u) {
+          const float t = __builtin_fmaf(pw[u], to_f32(val[u]), acc);
+          acc = pw[u] != 0.f ? t : acc;   // (an invisible key adds nothing, whatever its value is)
+        }
+        s_red[t8] = acc;
+      }
+      __syncthreads();
     }
   }
-  s_red[tid] = acc;
-  __syncthreads();
   if (tid < D) {
     float t = 0.f;
-    for (int i = 0; i < nslice; ++i) t += s_red[i * D + tid];
+    for (int i = 0; i < NS; ++i) t += s_red[i * D + tid];
     if (sizeof(T) == 2 && o_lo < 0) ((bf16_t*)o)[act_offset(o_lo, r, hq * D + tid, Hq * D)] = f32_to_f16_bits(t / denom);   // the consuming GEMM runs on half operands
     else o[((size_t)r * Hq + hq) * D + tid] = from_f32<T>(t / denom);
   }
@@ -207,8 +237,12 @@ void launch_fill_i32(hipStream_t st, int32_t* p, int n, int32_t v) {
 
 // Raises the dynamic-LDS limit of the kernels once (160 KB per workgroup on gfx950).
 int attention_init() {
-  hipError_t e = hipFuncSetAttribute((const void*)attn_generic_kernel<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_generic_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  hipError_t e = hipSuccess;
+  auto limit = [&](const void* f) { if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); };
+  limit((const void*)attn_generic_kernel<bf16_t, 32>); limit((const void*)attn_generic_kernel<float, 32>);
+  limit((const void*)attn_generic_kernel<bf16_t, 64>); limit((const void*)attn_generic_kernel<float, 64>);
+  limit((const void*)attn_generic_kernel<bf16_t, 128>); limit((const void*)attn_generic_kernel<float, 128>);
+  limit((const void*)attn_generic_kernel<bf16_t, 256>); limit((const void*)attn_generic_kernel<float, 256>);
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_flash_kernel<8, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_lds(8));
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_flash_kernel<8, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_lds(8));
   return e == hipSuccess ? 0 : -1;
@@ -216,25 +250,31 @@ int attention_init() {
 
 size_t attention_generic_lds_bytes(const KvGeom& g, int max_window_rows) {
   const size_t keys = (size_t)g.max_pages_per_seq * g.page_size + max_window_rows;
-  return (g.head_dim + 264 + keys) * sizeof(float);   // with 256 threads
+  return (g.head_dim + 264 + keys) * sizeof(float);
+}
+
+template <typename T, int D>
+static void launch_generic(hipStream_t st, const void* q, const void* k_win, const void* v_win, const void* k_pages, const void* v_pages,
+                           const KvGeom& g, const Plan& p, int rows_cap, int Hq, void* o, size_t lds_bytes, int o_lo) {
+  S2D2_LAUNCH((attn_generic_kernel<T, D>), dim3(rows_cap, Hq), dim3(1024), lds_bytes, st, (const T*)q, (const T*)k_win, (const T*)v_win,
+              (const T*)k_pages, (const T*)v_pages, g, p, Hq, (T*)o, 1.0f / sqrtf((float)D), o_lo);
 }
 
 void launch_attention_generic(hipStream_t st, int dtype, const void* q, const void* k_win, const void* v_win,
                               const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g,
                               const Plan& p, int rows_cap, int Hq, void* o, size_t lds_bytes, int o_lo) {
-  const float scale = 1.0f / sqrtf((float)g.head_dim);
-  // (lds_bytes: with 256 threads; 1024 need 3 KB more)
-  dim3 grid(rows_cap, Hq), block(lds_bytes + 3072 <= 160 * 1024 ? 1024 : 256);
-  if (block.x == 1024) lds_bytes += 3072;
-  if (dtype == S2D2_BF16) {
-    S2D2_LAUNCH(attn_generic_kernel<bf16_t>, grid, block, lds_bytes, st, (const bf16_t*)q,
-                       (const bf16_t*)k_win, (const bf16_t*)v_win, (const bf16_t*)k_pages_layer,
-                       (const bf16_t*)v_pages_layer, g, p, Hq, (bf16_t*)o, scale, o_lo);
-  } else {
-    S2D2_LAUNCH(attn_generic_kernel<float>, grid, block, lds_bytes, st, (const float*)q,
-                       (const float*)k_win, (const float*)v_win, (const float*)k_pages_layer,
-                       (const float*)v_pages_layer, g, p, Hq, (float*)o, scale, 0);
+#define S2D2_GENERIC(DV)                                                                                                          \
+  case DV:                                                                                                                        \
+    if (dtype == S2D2_BF16) launch_generic<bf16_t, DV>(st, q, k_win, v_win, k_pages_layer, v_pages_layer, g, p, rows_cap, Hq, o, lds_bytes, o_lo); \
+    else launch_generic<float, DV>(st, q, k_win, v_win, k_pages_layer, v_pages_layer, g, p, rows_cap, Hq, o, lds_bytes, 0);       \
+    break
+  switch (g.head_dim) {   // (the description's check admits no others)
+    S2D2_GENERIC(32);
+    S2D2_GENERIC(64);
+    S2D2_GENERIC(128);
+    S2D2_GENERIC(256);
   }
+#undef S2D2_GENERIC
 }
 
 }  // namespace s2d2

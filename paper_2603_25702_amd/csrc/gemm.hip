@@ -32,8 +32,8 @@ template <> struct Mma<float> {
   }
 };
 
-template <typename T, int EPI, int NW>
-__global__ __launch_bounds__(NW * 64) void gemm_rows16_kernel(const T* __restrict__ X, int ldx,
+template <typename T, int EPI, int PASSES>
+__global__ __launch_bounds__(256) void gemm_rows16_kernel(const T* __restrict__ X, int ldx,
                                                           const T* __restrict__ W, int K, int N,
                                                           const int32_t* __restrict__ m_count,
                                                           void* __restrict__ out, int ldo) {
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows16_kernel(const T* __restric
   constexpr int U = 4;               // fragment loads in flight per operand
   constexpr int KC = U * KSTEP;
   constexpr int NACC = EPI == EPI_SWIGLU ? 2 : 1;
-  __shared__ float red[NW][NACC][256];
+  __shared__ float red[4][NACC][256];
 
   const int M = *m_count;
   const int m0 = blockIdx.y * 16;
@@ -60,13 +60,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows16_kernel(const T* __restric
   f32x4_t acc[NACC];
   for (int a = 0; a < NACC; ++a) acc[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  for (int k0 = wave * KC; k0 < K; k0 += NW * KC) {
-    uint4 wa[U], wb[U], xb[U];
+  for (int k0 = wave * KC; k0 < K; k0 += PASSES * 4 * KC) {
+    constexpr int UP = U * PASSES;
+    uint4 wa[UP], wb[UP], xb[UP];
+    auto k_of = [&](int t) { return k0 + t / U * (4 * KC) + t % U * KSTEP; };
 #pragma unroll
-    for (int t = 0; t < U; ++t) {
+    for (int t = 0; t < UP; ++t) {
       // unconditional loads, clamped to K (a multiple of KSTEP): under a condition they would wait for each other;
       // window rows past the count read row m0, their results are never stored
-      const int k = min(k0 + t * KSTEP, K - KSTEP);
+      const int k = min(k_of(t), K - KSTEP);
       wa[t] = *(const uint4*)(wp + k);
       if (EPI == EPI_SWIGLU) wb[t] = *(const uint4*)(wp2 + k);
       xb[t] = *(const uint4*)(xp + k);
@@ -75,28 +77,23 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows16_kernel(const T* __restric
       acc[0] = Mma<T>::run(wa[t], xb[t], acc[0]);
       if (EPI == EPI_SWIGLU) acc[NACC - 1] = Mma<T>::run(wb[t], xb[t], acc[NACC - 1]);
     };
-    if (k0 + KC <= K) {   // a whole batch: nothing between its loads and its products
+    if (k_of(UP - 1) + KSTEP <= K) {   // whole passes: nothing between their loads and their products
 #pragma unroll
-      for (int t = 0; t < U; ++t) mac(t);
+      for (int t = 0; t < UP; ++t) mac(t);
     } else {
 #pragma unroll
-      for (int t = 0; t < U; ++t)
-        if (k0 + t * KSTEP < K) mac(t);
+      for (int t = 0; t < UP; ++t)
+        if (k_of(t) < K) mac(t);
     }
   }
   // acc[a][i] = Y[m0 + f][n0 + 4 g + i]
   for (int a = 0; a < NACC; ++a)
     for (int i = 0; i < 4; ++i) red[wave][a][i * 64 + lane] = acc[a][i];
   __syncthreads();
-  if (threadIdx.x >= 256) return;
   const int row = threadIdx.x >> 4, fe = threadIdx.x & 15;
   const int src = (fe & 3) * 64 + (fe >> 2) * 16 + row;
   float v[NACC];
-  for (int a = 0; a < NACC; ++a) {
-    v[a] = (red[0][a][src] + red[1][a][src]) + (red[2][a][src] + red[3][a][src]);
-#pragma unroll
-    for (int w = 4; w < NW; w += 4) v[a] += (red[w][a][src] + red[w + 1][a][src]) + (red[w + 2][a][src] + red[w + 3][a][src]);
-  }
+  for (int a = 0; a < NACC; ++a) v[a] = (red[0][a][src] + red[1][a][src]) + (red[2][a][src] + red[3][a][src]);
   const int m = m0 + row, n = n0 + fe;
   if (m >= M || n >= N) return;
   if (EPI == EPI_STORE_F32) {
@@ -112,13 +109,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows16_kernel(const T* __restric
 template <typename T, int EPI>
 static void launch_e(hipStream_t st, const T* X, int ldx, const T* W, int K, int N, const int32_t* m_count, int m_cap, void* out, int ldo) {
   const dim3 grid((N + 15) / 16, (m_cap + 15) / 16);
-  // A pass of the four wavefronts covers 64 to 128 inputs each.  Where K is longer and the workgroups are few, sixteen
-  // wavefronts take it in one pass instead of several round trips (down projection of the fp32 model, 16 workgroups,
-  // K 768: 10 -> 5 us).
-  if (K > 4 * 16 * Mma<T>::KV && (long long)grid.x * grid.y <= 256)
-    S2D2_LAUNCH((gemm_rows16_kernel<T, EPI, 16>), grid, dim3(1024), 0, st, X, ldx, W, K, N, m_count, out, ldo);
-  else
-    S2D2_LAUNCH((gemm_rows16_kernel<T, EPI, 4>), grid, dim3(256), 0, st, X, ldx, W, K, N, m_count, out, ldo);
+  // A pass of the four wavefronts covers 16 fragments (256 inputs in fp32).  Where K is longer and the workgroups are at
+  // most one per compute unit, the loads of up to four passes are in flight at once (down projection of the fp32 model, 16
+  // workgroups, K 768: 4.8 us per launch, 10 one pass at a time); past that the registers are better spent on further
+  // workgroups.  The products keep their order, so a row's result does not depend on the form.
+  const int passes = (K + 16 * 4 * Mma<T>::KV - 1) / (16 * 4 * Mma<T>::KV);
+#define S2D2_ROWS16(P) S2D2_LAUNCH((gemm_rows16_kernel<T, EPI, P>), grid, dim3(256), 0, st, X, ldx, W, K, N, m_count, out, ldo)
+  if (passes == 1 || (long long)grid.x * grid.y > 256) S2D2_ROWS16(1);
+  else if (passes == 2) S2D2_ROWS16(2);
+  else if (passes == 3) S2D2_ROWS16(3);
+  else S2D2_ROWS16(4);
+#undef S2D2_ROWS16
 }
 
 template <typename T>
