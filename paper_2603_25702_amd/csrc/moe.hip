@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict_
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int e = lane + 64 * j;
-    v[j] = e < E ? logits[(size_t)row * E + e] : -INFINITY;
+    v[j] = e < E ? logits[(size_t)row * E + e] + 0.0f : -INFINITY;   // (-0 becomes +0: the two are a tie)
     m = fmaxf(m, v[j]);
   }
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
