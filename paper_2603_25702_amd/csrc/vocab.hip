@@ -12,11 +12,15 @@
 
 namespace s2d2 {
 
-// Logits per workgroup: 256 lanes x VT float4.  Eight for the large vocabularies (256 rows of 152k: 36.5 -> 35 us), four
-// for small ones, whose rows are few workgroups (four rows of 4096: 4.4 us, 5.8 with eight).
-static int vocab_vt(int V) { return V > 32768 ? 8 : 4; }
+// Logits per workgroup: 256 lanes x VT float4.  A workgroup's loads are all in flight at once, so with few workgroups the
+// launch lasts as long as one of them: four float4 per lane, until there are 16384 workgroups (64 per compute unit), where
+// half as many of twice the size take less.  Four against eight, us per launch: rows of 151936 logits (38 workgroups each)
+// 4 rows 6.5 / 9.6, 16 8.2 / 10.7, 64 14.6 / 14.7, 256 33.7 / 35.2, 512 62.2 / 57.7, 1024 133 / 108; rows of 65536 (16 each)
+// 64 rows 9.0 / 11.4, 512 30.1 / 30.0, 1024 52.2 / 48.0; rows of 40000 (10 each) 1024 rows 34.4 / 35.0.
+static int chunks_of(int V, int vt) { return (V + 1024 * vt - 1) / (1024 * vt); }
+static int vocab_vt(int V, int rows) { return (long long)rows * chunks_of(V, 4) >= 16384 ? 8 : 4; }
 
-int vocab_chunks(int V) { return (V + 1024 * vocab_vt(V) - 1) / (1024 * vocab_vt(V)); }
+int vocab_chunks(int V) { return chunks_of(V, 4); }   // the most that any launch uses
 
 struct Stat {
   float m;    // max logit
@@ -105,9 +109,12 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   }
 }
 
-static void launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
-  if (vocab_vt(V) == 8) S2D2_LAUNCH(vocab_partial_kernel<8>, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
-  else S2D2_LAUNCH(vocab_partial_kernel<4>, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
+// Returns the chunks per row that it wrote.
+static int launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
+  const int vt = vocab_vt(V, rows_cap), chunks = chunks_of(V, vt);
+  if (vt == 8) S2D2_LAUNCH(vocab_partial_kernel<8>, dim3(chunks, rows_cap), dim3(256), 0, st, logits, V, count, chunks, inv_t, ws.part);
+  else S2D2_LAUNCH(vocab_partial_kernel<4>, dim3(chunks, rows_cap), dim3(256), 0, st, logits, V, count, chunks, inv_t, ws.part);
+  return chunks;
 }
 
 // Chunk partials of one row, merged by one wavefront: lane c takes chunks c, c + 64, ..., then a butterfly over the
@@ -172,8 +179,8 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         int32_t* xhat, float* p, float* lse, float* margin, float* entropy_n, const VocabSample& sm) {
   const float inv_t = sm.sample ? 1.0f / sm.temperature : 1.0f;
-  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
+  const int chunks = launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
+  S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, chunks, V,
                      count, logit_seq, logit_idx, B, xhat, p, lse, margin, entropy_n);
   if (sm.sample)
     S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
@@ -183,8 +190,8 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
 void launch_vocab_score(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         const int32_t* token, float* q, float* lse, float inv_t) {
-  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
+  const int chunks = launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
+  S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, chunks, V,
                      logits, count, logit_seq, logit_idx, B, token, inv_t, q, lse);
 }
 
