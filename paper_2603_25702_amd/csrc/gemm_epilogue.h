@@ -7,13 +7,20 @@ namespace s2d2 {
 
 // v0 (and v1, the up projection, for SwiGLU): v[i] = sum of output row orow (this lane's row; live: it exists), feature
 // nt * 16 + 4 g + i, g = lane / 16; rs scales it.  The whole wavefront calls it with one nt (the norm's partial sums and
-// the rotation pairs travel between lanes); nt >= NT does nothing.  h0: the residual's four values at that place,
-// requested by the caller ahead of time (SEPI_ADD_F32).
-template <int EPI>
+// the rotation pairs travel between lanes); nt >= NT does nothing.  h0 (SEPI_ADD_F32): the residual's four values at that
+// place where the caller has requested them ahead of time, else they are read here.  FRAG_OUT: activation rows may be
+// wanted in fragment order; false where they never are.  (The tiled kernel's residual adds on row-major inputs, with the
+// values read in a region of their own and the choice of the layout compiled in, took 70 us per launch; without either
+// 66.5.  8B-shaped output and down projection, 512 rows.)
+template <int EPI, bool FRAG_OUT>
 __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const bool live, const int orow, const float rs,
-                                              const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4& h0) {
+                                              const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4* h0) {
   if (nt >= a.NT) return;   // uniform over the wavefront
   const int n = nt * 16 + 4 * g;
+  auto put4 = [&](bf16_t* base, int lo, int ld, float x, float y, float z, float w) __attribute__((always_inline)) {
+    if (FRAG_OUT) act_put4(base, lo, orow, n, ld, x, y, z, w);
+    else act_store4(base + (size_t)orow * ld + n, lo, x, y, z, w);
+  };
   if (EPI == SEPI_STORE_F32) {
     if (live) {
       float* op = (float*)a.out + (size_t)orow * a.ldo + n;
@@ -26,14 +33,16 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
   } else if (EPI == SEPI_ADD_F32) {   // N is a multiple of 16 here: four features per lane as one 16-byte access
     float hv[4] = {0.f, 0.f, 0.f, 0.f};
     if (live) {
-      hv[0] = h0.x + v0[0] * rs;
-      hv[1] = h0.y + v0[1] * rs;
-      hv[2] = h0.z + v0[2] * rs;
-      hv[3] = h0.w + v0[3] * rs;
-      *(float4*)((float*)a.out + (size_t)orow * a.ldo + n) = make_float4(hv[0], hv[1], hv[2], hv[3]);
+      float4* hp = (float4*)((float*)a.out + (size_t)orow * a.ldo + n);
+      const float4 h = h0 ? *h0 : *hp;
+      hv[0] = h.x + v0[0] * rs;
+      hv[1] = h.y + v0[1] * rs;
+      hv[2] = h.z + v0[2] * rs;
+      hv[3] = h.w + v0[3] * rs;
+      *hp = make_float4(hv[0], hv[1], hv[2], hv[3]);
       if (a.xg_out) {
         const float4 gn = *(const float4*)(a.gain_next + n);
-        act_put4(a.xg_out, a.xg_lo, orow, n, a.xg_ld, hv[0] * gn.x, hv[1] * gn.y, hv[2] * gn.z, hv[3] * gn.w);
+        put4(a.xg_out, a.xg_lo, a.xg_ld, hv[0] * gn.x, hv[1] * gn.y, hv[2] * gn.z, hv[3] * gn.w);
       }
     }
     if (a.ss_out) {
@@ -50,7 +59,7 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
         const float gate = v0[i] * rs, up = v1[i] * rs;
         sv[i] = gate / (1.0f + __expf(-gate)) * up;
       }
-      act_put4((bf16_t*)a.out, a.out_lo, orow, n, a.ldo, sv[0], sv[1], sv[2], sv[3]);
+      put4((bf16_t*)a.out, a.out_lo, a.ldo, sv[0], sv[1], sv[2], sv[3]);
     }
   } else {  // SEPI_QKV_ROPE: features 0-7 of a tile pair with features 8-15 (lanes 32 apart)
     const int D = a.D, half = D >> 1, tiles_per_head = D / 16;

@@ -242,7 +242,7 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
         }
       }
       const int r = rb * 16 + fm;
-      gemm_epi_unit<EPI>(a, r < Mloc, m0 + min(r, Mloc - 1), EPI == SEPI_ADD_F32 ? 1.0f : s_rs[r], nt, gm, sum[0], sum[NACC - 1], h0[q]);
+      gemm_epi_unit<EPI, true>(a, r < Mloc, m0 + min(r, Mloc - 1), EPI == SEPI_ADD_F32 ? 1.0f : s_rs[r], nt, gm, sum[0], sum[NACC - 1], &h0[q]);
     }
   }
 }

@@ -374,9 +374,7 @@ __device__ __forceinline__ bool gemm_tile_body(const GemmStreamArgs& a, const in
     const int orow = live ? s_orow[r] : 0;
     const float rs = s_rs[r];
     const int nt = nt0 + t;
-    float4 h0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (EPI == SEPI_ADD_F32 && live && nt < a.NT) h0 = *(const float4*)((const float*)a.out + (size_t)orow * a.ldo + nt * 16 + 4 * g);
-    gemm_epi_unit<EPI>(a, live, orow, rs, nt, g, v0, v1, h0);
+    gemm_epi_unit<EPI, FRAG>(a, live, orow, rs, nt, g, v0, v1, nullptr);
   };
 
   if (KS == 1) {
