@@ -370,7 +370,7 @@ void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_ca
     case SEPI_QKV_ROPE: S2D2_MID(SEPI_QKV_ROPE); break;
     case SEPI_ADD_F32: S2D2_MID(SEPI_ADD_F32); break;
     case SEPI_SWIGLU: S2D2_MID(SEPI_SWIGLU); break;
-    case SEPI_STORE_F32: S2D2_MID(SEPI_STORE_F32); break;
+    case SEPI_STORE_F32: launch_mid_kind<SEPI_STORE_F32, 4>(st, a, m_cap); break;   // (taken up to 64 rows only)
   }
 #undef S2D2_MID
 }
