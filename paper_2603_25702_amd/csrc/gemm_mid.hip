@@ -292,7 +292,7 @@ __global__ __launch_bounds__(MID_NW * 64, 2) void gemm_mid_kernel(const GemmStre
 }
 
 // Most rows of a QKV, output or down projection (see below).
-int gemm_mid_most_rows(int NT, int KT) { const long long tiles = (long long)NT * KT; return tiles <= 16384 ? 256 : tiles <= 65536 ? 192 : 160; }
+int gemm_mid_most_rows(int NT, int KT) { const long long tiles = (long long)NT * KT; return tiles <= 16384 ? 256 : tiles <= 65536 ? 192 : MID_LEAST_MOST_ROWS; }
 
 // The lines against the neighbours (us per launch, weights from memory; this kernel / the other one):
 //   16 rows and fewer stay with the streaming kernel: 1.7B-shaped layer 37 / 32 (QKV, output, gate / up, down added up)

@@ -393,6 +393,8 @@ static void launch_pair(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
   S2D2_LAUNCH((gemm_stream_kernel<SEPI_ADD_F32, SPRO_BF16, NW, 1, U, OPM, true>), grid, block, lds, st, a);
 }
 
+static constexpr int STREAM_MOST_ROWS = 32;   // two row tiles
+
 // Launch shapes (wavefronts per workgroup, feature tiles per workgroup, loads in flight per wavefront), tuned on the
 // 1.7B shape: the layer matrices want >= 256 workgroups; with the sliding-window K loop the step time moved by less
 // than 2 % over twenty shapes, so one shape per kind is compiled, and each is compared with the CPU reference by the
@@ -408,7 +410,12 @@ void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m
     launch_gemm_mid(st, kind, a, m_cap);
     return;
   }
-  if (m_cap > 32 && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) {
+  // The streaming kernel below takes half operands in fragment order only, except the ones that a store reads: a forward
+  // lays them out so whenever it expects at most MID_LEAST_MOST_ROWS rows, and a caller that did not is sent to the tiled
+  // kernel, which takes rows too.
+  static_assert(MID_LEAST_MOST_ROWS >= STREAM_MOST_ROWS, "windows of the streaming kernel are laid out in fragment order");
+  const bool half_rows = a.x_lo == LO_F16 && kind != SEPI_STORE_F32;
+  if ((m_cap > STREAM_MOST_ROWS || half_rows) && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) {
     launch_gemm_tile(st, kind, kind == SEPI_ADD_F32 ? SPRO_BF16 : SPRO_BF16S, a, (m_cap + 127) / 128);
     return;
   }

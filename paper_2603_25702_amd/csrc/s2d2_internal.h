@@ -230,7 +230,7 @@ struct GemmStreamArgs {
   int32_t m_hint;           // host: rows the caller expects (0 = unknown); only steers the choice of launch shape
   const bf16_t* X;          // activations [*, ldx] (for SPRO_BF16S: h * gain, not yet divided by the rms)
   int32_t ldx;
-  int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16P: half values in fragment order)
+  int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16 / LO_F16P: half values in rows / in fragment order)
   const int32_t* gather;    // optional row indices into X / ss_part
   const float* ss_part;     // SPRO_BF16S: [*, ss_stride] partial sums of squares of the residual rows
   int32_t ss_stride, ss_count;
@@ -290,6 +290,7 @@ void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, 
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
 void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
 // gemm_mid.hip : windows of 17 to about 128 rows, half operands in fragment order
+constexpr int MID_LEAST_MOST_ROWS = 160;   // gemm_mid_most_rows of the largest matrices
 int gemm_mid_most_rows(int NT, int KT);
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a);
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
