@@ -10,8 +10,8 @@ namespace s2d2 {
 // the rotation pairs travel between lanes); nt >= NT does nothing.  h0 (SEPI_ADD_F32): the residual's four values at that
 // place where the caller has requested them ahead of time, else they are read here.  FRAG_OUT: activation rows may be
 // wanted in fragment order; false where they never are.  (The tiled kernel's residual adds on row-major inputs, with the
-// values read in a region of their own and the choice of the layout compiled in, took 70 us per launch; without either
-// 66.5.  8B-shaped output and down projection, 512 rows.)
+// values read in a region of their own and the choice of the layout compiled in, took 70.1 us per launch; without either
+// 67.9.  8B-shaped output and down projection, 512 rows.)
 template <int EPI, bool FRAG_OUT>
 __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const bool live, const int orow, const float rs,
                                               const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4* h0) {
