@@ -103,6 +103,12 @@ int main() {
   EXPECT(s2d2_block_advance(nullptr, &kv, &st, 1, 4, nullptr) == S2D2_EINVAL);
   EXPECT(s2d2_commit_threshold(nullptr, &st, 1, 4, &d) == S2D2_EINVAL);
   EXPECT(s2d2_route(nullptr, 1, 4, &rp, &d, nullptr, nullptr) == S2D2_EINVAL);
+  EXPECT(s2d2_prefill(nullptr, &kv, 1, 4, (const int32_t*)fake, 4, (const int32_t*)fake, fake, fake) == S2D2_EINVAL);
+  EXPECT(s2d2_prefill(nullptr, nullptr, INT32_MIN, INT32_MAX, nullptr, INT32_MIN, nullptr, nullptr, nullptr) == S2D2_EINVAL);
+  EXPECT(s2d2_vocab_draft_stats(nullptr, (const float*)fake, 1, nullptr, nullptr, nullptr, nullptr, nullptr) == S2D2_EINVAL);
+  EXPECT(s2d2_vocab_score(nullptr, (const float*)fake, 1, nullptr, nullptr, nullptr) == S2D2_EINVAL);
+  EXPECT(s2d2_moe_choices(nullptr, 1, nullptr) == S2D2_EINVAL);
+  EXPECT(s2d2_debug_buffer(nullptr, "h", nullptr) == S2D2_EINVAL);
   EXPECT(s2d2_set_stream(nullptr, nullptr) == S2D2_EINVAL);
   EXPECT(s2d2_status(nullptr) == S2D2_EINVAL);
   EXPECT(s2d2_destroy(nullptr) == S2D2_EINVAL || s2d2_destroy(nullptr) == S2D2_OK);

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("N,B,d_ffn,vocab,steps", [
     (1, 17, 1536, 32000, 2),    # 17 draft rows, 34 verifier rows
     (2, 24, 4096, 32007, 2),    # 48 / 96 rows, long K of the down projection, vocabulary that ends inside a tile
-    (13, 5, 1568, 32000, 2),    # 65 / 130 rows, 98 feature tiles, 49 K tiles
-    (4, 32, 1536, 4096, 1),     # 128 / 256 rows
+    (13, 5, 1568, 32000, 4),    # 65 / 130 rows, 98 feature tiles, 49 K tiles
+    (4, 32, 1536, 32000, 2),    # 128 / 256 rows
 ])
 def test_windows_between_the_streaming_and_the_tiled_kernel(N, B, d_ffn, vocab, steps):
     cfg = I.ModelCfg("mid-rows", 2, 1024, 8, 4, 128, d_ffn, vocab)

@@ -4,7 +4,14 @@ gets past its checks, so nothing touches a device; device code is not instrument
 import os
 import subprocess
 
-from paper_2603_25702_amd import build
+from paper_2603_25702_amd import binding, build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def test_the_driver_calls_every_entry_point():
+    source = open(os.path.join(HERE, "host", "host_check.cpp")).read()
+    assert [n for n in binding.EXPORTS if n + "(" not in source] == []
 
 
 def test_argument_checks_and_size_arithmetic_are_clean_under_asan_and_ubsan():
