@@ -28,13 +28,16 @@ HEADLINE, OTHERS = 4, (2, 3, 5)
 # step, from the FETCH_SIZE / WRITE_SIZE counter runs summarised under profiles/ (rocprofv3 --pmc on this file with
 # the default operand mode; a plain copy of 1 GiB reads FETCH_SIZE = 524300 KiB and WRITE_SIZE = 1048576 KiB, so
 # bytes = FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024).  Averages over all GEMM launches of two steps.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31224525, 3: 89565184, 4: 199932416, 5: 340076037}
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31340851, 3: 84110746, 4: 200105882, 5: 338967450}
 STEP_TRAFFIC_BYTES = {   # all kernels of a step: (FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024) summed over the step's launches
-    2: (1690673.1 + 3417419.0 + 3216.1) * 2048 + (44688.0 + 56515.1 + 649.7) * 1024,
-    3: (3967161.5 + 10775508.1 + 41642.3) * 2048 + (1853479.4 + 3814144.6 + 10579.1) * 1024,
-    4: (20326794.5 + 23919422.5 + 159398.6) * 2048 + (3800861.3 + 8782625.1 + 29411.1) * 1024,
-    5: (4899233.2 + 278935.0 + 29215321.8 + 2673974.5) * 2048 + (2783471.0 + 14287.5 + 8082510.8 + 839212.4) * 1024,
+    2: 5124041.7 * 2048 + 102234.9 * 1024,
+    3: 14176416.3 * 2048 + 4090623.7 * 1024,
+    4: 44151001.3 * 2048 + 10828505.4 * 1024,
+    5: 36819772.5 * 2048 + 10425801.8 * 1024,
 }
+# The kernel with most of a configuration's GEMM time (config 3: 254 of 290 launches and 5.2 of 6.7 ms; the verifier's gate /
+# up projections are the tiled kernel's)
+GEMM_KERNEL = {2: "gemm_stream_kernel", 3: "gemm_mid_kernel", 4: "gemm_tile_kernel", 5: "gemm_tile_kernel"}
 
 
 def log(*a):
@@ -142,12 +145,11 @@ def bench_config(args, cfg_id: int, K: int, Wm: int, cpu_baseline: bool) -> dict
         if prof["vocab"]["launches"]:
             t = prof["vocab"]["ms"] * 1e-3 / Kp
             phases["vocab"].update(hbm_GBs=round(vocab_bytes / t / 1e9, 1), hbm_frac=round(vocab_bytes / t / 1e9 / HBM_PEAK_GBS, 4))
-        # dominant kernel: the GEMM kernel of this window width (all its launches of a step).  It is bound by the
+        # dominant kernel: the GEMM kernel with most of the time at this window width (figures over all GEMM launches of a step).  It is bound by the
         # matrix pipes when the method's flops at the MFMA peak take longer than its weight bytes at the HBM peak.
         g = prof["gemm"]
-        wide = 3 * N * B > 32                     # windows above 32 rows run the LDS-tiled kernel (launch_gemm_stream)
         t_mfma, t_hbm = g["flops"] / (mfma_peak * 1e12), g["bytes"] / (HBM_PEAK_GBS * 1e9)
-        common = {"kernel": "gemm_tile_kernel" if wide else "gemm_stream_kernel",
+        common = {"kernel": GEMM_KERNEL[cfg_id],
                   "traffic": GEMM_TRAFFIC_BYTES_PER_LAUNCH.get(cfg_id) if not (args.layers or args.right_shifted) else None,
                   "avg_launch_us": round(g["ms"] * 1e3 / g["launches"], 3), "launches_per_step": g["launches"] // Kp,
                   "bytes_per_launch": round(g["bytes"] / g["launches"]), "flops_per_launch": round(g["flops"] / g["launches"])}
