@@ -30,8 +30,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 //
 // The launch is a chain of round trips to memory, so its 1024 threads request what they can at once and hand the chains
 // on: four lanes take 16 bytes of a key's row each, in turn; P V runs through four quarters of the workgroup, VB keys of
-// a chain each, whose V values are requested ahead of the scores.  8 and 12 rows over 136 keys of 64 floats: 12.9 and
-// 13.4 us per launch; 256 threads with a key each and one V value per iteration took 16.8.
+// a chain each, whose V values are requested ahead of the scores.  8 and 12 rows over 136 keys of 64 floats: 10.6 and
+// 11.3 us per launch (12.9 and 13.4 with the page look-ups under a condition: each was waited for); 256 threads with a key
+// each and one V value per iteration took 16.8.
 template <typename T, int D>
 __global__ __launch_bounds__(1024) void attn_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k_win, const T* __restrict__ v_win,
@@ -55,45 +56,64 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   const int tid = threadIdx.x, wave = tid >> 6;
   const int32_t* pt = g.page_table + (size_t)n * g.max_pages_per_seq;
 
-  // V values of the keys at places e0 + VB (tid / 256) .. of this thread's chain (key = slice + NS place; past the end the last key)
-  const int quarter = tid >> 8, t8 = tid & 255, d = t8 % D, sl = t8 / D;
-  T val[VB];
-  auto load_v = [&](int e0) __attribute__((always_inline)) {
-    int page[VB];
+  // Requests in the order in which they are needed (loads return in order): the query, the page of this lane's first key, the
+  // pages of the first V values, the key, the V values.  Behind the query's store to LDS only those are in flight.
+  const float q0 = tid < D ? to_f32(q[((size_t)r * Hq + hq) * D + tid]) : 0.f;
+  const int part = tid & 3, quarter = tid >> 8, t8 = tid & 255, d = t8 % D, sl = t8 / D;
+  // (a load under a condition is waited for before the next one: without cached keys the first page is looked up all the same)
+  auto place = [&](int s, int& page, int& slot) __attribute__((always_inline)) {
+    const int c = max(min(s, S - 1), 0), i = c / ps;
+    page = pt[i];
+    slot = c - i * ps;
+  };
+  auto page0 = [&](int page) __attribute__((always_inline)) { return (size_t)min(max(page, 0), g.n_pages - 1) * Hkv + kvh; };
+  auto win0 = [&](int s) __attribute__((always_inline)) { return (size_t)(row0 + max(s - S, 0)) * Hkv + kvh; };
+  auto key_row = [&](int s, int page, int slot) __attribute__((always_inline)) {
+    const T* cached = k_pages + (page0(page) * ps + slot) * D;
+    const T* own = k_win + win0(s) * D;
+    return s < S ? cached : own;
+  };
+  uint4 kv[CB];   // pieces of the key's row that this lane adds next
+  auto load_k = [&](const T* kp, int c0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < VB; ++u) page[u] = S > 0 ? pt[min(sl + (e0 + quarter * VB + u) * NS, S - 1) / ps] : 0;
+    for (int c = 0; c < CB; ++c) kv[c] = *(const uint4*)(kp + ((c0 + c) * 4 + part) * VE);
+  };
+  // V values of the keys at places e0 + VB quarter .. of this thread's chain (key = slice + NS place; past the end the last key)
+  T val[VB];
+  int vpage[VB], vslot[VB];
+  auto key_of = [&](int e0, int u) __attribute__((always_inline)) { return sl + (e0 + quarter * VB + u) * NS; };
+  auto find_v = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < VB; ++u) place(key_of(e0, u), vpage[u], vslot[u]);
+  };
+  auto load_v = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
-      const int s = min(sl + (e0 + quarter * VB + u) * NS, total - 1);
-      const T* vp = s < S ? v_pages + (((size_t)min(max(page[u], 0), g.n_pages - 1) * Hkv + kvh) * D + d) * ps + (s % ps)   // cache V is stored [D, page_size]
-                          : v_win + ((size_t)(row0 + (s - S)) * Hkv + kvh) * D + d;
-      val[u] = *vp;
+      const int s = min(key_of(e0, u), total - 1);
+      const T* cached = v_pages + (page0(vpage[u]) * D + d) * ps + vslot[u];   // cache V is stored [D, page_size]
+      const T* own = v_win + win0(s) * D + d;
+      val[u] = *(s < S ? cached : own);
     }
   };
+  const int first = min(tid >> 2, total - 1);
+  int kpage, kslot;
+  place(first, kpage, kslot);
+  find_v(0);
+  load_k(key_row(first, kpage, kslot), 0);
   load_v(0);
-  for (int i = tid; i < D; i += NT) s_q[i] = to_f32(q[((size_t)r * Hq + hq) * D + i]) * scale;
+  if (tid < D) s_q[tid] = q0 * scale;
   __syncthreads();
 
-  const int part = tid & 3;
   float lmax = -INFINITY;
   for (int s0 = 0; s0 < total; s0 += NT / 4) {
-    const int s = min(s0 + (tid >> 2), total - 1);
-    const T* kp;
-    bool vis = true;
-    if (s < S) {
-      const int page = min(max(pt[s / ps], 0), g.n_pages - 1);
-      kp = k_pages + (((size_t)page * Hkv + kvh) * ps + (s % ps)) * D;
-    } else {
-      const int w = row0 + (s - S);
-      vis = (w >= lo && w < hi) || w == r;
-      kp = k_win + ((size_t)w * Hkv + kvh) * D;
-    }
+    const int s = min(s0 + (tid >> 2), total - 1), w = row0 + (s - S);
+    const bool vis = s < S || (w >= lo && w < hi) || w == r;
+    if (s0) place(s, kpage, kslot);
+    const T* kp = key_row(s, kpage, kslot);
     float dot = 0.f;   // the same in all four lanes of the key
 #pragma unroll
     for (int c0 = 0; c0 < NCH; c0 += CB) {
-      uint4 kv[CB];
-#pragma unroll
-      for (int c = 0; c < CB; ++c) kv[c] = *(const uint4*)(kp + ((c0 + c) * 4 + part) * VE);
+      if (s0 || c0) load_k(kp, c0);
 #pragma unroll
       for (int c = 0; c < CB; ++c) {
         const T* e = (const T*)&kv[c];
@@ -135,13 +155,10 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   __syncthreads();
 
   for (int e0 = 0; e0 * NS < total; e0 += 4 * VB) {
-    if (e0) load_v(e0);
+    if (e0) { find_v(e0); load_v(e0); }
     float pw[VB];
 #pragma unroll
-    for (int u = 0; u < VB; ++u) {
-      const int s = sl + (e0 + quarter * VB + u) * NS;
-      pw[u] = s < total ? s_sc[s] : 0.f;
-    }
+    for (int u = 0; u < VB; ++u) pw[u] = key_of(e0, u) < total ? s_sc[key_of(e0, u)] : 0.f;
     for (int w = 0; w < 4; ++w) {
       if (quarter == w) {
         float acc = e0 + w ? s_red[t8] : 0.f;
