@@ -386,21 +386,19 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     if (LR == 0 && l == d.n_layers - 1) return check_launch("forward");
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;
     const void* vp = (const uint8_t*)kv->v_pages + l * page_layer;
-    if (flash) {
+    if (wide) {
+      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
+      if (Z > 1) { ProfScope ps(c, 1, 0.0); launch_attention_wide_merge(st, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
+    } else if (flash) {
+      // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the
+      // compute units.  Workgroups behind the attention's own read the weights of the next two GEMMs (the packed
+      // matrices of a layer lie one behind the other: wo, gate, up, down) into the memory-side cache meanwhile.
+      size_t ahead = 0;
+      if (fused && d.n_experts == 0 && R <= 32 && Z * q_tiles * N * d.n_kv_heads <= 128)
+        ahead = packed_weight_bytes(d.d_model, HqD) + 2 * packed_weight_bytes(d.d_ffn, d.d_model);
       ProfScope ps(c, 1, 0.0);
-      if (wide)
-        launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries);
-      else
-      {
-        // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the
-        // compute units.  Workgroups behind the attention's own read the weights of the next two GEMMs (the packed
-        // matrices of a layer lie one behind the other: wo, gate, up, down) into the memory-side cache meanwhile.
-        size_t ahead = 0;
-        if (fused && d.n_experts == 0 && R <= 32 && Z * q_tiles * N * d.n_kv_heads <= 128)
-          ahead = packed_weight_bytes(d.d_model, HqD) + 2 * packed_weight_bytes(d.d_ffn, d.d_model);
-        launch_attention_flash(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_counters,
-                               ahead ? c->pk[l].wo : nullptr, ahead, c->prefetch_wgs);
-      }
+      launch_attention_flash(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_counters,
+                             ahead ? c->pk[l].wo : nullptr, ahead, c->prefetch_wgs);
     } else {
       ProfScope ps(c, 1, 0.0);
       launch_attention_generic(st, dt, c->qbuf, kw, vw, kp, vp, g, c->plan, R, d.n_q_heads, c->obuf, lds, lo_o);

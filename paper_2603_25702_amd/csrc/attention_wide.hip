@@ -441,9 +441,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
 }
 
 // Sums of the key splits, in split order: one wavefront per 32 query rows x 8 output columns (the 64 x 16 bytes its
-// accumulator group has in every split), the partials of 12 splits requested at once.  A launch of its own costs 4-5 us, all
-// of it latency; when the split that arrived last added up its workgroup's tiles by itself, that was one memory round
-// trip per query tile, pass and four splits behind each other, on one compute unit, 6 to 27 us of the launch.
+// accumulator group has in every split), the partials of 12 splits requested at once.  A launch of its own costs 5-6 us of
+// latency (4B shape), 9-14 where it reads 34 MB of partials (8B and MoE); when the split that arrived last added up its
+// workgroup's tiles by itself, that was one memory round trip per query tile, pass and four splits behind each other, on one
+// compute unit, 6 to 27 us of the launch.  Attention and merge per launch before and now: 4B verifier 46 -> 28 + 6 us (with
+// equal runs of tiles per split), 8B verifier 166 -> 142 + 12, 8B draft 126 -> 114 + 9, MoE draft 79 -> 48 + 14.
 __global__ __launch_bounds__(256) void attn_wide_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml, KvGeom g,
                                                               Plan p, int Hq, int Z, bf16_t* __restrict__ o, int o_ld, int o_lo) {
   constexpr int D = FA_D, ZB = 12;
@@ -529,7 +531,6 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
                            int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)g.head_dim);
-  const int items = N * g.n_kv_heads;
   const int qgroups = (q_tiles + 7) / 8, per = (q_tiles + qgroups - 1) / qgroups;   // tiles per workgroup, balanced
   const int nw = attention_wide_nw(q_tiles);
   const int pt_cap = attention_wide_pt_cap(g, N, Z, target);
@@ -546,7 +547,12 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
   if (nw == 4) S2D2_WIDE(4);
   else S2D2_WIDE(8);
 #undef S2D2_WIDE
-  if (Z > 1) S2D2_LAUNCH(attn_wide_merge_kernel, dim3(4, q_tiles, items), dim3(256), 0, st, part_o, part_ml, g, p, Hq, Z, (bf16_t*)o, o_ld, o_lo);
+}
+
+void launch_attention_wide_merge(hipStream_t st, const KvGeom& g, const Plan& p, int N, int Hq, int q_tiles, int Z, void* o, int o_ld,
+                                 int o_lo, const float* part, size_t part_entries) {
+  S2D2_LAUNCH(attn_wide_merge_kernel, dim3(4, q_tiles, N * g.n_kv_heads), dim3(256), 0, st, part, part + part_entries * 32 * FA_D, g, p, Hq, Z,
+              (bf16_t*)o, o_ld, o_lo);
 }
 
 template <int NW, int QM>

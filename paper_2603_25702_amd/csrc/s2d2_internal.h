@@ -329,6 +329,9 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
                            int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries);
+// with Z > 1, behind it: the sums of the sequences that were split
+void launch_attention_wide_merge(hipStream_t st, const KvGeom& g, const Plan& p, int N, int Hq, int q_tiles, int Z, void* o, int o_ld,
+                                 int o_lo, const float* part, size_t part_entries);
 void launch_fill_i32(hipStream_t st, int32_t* p, int n, int32_t v);
 void launch_attn_ts_copy(hipStream_t st, void* out);   // timing build only
 void launch_wide_ts_copy(hipStream_t st, void* out);   // timing build only

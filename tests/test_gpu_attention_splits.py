@@ -3,6 +3,7 @@ splits; a lone long sequence of a small model is cut into more."""
 import pytest
 
 import s2d2_inputs as I
+from paper_2603_25702_amd import Params
 from tests import harness as H
 from tests.test_gpu_parity import run_steps
 
@@ -26,3 +27,8 @@ def test_more_splits_than_a_round_of_the_merge(lens):
     run, rep = run_steps(case, 2)
     print("splits:", lens, rep)
     assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
+    # the launch timer books the attention launch and the merge behind it, of either forward and each layer
+    run.eng.s2d2_profile_start(4096)
+    run.step(Params(step=2, seed=1234), advance=False)
+    prof = run.eng.s2d2_profile_stop()
+    assert prof["attention"]["launches"] == 2 * cfg.n_layers * 2
