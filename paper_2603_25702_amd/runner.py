@@ -13,7 +13,7 @@ import dataclasses
 
 from .binding import AcceptOut, BlockState, DraftOut, Engine, KvCache, Params, RouteOut, RouteParams, VerifyOut
 
-PREFILL_BLOCK = 64  # window used to push prompt tokens through the causal rows of the verifier
+PREFILL_BLOCK = 64  # least max_block of a session's workspace: a prefill forward takes 3 * max_block tokens of every sequence
 
 
 class Session:
