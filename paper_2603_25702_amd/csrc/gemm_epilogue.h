@@ -9,9 +9,9 @@ namespace s2d2 {
 // nt * 16 + 4 g + i, g = lane / 16; rs scales it.  The whole wavefront calls it with one nt (the norm's partial sums and
 // the rotation pairs travel between lanes); nt >= NT does nothing.  h0 (SEPI_ADD_F32): the residual's four values at that
 // place where the caller has requested them ahead of time, else they are read here.  FRAG_OUT: activation rows may be
-// wanted in fragment order; false where they never are.  (The tiled kernel's residual adds on row-major inputs, with the
-// values read in a region of their own and the choice of the layout compiled in, took 70.1 us per launch; without either
-// 67.9.  8B-shaped output and down projection, 512 rows.)
+// wanted in fragment order; false where they never are.  (Both keep instructions out of the tiled kernel, whose unsplit
+// epilogue is unrolled over all units of a tile: values read in a region of their own and the layout chosen at run time
+// made its residual-add kernel 18653 instructions for 16873.)
 template <int EPI, bool FRAG_OUT>
 __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const bool live, const int orow, const float rs,
                                               const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4* h0) {
