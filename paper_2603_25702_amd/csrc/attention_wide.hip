@@ -441,14 +441,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
 }
 
 // Sums of the key splits, in split order: one wavefront per 32 query rows x 8 output columns (the 64 x 16 bytes its
-// accumulator group has in every split), the partials of 12 splits requested at once.  A launch of its own costs 5-6 us of
-// latency (4B shape), 9-14 where it reads 34 MB of partials (8B and MoE); when the split that arrived last added up its
+// accumulator group has in every split), the partials of all splits up to 12 requested at once (always of 12, with the last one again
+// where there are fewer: 9.0 -> 6.8 us per launch for two splits of 32 sequences).  A launch of its own costs 5-7 us of
+// latency, 7-11 where it reads tens of MB of partials (8B and MoE); when the split that arrived last added up its
 // workgroup's tiles by itself, that was one memory round trip per query tile, pass and four splits behind each other, on one
 // compute unit, 6 to 27 us of the launch.  Attention and merge per launch before and now: 4B verifier 46 -> 28 + 6 us (with
-// equal runs of tiles per split), 8B verifier 166 -> 142 + 12, 8B draft 126 -> 114 + 9, MoE draft 79 -> 48 + 14.
+// equal runs of tiles per split), 8B verifier 166 -> 142 + 12, 8B draft 126 -> 114 + 9, MoE draft 79 -> 48 + 14 (the merges with
+// loads of 12 splits).
 __global__ __launch_bounds__(256) void attn_wide_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml, KvGeom g,
                                                               Plan p, int Hq, int Z, bf16_t* __restrict__ o, int o_ld, int o_lo) {
-  constexpr int D = FA_D, ZB = 12;
+  constexpr int D = FA_D;
   const int lane = threadIdx.x & 63, g16 = blockIdx.x * 4 + (threadIdx.x >> 6), qt = blockIdx.y, item = blockIdx.z;
   const int Hkv = g.n_kv_heads, grp = Hq / Hkv, n = item / Hkv, kvh = item % Hkv, c = lane & 31;
   const int row0 = p.seq_row0[n], nq = p.seq_rows[n] * grp, Zn = p.seq_splits[n];
@@ -456,33 +458,40 @@ __global__ __launch_bounds__(256) void attn_wide_merge_kernel(const float* __res
   const size_t item0 = ((size_t)item * gridDim.y + qt) * Z;
   float M = -INFINITY, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int z0 = 0; z0 < Zn; z0 += ZB) {
-    float m[ZB], l[ZB];
-    float4 v[ZB];
+  auto rounds = [&](auto zb) __attribute__((always_inline)) {
+    constexpr int ZB = decltype(zb)::value;
+    for (int z0 = 0; z0 < Zn; z0 += ZB) {
+      float m[ZB], l[ZB];
+      float4 v[ZB];
 #pragma unroll
-    for (int k = 0; k < ZB; ++k) {
-      const size_t e = item0 + min(z0 + k, Zn - 1);   // clamped duplicates get no weight below
-      m[k] = part_ml[e * 64 + c];
-      l[k] = part_ml[e * 64 + 32 + c];
-      v[k] = *(const float4*)(part_o + e * 32 * D + (g16 * 64 + lane) * 4);
-    }
-    float Mn = M;
+      for (int k = 0; k < ZB; ++k) {
+        const size_t e = item0 + min(z0 + k, Zn - 1);   // clamped duplicates get no weight below
+        m[k] = part_ml[e * 64 + c];
+        l[k] = part_ml[e * 64 + 32 + c];
+        v[k] = *(const float4*)(part_o + e * 32 * D + (g16 * 64 + lane) * 4);
+      }
+      float Mn = M;
 #pragma unroll
-    for (int k = 0; k < ZB; ++k) {
-      if (z0 + k >= Zn) m[k] = -INFINITY;
-      Mn = fmaxf(Mn, m[k]);
-    }
-    const float ref = Mn == -INFINITY ? 0.f : Mn;   // (nothing seen yet: all weights are exp2(-inf) = 0)
-    const float fo = __builtin_amdgcn_exp2f(M - ref);
-    L *= fo; acc.x *= fo; acc.y *= fo; acc.z *= fo; acc.w *= fo;
+      for (int k = 0; k < ZB; ++k) {
+        if (z0 + k >= Zn) m[k] = -INFINITY;
+        Mn = fmaxf(Mn, m[k]);
+      }
+      const float ref = Mn == -INFINITY ? 0.f : Mn;   // (nothing seen yet: all weights are exp2(-inf) = 0)
+      const float fo = __builtin_amdgcn_exp2f(M - ref);
+      L *= fo; acc.x *= fo; acc.y *= fo; acc.z *= fo; acc.w *= fo;
 #pragma unroll
-    for (int k = 0; k < ZB; ++k) {
-      const float f = __builtin_amdgcn_exp2f(m[k] - ref);
-      L += f * l[k];
-      acc.x += f * v[k].x; acc.y += f * v[k].y; acc.z += f * v[k].z; acc.w += f * v[k].w;
+      for (int k = 0; k < ZB; ++k) {
+        const float f = __builtin_amdgcn_exp2f(m[k] - ref);
+        L += f * l[k];
+        acc.x += f * v[k].x; acc.y += f * v[k].y; acc.z += f * v[k].z; acc.w += f * v[k].w;
+      }
+      M = Mn;
     }
-    M = Mn;
-  }
+  };
+  if (Zn <= 2) rounds(std::integral_constant<int, 2>{});
+  else if (Zn <= 4) rounds(std::integral_constant<int, 4>{});
+  else if (Zn <= 8) rounds(std::integral_constant<int, 8>{});
+  else rounds(std::integral_constant<int, 12>{});
   const int qi = qt * 32 + c, d0 = (g16 >> 2) * 32 + 8 * (g16 & 3) + 4 * (lane >> 5);
   if (qi >= nq) return;
   const float inv = L > 0.f ? 1.0f / L : 0.f;
@@ -510,9 +519,15 @@ int attention_wide_nw(int q_tiles) {
   return need <= 4 ? 4 : 8;   // (two wavefronts for two tiles measured slower: four share the fetch work, 3.76 -> 3.27 ms of attention per step on the 4B shape)
 }
 
-// Most splits of a sequence: a split keeps at least four key tiles, the partials fit their buffer.
+// Most splits of a sequence: a split keeps at least four key tiles, the partials fit their buffer.  One, and so no merge
+// launch, where the cache holds so few tiles that cutting them saves less than that launch costs (2-3 us when nothing was
+// cut, 5-11 else), which depends on how many workgroups there are without: forwards over prefixes that fill their cache,
+// uncut against cut, us: 32 sequences of block 8, 4B (256 workgroups) 6 tiles 6460 / 6700, 8 6614 / 6795, 10 6666 / 6916, 13
+// 6740 / 6846; 21 sequences, two planes (168) 6 tiles 7800 / 7943, 8 7916 / 8039, 10 7972 / 7999, 13 8153 / 8082; 16
+// sequences (128) 6 tiles 4762 / 4823, 8 4868 / 4839; one sequence (8) 6 tiles 1593 / 1574.
 int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target) {
-  const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32;
+  const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32, wgs = items * ((q_tiles + 7) / 8);
+  if (cap_tiles <= (wgs >= 256 ? 18 : wgs >= 128 ? 7 : WIDE_MIN_TILES)) return 1;
   int Z = std::max(1, std::min(std::min((cap_tiles + WIDE_MIN_TILES - 1) / WIDE_MIN_TILES, 64), target + 1));
   while (Z > 1 && (size_t)Z * items * q_tiles > part_entries) --Z;
   return Z;
