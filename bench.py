@@ -28,12 +28,12 @@ HEADLINE, OTHERS = 4, (2, 3, 5)
 # step, from the FETCH_SIZE / WRITE_SIZE counter runs summarised under profiles/ (rocprofv3 --pmc on this file with
 # the default operand mode; a plain copy of 1 GiB reads FETCH_SIZE = 524300 KiB and WRITE_SIZE = 1048576 KiB, so
 # bytes = FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024).  Averages over all GEMM launches of two steps.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31340851, 3: 84110746, 4: 200105882, 5: 338967450}
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31340851, 3: 84114227, 4: 199593267, 5: 338396058}
 STEP_TRAFFIC_BYTES = {   # all kernels of a step: (FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024) summed over the step's launches
-    2: 5124041.7 * 2048 + 102234.9 * 1024,
-    3: 14176416.3 * 2048 + 4090623.7 * 1024,
-    4: 44151001.3 * 2048 + 10828505.4 * 1024,
-    5: 36819772.5 * 2048 + 10425801.8 * 1024,
+    2: 5124024.9 * 2048 + 102234.8 * 1024,
+    3: 14177504.3 * 2048 + 4090622.5 * 1024,
+    4: 44077973.9 * 2048 + 10830020.1 * 1024,
+    5: 36764013.8 * 2048 + 10424475.8 * 1024,
 }
 # The kernel with most of a configuration's GEMM time (config 3: 254 of 290 launches and 5.2 of 6.7 ms; the verifier's gate /
 # up projections are the tiled kernel's)
