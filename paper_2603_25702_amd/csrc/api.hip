@@ -297,7 +297,8 @@ WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) 
 // Bounds of a forward: rows of one window, rows, logit rows of all windows, and the rows the caller expects.
 struct FwdSize { int win, R, LR, hint; };
 FwdSize draft_size(int N, int B) { return {2 * B, 2 * N * B, N * B, N * B}; }        // carry + block; a fresh block has B rows
-FwdSize verify_size(int N, int B) { return {3 * B, 3 * N * B, N * B, 2 * N * B}; }   // carry + 2L; a fresh block has 2 B (more only with carried or pending committed tokens)
+// carry + 2L; a fresh block has 2 B (more only with carried or pending committed tokens), of a right-shifted model lead + L - 1
+FwdSize verify_size(int N, int B, int shifted) { return {3 * B, 3 * N * B, N * B, (shifted ? 1 : 2) * N * B}; }
 FwdSize prefill_size(int N, int T) { return {T, N * T, 0, N * T}; }
 
 // Without logit rows (LR = 0) the forward ends with the K/V of the last layer.
@@ -341,13 +342,19 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     x.tile_partial_cap = TILE_PARTIAL_CAP; x.tile_counter_cap = TILE_COUNTER_CAP; x.coop_wgs = c->n_cus;
     x.pair_buf = c->pair_buf; x.pair_status = c->dev_status + 1; x.pair_cap = PAIR_CAP;
   };
-  // GEMM inputs: one plane of half values, in fragment order where the streaming and the mid-size kernel have most of
-  // the work, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which (0: one bf16 plane).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
+  // GEMM inputs: one plane of half values, in fragment order where a kernel that wants it takes one of the matrices, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which (0: one bf16 plane).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
   // (the generic attention kernel reads and writes single planes: two-plane models then run on their high plane)
   const int mode = operand_mode_of(d);
   const int opm = !fused ? OPM_BF16 : (flash || mode == OPM_F16 ? mode : OPM_BF16);
   const int P = opm == OPM_BF16X2 ? 2 : 1;
-  const bool frag = opm == OPM_F16 && m_hint <= gemm_mid_most_rows(qkv_n / 16, d.d_model / 32);
+  auto blocks = [&](int kind, int N_, int K_) {
+    GemmStreamArgs x{};
+    x.NT = N_ / 16; x.KT = K_ / 32; x.N = N_; x.K = K_; x.x_lo = LO_F16P; x.m_count = n_rows;
+    sk(x);
+    return gemm_block_takes(kind, x, R);
+  };
+  const bool frag = opm == OPM_F16 && (m_hint <= MID_MOST_ROWS || blocks(SEPI_QKV_ROPE, qkv_n, d.d_model) || blocks(SEPI_ADD_F32, d.d_model, HqD) ||
+                                       (d.n_experts == 0 && (blocks(SEPI_SWIGLU, d.d_ffn, d.d_model) || blocks(SEPI_ADD_F32, d.d_model, d.d_ffn))));
   auto lo_row = [&](int width) { return opm == OPM_F16 ? LO_F16 : (P == 2 ? width : 0); };   // rows of the MoE FFN
   auto lo_of = [&](int width) { return opm == OPM_F16 ? (frag ? LO_F16P : LO_F16) : (P == 2 ? width : 0); };
   const int ld_a = P * d.d_model, lo_a = lo_of(d.d_model);
@@ -363,6 +370,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   const int ld_q = PQ * HqD, lo_q = q_f16 ? LO_F16 : (PQ == 2 ? HqD : 0);
   if (fused) { ProfScope ps(c, 3, 0.0); launch_embed_norm(st, c->w.embed, d.d_model, c->plan, R, c->layers[0].norm1, c->h, c->a, ld_a, lo_a, c->ss, ss_stride, c->rope_cs, d.head_dim, d.rope_theta); }
   else { ProfScope ps(c, 3, 0.0); launch_embed(st, dt, c->w.embed, d.d_model, c->plan, R, c->h); }
+  int ss_count = 1;   // partial sums of squares per residual row that the last producer left
   for (int l = 0; l < d.n_layers; ++l) {
     const s2d2_layer_weights& L = c->layers[l];
     void* kw = k_stage ? (uint8_t*)k_stage + l * stage_layer : c->kwin;
@@ -371,7 +379,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       GemmStreamArgs a{};
       a.Wp = c->pk[l].wqkv; a.NT = qkv_n / 16; a.KT = d.d_model / 32; a.N = qkv_n; a.K = d.d_model;
       a.m_count = n_rows; a.X = (const bf16_t*)c->a; a.ldx = ld_a; a.x_lo = lo_a; a.ss_part = c->ss; a.ss_stride = ss_stride;
-      a.ss_count = l == 0 ? 1 : ss_stride; a.eps = d.rms_eps;
+      a.ss_count = ss_count; a.eps = d.rms_eps;
       a.rope_cs = c->rope_cs; a.Hq = d.n_q_heads; a.Hkv = d.n_kv_heads; a.D = d.head_dim; a.wpad = c->wpad;
       a.q_out = (bf16_t*)c->qbuf; a.q_ld = ld_q; a.q_lo = lo_q; a.k_out = (bf16_t*)kw; a.v_out = (bf16_t*)vw; a.vT_out = flash ? (bf16_t*)c->vT_win : nullptr;
       a.row_seq = c->plan.row_seq; a.seq_row0 = c->plan.seq_row0;
@@ -409,13 +417,13 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       a.Wp = c->pk[l].wo; a.NT = d.d_model / 16; a.KT = HqD / 32; a.N = d.d_model; a.K = HqD;
       a.X = (const bf16_t*)c->obuf; a.ldx = ld_o; a.x_lo = lo_o; a.out = c->h; a.ldo = d.d_model;
       a.xg_out = (bf16_t*)c->a; a.xg_ld = ld_a; a.xg_lo = d.n_experts ? lo_row(d.d_model) : lo_a; a.gain_next = L.norm2; a.ss_out = c->ss; a.ss_stride = ss_stride;
-      { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); sk(a); launch_gemm_stream(st, SEPI_ADD_F32, a, R); }
+      { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); sk(a); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, a, R); }
       const float* gain_after = l + 1 < d.n_layers ? c->layers[l + 1].norm1 : c->w.norm_f;
       if (d.n_experts == 0) {
         GemmStreamArgs b{};
         b.m_count = n_rows;
         b.Wp = c->pk[l].wg; b.Wp2 = c->pk[l].wu; b.NT = d.d_ffn / 16; b.KT = d.d_model / 32; b.N = d.d_ffn; b.K = d.d_model;
-        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_a; b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_stride;
+        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_a; b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
         b.eps = d.rms_eps; b.out = c->ffn; b.ldo = ld_f; b.out_lo = lo_f;
         { ProfScope ps(c, 0, 2.0 * d.d_ffn * d.d_model * es, fr * 2.0 * d.d_ffn * d.d_model, 6); sk(b); launch_gemm_stream(st, SEPI_SWIGLU, b, R); }
         GemmStreamArgs e{};
@@ -423,7 +431,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         e.Wp = c->pk[l].wdown; e.NT = d.d_model / 16; e.KT = d.d_ffn / 32; e.N = d.d_model; e.K = d.d_ffn;
         e.X = (const bf16_t*)c->ffn; e.ldx = ld_f; e.x_lo = lo_f; e.out = c->h; e.ldo = d.d_model;
         e.xg_out = (bf16_t*)c->a; e.xg_ld = ld_a; e.xg_lo = lo_a; e.gain_next = gain_after; e.ss_out = c->ss; e.ss_stride = ss_stride;
-        { ProfScope ps(c, 0, (double)d.d_model * d.d_ffn * es, fr * d.d_model * d.d_ffn, 7); sk(e); launch_gemm_stream(st, SEPI_ADD_F32, e, R); }
+        { ProfScope ps(c, 0, (double)d.d_model * d.d_ffn * es, fr * d.d_model * d.d_ffn, 7); sk(e); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, e, R); }
       } else {
         // MoE FFN: router -> top-k -> group by expert -> grouped gate/up + SwiGLU -> grouped down -> combine
         const int E = d.n_experts, Fe = d.d_expert, tk = d.top_k;
@@ -431,7 +439,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         GemmStreamArgs r{};
         r.m_count = n_rows;
         r.Wp = c->pk[l].router; r.NT = (E + 15) / 16; r.KT = d.d_model / 32; r.N = E; r.K = d.d_model;
-        r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_row(d.d_model); r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_stride;
+        r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_row(d.d_model); r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_count;
         r.eps = d.rms_eps; r.out = c->router_logits; r.ldo = E;
         { ProfScope ps(c, 0, (double)E * d.d_model * es, fr * E * d.d_model); sk(r); launch_gemm_stream(st, SEPI_STORE_F32, r, R); }
         { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w); }
@@ -443,7 +451,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         b.tile_row0 = c->moe_tile_row0; b.tile_rows = c->moe_tile_rows; b.sorted = c->moe_sorted; b.route_w = c->moe_w;
         b.expert_stride = packed_weight_bytes(Fe, d.d_model) / 16;
         b.Wp = c->pk[l].eg; b.Wp2 = c->pk[l].eu; b.NT = Fe / 16; b.KT = d.d_model / 32; b.N = Fe; b.K = d.d_model;
-        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_row(d.d_model); b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_stride;
+        b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_row(d.d_model); b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
         b.eps = d.rms_eps; b.out = c->moe_act; b.ldo = ld_e; b.out_lo = lo_row(d.d_expert);
         { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); launch_gemm_tile(st, SEPI_SWIGLU, SPRO_BF16S, b, tile_cap); }
         GemmStreamArgs e{};
@@ -453,7 +461,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         e.Wp = c->pk[l].ed; e.NT = d.d_model / 16; e.KT = Fe / 32; e.N = d.d_model; e.K = Fe;
         e.X = (const bf16_t*)c->moe_act; e.ldx = ld_e; e.x_lo = lo_row(d.d_expert); e.out = c->moe_y; e.ldo = d.d_model;
         { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); launch_gemm_tile(st, SEPI_STORE_F32, SPRO_BF16, e, tile_cap); }
-        { ProfScope ps(c, 3, 0.0); launch_moe_combine(st, c->moe_y, d.d_model, tk, n_rows, R, c->h, c->a, ld_a, lo_a, gain_after, c->ss, ss_stride); }
+        { ProfScope ps(c, 3, 0.0); launch_moe_combine(st, c->moe_y, d.d_model, tk, n_rows, R, c->h, c->a, ld_a, lo_a, gain_after, c->ss, ss_stride); ss_count = 1; }
       }
     } else {
       { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); launch_gemm(st, dt, EPI_ADD_F32, c->obuf, HqD, L.wo, HqD, d.d_model, n_rows, R, c->h, d.d_model); }
@@ -467,7 +475,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     GemmStreamArgs a{};
     a.Wp = c->pk_unembed; a.NT = (d.vocab + 15) / 16; a.KT = d.d_model / 32; a.N = d.vocab; a.K = d.d_model;
     a.m_count = n_logit; a.X = (const bf16_t*)c->a; a.ldx = ld_a; a.x_lo = lo_a; a.gather = c->plan.logit_src;
-    a.ss_part = c->ss; a.ss_stride = ss_stride; a.ss_count = ss_stride; a.eps = d.rms_eps;
+    a.ss_part = c->ss; a.ss_stride = ss_stride; a.ss_count = ss_count; a.eps = d.rms_eps;
     a.out = logits; a.ldo = d.vocab;
     ProfScope ps(c, 0, (double)d.vocab * d.d_model * es, fl * d.vocab * d.d_model, 8);
     sk(a); launch_gemm_stream(st, SEPI_STORE_F32, a, LR);
@@ -692,11 +700,11 @@ int32_t s2d2_verify(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state*
       (rc = check_draft_out(draft)) || (rc = check_verify_out(out)))
     return rc;
   const s2d2_model_desc& d = c->desc;
-  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B).win);
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, d.right_shifted).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 1, d.right_shifted, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               draft->xhat, c->plan, out->logit_row_of, nullptr, nullptr, out->stage_row0, out->stage_lead, prm->active, kv->status,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, out->q, out->lse_ver); }
-  if ((rc = forward(c, kv, N, verify_size(N, B), out->k_stage, out->v_stage, out->logits_ver))) return rc;
+  if ((rc = forward(c, kv, N, verify_size(N, B, d.right_shifted), out->k_stage, out->v_stage, out->logits_ver))) return rc;
   { ProfScope ps(c, 2, 0.0); launch_vocab_score(c->stream, out->logits_ver, d.vocab, c->plan.counts + 1, N * B, c->vws, c->plan.logit_seq,
                      c->plan.logit_idx, B, draft->xhat, out->q, out->lse_ver, inv_temperature(prm)); }
   return check_launch("s2d2_verify");
@@ -760,11 +768,11 @@ int32_t s2d2_block_complete(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_bloc
   const s2d2_model_desc& d = c->desc;
   if (d.right_shifted) return fail(S2D2_EINVAL, "s2d2_block_complete is not defined for right-shifted models (their cache lags one token)");
   if (causal != 0 && causal != 1) return fail(S2D2_EINVAL, "causal must be 0 or 1");
-  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B).win);
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, 0).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, causal ? 3 : 2, 0, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               nullptr, c->plan, scratch->logit_row_of, nullptr, nullptr, scratch->stage_row0, scratch->stage_lead, nullptr, nullptr,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
-  if ((rc = forward(c, kv, N, verify_size(N, B), scratch->k_stage, scratch->v_stage, scratch->logits_ver))) return rc;
+  if ((rc = forward(c, kv, N, verify_size(N, B, 0), scratch->k_stage, scratch->v_stage, scratch->logits_ver))) return rc;
   const KvGeom g = geom(c, kv);
   // every staged row is appended: lead = rows, accepted = 0 (the zero array stands in for n_accept and span_len)
   { ProfScope ps(c, 3, 0.0); launch_kv_append(c->stream, d.dtype, d.n_layers, N, c->rows_cap, g, kv->k_pages, kv->v_pages,

@@ -8,13 +8,17 @@ namespace s2d2 {
 // v0 (and v1, the up projection, for SwiGLU): v[i] = sum of output row orow (this lane's row; live: it exists), feature
 // nt * 16 + 4 g + i, g = lane / 16; rs scales it.  The whole wavefront calls it with one nt (the norm's partial sums and
 // the rotation pairs travel between lanes); nt >= NT does nothing.  h0 (SEPI_ADD_F32): the residual's four values at that
-// place where the caller has requested them ahead of time, else they are read here.  FRAG_OUT: activation rows may be
+// place where the caller has requested them ahead of time, else they are read here; sq_sum: takes the row's sum of squares
+// instead of the tile's entry in ss_out; ahead: what gemm_epi_request has read for this place (and the sequence of the row and
+// its first row, for the values' copy), else read here.  FRAG_OUT: activation rows may be
 // wanted in fragment order; false where they never are.  (Both keep instructions out of the tiled kernel, whose unsplit
 // epilogue is unrolled over all units of a tile: values read in a region of their own and the layout chosen at run time
 // made its residual-add kernel 18653 instructions for 16873.)
+struct EpiAhead { float4 a, b; int seq, row0; };   // see gemm_epi_request
 template <int EPI, bool FRAG_OUT>
 __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const bool live, const int orow, const float rs,
-                                              const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4* h0) {
+                                              const int nt, const int g, const f32x4_t& v0, const f32x4_t& v1, const float4* h0, float* sq_sum = nullptr,
+                                              const EpiAhead* ahead = nullptr) {
   if (nt >= a.NT) return;   // uniform over the wavefront
   const int n = nt * 16 + 4 * g;
   auto put4 = [&](bf16_t* base, int lo, int ld, float x, float y, float z, float w) __attribute__((always_inline)) {
@@ -41,7 +45,7 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
       hv[3] = h.w + v0[3] * rs;
       *hp = make_float4(hv[0], hv[1], hv[2], hv[3]);
       if (a.xg_out) {
-        const float4 gn = *(const float4*)(a.gain_next + n);
+        const float4 gn = ahead ? ahead->a : *(const float4*)(a.gain_next + n);
         put4(a.xg_out, a.xg_lo, a.xg_ld, hv[0] * gn.x, hv[1] * gn.y, hv[2] * gn.z, hv[3] * gn.w);
       }
     }
@@ -49,7 +53,8 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
       float sq = (hv[0] * hv[0] + hv[1] * hv[1]) + (hv[2] * hv[2] + hv[3] * hv[3]);
       sq += __shfl_xor(sq, 16, 64);
       sq += __shfl_xor(sq, 32, 64);
-      if (live && g == 0) a.ss_out[(size_t)orow * a.ss_stride + nt] = sq;
+      if (sq_sum) *sq_sum += sq;
+      else if (live && g == 0) a.ss_out[(size_t)orow * a.ss_stride + nt] = sq;
     }
   } else if (EPI == SEPI_SWIGLU) {
     if (live) {
@@ -76,7 +81,7 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
         const bool is_q = head < a.Hq;
         bf16_t* dst = is_q ? a.q_out + (size_t)orow * a.q_ld + head * D
                            : a.k_out + ((size_t)orow * a.Hkv + (head - a.Hq)) * D;
-        const float4 c01 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0), c23 = *(const float4*)(a.rope_cs + (size_t)orow * half + i0 + 2);
+        const float4 c01 = ahead ? ahead->a : *(const float4*)(a.rope_cs + (size_t)orow * half + i0), c23 = ahead ? ahead->b : *(const float4*)(a.rope_cs + (size_t)orow * half + i0 + 2);
         const float cs_c[4] = {c01.x, c01.z, c23.x, c23.z}, cs_s[4] = {c01.y, c01.w, c23.y, c23.w};
         float y[4];
 #pragma unroll
@@ -88,7 +93,7 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
       } else {
         const int vh = head - a.Hq - a.Hkv;
         bf16_t* dst = a.v_out + ((size_t)orow * a.Hkv + vh) * D + (second ? half : 0);
-        const int sq = a.row_seq[orow], tw = orow - a.seq_row0[sq];
+        const int sq = ahead ? ahead->seq : a.row_seq[orow], tw = orow - (ahead ? ahead->row0 : a.seq_row0[sq]);
         bf16_t b[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = f32_to_bf16(own[i]);
@@ -100,6 +105,19 @@ __device__ __forceinline__ void gemm_epi_unit(const GemmStreamArgs& a, const boo
         }
       }
     }
+  }
+}
+
+// What gemm_epi_unit reads besides the residual, requested ahead of time for all units of a wavefront: unit by unit, between the stores,
+// each read is waited for (rotation epilogue, 8B shape, 256 / 512 rows: 6 and 9 us of 32 and 52).
+template <int EPI>
+__device__ __forceinline__ void gemm_epi_request(const GemmStreamArgs& a, const int orow, const int nt, const int g, EpiAhead& e) {
+  e.a = e.b = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (EPI == SEPI_ADD_F32 && a.xg_out) e.a = *(const float4*)(a.gain_next + nt * 16 + 4 * g);
+  if (EPI == SEPI_QKV_ROPE) {   // (places without a rotation read one all the same)
+    const float4* cs = (const float4*)(a.rope_cs + (size_t)orow * (a.D >> 1) + 8 * (nt % (a.D / 16)) + 4 * (g & 1));
+    e.a = cs[0];
+    e.b = cs[1];
   }
 }
 

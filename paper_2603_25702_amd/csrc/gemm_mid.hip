@@ -1,5 +1,5 @@
-// GEMM on the packed weights for windows between the streaming kernel's 16 rows and the tiled kernel's 128 x 256 tiles:
-//   Y[m, n] = sum_k X[m, k] W[n, k],  17 to about 128 rows, half operands, X in fragment order (LO_F16P).
+// GEMM on the packed weights for windows between the streaming kernel's 16 rows and the blocks of gemm_block.hip:
+//   Y[m, n] = sum_k X[m, k] W[n, k],  17 to 48 rows (unembedding: 64), half operands, X in fragment order (LO_F16P).
 //
 // At these sizes a launch is bound by reading the weights once, and on the way there by everything that is not the
 // K loop: the tiled kernel pads the rows to 128, splits K over compute units to fill the chip, and pays row maps,
@@ -18,7 +18,7 @@
 // 27.3 (100 MB: 3.7 TB/s), down 18.9; the tiled kernel took 25.5, 22.9, 35.4, 32.6.
 //
 // The row count is on the device: the weights of the first tiles are requested before it is known, then the kernel
-// switches on the row blocks there are (compiled for 1 .. RBM of them); more rows than 16 RBM are taken by further workgroups.
+// switches on the row blocks there are (compiled for 1 .. 4 of them); more rows than 64 are taken by further workgroups.
 #include "gemm_epilogue.h"
 #include "../../include/s2d2.h"
 
@@ -26,13 +26,13 @@
 
 namespace s2d2 {
 
-static constexpr int MID_NW = 8;
+static constexpr int MID_NW = 8, MID_RB = 4;   // wavefronts; most row blocks of 16 of a workgroup
 
 // LDS accesses of this wavefront done, then the workgroup's barrier; global loads stay in flight.
 __device__ __forceinline__ void mid_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Rows m0 .. of the window (at most 16 RB of them); w holds the first U tiles of the workgroup's first group.
-template <int EPI, int TPW, int RB, int U, int SLOTS, bool SHARED>
+template <int EPI, int TPW, int RB, int U, bool SHARED>
 __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (&w)[TPW * (EPI == SEPI_SWIGLU ? 2 : 1)][U],
                                               const int m0, const int M, const int KS_, uint8_t* smem) {
   constexpr int NACC = EPI == SEPI_SWIGLU ? 2 : 1, TA = TPW * NACC, NU = RB * TPW, HW = MID_NW / 2;
@@ -86,8 +86,8 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
   // ---- 1/rms of the rows from the producer's partial sums of squares, behind the first tiles (the accumulators'
   // registers are still free) ----
   if (EPI != SEPI_ADD_F32) {
-    constexpr int TPR = RB == 1 ? 32 : RB == 2 ? 16 : RB <= 4 ? 8 : 4;   // threads per row
-    constexpr int SSV = RB == 8 ? 8 : 64 / TPR;                           // float4 per thread and round
+    constexpr int TPR = RB == 1 ? 32 : RB == 2 ? 16 : 8;   // threads per row
+    constexpr int SSV = 64 / TPR;                           // float4 per thread and round
     const int ss_row = tid / TPR, ss_sub = tid % TPR;
     const int rr = min(m0 + ss_row, M - 1);   // rows past the count read a valid row; their 1/rms is never used
     const float* pp = a.ss_part + (size_t)(gather ? gather[rr] : rr) * a.ss_stride;
@@ -198,9 +198,9 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
         // are there, adds them in share order, clears them for the next launch and finishes the unit.  The
         // wait is bounded; one that runs out sets *pair_status and goes on with what is there.
         constexpr int KSM = 4;
-        unsigned long long* slot0 = a.pair_buf + (((size_t)blockIdx.y * sets + set) * (KSM - 1) * SLOTS + u * NACC) * 256 + lm;
+        unsigned long long* slot0 = a.pair_buf + (((size_t)blockIdx.y * sets + set) * (KSM - 1) * MID_RB * TA + u * NACC) * 256 + lm;
         if (ks > 0) {
-          unsigned long long* slot = slot0 + (size_t)(ks - 1) * SLOTS * 256;
+          unsigned long long* slot = slot0 + (size_t)(ks - 1) * MID_RB * TA * 256;
 #pragma unroll
           for (int c = 0; c < NACC; ++c)
 #pragma unroll
@@ -214,7 +214,7 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
           unsigned long long all = ~0ull;
 #pragma unroll
           for (int k = 0; k < KSM - 1; ++k) {
-            const size_t ko = (size_t)min(k, KS - 2) * SLOTS * 256;   // (fewer shares: the last one again)
+            const size_t ko = (size_t)min(k, KS - 2) * MID_RB * TA * 256;   // (fewer shares: the last one again)
 #pragma unroll
             for (int c = 0; c < NACC; ++c)
 #pragma unroll
@@ -236,7 +236,7 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
           for (int c = 0; c < NACC; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              __hip_atomic_store(slot0 + (size_t)k * SLOTS * 256 + c * 256 + i * 64, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(slot0 + (size_t)k * MID_RB * TA * 256 + c * 256 + i * 64, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               sum[c][i] += __uint_as_float((uint32_t)v[k][c][i]);
             }
         }
@@ -247,17 +247,17 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
   }
 }
 
-// Tiles in flight per wavefront (U): what fits next to the accumulators of RBM row blocks in 256 registers.
-constexpr int mid_u(int RBM, int TA) {
-  return 4 * RBM * TA + 16 * (RBM + TA) <= 150 ? 4 : 2;
+// Tiles in flight per wavefront (U): what fits next to the accumulators in 256 registers.
+constexpr int mid_u(int TA) {
+  return 4 * MID_RB * TA + 16 * (MID_RB + TA) <= 150 ? 4 : 2;
 }
 
-template <int EPI, int TPW, int RBM, bool SHARED>
+template <int EPI, int TPW, bool SHARED>
 __global__ __launch_bounds__(MID_NW * 64, 2) void gemm_mid_kernel(const GemmStreamArgs a, const int KS_) {
   extern __shared__ __align__(16) uint8_t smem[];
-  constexpr int NACC = EPI == SEPI_SWIGLU ? 2 : 1, TA = TPW * NACC, U = mid_u(RBM, TA);
+  constexpr int NACC = EPI == SEPI_SWIGLU ? 2 : 1, TA = TPW * NACC, U = mid_u(TA);
   const int KS = SHARED ? KS_ : 1;
-  const int m0 = blockIdx.y * 16 * RBM;
+  const int m0 = blockIdx.y * 16 * MID_RB;
   int M = 0;
   if (blockIdx.y != 0) {   // passes the row count may not need: request no weights for nothing
     M = *a.m_count;
@@ -280,99 +280,84 @@ __global__ __launch_bounds__(MID_NW * 64, 2) void gemm_mid_kernel(const GemmStre
   }
   if (blockIdx.y == 0) M = *a.m_count;
   if (M <= m0) return;
-  const int nb = min(RBM, (M - m0 + 15) >> 4);
-#define S2D2_MID_BODY(RB) gemm_mid_body<EPI, TPW, RB, U, RBM * TA, SHARED>(a, w, m0, M, KS, smem)
+  const int nb = min(MID_RB, (M - m0 + 15) >> 4);
+#define S2D2_MID_BODY(RB) gemm_mid_body<EPI, TPW, RB, U, SHARED>(a, w, m0, M, KS, smem)
   if (nb == 1) S2D2_MID_BODY(1);
   else if (nb == 2) S2D2_MID_BODY(2);
   else if (nb == 3) S2D2_MID_BODY(3);
-  else if (nb == 4) S2D2_MID_BODY(4);
-  else if (RBM > 4 && nb <= 6) S2D2_MID_BODY(6);
-  else if (RBM > 4) S2D2_MID_BODY(8);
+  else S2D2_MID_BODY(4);
 #undef S2D2_MID_BODY
 }
-
-// Most rows of a QKV, output or down projection (see below).
-int gemm_mid_most_rows(int NT, int KT) { const long long tiles = (long long)NT * KT; return tiles <= 16384 ? 256 : tiles <= 65536 ? 192 : MID_LEAST_MOST_ROWS; }
 
 // The lines against the neighbours (us per launch, weights from memory; this kernel / the other one):
 //   16 rows and fewer stay with the streaming kernel: 1.7B-shaped layer 37 / 32 (QKV, output, gate / up, down added up)
 //   32 rows: 55 / 84 against two row tiles of the streaming kernel, 4B-shaped layer
-//   64 rows: 73 / 116 (4B), 45 / 96 (1.7B), 113 / 154 (8B) against the tiled kernel; 128 rows 109 / 139, 69 / 113, 160 / 177
-//   gate / up, which has two accumulators per feature: 8B 54 / 54 at 80 rows, 66 / 57 at 128; 1.7B 26 / 35 at 128
-//   QKV, output and down projections past 128 rows (two passes over the weights): 4B 92 / 111 at 192 rows, 111 / 106 at
-//   256, the 1.7B-shaped QKV 24 / 39 at 256; the 8B down projection 59 / 65 at 144 rows, 73 / 67 at 192
-//   unembedding: 4B 184 / 182 at 64 rows, 224 / 198 at 96
+//   48 rows: 66 / 64 (4B), 41 / 41 (1.7B), 97 / 97 (8B) against gemm_block.hip, 64 rows: 76 / 68, 46 / 44, 116 / 100
+//   unembedding, against the tiled kernel: 4B 184 / 182 at 64 rows, 224 / 198 at 96
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a) {
   if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * MID_NW || a.m_hint <= 16) return false;
-  const long long tiles = (long long)a.NT * a.KT;   // KB of one matrix
-  if (kind == SEPI_STORE_F32) return a.m_hint <= 64 && (a.NT > 8 || a.gather);   // (a matrix of a few feature tiles: see the streaming kernel's launcher)
-  if (kind == SEPI_SWIGLU) return a.m_hint <= (tiles <= 32768 ? 128 : 80);
-  return a.m_hint <= gemm_mid_most_rows(a.NT, a.KT);
+  return kind != SEPI_STORE_F32 ? a.m_hint <= MID_MOST_ROWS : a.m_hint <= 64 && (a.NT > 8 || a.gather);   // (a matrix of a few feature tiles: see the streaming kernel's launcher)
 }
 
-template <int EPI, int TPW, int RBM, bool SHARED>
+template <int EPI, int TPW, bool SHARED>
 static void launch_mid_as(hipStream_t st, const GemmStreamArgs& a, int wgs, int passes, int KS) {
-  const unsigned lds = 512 + MID_NW / 2 * RBM * TPW * (EPI == SEPI_SWIGLU ? 2 : 1) * 1024;
+  const unsigned lds = 512 + MID_NW / 2 * MID_RB * TPW * (EPI == SEPI_SWIGLU ? 2 : 1) * 1024;
   static bool lds_set[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = -1;
   if (lds > 64 * 1024 && dev >= 0 && dev < 64 && !lds_set[dev] &&
-      hipFuncSetAttribute((const void*)gemm_mid_kernel<EPI, TPW, RBM, SHARED>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)
+      hipFuncSetAttribute((const void*)gemm_mid_kernel<EPI, TPW, SHARED>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)
     lds_set[dev] = true;   // on failure the launch below fails too, and the entry point reports that error
-  S2D2_LAUNCH((gemm_mid_kernel<EPI, TPW, RBM, SHARED>), dim3(wgs, passes), dim3(MID_NW * 64), lds, st, a, KS);
+  S2D2_LAUNCH((gemm_mid_kernel<EPI, TPW, SHARED>), dim3(wgs, passes), dim3(MID_NW * 64), lds, st, a, KS);
 }
 
-template <int EPI, int TPW, int RBM>
+template <int EPI, int TPW>
 static void launch_mid(hipStream_t st, const GemmStreamArgs& a, int passes, int KS) {
   const int groups = (a.NT + TPW - 1) / TPW;
   if constexpr (EPI != SEPI_STORE_F32)
-    if (KS > 1) return launch_mid_as<EPI, TPW, RBM, true>(st, a, groups * KS, passes, KS);
-  launch_mid_as<EPI, TPW, RBM, false>(st, a, std::min(groups, a.coop_wgs), passes, 1);
+    if (KS > 1) return launch_mid_as<EPI, TPW, true>(st, a, groups * KS, passes, KS);
+  launch_mid_as<EPI, TPW, false>(st, a, std::min(groups, a.coop_wgs), passes, 1);
 }
 
 // Feature tiles per workgroup (of each matrix) and workgroups that share K, by a model of the launch fitted to timings
 // of all three dense models' matrices at 20, 64 and 128 rows (it is within 15 % of most of them): the larger of what
 // memory and L2 deliver in all (6 and 20 TB/s, not overlapped) and to the busiest compute unit (30 and 100 GB/s), the
 // merge of the wavefronts' sums, and 2.5 us for handing sums over.
-static void mid_shape(int kind, const GemmStreamArgs& a, int RBM, int passes, int& tpw, int& KS) {
-  const int nacc = kind == SEPI_SWIGLU ? 2 : 1, rb = std::min(RBM, (a.m_hint + 15) / 16);
+static void mid_shape(int kind, const GemmStreamArgs& a, int passes, int& tpw, int& KS) {
+  const int nacc = kind == SEPI_SWIGLU ? 2 : 1, rb = std::min(MID_RB, (a.m_hint + 15) / 16);
   // (what the accumulators and two tiles of operands in flight leave of 256 registers)
-  const int most = kind == SEPI_SWIGLU ? (RBM == 4 ? 3 : 1) : kind == SEPI_STORE_F32 ? 4 : 3;
+  const int most = kind == SEPI_STORE_F32 ? 4 : 3;
   double best = 1e30;
   tpw = KS = 1;
   for (int t = 1; t <= most; ++t)
     for (int k = 1; k <= 4; ++k) {
       const int groups = (a.NT + t - 1) / t, ta = t * nacc;
       if (k > 1 && (kind == SEPI_STORE_F32 || groups * k > a.coop_wgs || a.KT < 4 * MID_NW * k || !a.pair_buf ||
-                    (long long)groups * passes * 3 * RBM * ta > a.pair_cap)) break;
+                    (long long)groups * passes * 3 * MID_RB * ta > a.pair_cap)) break;
       const double rounds = (groups * k + a.coop_wgs - 1) / a.coop_wgs, w = ta * a.KT * 1.024e-3, x = rb * a.KT * 1.024e-3;   // MB of a group
       const double us = std::max(groups * (w / 6.0 + x / 20.0), rounds / k * (w * 1e3 / 30.0 + x * 1e3 / 100.0)) + rounds * 0.12 * rb * ta + (k > 1 ? 2.5 : 0.0);
       if (us < best) { best = us; tpw = t; KS = k; }
     }
 }
 
-template <int EPI, int RBM>
+template <int EPI>
 static void launch_mid_kind(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
-  const int passes = (m_cap + 16 * RBM - 1) / (16 * RBM);
+  const int passes = (m_cap + 16 * MID_RB - 1) / (16 * MID_RB);
   int tpw, KS;
-  mid_shape(EPI, a, RBM, passes, tpw, KS);
-  if constexpr (EPI == SEPI_STORE_F32) { if (tpw == 4) return launch_mid<EPI, 4, RBM>(st, a, passes, KS); }
-  if constexpr (EPI != SEPI_SWIGLU || RBM == 4) {
-    if (tpw == 3) return launch_mid<EPI, 3, RBM>(st, a, passes, KS);
-    if (tpw == 2) return launch_mid<EPI, 2, RBM>(st, a, passes, KS);
-  }
-  launch_mid<EPI, 1, RBM>(st, a, passes, KS);
+  mid_shape(EPI, a, passes, tpw, KS);
+  if constexpr (EPI == SEPI_STORE_F32) { if (tpw == 4) return launch_mid<EPI, 4>(st, a, passes, KS); }
+  if (tpw == 3) return launch_mid<EPI, 3>(st, a, passes, KS);
+  if (tpw == 2) return launch_mid<EPI, 2>(st, a, passes, KS);
+  launch_mid<EPI, 1>(st, a, passes, KS);
 }
 
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
-#define S2D2_MID(EPI) (a.m_hint <= 64 ? launch_mid_kind<EPI, 4>(st, a, m_cap) : launch_mid_kind<EPI, 8>(st, a, m_cap))
   switch (kind) {
-    case SEPI_QKV_ROPE: S2D2_MID(SEPI_QKV_ROPE); break;
-    case SEPI_ADD_F32: S2D2_MID(SEPI_ADD_F32); break;
-    case SEPI_SWIGLU: S2D2_MID(SEPI_SWIGLU); break;
-    case SEPI_STORE_F32: launch_mid_kind<SEPI_STORE_F32, 4>(st, a, m_cap); break;   // (taken up to 64 rows only)
+    case SEPI_QKV_ROPE: launch_mid_kind<SEPI_QKV_ROPE>(st, a, m_cap); break;
+    case SEPI_ADD_F32: launch_mid_kind<SEPI_ADD_F32>(st, a, m_cap); break;
+    case SEPI_SWIGLU: launch_mid_kind<SEPI_SWIGLU>(st, a, m_cap); break;
+    case SEPI_STORE_F32: launch_mid_kind<SEPI_STORE_F32>(st, a, m_cap); break;
   }
-#undef S2D2_MID
 }
 
 }  // namespace s2d2

@@ -402,22 +402,25 @@ static constexpr int STREAM_MOST_ROWS = 32;   // two row tiles
 // The down projection has only d_model / 16 feature tiles (128 for the 1.7B shape): there K is shared by pairs of
 // workgroups (256 workgroups: 9.6 us per launch against 13.0 us with 128 workgroups of 16 wavefronts, which
 // streamed at half the rate of the other layer GEMMs).
-void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
+int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
   // wide windows: the LDS-tiled kernel reads the weights once per 128 rows instead of once per 16.  Not for a matrix
   // of a few feature tiles (the MoE router, 64 experts): its weights stay in L2, a 256-column tile would be mostly
   // empty, and a row tile of 16 per workgroup spreads the rows over the whole chip.
+  if (gemm_block_takes(kind, a, m_cap)) {
+    return launch_gemm_block(st, kind, a, m_cap);
+  }
   if (gemm_mid_takes(kind, a)) {
     launch_gemm_mid(st, kind, a, m_cap);
-    return;
+    return a.NT;
   }
   // The streaming kernel below takes half operands in fragment order only, except the ones that a store reads: a forward
-  // lays them out so whenever it expects at most MID_LEAST_MOST_ROWS rows, and a caller that did not is sent to the tiled
+  // lays them out so whenever it expects at most MID_MOST_ROWS rows, and a caller that did not is sent to the tiled
   // kernel, which takes rows too.
-  static_assert(MID_LEAST_MOST_ROWS >= STREAM_MOST_ROWS, "windows of the streaming kernel are laid out in fragment order");
+  static_assert(MID_MOST_ROWS >= STREAM_MOST_ROWS, "windows of the streaming kernel are laid out in fragment order");
   const bool half_rows = a.x_lo == LO_F16 && kind != SEPI_STORE_F32;
   if ((m_cap > STREAM_MOST_ROWS || half_rows) && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) {
     launch_gemm_tile(st, kind, kind == SEPI_ADD_F32 ? SPRO_BF16 : SPRO_BF16S, a, (m_cap + 127) / 128);
-    return;
+    return a.NT;
   }
   const int opm = operand_mode(a.x_lo);
 #define S2D2_CFG(EPI, PRO, NW, TPW, U)                                                     \
@@ -451,6 +454,7 @@ void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m
       break;
   }
 #undef S2D2_CFG
+  return a.NT;
 }
 
 // First norm of the forward: xg = bf16(h * gain), one partial sum of squares per row; and the row's RoPE table

@@ -619,37 +619,61 @@ void launch_tile_ts_copy(hipStream_t st, void* out) { S2D2_LAUNCH(tile_ts_copy_k
 void launch_tile_ts_copy(hipStream_t, void*) {}
 #endif
 
-template <int EPI, int PRO>
-static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) {
-  constexpr int COLS = (EPI == SEPI_SWIGLU ? 2 : 4) * WC;   // 16-feature tiles per workgroup
-  constexpr int RESIDENT = 256;                              // workgroups of one round over the chip
-  constexpr double PART_BYTES = 32768.0 * WC;                // fp32 partial of one tile and split
-  const int col_tiles = (a.NT + COLS - 1) / COLS;
-  // K is split over blockIdx.z when that shortens the launch.  The choice minimises a small cost model fitted to
-  // kernel traces of the batched configurations (microseconds; a round is as many workgroups as are resident on
-  // the chip at once):
-  //   rounds * (K steps per split * 1.05 + 6)                       K loop + prologue / epilogue per round
-  //   + [splits > 1] * 10                                           partial write, wait and shared merge, or, when the
-  //     launch has more workgroups than compute units (nobody waits, the last arrival merges the tile):
-  //     8 + live tiles * splits * partial bytes * 2 / 3 TB/s
-  // It is judged on the rows the caller expects (m_hint).  Every split keeps at least 4 K steps and the partials
-  // must fit their buffer.
-  int KS = 1;
+// K is split over blockIdx.z when that shortens the launch.  The choice minimises a small cost model fitted to
+// kernel traces of the batched configurations (microseconds; a round is as many workgroups as are resident on
+// the chip at once):
+//   rounds * (K steps per split * 1.05 + 6)                       K loop + prologue / epilogue per round
+//   + [splits > 1] * 10                                           partial write, wait and shared merge, or, when the
+//     launch has more workgroups than compute units (nobody waits, the last arrival merges the tile):
+//     8 + live tiles * splits * partial bytes * 2 / 3 TB/s
+// It is judged on the rows the caller expects (m_hint).  Every split keeps at least 4 K steps and the partials
+// must fit their buffer.
+struct TileSplits { int KS; double loop_us; };
+static TileSplits tile_splits(int kind, const GemmStreamArgs& a, int row_tiles) {
+  constexpr int RESIDENT = 256;                   // workgroups of one round over the chip
+  constexpr double PART_BYTES = 32768.0 * WC;     // fp32 partial of one tile and split
+  const int cols = (kind == SEPI_SWIGLU ? 2 : 4) * WC, col_tiles = (a.NT + cols - 1) / cols;
   const long long tiles = (long long)col_tiles * row_tiles;
   const int hint_tiles = a.m_hint > 0 ? std::min(row_tiles, (a.m_hint + TM - 1) / TM) : row_tiles;
   const long long live = (long long)col_tiles * hint_tiles;
   const int nk = (a.K + TK - 1) / TK;
   const double step_us = 1.05, merge_us = 10.0, round_us = 6.0;
+  auto loop = [&](int ks) { return (double)((live * ks + RESIDENT - 1) / RESIDENT) * ((nk + ks - 1) / ks * step_us + round_us); };
+  int KS = 1;
   if (a.tile_partials && a.grouped == GROUP_NONE && tiles <= a.tile_counter_cap) {
     double best = 1e30;
     for (int ks = 1; ks <= 8; ++ks) {
       if (ks > 1 && (nk / ks < 4 || tiles * ks * (WC / 2) > a.tile_partial_cap)) break;
-      const double rounds = (double)((live * ks + RESIDENT - 1) / RESIDENT), steps = (double)((nk + ks - 1) / ks);
-      double t = rounds * (steps * step_us + round_us);
+      double t = loop(ks);
       if (ks > 1) t += live * ks <= a.coop_wgs ? merge_us : 8.0 + (double)live * ks * PART_BYTES * 2.0 / 3.0e6;
       if (t < best - 1e-9) { best = t; KS = ks; }
     }
   }
+  return {KS, loop(KS)};
+}
+// One and a half rounds of tiles run as such (see the kernel).
+static bool tile_stream_k(int kind, const GemmStreamArgs& a, int row_tiles, int KS) {
+  const int cols = (kind == SEPI_SWIGLU ? 2 : 4) * WC, col_tiles = (a.NT + cols - 1) / cols;
+  const int hint_tiles = a.m_hint > 0 ? std::min(row_tiles, (a.m_hint + TM - 1) / TM) : row_tiles;
+  const long long live = (long long)col_tiles * hint_tiles;
+  return a.grouped == GROUP_NONE && KS == 1 && hint_tiles > 1 && a.tile_partials && a.coop_wgs > 0 && 2 * live == 3LL * a.coop_wgs && (a.coop_wgs & 15) == 0 && (col_tiles & 7) == 0 &&
+         (a.coop_wgs / 16) % hint_tiles == 0 && live <= a.tile_counter_cap && live * 2 * (WC / 2) <= a.tile_partial_cap && (a.K + TK - 1) / TK >= 8;
+}
+// Time of a launch, for the choice between the kernels.  (What a split really costs grows with the number of splits: 8B
+// down projection, 512 rows, 4 splits 72 us, 256 rows, 8 splits 69.  With that in the model above fewer splits would be
+// chosen, which is slower.)
+double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles) {
+  const TileSplits s = tile_splits(kind, a, row_tiles);
+  if (tile_stream_k(kind, a, row_tiles, s.KS)) return 0.75 * s.loop_us;
+  return s.loop_us + (s.KS > 1 ? 7.0 + 3.0 * s.KS : 0.0);
+}
+
+template <int EPI, int PRO>
+static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) {
+  constexpr int COLS = (EPI == SEPI_SWIGLU ? 2 : 4) * WC;   // 16-feature tiles per workgroup
+  const int col_tiles = (a.NT + COLS - 1) / COLS;
+  const int hint_tiles = a.m_hint > 0 ? std::min(row_tiles, (a.m_hint + TM - 1) / TM) : row_tiles;
+  const int KS = tile_splits(EPI, a, row_tiles).KS;
   // blockIdx.y: the row tiles the caller expects (a workgroup walks on if there are more); all of them for the
   // expert-grouped launches, whose tile list lives on the device
   dim3 grid(col_tiles, a.grouped == GROUP_NONE ? hint_tiles : row_tiles, KS), block(128 * WC);
@@ -661,8 +685,7 @@ static void launch_tile(hipStream_t st, const GemmStreamArgs& a, int row_tiles) 
   // K splits dealt to XCDs (see the kernel): splits that divide the 8 XCDs, whole columns of tiles per XCD
   b.split_xcd = a.grouped == GROUP_NONE && KS > 1 && 8 % KS == 0 && col_tiles % (8 / KS) == 0 &&
                 ((long long)col_tiles * hint_tiles * KS) % 8 == 0;
-  if (b.xcd_order && a.tile_partials && a.coop_wgs > 0 && 2 * live == 3LL * a.coop_wgs && (a.coop_wgs & 15) == 0 && (col_tiles & 7) == 0 && (a.coop_wgs / 16) % hint_tiles == 0 &&
-      live <= a.tile_counter_cap && live * 2 * (WC / 2) <= a.tile_partial_cap && nk >= 8) {
+  if (tile_stream_k(EPI, a, row_tiles, KS)) {
     b.stream_k = hint_tiles;   // see the kernel: 3/2 tiles per workgroup, one workgroup per compute unit
     b.xcd_order = 0;
     grid = dim3(a.coop_wgs, 1, 1);

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
 }
 
 // h[row] += sum over slots (in slot order) of y[row, slot]; also the operand and the partial sums
-// of squares of the next norm (one partial per 16 features, like the GEMM epilogue writes them).
+// of squares of the next norm (one number per row).
 __global__ __launch_bounds__(256) void moe_combine_kernel(const float* __restrict__ y, int d, int top_k,
                                                           const int32_t* __restrict__ m_count, float* __restrict__ h,
                                                           bf16_t* __restrict__ xg, int xg_ld, int xg_lo,
@@ -148,6 +148,8 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const float* __restric
                                                           float* __restrict__ ss, int ss_stride) {
   const int row = blockIdx.x;
   if (row >= *m_count) return;
+  __shared__ float s_sq[4];
+  float sq = 0.f;
   for (int c = threadIdx.x * 4; c < d; c += 1024) {
     float4 acc = *(const float4*)(h + (size_t)row * d + c);
     for (int k = 0; k < top_k; ++k) {
@@ -158,11 +160,13 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const float* __restric
     const float4 gn = *(const float4*)(gain_next + c);
     const float xv[4] = {acc.x * gn.x, acc.y * gn.y, acc.z * gn.z, acc.w * gn.w};
     act_put4(xg, xg_lo, row, c, xg_ld, xv[0], xv[1], xv[2], xv[3]);
-    float sq = (acc.x * acc.x + acc.y * acc.y) + (acc.z * acc.z + acc.w * acc.w);
-    sq += __shfl_xor(sq, 1, 64);
-    sq += __shfl_xor(sq, 2, 64);
-    if ((threadIdx.x & 3) == 0) ss[(size_t)row * ss_stride + (c >> 4)] = sq;
+    sq += (acc.x * acc.x + acc.y * acc.y) + (acc.z * acc.z + acc.w * acc.w);
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+  if ((threadIdx.x & 63) == 0) s_sq[threadIdx.x >> 6] = sq;
+  __syncthreads();
+  if (threadIdx.x == 0) ss[(size_t)row * ss_stride] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
 }
 
 __global__ void moe_copy_choices_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int layers,

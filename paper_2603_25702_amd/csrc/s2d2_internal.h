@@ -242,7 +242,7 @@ struct GemmStreamArgs {
   bf16_t* xg_out;           // [*, xg_ld]
   int32_t xg_ld, xg_lo;     // row stride and low-plane offset (as x_lo) of xg_out
   const float* gain_next;   // [N]
-  float* ss_out;            // [*, ss_stride], entry nt of a row = this tile's share
+  float* ss_out;            // [*, ss_stride], an entry per feature tile, or per group of them (see launch_gemm_stream)
   // SEPI_QKV_ROPE
   const float2* rope_cs;    // [rows, D/2] (cos, sin)
   int32_t Hq, Hkv, D, wpad;
@@ -288,14 +288,18 @@ void launch_rope_table(hipStream_t st, const Plan& p, int rows_cap, int D, float
 void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, int rows_cap, const float* gain,
                        float* h, void* xg, int xg_ld, int xg_lo, float* ss, int ss_stride,
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
-void launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
-// gemm_mid.hip : windows of 17 to about 128 rows, half operands in fragment order
-constexpr int MID_LEAST_MOST_ROWS = 160;   // gemm_mid_most_rows of the largest matrices
-int gemm_mid_most_rows(int NT, int KT);
+// (a residual add returns the number of partial sums of squares it leaves per row)
+int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+// gemm_mid.hip : windows of 17 to 48 rows (unembedding: 64), half operands in fragment order
+constexpr int MID_MOST_ROWS = 48;
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a);
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+// gemm_block.hip : wider windows, half operands in fragment order
+bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap);
+int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
 // gemm_tile.hip : 128 x 256 LDS-tiled kernel on the same packed weights and argument block
 void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a, int row_tiles);
+double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // estimate
 
 // moe.hip
 void launch_moe_route(hipStream_t st, const float* logits, int E, int top_k, const int32_t* m_count, int rows_cap,

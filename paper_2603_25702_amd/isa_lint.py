@@ -51,6 +51,40 @@ def scan_asm(text: str) -> List[Tuple[str, int, str]]:
     return found
 
 
+_MFMA_AGPR = re.compile(r"^v_mfma_f32_16x16x32\w*\s+a\[(\d+):(\d+)\]")
+_AGPR_READ = re.compile(r"^(?:v_accvgpr_(?:read_b32|mov_b32)\s+\w+,\s*a(\d+)|ds_write\w*\s+.*\ba\[?(\d+))")
+MFMA_RESULT_WAIT = 11   # wait states between a product of eight passes and a vector instruction that reads it
+
+
+def scan_agpr_reads(text: str) -> List[Tuple[str, int, str]]:
+    """Returns (kernel, line number, instruction) for every read of an accumulator register too soon behind the MFMA that
+    writes it, in program order."""
+    kernel, now, written = "?", 0, {}
+    found = []
+    for no, raw in enumerate(text.splitlines(), 1):
+        m = _KERNEL.match(raw)
+        if m:
+            kernel, now, written = m.group(1), 0, {}
+        ins = raw.split(";")[0].strip()
+        if not ins or ins.startswith(".") or ins.endswith(":"):
+            continue
+        m = _AGPR_READ.match(ins)
+        if m:
+            reg = int(m.group(1) or m.group(2))
+            if now - written.get(reg, -10 ** 9) < MFMA_RESULT_WAIT:
+                found.append((kernel, no, ins))
+        m = re.match(r"^v_accvgpr_(?:write_b32|mov_b32)\s+a(\d+)", ins)
+        if m:
+            written.pop(int(m.group(1)), None)   # another value
+        nop = re.match(r"^s_nop\s+(\d+)", ins)
+        now += int(nop.group(1)) + 1 if nop else 1
+        m = _MFMA_AGPR.match(ins)
+        if m:
+            for reg in range(int(m.group(1)), int(m.group(2)) + 1):
+                written[reg] = now
+    return found
+
+
 def compile_to_asm(src: str, out_dir: str) -> str:
     out = os.path.join(out_dir, src.replace(".hip", ".s"))
     flags = [f for f in FLAGS if f != "-fPIC"]
@@ -69,7 +103,8 @@ def lint_sources(sources=None, jobs: int = 6) -> List[Tuple[str, str, int, str]]
             paths = list(ex.map(lambda s: compile_to_asm(s, tmp), sources))
         found = []
         for src, path in zip(sources, paths):
-            found += [(src, k, no, ins) for k, no, ins in scan_asm(open(path).read())]
+            text = open(path).read()
+            found += [(src, k, no, ins) for k, no, ins in scan_asm(text) + scan_agpr_reads(text)]
     return found
 
 
@@ -77,5 +112,5 @@ if __name__ == "__main__":
     bad = lint_sources()
     for src, k, no, ins in bad:
         print(f"{src}: {k}: line {no}: {ins}")
-    print(f"{len(bad)} matrix instruction(s) under a narrowed execution mask without a skip branch")
+    print(f"{len(bad)} matrix instruction(s) under a narrowed execution mask without a skip branch, or results read too early")
     sys.exit(1 if bad else 0)

@@ -37,6 +37,24 @@ def test_scanner_flags_an_mfma_in_a_mask_region_without_a_skip_branch():
     assert isa_lint.scan_asm(GOOD) == []
 
 
-def test_compiled_kernels_have_no_mfma_under_a_narrowed_execution_mask():
+EARLY = """
+_Z6kernelv:
+	v_mfma_f32_16x16x32_f16 a[4:7], v[6:9], v[46:49], a[4:7]
+	v_mfma_f32_16x16x32_f16 a[8:11], v[6:9], v[46:49], a[8:11]
+	s_nop 7
+	v_accvgpr_read_b32 v0, a4
+	v_accvgpr_read_b32 v1, a9
+	s_nop 7
+	v_accvgpr_read_b32 v1, a9
+	s_endpgm
+"""
+
+
+def test_scanner_flags_a_result_that_is_read_before_it_is_there():
+    found = isa_lint.scan_agpr_reads(EARLY)
+    assert [no for _, no, _ in found] == [6, 7]   # 9 and 9 wait states
+
+
+def test_compiled_kernels_have_no_mfma_under_a_narrowed_execution_mask_and_read_no_result_early():
     found = isa_lint.lint_sources()
     assert not found, "\n".join(f"{s}: {k}: line {no}: {ins}" for s, k, no, ins in found[:20])
