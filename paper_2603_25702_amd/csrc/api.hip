@@ -173,7 +173,7 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   c->plan.seq_j = cv.take<int32_t>(NB);
   c->plan.seq_L = cv.take<int32_t>(NB);
   c->plan.seq_splits = cv.take<int32_t>(NB);
-  c->plan.split_of = cv.take<int32_t>(NB + WIDE_MAX_TARGET);
+  c->plan.split_of = cv.take<int4>(2 * (NB + WIDE_MAX_TARGET));
   c->h = cv.take<float>(R * d.d_model);
   const size_t P = act_planes(d);
   // GEMM inputs: two bf16 planes, or whole blocks of 16 rows of half values (fragment order)
@@ -287,7 +287,8 @@ WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) 
   WideShape w;
   w.q_tiles = (win * (c->desc.n_q_heads / c->desc.n_kv_heads) + 31) / 32;
   const int wg = c->desc.n_kv_heads * ((w.q_tiles + 7) / 8);
-  w.target = std::max(1, std::min((c->wide_wgs + wg - 1) / wg, WIDE_MAX_TARGET));
+  const int fill = attention_wide_nw(w.q_tiles) == 8 ? c->wide_wgs / 2 : c->wide_wgs;   // (one workgroup of eight wavefronts per compute unit, two of four)
+  w.target = std::max(1, std::min((fill + wg - 1) / wg, WIDE_MAX_TARGET));
   w.Z = attention_wide_splits(geom(c, kv), N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
   return w;
 }
@@ -324,7 +325,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     Z = std::max(1, std::min(std::min(want, (cap_tiles + 7) / 8), c->attn_zmax));
     if (wide) {
       Z = ws.Z;
-      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, Z, ws.target)) > 160 * 1024) wide = false, Z = 1;
+      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, Z, ws.target), attention_wide_nw(q_tiles)) > 160 * 1024) wide = false, Z = 1;
     }
   }
   const size_t lds = flash ? 0 : attention_generic_lds_bytes(g, sz.win);

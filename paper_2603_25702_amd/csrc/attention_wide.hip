@@ -3,15 +3,22 @@
 // attn_flash_kernel gives every query tile a workgroup of its own, so a (sequence, KV head) pair with
 // q_tiles query tiles reads its cached K / V q_tiles times.  Here the NW wavefronts of a workgroup each own
 // ONE query tile of the same (sequence, KV head, key split) and walk the keys together: a 32-key tile of K
-// and of V^T is fetched from global memory once per workgroup (every thread one or a few 16-byte pieces),
-// parked in LDS, and read from there as MFMA operands by all wavefronts.  A wavefront never shares its
-// softmax state, so there is no merge inside the workgroup; key splits are added up by a second
-// launch, in split order.
+// and of V^T is fetched from global memory once per workgroup, parked in LDS, and read from there as MFMA operands by all
+// wavefronts.  Key splits are added up by a second launch, in split order.
 //
-// Pipeline: two tiles are in flight in registers (sets R0 / R1) while a third is being consumed from one of two
-// LDS buffers; a wavefront parks tile i + 1 in the other buffer after its own math on tile i, and one barrier
-// per tile separates that from the reads of tile i + 1.  The page-table entries of the split's key range are copied to LDS
-// once, so address generation never waits on a dependent global load.
+// Eight wavefronts (one workgroup per compute unit) of which at most half have a query tile with rows, as in every window without
+// committed tokens in front, stand in two key groups: the group of an even and of an odd tile, so a step of the walk is two tiles
+// long and every wavefront multiplies.  The two states of a query tile are merged in LDS at the end.
+//
+// Pipeline: two groups of tiles are in flight in registers while a third is being consumed from one of two LDS buffers; a
+// wavefront parks its pieces of group g + 1 in the other buffer after its own math on group g, and one barrier per group
+// separates that from the reads of group g + 1.  The page-table entries of the split's key range are copied to LDS
+// once, and read a group ahead of the loads that need them.  What bounds a long prefix is the issue of vector-ALU
+// instructions (softmax, conversions, addresses), then the clock, which falls to 1.7 .. 1.9 GHz here.
+// Attention per launch (without the merge), one tile at a time with separate fetching wavefronts / two tiles in two key groups:
+// 8B verification, 32 sequences of 2048 .. 8192 tokens 141 / 113 us, 8B draft 114 / 90; with the merge, 4B verification of
+// 2 x 32 behind 3000 tokens 45 / 32, MoE draft of 4 x 16 behind 600 18 / 16; a launch of four tiles a split over four
+// query tiles is 0.5 to 2 us longer (4B 2 x 32 behind 1000: 12.5 / 14.8).
 #include "attention_flash.h"
 #include <stdlib.h>
 #include <type_traits>
@@ -34,8 +41,9 @@ static constexpr int FW_VROW = 80;                // bytes per V^T row in LDS: 3
 static constexpr int FW_KBUF = 32 * FW_KROW;
 static constexpr int FW_BUF = FW_KBUF + 128 * FW_VROW;
 static constexpr int FW_RING = 2;
+constexpr int fw_tiles(int nw) { return nw == 8 ? 2 : 1; }   // most tiles walked at a time
 
-size_t attention_wide_lds_bytes(int pt_cap) { return (size_t)FW_RING * FW_BUF + (size_t)pt_cap * 4; }
+size_t attention_wide_lds_bytes(int pt_cap, int nw) { return (size_t)FW_RING * fw_tiles(nw) * FW_BUF + (size_t)pt_cap * 4; }
 
 struct FwTile { bool win; int kbase, limit; };
 
@@ -49,6 +57,11 @@ __device__ __forceinline__ uint4 fw_mask(uint4 v, int nv) {
     w[e] &= m;
   }
   return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// (every byte of the cache is read once per launch, past the caches: 7.0 TB/s for the 6.1 of plain loads)
+__device__ __forceinline__ uint4 ld_kv(uint64_t at) {
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t*)at));
 }
 
 // 8 bf16 values (one 16-byte operand piece) as IEEE half: exact for magnitudes in the half range (the 8-bit
@@ -71,37 +84,38 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
     float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift) {
-  constexpr int D = FA_D, T = NW * 64, U = 512 / T;
+  constexpr int D = FA_D, T = NW * 64;
   constexpr bool SPLIT = QM == OPM_BF16X2, F16 = QM == OPM_F16;
-  static_assert(U == 1 || U == 2, "8 or 4 wavefronts");
   extern __shared__ __align__(16) unsigned char lds[];
-  int32_t* s_pt = (int32_t*)(lds + FW_RING * FW_BUF);
+  int32_t* s_pt = (int32_t*)(lds + FW_RING * fw_tiles(NW) * FW_BUF);
   // Splits are numbered through over the sequences (Plan.split_of), so the workgroups without one are the last of the
   // grid.  Between the others they leave compute units empty that hold two workgroups elsewhere, one after the
   // other (the hardware deals workgroups out in turn, whether they leave at once or not): 125 -> 167 us.
   const int qgrp = blockIdx.y;
+  const int4 so = p.split_of[2 * blockIdx.z], sq = p.split_of[2 * blockIdx.z + 1];   // (one round trip for all of a split's description)
   if ((int)blockIdx.z >= p.counts[2]) return;
-  const int so = p.split_of[blockIdx.z], z = so >> 16;
+  const int n = so.x, z = so.y, t0 = so.z, t1 = so.w, Zn = sq.x, S = sq.y, row0 = sq.z, nw = sq.w;
   const int Hkv = g.n_kv_heads, ps = g.page_size;
-  const int n = so & 0xffff, kvh = blockIdx.x, item = n * Hkv + kvh;
+  const int kvh = blockIdx.x, item = n * Hkv + kvh;
   const int grp = Hq / Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, h = lane >> 5;
   const int cap = g.max_pages_per_seq * ps;
-  const int S = max(0, min(g.seq_len[n], cap));
-  const int row0 = p.seq_row0[n], nw = p.seq_rows[n];
   const int nq = nw * grp;
   // query tiles qgrp * per .. + per of this (sequence, KV head) belong to this workgroup, one per wavefront (per <= NW)
   if (qgrp * per * 32 >= nq) return;            // the whole workgroup: nothing to do (before any barrier)
-  const int qt = qgrp * per + wave, q0 = qt * 32;
-  const bool active = wave < per && q0 < nq;
+  // Query tiles with rows; with at least two of eight wavefronts for each, the wavefronts stand in two key groups that walk two
+  // 32-key tiles at a time, and their states are merged in LDS at the end.
+  const int n_live = min(per, (nq - qgrp * per * 32 + 31) >> 5);
+  const bool two = NW == 8 && 2 * n_live <= NW;
+  const int kg = two && wave >= n_live ? 1 : 0, wq = wave - kg * n_live;
+  const bool active = wq < n_live;
+  const int qt = qgrp * per + min(wq, n_live - 1), q0 = qt * 32;
   const int qi = min(q0 + c, nq - 1);
   const int r = row0 + qi / grp, head = kvh * grp + qi % grp;
   const int lo = p.row_lo[r], hi = p.row_hi[r];
 
-  const int Tc = (S + 31) >> 5, Tw = (nw + 31) >> 5;
-  const int Zn = p.seq_splits[n];
-  const int t0 = (int)((long long)Tc * z / Zn), t1 = (int)((long long)Tc * (z + 1) / Zn);
+  const int Tw = (nw + 31) >> 5;
   const int n_c = t1 - t0, n_w = z == Zn - 1 ? Tw : 0, n_it = n_c + n_w;
 
   // page-table slice of this split's keys
@@ -132,17 +146,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
 
   // (closures capture scalars by value: captured references would pin the locals to memory)
   // Leading tiles of this split that are full tiles of cached keys (all but, at most, the last cached tile of the
-  // last split).  The loops below run them through forms of fetch / park / compute that are compiled for exactly
-  // that case (FAST): no clamps, no second address form, no visibility mask.  Both kinds of wavefronts are bound
-  // by their vector-ALU instructions, not by the matrix pipes or by memory.
+  // last split).  They take forms of fetch / park / compute of their own: no clamps, no second address form, no visibility
+  // mask.  A wavefront issues an instruction every four to five cycles, which is what a step of the walk waits for (its matrix
+  // products and the memory take less), so the forms are chosen by branches on scalars, and with as few instructions as possible.
   const int n_fast = max(0, min(n_c, (S >> 5) - t0));
-  auto tile_fast = [=](int i) __attribute__((always_inline)) {
-    FwTile t;
-    t.win = false;
-    t.kbase = (t0 + i) * 32;
-    t.limit = S;
-    return t;
-  };
   auto tile_of = [=](int i) __attribute__((always_inline)) {
     FwTile t;
     i = min(i, n_it - 1);
@@ -151,64 +158,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     t.limit = t.win ? nw : S;
     return t;
   };
-  // piece idx of a tile: K row idx / 16, 16-byte piece idx % 16;  V^T row idx / 4, keys 8 (idx % 4) .. + 8.
-  // Thread tid handles pieces tid + u T, u < U (each piece in a named register set, never an indexed array).
-  // (offsets are written as  page * page_stride + [terms that depend on the thread alone] + [32-bit terms of the
-  // tile]: the middle part is computed once per thread ahead of the loop, and a piece costs one table look-up and
-  // one 64-bit multiply-add per tile; the fetching wavefronts share their SIMDs with the computing ones)
-  const size_t pstride = (size_t)Hkv * ps * D;   // elements of a page
-  auto fetchp = [=](auto fast, int idx, int i, uint4& kr, uint4& vr) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast)::value;
-    const int kk = idx >> 4, kch = idx & 15, vd = idx >> 2, vko = (idx & 3) * 8;
-    if (FAST) {
-      const int key = (t0 + i) * 32 + kk, kv0 = (t0 + i) * 32 + vko;
-      const int pk = s_pt[min((key >> ps_shift) - pb0, pt_cap - 1)];
-      const int pv = s_pt[min((kv0 >> ps_shift) - pb0, pt_cap - 1)];
-      kr = *(const uint4*)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D);
-      vr = *(const uint4*)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1)));
-      return;
-    }
-    const FwTile t = tile_of(i);
-    const int key = min(t.kbase + kk, t.limit - 1);   // rows beyond the region read a valid row; their scores are masked
-    const int key0 = t.kbase + vko;
-    // both address forms are computed and one is selected: no control flow around the loads
-    const int kv0 = min(key0, cap - 8);
-    const int pk = s_pt[max(0, min((key >> ps_shift) - pb0, pt_cap - 1))];
-    const int pv = s_pt[max(0, min((kv0 >> ps_shift) - pb0, pt_cap - 1))];
-    const bf16_t* kp_c = k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D;
-    const bf16_t* vp_c = v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1));
-    const bf16_t* kp_w = k_win + ((size_t)row0 * Hkv + kvh) * D + kch * 8 + (size_t)key * (Hkv * D);
-    const bf16_t* vp_w = vT_win + ((size_t)(n * Hkv + kvh) * D + vd) * wpad + min(key0, wpad - 8);
-    kr = *(const uint4*)(t.win ? kp_w : kp_c);
-    vr = *(const uint4*)(t.win ? vp_w : vp_c);
-  };
-  auto fetch1 = [=](auto fast, int u, int i, uint4& kr, uint4& vr) __attribute__((always_inline)) { fetchp(fast, min(tid + u * T, 511), i, kr, vr); };
-  auto stashp = [=](auto fast, int idx, int i, int b, uint4 kr, uint4 vr) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast)::value;
-    unsigned char* base = lds + b * FW_BUF;
-    const int kk = idx >> 4, kch = idx & 15, vd = idx >> 2, vko = (idx & 3) * 8;
-    if (FAST) {
-      *(uint4*)(base + kk * FW_KROW + kch * 16) = F16 ? fw_to_f16(kr) : kr;
-      *(uint4*)(base + FW_KBUF + vd * FW_VROW + vko * 2) = F16 ? fw_to_f16(vr) : vr;
-      return;
-    }
-    const FwTile t = tile_of(i);
-    // half mode: cached tiles are bf16 and are converted here; the window's own rows already come as half values
-    // (k_win / vT_win then point at the half copies the QKV projection wrote: 11 bits instead of the cache's 8)
-    const uint4 vm = t.kbase + 32 <= t.limit ? vr : fw_mask(vr, t.limit - (t.kbase + vko));   // (uniform: only a region's last tile is partial)
-    const bool cvt = F16 && !t.win;
-    *(uint4*)(base + kk * FW_KROW + kch * 16) = cvt ? fw_to_f16(kr) : kr;
-    *(uint4*)(base + FW_KBUF + vd * FW_VROW + vko * 2) = cvt ? fw_to_f16(vm) : vm;
-  };
-  auto stash1 = [=](auto fast, int u, int i, int b, uint4 kr, uint4 vr) __attribute__((always_inline)) { stashp(fast, min(tid + u * T, 511), i, b, kr, vr); };   // clamped duplicates rewrite the same bytes
+  // A tile is 8 KB of keys and 8 KB of values, 16 pieces of 1 KB, a piece one load of a wavefront.  Inside a page the keys of
+  // a head are contiguous, and so are its values ([D, page_size]), so a piece lies in one page: its address is the
+  // page's, the piece's place in it and an offset per lane.  Piece j of the keys: rows 4 j .. + 3.  Piece j of the
+  // values: kpp = min(page_size, 32) keys of page j / (kpp / 4) of the tile, for 512 / kpp head-dim rows.  Pieces 2 j and 2 j + 1 share
+  // their page.
+  const uint32_t pbytes = (uint32_t)Hkv * (uint32_t)ps * (D * 2);   // bytes of a page
+  const int kpp_sh = min(ps_shift, 5), kpp = 1 << kpp_sh, opl = kpp_sh - 3;   // log2 of the 8-key pieces in a row
+  const int vd_l = lane >> opl, vo_l = lane & ((1 << opl) - 1), vstep = (512 >> kpp_sh) * ps * 2;   // vstep: from a piece to the next of its page
+  const uint64_t kb_l = (uint64_t)(k_pages + (size_t)kvh * ps * D) + lane * 16, vb_l = (uint64_t)(v_pages + (size_t)kvh * ps * D) + (vd_l * ps + vo_l * 8) * 2;
+  auto v_key = [=](int j) __attribute__((always_inline)) { return (j >> (kpp_sh - 2)) * kpp; };                        // first key of piece j of the values, in its tile
+  auto v_row = [=](int j) __attribute__((always_inline)) { return (j & ((kpp >> 2) - 1)) << (9 - kpp_sh); };   // and its first head-dim row
   const int kperm = fa_perm(c);
-  auto compute = [=](auto fast, FaState& st, const uint4 (&qf)[8], const uint4 (&ql)[SPLIT ? 8 : 1], int i, int b) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast)::value;
-    const FwTile t = FAST ? tile_fast(i) : tile_of(i);
-    const unsigned char* kb = lds + b * FW_BUF + kperm * FW_KROW + 16 * h;
-    const unsigned char* vb = lds + b * FW_BUF + FW_KBUF + c * FW_VROW + 16 * h;
+  auto compute = [=](FaState& st, const uint4 (&qf)[8], const uint4 (&ql)[SPLIT ? 8 : 1], int i, const unsigned char* buf) __attribute__((always_inline)) {
+    const unsigned char* kb = buf + kperm * FW_KROW + 16 * h;
+    const unsigned char* vb = buf + FW_KBUF + c * FW_VROW + 16 * h;
     f32x16_t sacc;
-    S2D2_WTS(0, FAST && wave == 0 && i == 16);
+    S2D2_WTS(0, wave == 0 && i == 16);
 #pragma unroll
     for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
 #pragma unroll
@@ -226,13 +192,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     // the running maximum is kept in scaled units, exp2(s * scale - m) is one fused multiply-add per element.
 #ifdef S2D2_KERNEL_TIMING
     if (sacc[0] == 12345.678f) return;
-    S2D2_WTS(1, FAST && wave == 0 && i == 16);
+    S2D2_WTS(1, wave == 0 && i == 16);
 #endif
     float mx = -INFINITY;
-    if (FAST || (!t.win && t.kbase + 32 <= t.limit)) {   // a full tile of cached keys: every key is visible
+    if (i < n_fast) {   // every key is visible
 #pragma unroll
       for (int j = 0; j < 16; ++j) mx = fmaxf(mx, sacc[j]);
     } else {
+      const FwTile t = tile_of(i);
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         const int key = t.kbase + 16 * (j >> 3) + 8 * h + (j & 7);
@@ -245,7 +212,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
     // no divergent control flow around the MFMAs: a query row that sees nothing yet keeps m = -inf
     // and uses 0 as the reference, which makes every p below exp2(-inf) = 0
-    const float m_new = fmaxf(st.m, mx);
+    // The reference moves only when the maximum has outgrown it by 2^8 (or there was none): the weights stay below 256, far
+    // inside the half range, with the same significant bits, and the accumulators are rescaled in few tiles.
+    const float m_new = mx > st.m + 8.f ? mx : st.m;
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(st.m - m_ref);
     float ls = 0.f;
@@ -268,7 +237,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     st.m = m_new;
 #ifdef S2D2_KERNEL_TIMING
     if (ls == 12345.678f) return;
-    S2D2_WTS(2, FAST && wave == 0 && i == 16);
+    S2D2_WTS(2, wave == 0 && i == 16);
 #endif
     // the accumulators are rescaled only when some row's maximum moved (alpha = 1 leaves them as they are)
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
@@ -293,122 +262,201 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     }
 #ifdef S2D2_KERNEL_TIMING
     if (st.o[3][15] == 12345.678f) return;
-    S2D2_WTS(3, FAST && wave == 0 && i == 16);
+    S2D2_WTS(3, wave == 0 && i == 16);
 #endif
   };
 
-  // A workgroup of 8 wavefronts of which at most half own a query tile with rows (a fresh block fills 4 of the
-  // verifier's 6 tiles): the upper half of the wavefronts does all the fetching, PP pieces per thread in two
-  // register sets, and the wavefronts that compute do nothing else.  With every wavefront fetching its share, the
-  // address arithmetic and LDS stores of the fetch sat on the critical wavefronts; workgroups without idle
-  // wavefronts were slower still for the same reason.  (The same split in 4-wavefront workgroups, two fetching
-  // wavefronts with four pieces each, measured slower on two of three configurations and is not used.)
-  const int n_live = min(per, (nq - qgrp * per * 32 + 31) >> 5);
-  const bool spec = NW == 8 && 2 * n_live <= NW;
-  constexpr std::true_type FT_{};
-  constexpr std::false_type GT_{};
-  if (n_it > 0 && spec) {
-    if (wave >= NW / 2) {
-      constexpr int PP = 16 / NW;                       // pieces per fetching thread
-      const int pbase = tid - NW * 32;                  // 0 .. NW*32 - 1; piece u of this thread: pbase + u * NW * 32
-      uint4 ak[PP], av[PP], bk[PP], bv[PP];             // (indices are compile-time constants throughout)
+  // Groups of KG tiles: one is multiplied out of one LDS buffer, the next is parked in the other one from one of
+  // two register sets, which is then refilled with the group two further on; a barrier per group.
+  auto walk = [&](auto kg_tag) __attribute__((always_inline)) {
+    constexpr int KG = decltype(kg_tag)::value, NP = KG * 8 / NW;   // pieces of keys (and of values) per wavefront and group, all of one tile
+    constexpr int PL = NP > 1 ? 2 : 1, NL = NP / PL;                // pieces per table entry, entries
+    const int n_g = (n_it + KG - 1) / KG, slot = wave * NP >> 3, j0 = wave * NP & 7;   // this wavefront's tile of a group, its first piece
+    uint4 ak[NP] = {}, av[NP] = {}, bk[NP] = {}, bv[NP] = {};   // (indices are compile-time constants throughout)
+    // table entries of group gi's pieces (of some valid page where there is none), read ahead of their use
+    auto look = [&](int gi, uint32_t (&lk)[NL], uint32_t (&lv)[NL]) __attribute__((always_inline)) {
+      const int ti = gi * KG + slot;
+      const FwTile t = tile_of(ti);
 #pragma unroll
-      for (int u = 0; u < PP; ++u) fetchp(GT_, pbase + u * NW * 32, 0, ak[u], av[u]);
+      for (int u = 0; u < NL; ++u) {
+        const int j = j0 + u * PL;
+        lk[u] = s_pt[max(min((min(t.kbase + 4 * j, t.limit - 1) >> ps_shift) - pb0, pt_cap - 1), 0)];
+        lv[u] = s_pt[max(min((min(t.kbase + v_key(j), t.limit - 1) >> ps_shift) - pb0, pt_cap - 1), 0)];
+      }
+    };
+    auto fetch = [&](int gi, const uint32_t (&lk)[NL], const uint32_t (&lv)[NL], uint4 (&kr)[NP], uint4 (&vr)[NP]) __attribute__((always_inline)) {
+      const int ti = min(gi * KG + slot, n_it - 1);   // (behind the last tile: that one again, by the code that is there already)
+      if (ti < n_fast) {   // (both sides issue the same loads in the same order, so the compiler's count of those in flight holds)
+        const int key = (t0 + ti) * 32;
 #pragma unroll
-      for (int u = 0; u < PP; ++u) fetchp(GT_, pbase + u * NW * 32, 1, bk[u], bv[u]);
+        for (int u = 0; u < NL; ++u) {
+          const int j = j0 + u * PL;
+          const uint64_t ka = kb_l + ((key + 4 * j) & (ps - 1)) * (D * 2) + (uint64_t)lk[u] * pbytes;
+          const uint64_t va = vb_l + (uint32_t)(((key + v_key(j)) & (ps - 1)) * 2 + v_row(j) * ps * 2) + (uint64_t)lv[u] * pbytes;
 #pragma unroll
-      for (int u = 0; u < PP; ++u) stashp(GT_, pbase + u * NW * 32, 0, 0, ak[u], av[u]);
-#pragma unroll
-      for (int u = 0; u < PP; ++u) fetchp(GT_, pbase + u * NW * 32, 2, ak[u], av[u]);
-      __syncthreads();
-      // one pass: parks tiles i + 1, i + 2 and requests tiles i + 3, i + 4
-      auto pass = [&](auto fast, int i) __attribute__((always_inline)) {
-        S2D2_WTS(8, wave == NW / 2 && i == 16);
-#pragma unroll
-        for (int u = 0; u < PP; ++u) stashp(fast, pbase + u * NW * 32, i + 1, 1, bk[u], bv[u]);
-        S2D2_WTS(9, wave == NW / 2 && i == 16);
-#pragma unroll
-        for (int u = 0; u < PP; ++u) fetchp(fast, pbase + u * NW * 32, i + 3, bk[u], bv[u]);
-        S2D2_WTS(10, wave == NW / 2 && i == 16);
-        __syncthreads();
-        S2D2_WTS(11, wave == NW / 2 && i == 16);
-        if (i + 1 < n_it) {
-#pragma unroll
-          for (int u = 0; u < PP; ++u) stashp(fast, pbase + u * NW * 32, i + 2, 0, ak[u], av[u]);
-#pragma unroll
-          for (int u = 0; u < PP; ++u) fetchp(fast, pbase + u * NW * 32, i + 4, ak[u], av[u]);
-          S2D2_WTS(12, wave == NW / 2 && i == 16);
-          __syncthreads();
-          S2D2_WTS(13, wave == NW / 2 && i == 16);
+          for (int e = 0; e < PL; ++e) {
+            kr[u * PL + e] = ld_kv(ka + e * 1024);
+            vr[u * PL + e] = ld_kv(va + (uint32_t)(e * vstep));
+          }
         }
-      };
-      int i = 0;
-      for (; i + 4 < n_fast; i += 2) pass(FT_, i);
-      for (; i < n_it; i += 2) pass(GT_, i);
-    } else {
-      __syncthreads();
-      auto pass = [&](auto fast, int i) __attribute__((always_inline)) {
-        if (active) compute(fast, st, qf, ql, i, 0);
-        __syncthreads();
-        S2D2_WTS(4, wave == 0 && i == 16);
-        if (i + 1 < n_it) {
-          if (active) compute(fast, st, qf, ql, i + 1, 1);
-          __syncthreads();
-          S2D2_WTS(5, wave == 0 && i == 16);
+      } else {
+        const FwTile t = tile_of(ti);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+#pragma unroll
+          for (int e = 0; e < PL; ++e) {
+            const int j = j0 + u * PL + e, key = t.kbase + 4 * j, keyv = t.kbase + v_key(j);
+            // rows beyond the region are some rows of its last page; their scores are masked, their values zeroed in stash
+            const int kc = min(key, (t.limit - 1) & ~3), kcv = min(keyv, (t.limit - 1) & ~(kpp - 1));
+            const uint64_t k_c = kb_l + (kc & (ps - 1)) * (D * 2) + (uint64_t)lk[u] * pbytes;
+            const uint64_t k_w = (uint64_t)(k_win + ((size_t)(row0 + min(key + (lane >> 4), nw - 1)) * Hkv + kvh) * D + (lane & 15) * 8);
+            const uint64_t v_c = vb_l + (uint32_t)((kcv & (ps - 1)) * 2 + v_row(j) * ps * 2) + (uint64_t)lv[u] * pbytes;
+            const uint64_t v_w = (uint64_t)(vT_win + ((size_t)(n * Hkv + kvh) * D + v_row(j) + vd_l) * wpad + min(keyv, wpad - kpp) + vo_l * 8);
+            kr[u * PL + e] = ld_kv(t.win ? k_w : k_c);
+            vr[u * PL + e] = ld_kv(t.win ? v_w : v_c);
+          }
         }
-      };
-      int i = 0;
-      for (; i + 4 < n_fast; i += 2) pass(FT_, i);   // (the same split of the passes as in the fetching wavefronts: equal barrier counts)
-      for (; i < n_it; i += 2) pass(GT_, i);
+      }
+    };
+    // half mode: cached tiles are bf16 and are converted here; the window's own rows already come as half values (k_win /
+    // vT_win then point at the half copies the QKV projection wrote: 11 bits instead of the cache's 8)
+    auto stash = [&](int gi, const uint4 (&kr)[NP], const uint4 (&vr)[NP]) __attribute__((always_inline)) {
+      const int ti = min(gi * KG + slot, n_it - 1);
+      unsigned char* buf = lds + ((gi & 1) * KG + slot) * FW_BUF;
+      unsigned char* ks = buf + (4 * j0 + (lane >> 4)) * FW_KROW + (lane & 15) * 16;
+      unsigned char* vs = buf + FW_KBUF + vd_l * FW_VROW + vo_l * 16;
+      if (ti < n_fast) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          *(uint4*)(ks + 4 * u * FW_KROW) = F16 ? fw_to_f16(kr[u]) : kr[u];
+          *(uint4*)(vs + v_row(j0 + u) * FW_VROW + v_key(j0 + u) * 2) = F16 ? fw_to_f16(vr[u]) : vr[u];
+        }
+      } else {
+        const FwTile t = tile_of(ti);
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          const uint4 vm = fw_mask(vr[u], t.limit - (t.kbase + v_key(j0 + u) + vo_l * 8));
+          *(uint4*)(ks + 4 * u * FW_KROW) = F16 && !t.win ? fw_to_f16(kr[u]) : kr[u];
+          *(uint4*)(vs + v_row(j0 + u) * FW_VROW + v_key(j0 + u) * 2) = F16 && !t.win ? fw_to_f16(vm) : vm;
+        }
+      }
+    };
+    auto pass = [&](int gi, uint4 (&kr)[NP], uint4 (&vr)[NP]) __attribute__((always_inline)) {
+      uint32_t lk[NL], lv[NL];
+      look(gi + 3, lk, lv);
+      if (active && gi >= 0 && gi * KG + kg < n_it) compute(st, qf, ql, gi * KG + kg, lds + ((gi & 1) * KG + kg) * FW_BUF);
+      if (gi + 1 >= 0 && gi + 1 < n_g) stash(gi + 1, kr, vr);
+      fetch(gi + 3, lk, lv, kr, vr);
+      if (gi >= -1) __syncthreads();
+    };
+    // (gi < 0: the first groups' loads, nothing to multiply yet.  One copy of the pass per register set: most launches over
+    // short caches are four tiles a workgroup, and instructions that are executed once come from memory.)
+#pragma unroll 1
+    for (int gi = -3;; gi += 2) {
+      pass(gi, ak, av);
+      if (gi + 1 >= n_g) break;
+      pass(gi + 1, bk, bv);
+      if (gi + 2 >= n_g) break;
     }
-  } else if (n_it > 0) {
-    if constexpr (U == 1) {
-      // two tiles in flight in registers: set B holds tile i + 1 and set A tile i + 2 at the top of an (even) iteration
-      uint4 ak, av, bk, bv;
-      fetch1(GT_, 0, 0, ak, av);
-      fetch1(GT_, 0, 1, bk, bv);
-      stash1(GT_, 0, 0, 0, ak, av);
-      fetch1(GT_, 0, 2, ak, av);
+  };
+  // Four wavefronts (two workgroups to a compute unit): one tile at a time, every thread fetches two pieces of keys and of
+  // values (K row idx / 16, 16-byte piece idx % 16; V^T row idx / 4, keys 8 (idx % 4) .. + 8), one tile in flight, in forms
+  // compiled for full cached tiles (FAST) and for all.  Walked two tiles at a time like eight wavefronts, launches of short splits
+  // took 1 to 4 us longer (1.7B shape, four tiles a split, with the merge 25 for 19) and long ones were as fast.
+  auto walk4 = [&]() __attribute__((always_inline)) {
+    constexpr std::true_type FT_{};
+    constexpr std::false_type GT_{};
+    const size_t pstride = (size_t)Hkv * ps * D;   // elements of a page
+    auto fetch1 = [=](auto fast, int u, int i, uint4& kr, uint4& vr) __attribute__((always_inline)) {
+      constexpr bool FAST = decltype(fast)::value;
+      const int idx = tid + u * T, kk = idx >> 4, kch = idx & 15, vd = idx >> 2, vko = (idx & 3) * 8;
+      // (offsets are page * page_stride + [terms that depend on the thread alone] + [32-bit terms of the tile])
+      if (FAST) {
+        const int key = (t0 + i) * 32 + kk, kv0 = (t0 + i) * 32 + vko;
+        const int pk = s_pt[min((key >> ps_shift) - pb0, pt_cap - 1)];
+        const int pv = s_pt[min((kv0 >> ps_shift) - pb0, pt_cap - 1)];
+        kr = ld_kv((uint64_t)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D));
+        vr = ld_kv((uint64_t)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1))));
+        return;
+      }
+      const FwTile t = tile_of(i);
+      const int key = min(t.kbase + kk, t.limit - 1);   // rows beyond the region read a valid row; their scores are masked
+      const int key0 = t.kbase + vko;
+      // both address forms are computed and one is selected: no control flow around the loads
+      const int kv0 = min(key0, cap - 8);
+      const int pk = s_pt[max(0, min((key >> ps_shift) - pb0, pt_cap - 1))];
+      const int pv = s_pt[max(0, min((kv0 >> ps_shift) - pb0, pt_cap - 1))];
+      const bf16_t* kp_c = k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D;
+      const bf16_t* vp_c = v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1));
+      const bf16_t* kp_w = k_win + ((size_t)row0 * Hkv + kvh) * D + kch * 8 + (size_t)key * (Hkv * D);
+      const bf16_t* vp_w = vT_win + ((size_t)(n * Hkv + kvh) * D + vd) * wpad + min(key0, wpad - 8);
+      kr = ld_kv((uint64_t)(t.win ? kp_w : kp_c));
+      vr = ld_kv((uint64_t)(t.win ? vp_w : vp_c));
+    };
+    auto stash1 = [=](auto fast, int u, int i, int b, uint4 kr, uint4 vr) __attribute__((always_inline)) {
+      constexpr bool FAST = decltype(fast)::value;
+      unsigned char* base = lds + b * FW_BUF;
+      const int idx = tid + u * T, kk = idx >> 4, kch = idx & 15, vd = idx >> 2, vko = (idx & 3) * 8;
+      const FwTile t = FAST ? FwTile{false, 0, 0} : tile_of(i);
+      const uint4 vm = FAST || t.kbase + 32 <= t.limit ? vr : fw_mask(vr, t.limit - (t.kbase + vko));   // (uniform: only a region's last tile is partial)
+      const bool cvt = F16 && (FAST || !t.win);
+      *(uint4*)(base + kk * FW_KROW + kch * 16) = cvt ? fw_to_f16(kr) : kr;
+      *(uint4*)(base + FW_KBUF + vd * FW_VROW + vko * 2) = cvt ? fw_to_f16(vm) : vm;
+    };
+    uint4 k0, v0, k1, v1;
+    fetch1(GT_, 0, 0, k0, v0);
+    fetch1(GT_, 1, 0, k1, v1);
+    stash1(GT_, 0, 0, 0, k0, v0);
+    stash1(GT_, 1, 0, 0, k1, v1);
+    fetch1(GT_, 0, 1, k0, v0);
+    fetch1(GT_, 1, 1, k1, v1);
+    __syncthreads();
+    // one pass: computes tile i, parks tile i + 1, requests tile i + 2
+    auto pass = [&](auto fast, int i) __attribute__((always_inline)) {
+      if (active) compute(st, qf, ql, i, lds + (i & 1) * FW_BUF);
+      stash1(fast, 0, i + 1, (i + 1) & 1, k0, v0);
+      stash1(fast, 1, i + 1, (i + 1) & 1, k1, v1);
+      fetch1(fast, 0, i + 2, k0, v0);
+      fetch1(fast, 1, i + 2, k1, v1);
       __syncthreads();
-      auto pass = [&](auto fast, int i) __attribute__((always_inline)) {
-        if (active) compute(fast, st, qf, ql, i, 0);
-        stash1(fast, 0, i + 1, 1, bk, bv);
-        fetch1(fast, 0, i + 3, bk, bv);
-        __syncthreads();
-        if (i + 1 < n_it) {
-          if (active) compute(fast, st, qf, ql, i + 1, 1);
-          stash1(fast, 0, i + 2, 0, ak, av);
-          fetch1(fast, 0, i + 4, ak, av);
-          __syncthreads();
-        }
-      };
-      int i = 0;
-      for (; i + 4 < n_fast; i += 2) pass(FT_, i);
-      for (; i < n_it; i += 2) pass(GT_, i);
-    } else {
-      // smaller workgroups hold several pieces per thread: one tile in flight (two workgroups share a CU; with two, as above,
-      // launches of short splits took 2 us longer and long ones the same)
-      uint4 k0, v0, k1, v1;
-      fetch1(GT_, 0, 0, k0, v0);
-      fetch1(GT_, 1, 0, k1, v1);
-      stash1(GT_, 0, 0, 0, k0, v0);
-      stash1(GT_, 1, 0, 0, k1, v1);
-      fetch1(GT_, 0, 1, k0, v0);
-      fetch1(GT_, 1, 1, k1, v1);
-      __syncthreads();
-      // one pass: computes tile i, parks tile i + 1, requests tile i + 2
-      auto pass = [&](auto fast, int i) __attribute__((always_inline)) {
-        if (active) compute(fast, st, qf, ql, i, i & 1);
-        stash1(fast, 0, i + 1, (i + 1) & 1, k0, v0);
-        stash1(fast, 1, i + 1, (i + 1) & 1, k1, v1);
-        fetch1(fast, 0, i + 2, k0, v0);
-        fetch1(fast, 1, i + 2, k1, v1);
-        __syncthreads();
-      };
-      int i = 0;
-      for (; i + 2 < n_fast; ++i) pass(FT_, i);
-      for (; i < n_it; ++i) pass(GT_, i);
+    };
+    int i = 0;
+    for (; i + 2 < n_fast; ++i) pass(FT_, i);
+    for (; i < n_it; ++i) pass(GT_, i);
+  };
+  if (n_it > 0) {
+    if constexpr (NW == 4) walk4();
+    else if (two) walk(std::integral_constant<int, 2>{});
+    else walk(std::integral_constant<int, 1>{});
+  }
+  if (NW == 8 && two) {   // the second key group's states, through LDS (behind the last group's barrier: nobody reads tiles any more)
+    float4* s_o = (float4*)lds;                                    // [query tile][16][lane]
+    float2* s_ml = (float2*)(lds + (NW / 2) * 16384);              // [query tile][lane]
+    if (kg == 1 && active) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+          s_o[(wq * 16 + dt * 4 + i4) * 64 + lane] = make_float4(st.o[dt][4 * i4], st.o[dt][4 * i4 + 1], st.o[dt][4 * i4 + 2], st.o[dt][4 * i4 + 3]);
+      s_ml[wq * 64 + lane] = make_float2(st.m, st.l);
     }
+    __syncthreads();
+    if (kg == 1 || !active) return;
+    const float2 ml = s_ml[wq * 64 + lane];
+    const float M = fmaxf(st.m, ml.x), ref = M == -INFINITY ? 0.f : M;
+    const float f0 = __builtin_amdgcn_exp2f(st.m - ref), f1 = __builtin_amdgcn_exp2f(ml.x - ref);
+    st.m = M;
+    st.l = st.l * f0 + ml.y * f1;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const float4 v = s_o[(wq * 16 + dt * 4 + i4) * 64 + lane];
+        st.o[dt][4 * i4] = st.o[dt][4 * i4] * f0 + v.x * f1;
+        st.o[dt][4 * i4 + 1] = st.o[dt][4 * i4 + 1] * f0 + v.y * f1;
+        st.o[dt][4 * i4 + 2] = st.o[dt][4 * i4 + 2] * f0 + v.z * f1;
+        st.o[dt][4 * i4 + 3] = st.o[dt][4 * i4 + 3] * f0 + v.w * f1;
+      }
   }
 
   // ---- output: lane (c, h) holds head-dim positions dt*32 + 8*i4 + 4*h .. + 4 of query row c ----
@@ -552,7 +600,7 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
   float* part_o = part;
   float* part_ml = part + part_entries * 32 * FA_D;
   const dim3 grid(g.n_kv_heads, qgroups, std::min(N * Z, N + target));   // (N + target: a run more than the target per sequence at most)
-  const size_t lds = attention_wide_lds_bytes(pt_cap);
+  const size_t lds = attention_wide_lds_bytes(pt_cap, nw);
   int ps_shift = 0;
   while ((1 << ps_shift) < g.page_size) ++ps_shift;   // the caller has checked that page_size is a power of two
 #define S2D2_WIDE(NWV)                                                                                                  \

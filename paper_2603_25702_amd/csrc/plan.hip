@@ -89,7 +89,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(
   p.seq_j[n] = j;
   p.seq_L[n] = L;
   p.seq_splits[n] = splits;
-  for (int z = 0; z < splits; ++z) p.split_of[s_splits[n] - splits + z] = n | (z << 16);
+  plan_write_splits(p, s_splits[n] - splits, splits, n, tiles, max(0, min(S, seq_cap)), row0, rows);
   const int32_t* blk = block + (size_t)n * B;
   const int32_t* car = carry + (size_t)n * B;
   if (!verify) {
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int ma
     p.seq_rows[n] = rows;
     p.seq_lead[n] = rows;
     p.seq_splits[n] = splits;
-    for (int z = 0; z < splits; ++z) p.split_of[s_splits[n] - splits + z] = n | (z << 16);
+    plan_write_splits(p, s_splits[n] - splits, splits, n, tiles, max(0, min(S, seq_cap)), s_rows[n] - rows, rows);
   }
   for (int m = n >> 6; m < N; m += 16) {
     const int end = s_rows[m], row0 = m ? s_rows[m - 1] : 0, S0 = seq_len[m];

@@ -167,9 +167,20 @@ struct Plan {
   int32_t* seq_L;       // [max_batch] |C_t|
   // key splits of the wide attention kernel: the cached 32-key tiles of the batch in equal runs, none across sequences
   int32_t* seq_splits;  // [max_batch] splits of a sequence
-  int32_t* split_of;    // [max_batch + WIDE_MAX_TARGET] sequence | split << 16
+  int4* split_of;       // [max_batch + WIDE_MAX_TARGET][2]: {sequence, split, its first and last + 1 cached tile}, {splits of the
+                        // sequence, its cached keys, first window row, window rows}
   int32_t vocab;        // token ids outside [0, vocab) in the caller's state are read as [MASK]
 };
+
+// Splits first .. + splits - 1 of sequence n (rows rows from row0 on, S cached keys in `tiles` tiles).
+__device__ __forceinline__ void plan_write_splits(const Plan& p, int first, int splits, int n, int tiles, int S, int row0, int rows) {
+  const uint32_t per = (uint32_t)tiles / (uint32_t)splits, more = (uint32_t)tiles % (uint32_t)splits;   // the first `more` splits get one tile more
+  for (int z = 0; z < splits; ++z) {
+    const int t0 = (int)(per * z + min((uint32_t)z, more));
+    p.split_of[2 * (first + z)] = make_int4(n, z, t0, t0 + (int)per + ((uint32_t)z < more));
+    p.split_of[2 * (first + z) + 1] = make_int4(splits, S, row0, rows);
+  }
+}
 
 struct KvGeom {
   const int32_t* page_table;
@@ -328,7 +339,7 @@ int attention_wide_nw(int q_tiles);
 constexpr int WIDE_MIN_TILES = 4;   // key tiles (of 32) a split of the wide kernel keeps at least
 int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target);
 int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target);
-size_t attention_wide_lds_bytes(int pt_cap);
+size_t attention_wide_lds_bytes(int pt_cap, int nw);
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
                            int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
