@@ -421,10 +421,16 @@ static int launch_blk(hipStream_t st, const GemmStreamArgs& a, int KS, int m_cap
 
 template <int EPI, int RB, int TA>
 static int launch_blk_shape(hipStream_t st, const GemmStreamArgs& a, int KS, int m_cap) {
+  // Streaming loads leave what the next kernels need in L2 (their code, the plan, the rows that this one writes): with plain loads
+  // the 1.7B attention behind the QKV projection takes 16.4 us for 15.0, an embedding launch 8.3 for 7.6; 64 rows 1.7B, 4B, 8B
+  // 14 layers 1040 -> 1010 .. 990, ... us.  Where more row tiles read the same weights again they cost more than that (256
+  // rows 4B: down projection 36.5 -> 38.5, 128 rows 1.7B 15.5 -> 16.0).
+  constexpr int STREAM_ROWS = EPI == SEPI_SWIGLU && TA == 6 ? (RB > 4 ? 16 * RB : 64) : 64;
+  const bool stream = a.m_hint <= STREAM_ROWS;
   if constexpr (EPI == SEPI_ADD_F32 && blk_shares(RB, TA))
-    if (KS > 1) return launch_blk<EPI, RB, TA, true, false>(st, a, KS, m_cap);
-  if constexpr (EPI == SEPI_SWIGLU && TA == 6)   // one row tile: every weight is read once
-    if (a.m_hint <= 16 * RB) return launch_blk<EPI, RB, TA, false, true>(st, a, 1, m_cap);
+    if (KS > 1) return stream ? launch_blk<EPI, RB, TA, true, true>(st, a, KS, m_cap) : launch_blk<EPI, RB, TA, true, false>(st, a, KS, m_cap);
+  if constexpr (RB <= 4 || (EPI == SEPI_SWIGLU && TA == 6))
+    if (stream) return launch_blk<EPI, RB, TA, false, true>(st, a, 1, m_cap);
   return launch_blk<EPI, RB, TA, false, false>(st, a, 1, m_cap);
 }
 
