@@ -356,8 +356,8 @@ size_t attention_generic_lds_bytes(const KvGeom& g, int max_window_rows);
 
 // vocab.hip
 struct VocabWs {
-  float* part;       // [rows_cap_logits, chunks, 8] partial statistics (a launch of fewer chunks packs them)
-  int32_t chunks;    // most chunks per row that a launch uses
+  float* part;       // [rows_cap_logits, chunks, 8] partial statistics
+  int32_t chunks;    // chunks per row
 };
 int vocab_chunks(int V);
 struct VocabSample {   // sampling mode of SampleFromLogits: proposals drawn from softmax(logits / temperature)

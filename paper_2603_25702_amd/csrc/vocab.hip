@@ -9,18 +9,16 @@
 #include "../../include/s2d2.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace s2d2 {
 
-// Logits per workgroup: 256 lanes x VT float4.  A workgroup's loads are all in flight at once, so with few workgroups the
-// launch lasts as long as one of them: four float4 per lane, until there are 16384 workgroups (64 per compute unit), where
-// half as many of twice the size take less.  Four against eight, us per launch: rows of 151936 logits (38 workgroups each)
-// 4 rows 6.5 / 9.6, 16 8.2 / 10.7, 64 14.6 / 14.7, 256 33.7 / 35.2, 512 62.2 / 57.7, 1024 133 / 108; rows of 65536 (16 each)
-// 64 rows 9.0 / 11.4, 512 30.1 / 30.0, 1024 52.2 / 48.0; rows of 40000 (10 each) 1024 rows 34.4 / 35.0.
-static int chunks_of(int V, int vt) { return (V + 1024 * vt - 1) / (1024 * vt); }
-static int vocab_vt(int V, int rows) { return (long long)rows * chunks_of(V, 4) >= 16384 ? 8 : 4; }
+// Logits per workgroup: 256 lanes x VT float4, all in flight at once.  Eight float4 per lane take longer at every size, us per
+// launch, four / eight: rows of 151936 logits (38 workgroups each) 4 rows 4.9 / 7.1, 64 11.3 / 11.8, 256 28.2 / 32.5, 1024 98 / 106;
+// rows of 40000 (10 each) 64 rows 6.0 / 8.1, 1024 29.3 / 34.6.
+static constexpr int VT = 4;
 
-int vocab_chunks(int V) { return chunks_of(V, 4); }   // the most that any launch uses
+int vocab_chunks(int V) { return (V + 1024 * VT - 1) / (1024 * VT); }
 
 struct Stat {
   float m;    // max logit
@@ -54,10 +52,30 @@ __device__ __forceinline__ Stat stat_shfl_xor(const Stat& s, int off) {
   return r;
 }
 
+// Reductions over a wavefront in a fixed order, the same result in every lane: a butterfly of DPP moves inside the rows of 16
+// lanes (vector-ALU operands, no LDS trip), two exchanges between the rows.
+template <typename F>
+__device__ __forceinline__ float wave_all(float v, const F& op) {
+  auto row = [&](auto ctrl) __attribute__((always_inline)) {
+    v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)));
+  };
+  row(std::integral_constant<int, 0xb1>{});    // lane ^ 1
+  row(std::integral_constant<int, 0x4e>{});    // lane ^ 2
+  row(std::integral_constant<int, 0x141>{});   // the other four of the half row
+  row(std::integral_constant<int, 0x140>{});   // the other half of the row
+  v = op(v, __shfl_xor(v, 16, 64));
+  return op(v, __shfl_xor(v, 32, 64));
+}
+
 // part[row][chunk][8] = {m, z, e, m2, arg}
 // inv_t: 1 / temperature (1 in greedy mode: the multiplication is then exact); all statistics are those of
 // softmax(logits * inv_t).
-template <int VT>
+//
+// Bound: reading the logits, with the vector ALU close behind (ten instructions and an exponential a logit).  The exponentials
+// are taken against the wavefront's maximum, so that only sums are left to reduce over its lanes; with each lane's own maximum
+// and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions:
+// rows of 151936 logits, us per launch before / now: 4 rows 5.6 / 4.9, 64 13.4 / 11.3, 256 33.4 / 28.2 (4.7 / 5.5 TB/s), 1024
+// (eight float4 a lane before) 106 / 98 (6.3 TB/s).
 __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restrict__ logits, int V,
                                                             const int32_t* __restrict__ count, int chunks,
                                                             float inv_t, float* __restrict__ part) {
@@ -68,12 +86,10 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   const int base = chunk * 1024 * VT;
   const int tid = threadIdx.x;
   float v[4 * VT];
-  int idx0[VT];
   const bool vec_ok = (V & 3) == 0;
 #pragma unroll
   for (int t = 0; t < VT; ++t) {
     const int i = base + t * 1024 + tid * 4;
-    idx0[t] = i;
     if (vec_ok && i + 3 < V) {
       const f32x4_t f = ld_stream((const f32x4_t*)(x + i));
       v[4 * t] = f[0] * inv_t; v[4 * t + 1] = f[1] * inv_t; v[4 * t + 2] = f[2] * inv_t; v[4 * t + 3] = f[3] * inv_t;
@@ -82,24 +98,40 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
       for (int e = 0; e < 4; ++e) v[4 * t + e] = (i + e < V) ? x[i + e] * inv_t : -INFINITY;
     }
   }
-  Stat s = stat_empty();
+  float lm = -INFINITY, lm2 = -INFINITY;   // this lane's largest and second largest logit; the place of the first largest
+  int at = 0;
 #pragma unroll
   for (int t = 0; t < 4 * VT; ++t) {
-    const float l = v[t];
-    const int i = idx0[t >> 2] + (t & 3);
-    if (l > s.m) { s.m2 = s.m; s.m = l; s.arg = i; }
-    else if (l > s.m2) s.m2 = l;
+    at = v[t] > lm ? t : at;
+    lm2 = __builtin_amdgcn_fmed3f(v[t], lm, lm2);
+    lm = fmaxf(lm, v[t]);
   }
-  if (s.m > -INFINITY) {
+  auto larger = [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); };
+  auto sum = [](float a, float b) __attribute__((always_inline)) { return a + b; };
+  Stat s = stat_empty();
+  s.m = wave_all(lm, larger);
+  const bool own = lm > -INFINITY;   // (a lane without a comparable logit adds nothing)
+  float z = 0.f, e = 0.f;
+  if (own) {
 #pragma unroll
     for (int t = 0; t < 4 * VT; ++t) {
       const float d = v[t] - s.m;
       const float ex = __expf(d);          // exp(-inf) = 0 for padded slots
-      s.z += ex;
-      s.e += ex > 0.f ? ex * d : 0.f;
+      z += ex;
+      e = __builtin_fmaf(ex, fmaxf(d, -200.f), e);   // (-inf would make 0 * -inf; exp is 0 well above -200)
     }
   }
-  for (int off = 1; off < 64; off <<= 1) s = stat_merge(s, stat_shfl_xor(s, off));
+  s.z = wave_all(z, sum);
+  s.e = wave_all(e, sum);
+  const unsigned long long top = __ballot(own && lm == s.m);   // the lanes that hold the maximum
+  const bool one = __popcll(top) == 1;
+  s.m2 = wave_all(one && lm == s.m ? lm2 : lm, larger);
+  if (top) {
+    const int i = base + (at >> 2) * 1024 + tid * 4 + (at & 3);
+    s.arg = __builtin_amdgcn_readlane(i, __ffsll((long long)top) - 1);
+    if (!one)
+      for (unsigned long long rest = top & (top - 1); rest; rest &= rest - 1) s.arg = min(s.arg, __builtin_amdgcn_readlane(i, __ffsll((long long)rest) - 1));
+  }
   if ((tid & 63) == 0) s_w[tid >> 6] = s;
   __syncthreads();
   if (tid == 0) {
@@ -109,12 +141,8 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restr
   }
 }
 
-// Returns the chunks per row that it wrote.
-static int launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
-  const int vt = vocab_vt(V, rows_cap), chunks = chunks_of(V, vt);
-  if (vt == 8) S2D2_LAUNCH(vocab_partial_kernel<8>, dim3(chunks, rows_cap), dim3(256), 0, st, logits, V, count, chunks, inv_t, ws.part);
-  else S2D2_LAUNCH(vocab_partial_kernel<4>, dim3(chunks, rows_cap), dim3(256), 0, st, logits, V, count, chunks, inv_t, ws.part);
-  return chunks;
+static void launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
+  S2D2_LAUNCH(vocab_partial_kernel, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
 }
 
 // Chunk partials of one row, merged by one wavefront: lane c takes chunks c, c + 64, ..., then a butterfly over the
@@ -179,8 +207,8 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         int32_t* xhat, float* p, float* lse, float* margin, float* entropy_n, const VocabSample& sm) {
   const float inv_t = sm.sample ? 1.0f / sm.temperature : 1.0f;
-  const int chunks = launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, chunks, V,
+  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
+  S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
                      count, logit_seq, logit_idx, B, xhat, p, lse, margin, entropy_n);
   if (sm.sample)
     S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
@@ -190,8 +218,8 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
 void launch_vocab_score(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         const int32_t* token, float* q, float* lse, float inv_t) {
-  const int chunks = launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, chunks, V,
+  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
+  S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
                      logits, count, logit_seq, logit_idx, B, token, inv_t, q, lse);
 }
 
