@@ -224,8 +224,10 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   c->ts_scratch = cv.take<uint64_t>(1024);
   c->vws.chunks = vocab_chunks(d.vocab);
   c->vws.part = cv.take<float>(LR * (size_t)c->vws.chunks * 8);
-  c->accept_tiles = cv.take<float>(accept_tile_floats(c->max_batch, d.vocab));
+  c->accept_tiles = cv.take<float>(tile_sum_floats(c->max_batch, d.vocab));
   c->accept_arrive = cv.take<int32_t>(c->max_batch);
+  c->vws.sample_tiles = cv.take<float>(tile_sum_floats(sample_rows_shared((int)LR), d.vocab));
+  c->vws.sample_arrive = cv.take<int32_t>(sample_rows_shared((int)LR));
   return (cv.off + 255) & ~(size_t)255;
 }
 
@@ -621,6 +623,7 @@ int32_t s2d2_create(const s2d2_model_desc* desc, const s2d2_weights* weights, in
   launch_fill_i32(c->stream, c->attn_counters, c->attn_groups, 0);
   launch_fill_i32(c->stream, c->zeros_i32, c->max_batch, 0);
   launch_fill_i32(c->stream, c->accept_arrive, c->max_batch, 0);
+  launch_fill_i32(c->stream, c->vws.sample_arrive, sample_rows_shared(c->logit_cap), 0);
   if (c->tile_counters) launch_fill_i32(c->stream, c->tile_counters, TILE_COUNTER_CAP, 0);
   if (c->pair_buf) launch_fill_i32(c->stream, (int32_t*)c->pair_buf, PAIR_CAP * 256 * 2, 0);
   if (accept_static_scratch(nullptr, nullptr)) { (void)hipGetLastError(); free(c->pk); free(c->layers); free(c); return fail(S2D2_ELAUNCH, "could not look up the device address of the library's scratch array"); }

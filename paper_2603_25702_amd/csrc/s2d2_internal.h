@@ -358,8 +358,11 @@ size_t attention_generic_lds_bytes(const KvGeom& g, int max_window_rows);
 struct VocabWs {
   float* part;       // [rows_cap_logits, chunks, 8] partial statistics
   int32_t chunks;    // chunks per row
+  float* sample_tiles;      // [sample_rows_shared, vocabulary tiles] tile sums of the rows whose draw several workgroups share
+  int32_t* sample_arrive;   // [sample_rows_shared] their arrival counters, zero between launches
 };
 int vocab_chunks(int V);
+int sample_rows_shared(int rows);
 struct VocabSample {   // sampling mode of SampleFromLogits: proposals drawn from softmax(logits / temperature)
   bool sample;
   float temperature;
@@ -381,9 +384,9 @@ void launch_accept(hipStream_t st, int N, int B, int V, uint64_t seed, uint32_t 
                    const float* logits_d, const int32_t* row_of_d, const float* logits_v,
                    const int32_t* row_of_v, const int32_t* xhat, const float* p, const float* lse_d,
                    const float* q, const float* lse_v, int32_t* block, int32_t* n_accept, int32_t* n_commit,
-                   int32_t* resampled, float* u_used, const int32_t* active, float* tile_scratch /* accept_tile_floats, may be NULL */,
+                   int32_t* resampled, float* u_used, const int32_t* active, float* tile_scratch /* tile_sum_floats, may be NULL */,
                    int32_t* arrivals /* [max_batch], zero between launches, may be NULL */);
-size_t accept_tile_floats(int max_batch, int V);
+size_t tile_sum_floats(int rows, int V);   // tile sums of an inverse CDF over V weights in each of `rows` rows
 // Limits of the accept step that takes its scratch from a device array of the library, and the per-device address
 // of that array's two parts (looked up on the first call on a device; the device must be current).  0 on success.
 constexpr int ACCEPT_STATIC_MAX_BATCH = 128, ACCEPT_STATIC_MAX_VOCAB = 1 << 18;

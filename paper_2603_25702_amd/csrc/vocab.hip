@@ -18,6 +18,12 @@ namespace s2d2 {
 // rows of 40000 (10 each) 64 rows 6.0 / 8.1, 1024 29.3 / 34.6.
 static constexpr int VT = 4;
 
+// Workgroups that share the draw of a row: as many as there are compute units for, at most eight.  One / two / four / eight /
+// sixteen, us per launch, rows of 151936 logits: 4 rows 32.4 / 21.9 / 16.4 / 11.7 / 11.2, 16 33.0 / 22.0 / 16.7 / 12.5 / 13.6, 64
+// 39.1 / 26.6 / 20.2 / 22.8 / 36.7, 128 41.1 / 29.5 / 36.2, 256 44.5 / 53.6.
+static int sample_share(int rows) { return std::max(1, std::min(8, 256 / rows)); }
+int sample_rows_shared(int rows) { return std::min(rows, 128); }   // most rows with more than one
+
 int vocab_chunks(int V) { return (V + 1024 * VT - 1) / (1024 * VT); }
 
 struct Stat {
@@ -201,7 +207,8 @@ __global__ void vocab_score_final_kernel(const float* __restrict__ part, int chu
 __global__ void vocab_sample_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,
                                     const int32_t* __restrict__ logit_seq, const int32_t* __restrict__ logit_idx, int B,
                                     uint64_t seed, uint32_t step, const uint32_t* __restrict__ step_dev, float inv_t,
-                                    const float* __restrict__ lse, int32_t* __restrict__ xhat, float* __restrict__ p);
+                                    const float* __restrict__ lse, int32_t* __restrict__ xhat, float* __restrict__ p,
+                                    float* __restrict__ tile_scratch, int32_t* __restrict__ arrivals);
 
 void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
@@ -211,8 +218,8 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
   S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
                      count, logit_seq, logit_idx, B, xhat, p, lse, margin, entropy_n);
   if (sm.sample)
-    S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
-                sm.seed, sm.step, sm.step_dev, inv_t, lse, xhat, p);
+    S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap, sample_share(rows_cap)), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
+                sm.seed, sm.step, sm.step_dev, inv_t, lse, xhat, p, ws.sample_tiles, ws.sample_arrive);
 }
 
 void launch_vocab_score(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
@@ -412,17 +419,40 @@ __device__ __forceinline__ int inverse_cdf_block(const F& w4, int V, float u, fl
   return inverse_cdf_finish(w4, V, u, s_tile, s_w, s_tile_sel, s_before);
 }
 
+// Tile sums of one row by the G workgroups that share it: each forms its share and leaves it in `sums` (device-coherent
+// stores), counts its arrival, and the last one to arrive takes them all into s_tile and re-arms the counter.  False in the
+// workgroups that are done.  Nobody waits for another workgroup.
+template <typename F>
+__device__ __forceinline__ bool share_tile_sums(const F& w4, int V, int g, int G, float* sums, int32_t* arrivals, float* s_tile, int* s_last) {
+  const int tid = threadIdx.x, tiles = (V + RTILE - 1) / RTILE, share = (tiles + G - 1) / G;
+  inverse_cdf_tile_sums<true>(w4, min(tiles, g * share), min(tiles, (g + 1) * share), sums);
+  __builtin_amdgcn_s_waitcnt(0);   // the write-through stores have completed before the arrival is counted
+  __syncthreads();
+  if (tid == 0) {
+    const int prev = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_last = prev == G - 1;
+    if (prev == G - 1) __hip_atomic_store(arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!*s_last) return false;
+  for (int t = tid; t < tiles; t += blockDim.x) s_tile[t] = ld4f_coh(&sums[t]);
+  return true;
+}
+
 // SampleFromLogits in sampling mode: x_hat ~ softmax(logits / T) by inverse CDF in ascending vocabulary order with
-// the uniform of stream 2 at (step, sequence, block index); p = that token's probability.  One workgroup per
+// the uniform of stream 2 at (step, sequence, block index); p = that token's probability.  gridDim.y workgroups per
 // logit row; runs after the statistics kernels (reads lse, overwrites the arg-max proposal and its probability).
 // Sixteen wavefronts: a row of 152k logits is one stream through one compute unit (with four, 105 us per launch at 64 rows).
+// With few rows most compute units have none, so up to eight workgroups share a row (sample_share).  The sums
+// of the tiles, and with them the result, do not depend on gridDim.y.
 __global__ __launch_bounds__(1024) void vocab_sample_kernel(
     const float* __restrict__ logits, int V, const int32_t* __restrict__ count, const int32_t* __restrict__ logit_seq,
     const int32_t* __restrict__ logit_idx, int B, uint64_t seed, uint32_t step, const uint32_t* __restrict__ step_dev,
-    float inv_t, const float* __restrict__ lse, int32_t* __restrict__ xhat, float* __restrict__ p) {
+    float inv_t, const float* __restrict__ lse, int32_t* __restrict__ xhat, float* __restrict__ p, float* __restrict__ tile_scratch,
+    int32_t* __restrict__ arrivals) {
   __shared__ float s_tile[RMAX_TILES];
   __shared__ float s_w[4];
-  __shared__ int s_tile_sel;
+  __shared__ int s_tile_sel, s_last;
   __shared__ float s_before;
   const int row = blockIdx.x;
   if (row >= *count) return;
@@ -443,7 +473,13 @@ __global__ __launch_bounds__(1024) void vocab_sample_kernel(
       for (int e = 0; e < 4; ++e) r[e] = (i0 + e < V) ? __expf(x[i0 + e] * inv_t - z) : 0.f;
     }
   };
-  const int token = inverse_cdf_block(prob4, V, u, s_tile, s_w, &s_tile_sel, &s_before);
+  int token;
+  if (gridDim.y == 1) {
+    token = inverse_cdf_block(prob4, V, u, s_tile, s_w, &s_tile_sel, &s_before);
+  } else {
+    if (!share_tile_sums(prob4, V, blockIdx.y, gridDim.y, tile_scratch + (size_t)row * ((V + RTILE - 1) / RTILE), &arrivals[row], s_tile, &s_last)) return;
+    token = inverse_cdf_finish(prob4, V, u, s_tile, s_w, &s_tile_sel, &s_before);
+  }
   if (threadIdx.x == 0 && token >= 0) {   // (no mass cannot happen for a softmax; the arg-max proposal would stay)
     xhat[o] = token;
     p[o] = expf(x[token] * inv_t - z);
@@ -522,19 +558,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(
   if (G == 1) {
     token = inverse_cdf_block(residual4, V, u2, s_tile, s_w, &s_tile_sel, &s_before);
   } else {
-    const int tiles = (V + RTILE - 1) / RTILE, share = (tiles + G - 1) / G;
-    float* mine = tile_scratch + (size_t)n * tiles;
-    inverse_cdf_tile_sums<true>(residual4, min(tiles, g * share), min(tiles, (g + 1) * share), mine);
-    __builtin_amdgcn_s_waitcnt(0);   // the write-through stores have completed before the arrival is counted
-    __syncthreads();
-    if (tid == 0) {
-      const int prev = __hip_atomic_fetch_add(&arrivals[n], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = prev == G - 1;
-      if (prev == G - 1) __hip_atomic_store(&arrivals[n], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!s_last) return;
-    for (int t = tid; t < tiles; t += blockDim.x) s_tile[t] = ld4f_coh(&mine[t]);
+    if (!share_tile_sums(residual4, V, g, G, tile_scratch + (size_t)n * ((V + RTILE - 1) / RTILE), &arrivals[n], s_tile, &s_last)) return;
     token = inverse_cdf_finish(residual4, V, u2, s_tile, s_w, &s_tile_sel, &s_before);
   }
   if (tid == 0) {
@@ -560,7 +584,7 @@ void launch_accept(hipStream_t st, int N, int B, int V, uint64_t seed, uint32_t 
                      n_accept, n_commit, resampled, u_used, active, tile_scratch, arrivals);
 }
 
-size_t accept_tile_floats(int max_batch, int V) { return (size_t)max_batch * ((V + RTILE - 1) / RTILE); }
+size_t tile_sum_floats(int rows, int V) { return (size_t)rows * ((V + RTILE - 1) / RTILE); }
 
 // ---------------------------------------------------------------------------------------------
 // Scratch of the accept step for callers that cannot allocate (s2d2_accept_static): the residual tile sums that
