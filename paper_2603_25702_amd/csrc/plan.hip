@@ -8,6 +8,8 @@
 #include "s2d2_internal.h"
 #include "../../include/s2d2.h"
 
+#include <type_traits>
+
 namespace s2d2 {
 
 // The token arrays live on the device and cannot be checked by the host: an id outside the vocabulary (a caller's
@@ -242,40 +244,60 @@ void launch_plan_prefill(hipStream_t st, int N, int T, int mask_id, const int32_
 
 // ---------------------------------------------------------------------------------------------
 // Cache append: copy staged K/V rows [0, lead + n_accept) of each sequence to its next logical
-// positions.  One workgroup per (sequence, staged row, layer); 16-byte copies.
+// positions.  One workgroup per (sequence, G consecutive slots of a page, layer).
+//
+// V is cached key-minor, so a row alone leaves one element in every piece of G slots; a workgroup that takes the G rows of a
+// piece stores it whole, 16 bytes (the pieces at either end of the rows element by element).  Bound: the rows read and written.  768 rows of 28
+// layers of 8 x 128 halves 100 -> 43 us (176 MB, 4.1 TB/s), up to 16 rows of 16 sequences in 4 layers 9.8 -> 7.1.
 // ---------------------------------------------------------------------------------------------
+template <typename T, int G>
 __global__ __launch_bounds__(256) void kv_append_copy_kernel(
-    int elt_bytes, int per_seq, int rows_cap, KvGeom g, uint8_t* __restrict__ k_pages,
-    uint8_t* __restrict__ v_pages, const uint8_t* __restrict__ k_stage, const uint8_t* __restrict__ v_stage,
-    const int32_t* __restrict__ stage_row0, const int32_t* __restrict__ stage_lead,
+    int per_seq, int rows_cap, KvGeom g, T* __restrict__ k_pages, T* __restrict__ v_pages, const T* __restrict__ k_stage,
+    const T* __restrict__ v_stage, const int32_t* __restrict__ stage_row0, const int32_t* __restrict__ stage_lead,
     const int32_t* __restrict__ n_accept, const int32_t* __restrict__ span_len, int hold_back) {
-  const int n = blockIdx.x / per_seq, t = blockIdx.x % per_seq, l = blockIdx.y;
+  constexpr int VE = 16 / (int)sizeof(T);
+  const int n = blockIdx.x / per_seq, l = blockIdx.y;
   const int acc = max(0, min(n_accept[n], span_len[n] - hold_back));   // hold_back: no staged row for the last drafted token
   const int rows = stage_lead[n] + acc;
-  if (t >= rows) return;
   const int S = g.seq_len[n];
+  const int s0 = S - S % G + (blockIdx.x % per_seq) * G;   // first slot of this workgroup's piece
+  if (rows <= 0 || s0 >= S + rows) return;
   const int cap = g.max_pages_per_seq * g.page_size;
   if (S + rows > cap) return;  // whole sequence skipped; the update kernel flags it
-  const int s = S + t;
-  const int page = g.page_table[(size_t)n * g.max_pages_per_seq + s / g.page_size];
+  const int page = g.page_table[(size_t)n * g.max_pages_per_seq + s0 / g.page_size];
   if (page < 0 || page >= g.n_pages) return;
-  const int slot = s % g.page_size;
-  const size_t head_bytes = (size_t)g.head_dim * elt_bytes;
-  const size_t src = ((size_t)l * rows_cap + (stage_row0[n] + t)) * g.n_kv_heads * head_bytes;
-  const size_t layer_off = (size_t)l * g.n_pages * g.n_kv_heads * g.page_size * head_bytes;
-  const int vec_per_head = (int)(head_bytes / 16);
-  for (int v = threadIdx.x; v < g.n_kv_heads * vec_per_head; v += blockDim.x) {
-    const int h = v / vec_per_head, e = v % vec_per_head;
-    const size_t dst = layer_off + (((size_t)page * g.n_kv_heads + h) * g.page_size + slot) * head_bytes + (size_t)e * 16;
-    *(uint4*)(k_pages + dst) = *(const uint4*)(k_stage + src + (size_t)h * head_bytes + (size_t)e * 16);
+  const int slot = s0 % g.page_size, D = g.head_dim, HD = g.n_kv_heads * D;
+  const int u0 = max(0, S - s0), u1 = min(G, S + rows - s0);   // places of the piece that are written
+  const size_t src = ((size_t)l * rows_cap + stage_row0[n]) * HD;
+  const int t0 = s0 - S;                                       // staged row of place 0
+  const size_t page_off = ((size_t)l * g.n_pages + page) * HD * g.page_size;
+  const int vecs = HD / VE;   // 16-byte pieces of a staged row
+  for (int v = threadIdx.x; v < (u1 - u0) * vecs; v += 256) {
+    const int u = u0 + v / vecs, e = (v % vecs) * VE, h = e / D;
+    *(uint4*)(k_pages + page_off + ((size_t)h * g.page_size + slot + u) * D + e % D) = *(const uint4*)(k_stage + src + (size_t)(t0 + u) * HD + e);
   }
-  // V is cached key-minor: [page, Hkv, D, page_size]
-  for (int v = threadIdx.x; v < g.n_kv_heads * g.head_dim; v += blockDim.x) {
-    const int h = v / g.head_dim, d = v % g.head_dim;
-    const size_t dst = layer_off + ((((size_t)page * g.n_kv_heads + h) * g.head_dim + d) * g.page_size + slot) * elt_bytes;
-    const size_t so = src + (size_t)v * elt_bytes;
-    if (elt_bytes == 2) *(uint16_t*)(v_pages + dst) = *(const uint16_t*)(v_stage + so);
-    else *(uint32_t*)(v_pages + dst) = *(const uint32_t*)(v_stage + so);
+  // V is cached key-minor: [page, Hkv, D, page_size]; two elements of the head dimension per thread
+  for (int v = threadIdx.x * 2; v < HD; v += 512) {
+    alignas(16) T lo[G], hi[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      struct alignas(2 * sizeof(T)) Pair { T a, b; };
+      const Pair x = *(const Pair*)(v_stage + src + (size_t)(t0 + min(max(u, u0), u1 - 1)) * HD + v);   // (a place that is not written reads one that is)
+      lo[u] = x.a;
+      hi[u] = x.b;
+    }
+    T* dst = v_pages + page_off + (size_t)v * g.page_size + slot;
+    if (G * sizeof(T) == 16 && u0 == 0 && u1 == G) {
+      *(uint4*)dst = *(const uint4*)lo;
+      *(uint4*)(dst + g.page_size) = *(const uint4*)hi;
+    } else {
+#pragma unroll
+      for (int u = 0; u < G; ++u)
+        if (u >= u0 && u < u1) {
+          dst[u] = lo[u];
+          dst[g.page_size + u] = hi[u];
+        }
+    }
   }
 }
 
@@ -299,11 +321,19 @@ void launch_kv_append(hipStream_t st, int dtype, int n_layers, int N, int rows_c
                       void* k_pages, void* v_pages, const void* k_stage, const void* v_stage,
                       const int32_t* stage_row0, const int32_t* stage_lead, const int32_t* span_len,
                       const int32_t* n_accept, int32_t* seq_len, int32_t* status, int B, int hold_back) {
-  const int elt = dtype == S2D2_BF16 ? 2 : 4;
-  const int per_seq = 2 * B;  // upper bound of staged causal rows per sequence (carry + block)
-  S2D2_LAUNCH(kv_append_copy_kernel, dim3(N * per_seq, n_layers), dim3(256), 0, st, elt, per_seq,
-                     rows_cap, g, (uint8_t*)k_pages, (uint8_t*)v_pages, (const uint8_t*)k_stage,
-                     (const uint8_t*)v_stage, stage_row0, stage_lead, n_accept, span_len, hold_back);
+  // 2 B: upper bound of staged causal rows per sequence (carry + block); pieces of whole 16 bytes where no page cuts one
+  auto copy = [&](auto elt, auto group) {
+    using T = decltype(elt);
+    constexpr int G = decltype(group)::value;
+    const int per_seq = (2 * B + G - 2) / G + 1;   // rows may begin inside a piece
+    S2D2_LAUNCH((kv_append_copy_kernel<T, G>), dim3(N * per_seq, n_layers), dim3(256), 0, st, per_seq, rows_cap, g, (T*)k_pages, (T*)v_pages,
+                (const T*)k_stage, (const T*)v_stage, stage_row0, stage_lead, n_accept, span_len, hold_back);
+  };
+  if (dtype == S2D2_BF16) {
+    if (g.page_size % 8 == 0) copy(uint16_t{}, std::integral_constant<int, 8>{}); else copy(uint16_t{}, std::integral_constant<int, 1>{});
+  } else {
+    if (g.page_size % 4 == 0) copy(uint32_t{}, std::integral_constant<int, 4>{}); else copy(uint32_t{}, std::integral_constant<int, 1>{});
+  }
   S2D2_LAUNCH(kv_append_commit_kernel, dim3((N + 255) / 256), dim3(256), 0, st, N, g, stage_lead,
                      n_accept, span_len, seq_len, status, hold_back);
 }
