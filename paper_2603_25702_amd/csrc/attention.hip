@@ -185,7 +185,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int32_t* __restrict__ counters, int items, const uint4* __restrict__ pf, size_t pf_n16) {
+    float* __restrict__ part_ml, int32_t* __restrict__ counters, int items, const uint4* __restrict__ pf, size_t pf_n16, int columns) {
   extern __shared__ float smem[];
   if ((int)blockIdx.z >= items) {
     // Workgroups behind the attention's own: they read the weights of the GEMMs that follow this launch, so that
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(
     return;
   }
   attn_flash_body<NW, SPLIT, false>(q, q_ld, q_lo, k_win, vT_win, k_pages, v_pages, g, p, Hq, Z, wpad, scale_log2e, o, o_ld,
-                                    o_lo, part_o, part_ml, counters, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y, smem);
+                                    o_lo, part_o, part_ml, counters, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y, smem, columns != 0);
 }
 
 
@@ -221,20 +221,24 @@ void launch_attention_flash(hipStream_t st, const void* q, int q_ld, int q_lo, c
   const int items = N * g.n_kv_heads;
   float* part_o = part;
   float* part_ml = part + (size_t)items * q_tiles * Z * 32 * FA_D;
-  // extra slabs of Z * q_tiles workgroups that only read `prefetch` (see the kernel)
-  const int slabs = prefetch && prefetch_bytes >= 16 ? std::min(65535 - items, (prefetch_wgs + Z * q_tiles - 1) / (Z * q_tiles)) : 0;
+  // extra slabs of X * q_tiles workgroups that only read `prefetch` (see the kernel)
+  // One query tile, splits to merge, and no more workgroups than compute units: short caches by output columns
+  // (attn_flash_columns).
+  const int columns = q_tiles == 1 && Z > 1 && items * 4 <= 256;
+  const int X = columns ? std::max(Z, 4) : Z;
+  const int slabs = prefetch && prefetch_bytes >= 16 ? std::min(65535 - items, (prefetch_wgs + X * q_tiles - 1) / (X * q_tiles)) : 0;
   const uint4* pf = (const uint4*)prefetch;
   const size_t pf_n16 = slabs > 0 ? prefetch_bytes / 16 : 0;
   if (q_lo)
-    S2D2_LAUNCH((attn_flash_kernel<8, true>), dim3(Z, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
+    S2D2_LAUNCH((attn_flash_kernel<8, true>), dim3(X, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
                        (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win,
                        (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,
-                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16);
+                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16, columns);
   else
-    S2D2_LAUNCH((attn_flash_kernel<8, false>), dim3(Z, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
+    S2D2_LAUNCH((attn_flash_kernel<8, false>), dim3(X, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
                        (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win,
                        (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,
-                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16);
+                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16, columns);
 }
 
 #ifdef S2D2_KERNEL_TIMING
