@@ -290,14 +290,14 @@ __device__ __forceinline__ void attn_flash_columns(
 // or consumer is another workgroup of the SAME launch; the stand-alone kernel passes false).  The split partials
 // always are.
 // (z, qt, item) = (key split, query tile, sequence * Hkv + KV head); q_tiles = query tiles per item.
-// columns: short caches of more than one split go through attn_flash_columns (needs at least four workgroups per item, one query
+// COLUMNS: short caches of more than one split go through attn_flash_columns (needs at least four workgroups per item, one query
 // tile, and a window of at most 32 rows; workgroups past Z then have work in no other case).
-template <int NW, bool SPLIT, bool COH>
+template <int NW, bool SPLIT, bool COH, bool COLUMNS>
 __device__ __forceinline__ void attn_flash_body(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, const KvGeom& g, const Plan& p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int32_t* __restrict__ counters, int z, int qt, int item_zy, int q_tiles, float* smem, bool columns) {
+    float* __restrict__ part_ml, int32_t* __restrict__ counters, int z, int qt, int item_zy, int q_tiles, float* smem) {
   constexpr int D = FA_D;
   S2D2_ATS(0);
   const int Hkv = g.n_kv_heads, ps = g.page_size;
@@ -318,13 +318,13 @@ __device__ __forceinline__ void attn_flash_body(
 #pragma unroll
   for (int j = 0; j < 2; ++j) page_v[j] = pt[min(gw * 32 + 16 * j + 8 * h, cap - 1) / ps];
   int col_k[FA_COL_TILES], col_v[FA_COL_TILES][2];   // pages of the tiles that attn_flash_columns would give this wavefront: the same round trip
-  if (columns) {
+  if (COLUMNS) {
 #pragma unroll
     for (int t = 0; t < FA_COL_TILES; ++t) {
       const int k0 = (wave + t * NW) * 32;
-      col_k[t] = pt[min(k0 + kperm, cap - 1) / ps];
+      col_k[t] = pt[fa_div(min(k0 + kperm, cap - 1), ps)];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) col_v[t][j] = pt[min(k0 + 16 * j + 8 * h, cap - 1) / ps];
+      for (int j = 0; j < 2; ++j) col_v[t][j] = pt[fa_div(min(k0 + 16 * j + 8 * h, cap - 1), ps)];
     }
   }
   const int S = max(0, min(g.seq_len[n], cap));
@@ -360,7 +360,7 @@ __device__ __forceinline__ void attn_flash_body(
   // every second wavefront has a tile, more only when a wavefront would otherwise walk several tiles.
   const int T_all = Tc + Tw;
   const int Zeff = max(1, min(Z, max((T_all + NW - 1) / NW, min(4, (2 * T_all + NW - 1) / NW))));
-  if (columns && Zeff > 1 && S <= FA_COL_MAX * 32) {   // (the same in every workgroup of a sequence)
+  if (COLUMNS && Zeff > 1 && S <= FA_COL_MAX * 32) {   // (the same in every workgroup of a sequence)
     if (z < 4) attn_flash_columns<NW, SPLIT>(qf, ql, k_win, vT_win, k_pages, v_pages, g, Hq, wpad, scale_log2e, o, o_ld, o_lo, col_k, col_v, n, kvh, S, row0, nw, nq, lo, hi, r, z, smem);
     return;
   }
