@@ -1,5 +1,4 @@
-"""GPU: vocabulary statistics on either side of the line between 4096 and 8192 logits per workgroup (16384 workgroups of
-4096), against the same statistics in 64 bits: arg-max and runner-up at the ends of the chunks, ties across them, -inf."""
+"""GPU: vocabulary statistics of thousands of rows (16383 and 16386 workgroups of 4096 logits), against the same statistics in 64 bits: arg-max and runner-up at the ends of the chunks, ties across them, -inf."""
 import math
 
 import pytest
