@@ -28,16 +28,16 @@ HEADLINE, OTHERS = 4, (2, 3, 5)
 # step, from the FETCH_SIZE / WRITE_SIZE counter runs summarised under profiles/ (rocprofv3 --pmc on this file with
 # the default operand mode; a plain copy of 1 GiB reads FETCH_SIZE = 524300 KiB and WRITE_SIZE = 1048576 KiB, so
 # bytes = FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024).  Averages over all GEMM launches of two steps.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31340851, 3: 84114227, 4: 199593267, 5: 338396058}
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31339827, 3: 68681421, 4: 174737203, 5: 332358349}
 STEP_TRAFFIC_BYTES = {   # all kernels of a step: (FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024) summed over the step's launches
-    2: 5124024.9 * 2048 + 102234.8 * 1024,
-    3: 14177504.3 * 2048 + 4090622.5 * 1024,
-    4: 44077973.9 * 2048 + 10830020.1 * 1024,
-    5: 36764013.8 * 2048 + 10424475.8 * 1024,
+    2: 5199544.2 * 2048 + 58835.1 * 1024,
+    3: 13416653.5 * 2048 + 2069251.8 * 1024,
+    4: 42893975.0 * 2048 + 5729362.2 * 1024,
+    5: 36337021.9 * 2048 + 8573698.4 * 1024,
 }
-# The kernel with most of a configuration's GEMM time (config 3: 254 of 290 launches and 5.2 of 6.7 ms; the verifier's gate /
-# up projections are the tiled kernel's)
-GEMM_KERNEL = {2: "gemm_stream_kernel", 3: "gemm_mid_kernel", 4: "gemm_tile_kernel", 5: "gemm_tile_kernel"}
+# The kernel with most of a configuration's GEMM time (config 3: all but the unembedding, 5.7 of 6.0 ms; config 4: gate / up and the
+# draft's down projection, 10.1 of 17.0 ms)
+GEMM_KERNEL = {2: "gemm_stream_kernel", 3: "gemm_block_kernel", 4: "gemm_tile_kernel", 5: "gemm_tile_kernel"}
 
 
 def log(*a):
