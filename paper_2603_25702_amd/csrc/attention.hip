@@ -9,8 +9,6 @@
 #include "../../include/s2d2.h"
 #include "attention_flash.h"
 
-#include <type_traits>
-
 namespace s2d2 {
 
 template <int I> struct Lane { static constexpr int value = I; };
@@ -182,7 +180,7 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   }
 }
 
-template <int NW, bool SPLIT, bool COLUMNS>
+template <int NW, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
@@ -205,7 +203,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(
     }
     return;
   }
-  attn_flash_body<NW, SPLIT, false, COLUMNS>(q, q_ld, q_lo, k_win, vT_win, k_pages, v_pages, g, p, Hq, Z, wpad, scale_log2e, o, o_ld,
+  attn_flash_body<NW, SPLIT, false>(q, q_ld, q_lo, k_win, vT_win, k_pages, v_pages, g, p, Hq, Z, wpad, scale_log2e, o, o_ld,
                                     o_lo, part_o, part_ml, counters, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y, smem);
 }
 
@@ -223,24 +221,20 @@ void launch_attention_flash(hipStream_t st, const void* q, int q_ld, int q_lo, c
   const int items = N * g.n_kv_heads;
   float* part_o = part;
   float* part_ml = part + (size_t)items * q_tiles * Z * 32 * FA_D;
-  // extra slabs of X * q_tiles workgroups that only read `prefetch` (see the kernel)
-  // One query tile, splits to merge, and no more workgroups than compute units: short caches by output columns
-  // (attn_flash_columns).  Not in a cache with room for more than twice as many keys: the kernel that has both forms looks up
-  // the pages of both (4B, 4 x 2 behind 1103 to 3442 tokens: 3444 us for 3343).
-  const bool columns = q_tiles == 1 && Z > 1 && items * 4 <= 256 && g.max_pages_per_seq * g.page_size <= 2 * 32 * FA_COL_MAX;
-  const int X = columns ? std::max(Z, 4) : Z;
-  const int slabs = prefetch && prefetch_bytes >= 16 ? std::min(65535 - items, (prefetch_wgs + X * q_tiles - 1) / (X * q_tiles)) : 0;
+  // extra slabs of Z * q_tiles workgroups that only read `prefetch` (see the kernel)
+  const int slabs = prefetch && prefetch_bytes >= 16 ? std::min(65535 - items, (prefetch_wgs + Z * q_tiles - 1) / (Z * q_tiles)) : 0;
   const uint4* pf = (const uint4*)prefetch;
   const size_t pf_n16 = slabs > 0 ? prefetch_bytes / 16 : 0;
-  auto go = [&](auto split, auto cols) {
-    S2D2_LAUNCH((attn_flash_kernel<8, decltype(split)::value, decltype(cols)::value>), dim3(X, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
-                (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win, (const bf16_t*)k_pages_layer,
-                (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e, (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16);
-  };
-  if (q_lo && columns) go(std::true_type{}, std::true_type{});
-  else if (q_lo) go(std::true_type{}, std::false_type{});
-  else if (columns) go(std::false_type{}, std::true_type{});
-  else go(std::false_type{}, std::false_type{});
+  if (q_lo)
+    S2D2_LAUNCH((attn_flash_kernel<8, true>), dim3(Z, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
+                       (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win,
+                       (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,
+                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16);
+  else
+    S2D2_LAUNCH((attn_flash_kernel<8, false>), dim3(Z, q_tiles, items + slabs), dim3(8 * 64), fa_lds(8), st,
+                       (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win,
+                       (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,
+                       (bf16_t*)o, o_ld, o_lo, part_o, part_ml, counters, items, pf, pf_n16);
 }
 
 #ifdef S2D2_KERNEL_TIMING
@@ -266,9 +260,8 @@ int attention_init() {
   limit((const void*)attn_generic_kernel<bf16_t, 64>); limit((const void*)attn_generic_kernel<float, 64>);
   limit((const void*)attn_generic_kernel<bf16_t, 128>); limit((const void*)attn_generic_kernel<float, 128>);
   limit((const void*)attn_generic_kernel<bf16_t, 256>); limit((const void*)attn_generic_kernel<float, 256>);
-  for (const void* f : {(const void*)attn_flash_kernel<8, false, false>, (const void*)attn_flash_kernel<8, true, false>,
-                        (const void*)attn_flash_kernel<8, false, true>, (const void*)attn_flash_kernel<8, true, true>})
-    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_lds(8));
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_flash_kernel<8, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_lds(8));
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_flash_kernel<8, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_lds(8));
   return e == hipSuccess ? 0 : -1;
 }
 

@@ -141,158 +141,13 @@ __device__ __forceinline__ void fa_combine(const float* part_o, const float* par
   }
 }
 
-// The caches up to this many 32-key tiles (1024 keys) go through attn_flash_columns: FA_COL_TILES a wavefront of eight.
-static constexpr int FA_COL_TILES = 4, FA_COL_MAX = 8 * FA_COL_TILES;
-
-// Short caches: a workgroup takes ALL keys of a (sequence, KV head) and 32 of the 128 output columns, so that nothing is merged
-// through memory: three dependent round trips (partials written, arrival counted, partials read) for reading the keys four
-// times, out of L2.  The read-ahead of the weights then is what the launch lasts for (14.2 us for 14.1 to 14.5) and the GEMMs behind it find
-// them: one sequence of 512 tokens, 1.7B, draft 1343 -> 1327 us, verifier 1349 -> 1334.  Not where a sequence has one split only
-// (up to four tiles): nothing is merged there, and 3 x 3 behind 51 to 65 tokens took 1511 us for 1475.
-// dt: which 32 columns.  The wavefronts take the cached tiles in turn and the last one the window (at most 32 rows).
-template <int NW, bool SPLIT>
-__device__ __forceinline__ void attn_flash_columns(
-    const uint4 (&qf)[8], const uint4 (&ql)[SPLIT ? 8 : 1], const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
-    const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, const KvGeom& g, int Hq, int wpad, float scale_log2e,
-    bf16_t* __restrict__ o, int o_ld, int o_lo, const int (&page_k)[FA_COL_TILES], const int (&page_v)[FA_COL_TILES][2], int n, int kvh,
-    int S, int row0, int nw, int nq, int lo, int hi, int r, int dt, float* smem) {
-  constexpr int D = FA_D;
-  const int Hkv = g.n_kv_heads, ps = g.page_size, grp = Hq / Hkv;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c = lane & 31, h = lane >> 5, kperm = fa_perm(c);
-  const int Tc = __builtin_amdgcn_readfirstlane((S + 31) >> 5);
-  const int n_c = Tc > wave ? (Tc - wave + NW - 1) / NW : 0;   // cached tiles wave, wave + NW, ...
-  float m = -INFINITY, l = 0.f;
-  f32x16_t acc;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  struct Tile { uint4 k[8], v[2]; };
-  auto cached = [&](int it) __attribute__((always_inline)) {
-    Tile t;
-    const int kbase = (wave + it * NW) * 32;
-    const bf16_t* kp = k_pages + (((size_t)min(max(page_k[it], 0), g.n_pages - 1) * Hkv + kvh) * ps + (kbase + kperm) % ps) * D + 8 * h;
-#pragma unroll
-    for (int ds = 0; ds < 8; ++ds) t.k[ds] = *(const uint4*)(kp + ds * 16);   // (a key beyond seq_len is some valid row; its score is replaced)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int key0 = kbase + 16 * j + 8 * h;
-      t.v[j] = *(const uint4*)(v_pages + (((size_t)min(max(page_v[it][j], 0), g.n_pages - 1) * Hkv + kvh) * D + dt * 32 + c) * ps + key0 % ps);
-    }
-    return t;
-  };
-  auto window = [&]() __attribute__((always_inline)) {
-    Tile t;
-    const bf16_t* kp = k_win + ((size_t)(row0 + min(kperm, nw - 1)) * Hkv + kvh) * D + 8 * h;
-#pragma unroll
-    for (int ds = 0; ds < 8; ++ds) t.k[ds] = *(const uint4*)(kp + ds * 16);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) t.v[j] = *(const uint4*)(vT_win + ((size_t)(n * Hkv + kvh) * D + dt * 32 + c) * wpad + 16 * j + 8 * h);
-    return t;
-  };
-  // one tile: the arithmetic of attn_flash_body on one block of output columns
-  auto take = [&](const Tile& t, int kbase, bool win) __attribute__((always_inline)) {
-    const int limit = win ? nw : S;
-    f32x16_t sacc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
-#pragma unroll
-    for (int ds = 0; ds < 8; ++ds) {
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.k[ds]), __builtin_bit_cast(bf16x8_t, qf[ds]), sacc, 0, 0, 0);
-      if (SPLIT) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t.k[ds]), __builtin_bit_cast(bf16x8_t, ql[ds]), sacc, 0, 0, 0);
-    }
-    float sv[16];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = kbase + 16 * (i >> 3) + 8 * h + (i & 7);
-      bool ok = key < limit;
-      if (win) {
-        const int w = row0 + key;
-        ok = ok && ((w >= lo && w < hi) || w == r);
-      }
-      sv[i] = ok ? sacc[i] * scale_log2e : -INFINITY;
-      mx = fmaxf(mx, sv[i]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx);
-    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m - m_ref);
-    float ls = 0.f;
-    bf16x8_t pb[2], pl[SPLIT ? 2 : 1];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float pv = __builtin_amdgcn_exp2f(sv[i] - m_ref);
-      ls += pv;
-      const __bf16 ph = (__bf16)pv;
-      pb[i >> 3][i & 7] = ph;
-      if (SPLIT) pl[i >> 3][i & 7] = (__bf16)(pv - (float)ph);
-    }
-    ls += __shfl_xor(ls, 32, 64);
-    l = l * alpha + ls;
-    m = m_new;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] *= alpha;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint4 v = mask_keys(t.v[j], limit - (kbase + 16 * j + 8 * h));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v), pb[j], acc, 0, 0, 0);
-      if (SPLIT) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v), pl[j], acc, 0, 0, 0);
-    }
-  };
-  // two tiles in flight; past the wavefront's own the last one again, not taken
-  Tile a = cached(0), b = cached(1);
-  if (n_c > 0) take(a, wave * 32, false);
-  if (n_c > 2) a = cached(2);
-  if (n_c > 1) take(b, (wave + NW) * 32, false);
-  if (n_c > 2) {
-    if (n_c > 3) b = cached(3);
-    take(a, (wave + 2 * NW) * 32, false);
-    if (n_c > 3) take(b, (wave + 3 * NW) * 32, false);
-  }
-  if (wave == NW - 1) {
-    const Tile w = window();
-    take(w, 0, true);
-  }
-  // ---- merge the wavefronts in wavefront order: element (i4, lane) holds 4 consecutive columns of query row c ----
-  float* s_o = smem;                       // [NW][4][64] float4
-  float* s_m = smem + (size_t)NW * 1024;   // [NW][32]
-  float* s_l = s_m + NW * 32;              // [NW][32]
-  {
-    float4* dst = (float4*)(s_o + (size_t)wave * 1024) + lane;
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) dst[i4 * 64] = make_float4(acc[4 * i4], acc[4 * i4 + 1], acc[4 * i4 + 2], acc[4 * i4 + 3]);
-    if (h == 0) { s_m[wave * 32 + c] = m; s_l[wave * 32 + c] = l; }
-  }
-  __syncthreads();
-  if (threadIdx.x < 256) {
-    const int i4 = threadIdx.x >> 6;
-    float mw[NW], M = -INFINITY, L = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { mw[w] = s_m[w * 32 + c]; M = fmaxf(M, mw[w]); }
-    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float f = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);
-      const float4 v = ((const float4*)(s_o + (size_t)w * 1024))[i4 * 64 + lane];
-      L += f * s_l[w * 32 + c];
-      sum.x += f * v.x; sum.y += f * v.y; sum.z += f * v.z; sum.w += f * v.w;
-    }
-    if (c < nq) {
-      const float inv = L > 0.f ? 1.0f / L : 0.f;
-      fa_store4<false>(o, o_lo, row0 + c / grp, (kvh * grp + c % grp) * D + dt * 32 + 8 * i4 + 4 * h, o_ld, sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
-    }
-  }
-}
-
 // SPLIT: queries and softmax weights are used as high + low bf16 planes (16 significant bits): the
 // score and the P*V products are each issued twice against the same K / V operands.
 // COH: q, the window K / V and o are read and written with device-coherent accesses (for a caller whose producer
 // or consumer is another workgroup of the SAME launch; the stand-alone kernel passes false).  The split partials
 // always are.
 // (z, qt, item) = (key split, query tile, sequence * Hkv + KV head); q_tiles = query tiles per item.
-// COLUMNS: short caches of more than one split go through attn_flash_columns (needs at least four workgroups per item, one query
-// tile, and a window of at most 32 rows; workgroups past Z then have work in no other case).
-template <int NW, bool SPLIT, bool COH, bool COLUMNS>
+template <int NW, bool SPLIT, bool COH>
 __device__ __forceinline__ void attn_flash_body(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, const KvGeom& g, const Plan& p, int Hq, int Z,
@@ -317,16 +172,6 @@ __device__ __forceinline__ void attn_flash_body(
   int page_v[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) page_v[j] = pt[min(gw * 32 + 16 * j + 8 * h, cap - 1) / ps];
-  int col_k[FA_COL_TILES], col_v[FA_COL_TILES][2];   // pages of the tiles that attn_flash_columns would give this wavefront: the same round trip
-  if (COLUMNS) {
-#pragma unroll
-    for (int t = 0; t < FA_COL_TILES; ++t) {
-      const int k0 = (wave + t * NW) * 32;
-      col_k[t] = pt[fa_div(min(k0 + kperm, cap - 1), ps)];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) col_v[t][j] = pt[fa_div(min(k0 + 16 * j + 8 * h, cap - 1), ps)];
-    }
-  }
   const int S = max(0, min(g.seq_len[n], cap));
   const int row0 = p.seq_row0[n], nw = p.seq_rows[n];
   const int nq = nw * grp, q0 = qt * 32;
@@ -360,10 +205,6 @@ __device__ __forceinline__ void attn_flash_body(
   // every second wavefront has a tile, more only when a wavefront would otherwise walk several tiles.
   const int T_all = Tc + Tw;
   const int Zeff = max(1, min(Z, max((T_all + NW - 1) / NW, min(4, (2 * T_all + NW - 1) / NW))));
-  if (COLUMNS && Zeff > 1 && S <= FA_COL_MAX * 32) {   // (the same in every workgroup of a sequence)
-    if (z < 4) attn_flash_columns<NW, SPLIT>(qf, ql, k_win, vT_win, k_pages, v_pages, g, Hq, wpad, scale_log2e, o, o_ld, o_lo, col_k, col_v, n, kvh, S, row0, nw, nq, lo, hi, r, z, smem);
-    return;
-  }
   if (z >= Zeff) return;
   const int GW = Zeff * NW;
   const int n_c = Tc > gw ? fa_div(Tc - gw + GW - 1, GW) : 0;      // cached tiles gw, gw + GW, ...
