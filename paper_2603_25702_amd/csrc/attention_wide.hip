@@ -7,8 +7,10 @@
 // wavefronts.  Key splits are added up by a second launch, in split order.
 //
 // Eight wavefronts (one workgroup per compute unit) of which at most half have a query tile with rows, as in every window without
-// committed tokens in front, stand in two key groups: the group of an even and of an odd tile, so a step of the walk is two tiles
-// long and every wavefront multiplies.  The two states of a query tile are merged in LDS at the end.
+// committed tokens in front: in splits of more than FW_SHORT tiles they stand in two key groups, the group of an even and of an odd
+// tile, so a step of the walk is two tiles long and every wavefront multiplies; the two states of a query tile are merged in LDS at the end.
+// In shorter splits the lower four multiply and the upper four fetch, one tile at a time, with plain loads: what two groups
+// save over a few tiles is less than their merge and the streaming loads' longer way cost.
 //
 // Pipeline: two groups of tiles are in flight in registers while a third is being consumed from one of two LDS buffers; a
 // wavefront parks its pieces of group g + 1 in the other buffer after its own math on group g, and one barrier per group
@@ -16,9 +18,7 @@
 // once, and read a group ahead of the loads that need them.  What bounds a long prefix is the issue of vector-ALU
 // instructions (softmax, conversions, addresses), then the clock, which falls to 1.7 .. 1.9 GHz here.
 // Attention per launch (without the merge), one tile at a time with separate fetching wavefronts / two tiles in two key groups:
-// 8B verification, 32 sequences of 2048 .. 8192 tokens 141 / 113 us, 8B draft 114 / 90; with the merge, 4B verification of
-// 2 x 32 behind 3000 tokens 45 / 32, MoE draft of 4 x 16 behind 600 18 / 16; a launch of four tiles a split over four
-// query tiles is 0.5 to 2 us longer (4B 2 x 32 behind 1000: 12.5 / 14.8).
+// 8B verification, 32 sequences of 2048 .. 8192 tokens 141 / 113 us.
 #include "attention_flash.h"
 #include <stdlib.h>
 #include <type_traits>
@@ -27,7 +27,7 @@ namespace s2d2 {
 
 #ifdef S2D2_KERNEL_TIMING
 __device__ unsigned long long g_wide_ts[64];
-// stamps of the first computing (k < 8) and the first fetching wavefront (k >= 8) of workgroup (0, 0, 0), tile 16
+// stamps of the first wavefront of workgroup (0, 0, 0), tile 16
 #define S2D2_WTS(k, cond) do { if ((cond) && lane == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) g_wide_ts[(k)] = wall_clock64(); } while (0)
 __global__ void wide_ts_copy_kernel(unsigned long long* out) { if (threadIdx.x < 64) out[threadIdx.x] = g_wide_ts[threadIdx.x]; }
 void launch_wide_ts_copy(hipStream_t st, void* out) { S2D2_LAUNCH(wide_ts_copy_kernel, dim3(1), dim3(64), 0, st, (unsigned long long*)out); }
@@ -41,6 +41,10 @@ static constexpr int FW_VROW = 80;                // bytes per V^T row in LDS: 3
 static constexpr int FW_KBUF = 32 * FW_KROW;
 static constexpr int FW_BUF = FW_KBUF + 128 * FW_VROW;
 static constexpr int FW_RING = 2;
+// Tiles up to which four wavefronts fetch for four (see the header).  us per launch with the merge, fetching / two key groups: 5 tiles 4B
+// draft 2 x 32 behind 1000 16.3 / 18.5 (two planes 20.3 / 21.8), MoE 4 x 16 17.1 / 20.0, 8 tiles 4B 21.6 / 23.6, 17 tiles 8B 16 x 16
+// 31.0 / 34.5, 25 tiles 8B 16 x 16 37.0 / 39.1, 8 x 16 36.6 / 36.2, 33 tiles 8 x 16 41.5 / 41.4, 129 tiles 16 x 16 126 / 115.
+static constexpr int FW_SHORT = 24;
 constexpr int fw_tiles(int nw) { return nw == 8 ? 2 : 1; }   // most tiles walked at a time
 
 size_t attention_wide_lds_bytes(int pt_cap, int nw) { return (size_t)FW_RING * fw_tiles(nw) * FW_BUF + (size_t)pt_cap * 4; }
@@ -59,8 +63,11 @@ __device__ __forceinline__ uint4 fw_mask(uint4 v, int nv) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// (every byte of the cache is read once per launch, past the caches: 7.0 TB/s for the 6.1 of plain loads)
+// (Every byte of the cache is read once per launch.  STREAM: past the caches, 7.0 TB/s for the 6.1 of plain loads in a long walk; a short one
+// ends sooner with plain loads, 4B draft 2 x 32 behind 1000 16.4 / 17.2 us.)
+template <bool STREAM>
 __device__ __forceinline__ uint4 ld_kv(uint64_t at) {
+  if (!STREAM) return __builtin_bit_cast(uint4, *(const __attribute__((address_space(1))) u32x4_t*)at);
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t*)at));
 }
 
@@ -75,7 +82,7 @@ __device__ __forceinline__ uint4 fw_to_f16(uint4 v) {
 
 // QM: how the queries come and the arithmetic type of both products.  OPM_BF16 / OPM_BF16X2: bf16 MFMA on the
 // cache's bf16 keys and values, queries and softmax weights as one or as a high + low bf16 plane.  OPM_F16: queries
-// as IEEE half, keys and values converted to half on their way into LDS (by the fetching wavefronts), softmax
+// as IEEE half, keys and values converted to half on their way into LDS, softmax
 // weights as half: one 11-bit plane on the f16 MFMA, half the matrix instructions of the two-plane form and no
 // high / low split of the weights.
 template <int NW, int QM>
@@ -104,19 +111,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   const int nq = nw * grp;
   // query tiles qgrp * per .. + per of this (sequence, KV head) belong to this workgroup, one per wavefront (per <= NW)
   if (qgrp * per * 32 >= nq) return;            // the whole workgroup: nothing to do (before any barrier)
-  // Query tiles with rows; with at least two of eight wavefronts for each, the wavefronts stand in two key groups that walk two
-  // 32-key tiles at a time, and their states are merged in LDS at the end.
+  // Query tiles with rows; see the header for what at least two of eight wavefronts for each are used for.
   const int n_live = min(per, (nq - qgrp * per * 32 + 31) >> 5);
-  const bool two = NW == 8 && 2 * n_live <= NW;
+  const int Tw = (nw + 31) >> 5;
+  const int n_c = t1 - t0, n_w = z == Zn - 1 ? Tw : 0, n_it = n_c + n_w;
+  const bool half_live = NW == 8 && 2 * n_live <= NW, two = half_live && n_it > FW_SHORT;
   const int kg = two && wave >= n_live ? 1 : 0, wq = wave - kg * n_live;
   const bool active = wq < n_live;
   const int qt = qgrp * per + min(wq, n_live - 1), q0 = qt * 32;
   const int qi = min(q0 + c, nq - 1);
   const int r = row0 + qi / grp, head = kvh * grp + qi % grp;
   const int lo = p.row_lo[r], hi = p.row_hi[r];
-
-  const int Tw = (nw + 31) >> 5;
-  const int n_c = t1 - t0, n_w = z == Zn - 1 ? Tw : 0, n_it = n_c + n_w;
 
   // page-table slice of this split's keys
   const int pb0 = (t0 * 32) >> ps_shift;   // page_size = 1 << ps_shift
@@ -266,12 +271,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
 #endif
   };
 
-  // Groups of KG tiles: one is multiplied out of one LDS buffer, the next is parked in the other one from one of
+  // Groups of KG tiles, fetched by the last FW wavefronts: one is multiplied out of one LDS buffer, the next is parked in the other one from one of
   // two register sets, which is then refilled with the group two further on; a barrier per group.
-  auto walk = [&](auto kg_tag) __attribute__((always_inline)) {
-    constexpr int KG = decltype(kg_tag)::value, NP = KG * 8 / NW;   // pieces of keys (and of values) per wavefront and group, all of one tile
+  auto walk = [&](auto kg_tag, auto fw_tag) __attribute__((always_inline)) {
+    constexpr int KG = decltype(kg_tag)::value, FW = decltype(fw_tag)::value, NP = KG * 8 / FW;   // pieces of keys (and of values) per wavefront and group, all of one tile
     constexpr int PL = NP > 1 ? 2 : 1, NL = NP / PL;                // pieces per table entry, entries
-    const int n_g = (n_it + KG - 1) / KG, slot = wave * NP >> 3, j0 = wave * NP & 7;   // this wavefront's tile of a group, its first piece
+    const int n_g = (n_it + KG - 1) / KG;
+    if (FW < NW && wave < NW - FW) {   // the others fetch: a barrier ahead of the first tile and one behind each, as they have
+      __syncthreads();
+#pragma unroll 1
+      for (int gi = 0; gi < n_g; ++gi) {
+        if (active) compute(st, qf, ql, gi, lds + (gi & 1) * FW_BUF);
+        __syncthreads();
+      }
+      return;
+    }
+    const int fwave = wave - (NW - FW), slot = fwave * NP >> 3, j0 = fwave * NP & 7;   // this wavefront's tile of a group, its first piece
     uint4 ak[NP] = {}, av[NP] = {}, bk[NP] = {}, bv[NP] = {};   // (indices are compile-time constants throughout)
     // table entries of group gi's pieces (of some valid page where there is none), read ahead of their use
     auto look = [&](int gi, uint32_t (&lk)[NL], uint32_t (&lv)[NL]) __attribute__((always_inline)) {
@@ -295,8 +310,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
           const uint64_t va = vb_l + (uint32_t)(((key + v_key(j)) & (ps - 1)) * 2 + v_row(j) * ps * 2) + (uint64_t)lv[u] * pbytes;
 #pragma unroll
           for (int e = 0; e < PL; ++e) {
-            kr[u * PL + e] = ld_kv(ka + e * 1024);
-            vr[u * PL + e] = ld_kv(va + (uint32_t)(e * vstep));
+            kr[u * PL + e] = ld_kv<FW == NW>(ka + e * 1024);
+            vr[u * PL + e] = ld_kv<FW == NW>(va + (uint32_t)(e * vstep));
           }
         }
       } else {
@@ -312,8 +327,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
             const uint64_t k_w = (uint64_t)(k_win + ((size_t)(row0 + min(key + (lane >> 4), nw - 1)) * Hkv + kvh) * D + (lane & 15) * 8);
             const uint64_t v_c = vb_l + (uint32_t)((kcv & (ps - 1)) * 2 + v_row(j) * ps * 2) + (uint64_t)lv[u] * pbytes;
             const uint64_t v_w = (uint64_t)(vT_win + ((size_t)(n * Hkv + kvh) * D + v_row(j) + vd_l) * wpad + min(keyv, wpad - kpp) + vo_l * 8);
-            kr[u * PL + e] = ld_kv(t.win ? k_w : k_c);
-            vr[u * PL + e] = ld_kv(t.win ? v_w : v_c);
+            kr[u * PL + e] = ld_kv<FW == NW>(t.win ? k_w : k_c);
+            vr[u * PL + e] = ld_kv<FW == NW>(t.win ? v_w : v_c);
           }
         }
       }
@@ -344,7 +359,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     auto pass = [&](int gi, uint4 (&kr)[NP], uint4 (&vr)[NP]) __attribute__((always_inline)) {
       uint32_t lk[NL], lv[NL];
       look(gi + 3, lk, lv);
-      if (active && gi >= 0 && gi * KG + kg < n_it) compute(st, qf, ql, gi * KG + kg, lds + ((gi & 1) * KG + kg) * FW_BUF);
+      if (FW == NW && active && gi >= 0 && gi * KG + kg < n_it) compute(st, qf, ql, gi * KG + kg, lds + ((gi & 1) * KG + kg) * FW_BUF);
       if (gi + 1 >= 0 && gi + 1 < n_g) stash(gi + 1, kr, vr);
       fetch(gi + 3, lk, lv, kr, vr);
       if (gi >= -1) __syncthreads();
@@ -375,8 +390,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
         const int key = (t0 + i) * 32 + kk, kv0 = (t0 + i) * 32 + vko;
         const int pk = s_pt[min((key >> ps_shift) - pb0, pt_cap - 1)];
         const int pv = s_pt[min((kv0 >> ps_shift) - pb0, pt_cap - 1)];
-        kr = ld_kv((uint64_t)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D));
-        vr = ld_kv((uint64_t)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1))));
+        kr = ld_kv<true>((uint64_t)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D));
+        vr = ld_kv<true>((uint64_t)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1))));
         return;
       }
       const FwTile t = tile_of(i);
@@ -390,8 +405,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
       const bf16_t* vp_c = v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1));
       const bf16_t* kp_w = k_win + ((size_t)row0 * Hkv + kvh) * D + kch * 8 + (size_t)key * (Hkv * D);
       const bf16_t* vp_w = vT_win + ((size_t)(n * Hkv + kvh) * D + vd) * wpad + min(key0, wpad - 8);
-      kr = ld_kv((uint64_t)(t.win ? kp_w : kp_c));
-      vr = ld_kv((uint64_t)(t.win ? vp_w : vp_c));
+      kr = ld_kv<true>((uint64_t)(t.win ? kp_w : kp_c));
+      vr = ld_kv<true>((uint64_t)(t.win ? vp_w : vp_c));
     };
     auto stash1 = [=](auto fast, int u, int i, int b, uint4 kr, uint4 vr) __attribute__((always_inline)) {
       constexpr bool FAST = decltype(fast)::value;
@@ -426,8 +441,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   };
   if (n_it > 0) {
     if constexpr (NW == 4) walk4();
-    else if (two) walk(std::integral_constant<int, 2>{});
-    else walk(std::integral_constant<int, 1>{});
+    else if (two) walk(std::integral_constant<int, 2>{}, std::integral_constant<int, NW>{});
+    else if (half_live) walk(std::integral_constant<int, 1>{}, std::integral_constant<int, NW / 2>{});
+    else walk(std::integral_constant<int, 1>{}, std::integral_constant<int, NW>{});
   }
   if (NW == 8 && two) {   // the second key group's states, through LDS (behind the last group's barrier: nobody reads tiles any more)
     float4* s_o = (float4*)lds;                                    // [query tile][16][lane]
