@@ -283,15 +283,21 @@ KvGeom geom(const s2d2_ctx* c, const s2d2_kv_view* kv) {
 }
 
 // Shape of the wide attention launch: q_tiles 32-row query tiles per window; target key splits of all sequences together,
-// per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence.
-struct WideShape { int q_tiles, target, Z; };
+// per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence; LDS for
+// `tiles` key tiles at a time beside a split's share of the page table, 0 if that is too long.
+struct WideShape { int q_tiles, target, Z, tiles; };
 WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) {
   WideShape w;
+  const KvGeom g = geom(c, kv);
   w.q_tiles = (win * (c->desc.n_q_heads / c->desc.n_kv_heads) + 31) / 32;
-  const int wg = c->desc.n_kv_heads * ((w.q_tiles + 7) / 8);
-  const int fill = attention_wide_nw(w.q_tiles) == 8 ? c->wide_wgs / 2 : c->wide_wgs;   // (one workgroup of eight wavefronts per compute unit, two of four)
-  w.target = std::max(1, std::min((fill + wg - 1) / wg, WIDE_MAX_TARGET));
-  w.Z = attention_wide_splits(geom(c, kv), N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
+  const int wg = c->desc.n_kv_heads * ((w.q_tiles + 7) / 8), nw = attention_wide_nw(w.q_tiles);
+  // One workgroup of eight wavefronts per compute unit, two of four; where the page table is too long for that, more and shorter splits.
+  for (int fill : {nw == 8 ? c->wide_wgs / 2 : c->wide_wgs, c->wide_wgs}) {
+    w.target = std::max(1, std::min((fill + wg - 1) / wg, WIDE_MAX_TARGET));
+    w.Z = attention_wide_splits(g, N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
+    for (w.tiles = nw == 8 ? 2 : 1; w.tiles > 0; --w.tiles)
+      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, w.Z, w.target), w.tiles) <= 160 * 1024) return w;
+  }
   return w;
 }
 
@@ -327,7 +333,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     Z = std::max(1, std::min(std::min(want, (cap_tiles + 7) / 8), c->attn_zmax));
     if (wide) {
       Z = ws.Z;
-      if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, Z, ws.target), attention_wide_nw(q_tiles)) > 160 * 1024) wide = false, Z = 1;
+      if (ws.tiles == 0) wide = false, Z = 1;
     }
   }
   const size_t lds = flash ? 0 : attention_generic_lds_bytes(g, sz.win);
@@ -398,7 +404,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;
     const void* vp = (const uint8_t*)kv->v_pages + l * page_layer;
     if (wide) {
-      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
+      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, ws.tiles, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
       if (Z > 1) { ProfScope ps(c, 1, 0.0); launch_attention_wide_merge(st, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
     } else if (flash) {
       // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the

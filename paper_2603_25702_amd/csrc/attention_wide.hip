@@ -9,7 +9,7 @@
 // Eight wavefronts (one workgroup per compute unit) of which at most half have a query tile with rows, as in every window without
 // committed tokens in front: in splits of more than FW_SHORT tiles they stand in two key groups, the group of an even and of an odd
 // tile, so a step of the walk is two tiles long and every wavefront multiplies; the two states of a query tile are merged in LDS at the end.
-// In shorter splits the lower four multiply and the upper four fetch, one tile at a time, with plain loads: what two groups
+// In shorter splits, and beside a page table that leaves no LDS for four tiles, the lower four multiply and the upper four fetch, one tile at a time, with plain loads: what two groups
 // save over a few tiles is less than their merge and the streaming loads' longer way cost.
 //
 // Pipeline: two groups of tiles are in flight in registers while a third is being consumed from one of two LDS buffers; a
@@ -45,9 +45,8 @@ static constexpr int FW_RING = 2;
 // draft 2 x 32 behind 1000 16.3 / 18.5 (two planes 20.3 / 21.8), MoE 4 x 16 17.1 / 20.0, 8 tiles 4B 21.6 / 23.6, 17 tiles 8B 16 x 16
 // 31.0 / 34.5, 25 tiles 8B 16 x 16 37.0 / 39.1, 8 x 16 36.6 / 36.2, 33 tiles 8 x 16 41.5 / 41.4, 129 tiles 16 x 16 126 / 115.
 static constexpr int FW_SHORT = 24;
-constexpr int fw_tiles(int nw) { return nw == 8 ? 2 : 1; }   // most tiles walked at a time
 
-size_t attention_wide_lds_bytes(int pt_cap, int nw) { return (size_t)FW_RING * fw_tiles(nw) * FW_BUF + (size_t)pt_cap * 4; }
+size_t attention_wide_lds_bytes(int pt_cap, int tiles) { return (size_t)FW_RING * tiles * FW_BUF + (size_t)pt_cap * 4; }
 
 struct FwTile { bool win; int kbase, limit; };
 
@@ -90,11 +89,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift) {
+    float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles /* there is LDS for */) {
   constexpr int D = FA_D, T = NW * 64;
   constexpr bool SPLIT = QM == OPM_BF16X2, F16 = QM == OPM_F16;
   extern __shared__ __align__(16) unsigned char lds[];
-  int32_t* s_pt = (int32_t*)(lds + FW_RING * fw_tiles(NW) * FW_BUF);
+  int32_t* s_pt = (int32_t*)(lds + FW_RING * tiles * FW_BUF);
   // Splits are numbered through over the sequences (Plan.split_of), so the workgroups without one are the last of the
   // grid.  Between the others they leave compute units empty that hold two workgroups elsewhere, one after the
   // other (the hardware deals workgroups out in turn, whether they leave at once or not): 125 -> 167 us.
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   const int n_live = min(per, (nq - qgrp * per * 32 + 31) >> 5);
   const int Tw = (nw + 31) >> 5;
   const int n_c = t1 - t0, n_w = z == Zn - 1 ? Tw : 0, n_it = n_c + n_w;
-  const bool half_live = NW == 8 && 2 * n_live <= NW, two = half_live && n_it > FW_SHORT;
+  const bool half_live = NW == 8 && 2 * n_live <= NW, two = half_live && n_it > FW_SHORT && tiles == 2;
   const int kg = two && wave >= n_live ? 1 : 0, wq = wave - kg * n_live;
   const bool active = wq < n_live;
   const int qt = qgrp * per + min(wq, n_live - 1), q0 = qt * 32;
@@ -566,10 +565,10 @@ template <int NW>
 static void launch_wide(hipStream_t st, int qm, dim3 grid, size_t lds, const bf16_t* q, int q_ld, int q_lo,
                         const bf16_t* k_win, const bf16_t* vT_win, const bf16_t* kp, const bf16_t* vp, const KvGeom& g,
                         const Plan& p, int Hq, int Z, int wpad, float scale_log2e, bf16_t* o, int o_ld, int o_lo,
-                        float* part_o, float* part_ml, int q_tiles, int per, int pt_cap, int ps_shift) {
+                        float* part_o, float* part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles) {
 #define S2D2_WIDE_QM(QMV)                                                                                                    \
   S2D2_LAUNCH((attn_flash_wide_kernel<NW, QMV>), grid, dim3(NW * 64), lds, st, q, q_ld, q_lo, k_win, vT_win, kp, vp, g, p, \
-              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift)
+              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles)
   if (qm == OPM_F16) S2D2_WIDE_QM(OPM_F16);
   else if (qm == OPM_BF16X2) S2D2_WIDE_QM(OPM_BF16X2);
   else S2D2_WIDE_QM(OPM_BF16);
@@ -607,7 +606,7 @@ int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
 
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int target, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           int Hq, int q_tiles, int Z, int target, int tiles, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)g.head_dim);
   const int qgroups = (q_tiles + 7) / 8, per = (q_tiles + qgroups - 1) / qgroups;   // tiles per workgroup, balanced
@@ -616,13 +615,13 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
   float* part_o = part;
   float* part_ml = part + part_entries * 32 * FA_D;
   const dim3 grid(g.n_kv_heads, qgroups, std::min(N * Z, N + target));   // (N + target: a run more than the target per sequence at most)
-  const size_t lds = attention_wide_lds_bytes(pt_cap, nw);
+  const size_t lds = attention_wide_lds_bytes(pt_cap, tiles);
   int ps_shift = 0;
   while ((1 << ps_shift) < g.page_size) ++ps_shift;   // the caller has checked that page_size is a power of two
 #define S2D2_WIDE(NWV)                                                                                                  \
   launch_wide<NWV>(st, operand_mode(q_lo), grid, lds, (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win, \
                    (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,          \
-                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift)
+                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles)
   if (nw == 4) S2D2_WIDE(4);
   else S2D2_WIDE(8);
 #undef S2D2_WIDE

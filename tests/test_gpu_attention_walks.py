@@ -2,8 +2,10 @@
 one; other tests have pages of 16): four wavefronts that fetch for four in short splits, two key groups in splits of more than 24 tiles of
 32 keys, one group where more than half of the wavefronts have query rows."""
 import pytest
+import torch
 
 import s2d2_inputs as I
+from paper_2603_25702_amd import Params
 from tests import harness as H
 from tests.test_gpu_parity import run_steps
 
@@ -34,4 +36,23 @@ def test_walks(B, lens, page_size, act_planes):
                     case.v_pages[l][int(page)] += offset
     run, rep = run_steps(case, 1, act_planes=act_planes)
     print("walks:", B, lens, page_size, act_planes, rep)
+    assert rep.max_logit_err_draft <= RTOL and rep.max_logit_err_verify <= RTOL
+
+
+@pytest.mark.parametrize("pages,B", [
+    (25000, 32),   # 100 KB of page table: no LDS for the tiles of two key groups; a split of 31 tiles per sequence
+    (40000, 32),   # 160 KB: twice as many splits
+])
+def test_long_page_tables(pages, B):
+    """Caches with room for 200 000 tokens and more in pages of 8: still the wide kernel and its merge, two launches per layer and
+    forward (the narrow kernel is one)."""
+    lens = [900 + n for n in range(16)]
+    case = H.make_case(CFG, len(lens), B, lens, seed=38, synthetic_kv=True, page_size=8, room=96 + 2 * B)
+    run = H.DeviceRun(case)
+    table = run.kv.page_table
+    run.kv.page_table = torch.cat([table, table.new_zeros((len(lens), pages - table.shape[1]))], 1).contiguous()
+    run.eng.s2d2_profile_start(4096)
+    run.step(Params(seed=1234), advance=False)
+    assert run.eng.s2d2_profile_stop()["attention"]["launches"] == 2 * CFG.n_layers * 2
+    rep = H.check_step(case, run, run.fetch(), Params(seed=1234), seqs=[0, 7, 15])
     assert rep.max_logit_err_draft <= RTOL and rep.max_logit_err_verify <= RTOL
