@@ -22,7 +22,7 @@ S2D2_GREEDY, S2D2_SAMPLE = 0, 1
 EXPORTS = [
     "s2d2_last_error", "s2d2_version", "s2d2_stage_rows", "s2d2_workspace_bytes", "s2d2_packed_bytes", "s2d2_create", "s2d2_destroy",
     "s2d2_set_stream", "s2d2_draft", "s2d2_verify", "s2d2_accept", "s2d2_accept_static", "s2d2_kv_append", "s2d2_block_advance",
-    "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_prefill", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score", "s2d2_profile_start", "s2d2_profile_stop",
+    "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_prefill", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score", "s2d2_gemm_choice", "s2d2_profile_start", "s2d2_profile_stop",
 ]
 PROFILE_CLASSES = ("gemm", "attention", "vocab", "other", "gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "gemm_unembed")
 
@@ -148,9 +148,10 @@ def load_library():
     lib.s2d2_moe_choices.restype = C.c_int32
     lib.s2d2_vocab_draft_stats.argtypes = [C.c_void_p, C.c_void_p, C.c_int32] + [C.c_void_p] * 5
     lib.s2d2_vocab_score.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+    lib.s2d2_gemm_choice.argtypes = [C.POINTER(ModelDesc)] + [C.c_int32] * 5 + [C.POINTER(C.c_int32)]
     lib.s2d2_profile_start.argtypes = [C.c_void_p, C.c_int32]
     lib.s2d2_profile_stop.argtypes = [C.c_void_p, C.POINTER(ProfileC)]
-    for name in ("s2d2_profile_start", "s2d2_profile_stop", "s2d2_destroy", "s2d2_set_stream", "s2d2_draft", "s2d2_verify", "s2d2_accept", "s2d2_kv_append",
+    for name in ("s2d2_gemm_choice", "s2d2_profile_start", "s2d2_profile_stop", "s2d2_destroy", "s2d2_set_stream", "s2d2_draft", "s2d2_verify", "s2d2_accept", "s2d2_kv_append",
                  "s2d2_block_advance", "s2d2_commit_threshold", "s2d2_block_complete", "s2d2_prefill", "s2d2_route", "s2d2_moe_choices", "s2d2_debug_buffer", "s2d2_status", "s2d2_vocab_draft_stats", "s2d2_vocab_score"):
         getattr(lib, name).restype = C.c_int32
     _LIB = lib
@@ -170,6 +171,16 @@ def model_desc(cfg, act_planes: int = 0) -> ModelDesc:
     return ModelDesc(cfg.n_layers, cfg.d_model, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.d_ffn, cfg.vocab,
                      cfg.n_experts, cfg.top_k, cfg.d_expert, S2D2_BF16 if cfg.dtype == "bf16" else S2D2_F32,
                      cfg.mask_id, act_planes, int(bool(getattr(cfg, "right_shifted", False))), cfg.rope_theta, cfg.rms_eps)
+
+
+def s2d2_gemm_choice(cfg, forward: str, N: int, B: int, matrix: str, cus: int = 256, act_planes: int = 0):
+    """The GEMM kernel that a forward ("draft", "verify", "prefill") runs on a matrix ("qkv", "o", "gateup", "down", "unembed"):
+    ("stream" | "mid" | "block" | "tile", row blocks, feature tiles, workgroups that share K, streaming loads)."""
+    lib = load_library()
+    out = (C.c_int32 * 5)()
+    _check(lib, lib.s2d2_gemm_choice(C.byref(model_desc(cfg, act_planes)), ("draft", "verify", "prefill").index(forward), N, B, cus,
+                                     4 + ("qkv", "o", "gateup", "down", "unembed").index(matrix), out))
+    return (("stream", "mid", "block", "tile")[out[0]], out[1], out[2], out[3], bool(out[4]))
 
 
 @dataclass

@@ -310,6 +310,46 @@ FwdSize draft_size(int N, int B) { return {2 * B, 2 * N * B, N * B, N * B}; }   
 FwdSize verify_size(int N, int B, int shifted) { return {3 * B, 3 * N * B, N * B, (shifted ? 1 : 2) * N * B}; }
 FwdSize prefill_size(int N, int T) { return {T, N * T, 0, N * T}; }
 
+// What the GEMMs on packed weights have beside their operands: compute units and the buffers of the K splits.
+struct GemmEnv {
+  int cus;
+  float* tile_partials;
+  int32_t* tile_counters;
+  unsigned long long* pair_buf;
+  int32_t* pair_status;
+  void put(GemmStreamArgs& x, int rows) const {
+    x.m_hint = rows; x.coop_wgs = cus;
+    x.tile_partials = tile_partials; x.tile_counters = tile_counters; x.tile_partial_cap = TILE_PARTIAL_CAP; x.tile_counter_cap = TILE_COUNTER_CAP;
+    x.pair_buf = pair_buf; x.pair_status = pair_status; x.pair_cap = PAIR_CAP;
+  }
+};
+// The matrices of a layer by the classes of the launch timer: 4 QKV, 5 output, 6 gate / up, 7 down projection, 8 unembedding.
+struct GemmMatrix { int kind, N, K; };
+GemmMatrix matrix_of(const s2d2_model_desc& d, int which) {
+  switch (which) {
+    case 4: return {SEPI_QKV_ROPE, (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim, d.d_model};
+    case 5: return {SEPI_ADD_F32, d.d_model, d.n_q_heads * d.head_dim};
+    case 6: return {SEPI_SWIGLU, d.d_ffn, d.d_model};
+    case 7: return {SEPI_ADD_F32, d.d_model, d.d_ffn};
+  }
+  return {SEPI_STORE_F32, d.vocab, d.d_model};
+}
+GemmChoice choice_of(const s2d2_model_desc& d, int which, int lo, const FwdSize& sz, const GemmEnv& env) {
+  const GemmMatrix m = matrix_of(d, which);
+  GemmStreamArgs x{};
+  x.NT = (m.N + 15) / 16; x.KT = m.K / 32; x.N = m.N; x.K = m.K; x.x_lo = lo;
+  if (which == 8) x.gather = env.tile_counters;   // (any: the unembedding has one)
+  env.put(x, which == 8 ? sz.LR : sz.hint);
+  return gemm_choice(m.kind, x, which == 8 ? sz.LR : sz.R);
+}
+// Half operands go in fragment order where a kernel that wants it takes one of the matrices.
+bool fragment_order(const s2d2_model_desc& d, int opm, const FwdSize& sz, const GemmEnv& env) {
+  if (opm != OPM_F16) return false;
+  bool frag = sz.hint <= MID_MOST_ROWS;
+  for (int which = 4; which <= (d.n_experts == 0 ? 7 : 5) && !frag; ++which) frag = choice_of(d, which, LO_F16P, sz, env).kernel == GEMM_BLOCK;
+  return frag;
+}
+
 // Without logit rows (LR = 0) the forward ends with the K/V of the last layer.
 int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& sz, void* k_stage, void* v_stage, float* logits) {
   const s2d2_model_desc& d = c->desc;
@@ -345,25 +385,14 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   const int ss_stride = (d.d_model + 15) / 16;
   const int m_hint = sz.hint;
   const double fr = 2.0 * m_hint, fl = 2.0 * LR;   // flops per weight element: layer GEMMs, unembedding (method's flops, one plane)
-  auto sk = [&](GemmStreamArgs& x) {   // split-K buffers of the tiled GEMM, expected rows
-    x.m_hint = x.m_count == c->plan.counts + 1 ? LR : m_hint;   // (logit rows: one per masked position)
-    x.tile_partials = c->tile_partials; x.tile_counters = c->tile_counters;
-    x.tile_partial_cap = TILE_PARTIAL_CAP; x.tile_counter_cap = TILE_COUNTER_CAP; x.coop_wgs = c->n_cus;
-    x.pair_buf = c->pair_buf; x.pair_status = c->dev_status + 1; x.pair_cap = PAIR_CAP;
-  };
-  // GEMM inputs: one plane of half values, in fragment order where a kernel that wants it takes one of the matrices, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which (0: one bf16 plane).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
+  const GemmEnv env{c->n_cus, c->tile_partials, c->tile_counters, c->pair_buf, c->dev_status + 1};
+  auto sk = [&](GemmStreamArgs& x) { env.put(x, x.m_count == c->plan.counts + 1 ? LR : m_hint); };   // (logit rows: one per masked position)
+  // GEMM inputs: one plane of half values, in fragment order or in rows, or P bf16 planes per row ([hi | lo]); the low-plane offsets say which (0: one bf16 plane).  The plain kernels (no packed copy, or the generic attention) use one bf16 plane.
   // (the generic attention kernel reads and writes single planes: two-plane models then run on their high plane)
   const int mode = operand_mode_of(d);
   const int opm = !fused ? OPM_BF16 : (flash || mode == OPM_F16 ? mode : OPM_BF16);
   const int P = opm == OPM_BF16X2 ? 2 : 1;
-  auto blocks = [&](int kind, int N_, int K_) {
-    GemmStreamArgs x{};
-    x.NT = N_ / 16; x.KT = K_ / 32; x.N = N_; x.K = K_; x.x_lo = LO_F16P; x.m_count = n_rows;
-    sk(x);
-    return gemm_block_takes(kind, x, R);
-  };
-  const bool frag = opm == OPM_F16 && (m_hint <= MID_MOST_ROWS || blocks(SEPI_QKV_ROPE, qkv_n, d.d_model) || blocks(SEPI_ADD_F32, d.d_model, HqD) ||
-                                       (d.n_experts == 0 && (blocks(SEPI_SWIGLU, d.d_ffn, d.d_model) || blocks(SEPI_ADD_F32, d.d_model, d.d_ffn))));
+  const bool frag = fragment_order(d, opm, sz, env);
   auto lo_row = [&](int width) { return opm == OPM_F16 ? LO_F16 : (P == 2 ? width : 0); };   // rows of the MoE FFN
   auto lo_of = [&](int width) { return opm == OPM_F16 ? (frag ? LO_F16P : LO_F16) : (P == 2 ? width : 0); };
   const int ld_a = P * d.d_model, lo_a = lo_of(d.d_model);
@@ -844,6 +873,23 @@ int32_t s2d2_route(s2d2_ctx* c, int32_t N, int32_t B, const s2d2_route_params* r
   { ProfScope ps(c, 3, 0.0); launch_route(c->stream, N, B, *rp, draft->span_start, draft->span_len, draft->margin, draft->entropy_n, draft->n_hi,
                draft->unmask, hysteresis, out->do_verify, out->khat, out->score, out->unmask_fallback); }
   return check_launch("s2d2_route");
+}
+
+int32_t s2d2_gemm_choice(const s2d2_model_desc* desc, int32_t forward, int32_t N, int32_t B, int32_t cus, int32_t matrix, int32_t* out) {
+  const int32_t rc = check_desc(desc);
+  if (rc) return rc;
+  if (forward < 0 || forward > 2 || N < 1 || N > 1024 || B < 1 || B > (forward == 2 ? 3 * S2D2_MAX_BLOCK : S2D2_MAX_BLOCK) || cus < 1 || cus > 4096 || matrix < 4 || matrix > 8 || !out) return fail(S2D2_EINVAL, "s2d2_gemm_choice: an argument is out of range");
+  if (desc->dtype != S2D2_BF16 || (desc->n_experts > 0 && (matrix == 6 || matrix == 7))) return fail(S2D2_EINVAL, "s2d2_gemm_choice: the matrices of bf16 models, not those of experts");
+  const FwdSize sz = forward == 0 ? draft_size(N, B) : forward == 1 ? verify_size(N, B, desc->right_shifted) : prefill_size(N, B);
+  if (matrix == 8 && sz.LR == 0) return fail(S2D2_EINVAL, "s2d2_gemm_choice: a prefill has no logits");
+  static int there;   // (buffers count as there; nothing is launched)
+  const GemmEnv env{cus, (float*)&there, &there, (unsigned long long*)&there, &there};
+  const int opm = operand_mode_of(*desc);
+  const GemmMatrix m = matrix_of(*desc, matrix);
+  const int lo = opm == OPM_F16 ? (fragment_order(*desc, opm, sz, env) ? LO_F16P : LO_F16) : opm == OPM_BF16X2 ? m.K : 0;
+  const GemmChoice c = choice_of(*desc, matrix, lo, sz, env);
+  out[0] = c.kernel; out[1] = c.rb; out[2] = c.ta; out[3] = c.KS; out[4] = c.stream;
+  return S2D2_OK;
 }
 
 int32_t s2d2_profile_start(s2d2_ctx* c, int32_t max_launches) {

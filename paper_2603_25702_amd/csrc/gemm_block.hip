@@ -419,25 +419,29 @@ static int launch_blk(hipStream_t st, const GemmStreamArgs& a, int KS, int m_cap
   return std::min((groups + 3) & ~3, a.ss_stride);
 }
 
+// Streaming loads leave what the next kernels need in L2 (their code, the plan, the rows that this one writes): with plain loads
+// the 1.7B attention behind the QKV projection takes 16.4 us for 15.0, an embedding launch 8.3 for 7.6.  Where more row tiles read the
+// same weights again they cost more than that (256 rows 4B: down projection 36.5 -> 38.5, 128 rows 1.7B 15.5 -> 16.0).
+constexpr bool blk_streams(int kind, int RB, int TA) { return RB <= 4 || (kind == SEPI_SWIGLU && TA == 6); }   // compiled; up to 64 rows the pick has four row blocks or fewer in all other shapes
+static bool blk_stream(int kind, const BlkPick& p, int rows) {
+  return blk_streams(kind, p.rb, p.ta) && rows <= (kind == SEPI_SWIGLU && p.ta == 6 && p.rb > 4 ? 16 * p.rb : 64);
+}
+
 template <int EPI, int RB, int TA>
-static int launch_blk_shape(hipStream_t st, const GemmStreamArgs& a, int KS, int m_cap) {
-  // Streaming loads leave what the next kernels need in L2 (their code, the plan, the rows that this one writes): with plain loads
-  // the 1.7B attention behind the QKV projection takes 16.4 us for 15.0, an embedding launch 8.3 for 7.6; 64 rows 1.7B, 4B, 8B
-  // 14 layers 1040 -> 1010 .. 990, ... us.  Where more row tiles read the same weights again they cost more than that (256
-  // rows 4B: down projection 36.5 -> 38.5, 128 rows 1.7B 15.5 -> 16.0).
-  constexpr int STREAM_ROWS = EPI == SEPI_SWIGLU && TA == 6 ? (RB > 4 ? 16 * RB : 64) : 64;
-  const bool stream = a.m_hint <= STREAM_ROWS;
-  if constexpr (EPI == SEPI_ADD_F32 && blk_shares(RB, TA))
-    if (KS > 1) return stream ? launch_blk<EPI, RB, TA, true, true>(st, a, KS, m_cap) : launch_blk<EPI, RB, TA, true, false>(st, a, KS, m_cap);
-  if constexpr (RB <= 4 || (EPI == SEPI_SWIGLU && TA == 6))
-    if (stream) return launch_blk<EPI, RB, TA, false, true>(st, a, 1, m_cap);
+static int launch_blk_shape(hipStream_t st, const GemmStreamArgs& a, const GemmChoice& c, int m_cap) {
+  if constexpr (EPI == SEPI_ADD_F32 && blk_shares(RB, TA)) {
+    if constexpr (blk_streams(EPI, RB, TA))
+      if (c.KS > 1 && c.stream) return launch_blk<EPI, RB, TA, true, true>(st, a, c.KS, m_cap);
+    if (c.KS > 1) return launch_blk<EPI, RB, TA, true, false>(st, a, c.KS, m_cap);
+  }
+  if constexpr (blk_streams(EPI, RB, TA))
+    if (c.stream) return launch_blk<EPI, RB, TA, false, true>(st, a, 1, m_cap);
   return launch_blk<EPI, RB, TA, false, false>(st, a, 1, m_cap);
 }
 
 template <int EPI>
-static int launch_blk_kind(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
-  const BlkPick p = blk_pick(EPI, a, m_cap);
-#define S2D2_BLK(RB, TA) if (p.rb == RB && p.ta == TA) return launch_blk_shape<EPI, RB, TA>(st, a, p.KS, m_cap)
+static int launch_blk_kind(hipStream_t st, const GemmStreamArgs& a, const GemmChoice& c, int m_cap) {
+#define S2D2_BLK(RB, TA) if (c.rb == RB && c.ta == TA) return launch_blk_shape<EPI, RB, TA>(st, a, c, m_cap)
   S2D2_BLK(2, 2); S2D2_BLK(4, 2); S2D2_BLK(4, 4); S2D2_BLK(4, 6); S2D2_BLK(8, 4); S2D2_BLK(8, 6);
   if constexpr (EPI == SEPI_SWIGLU) { S2D2_BLK(6, 4); S2D2_BLK(6, 6); }
   else { S2D2_BLK(4, 3); }
@@ -451,18 +455,20 @@ static int launch_blk_kind(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
 // 48 / 54, 4B 22 / 35, 35 / 43, 1.7B 512 rows 22 / 35, MoE 1024 rows 32 / 40; output 8B 23 / 35, 34 / 39, 4B 18 / 29, 27 / 45, 1.7B
 // 14 / 28, MoE 21 / 35; down 8B 56 / 69, 4B 37 / 43, 51 / 68, 1.7B 29 / 35; gate / up 4B 512 rows 71 / 85, 128 rows 34 / 45, 1.7B 128
 // rows 18 / 26, 8B 96 rows 46 / 58, and left to the tiled kernel 8B 256 rows 82 / 73, 512 141 / 109, 4B 256 53 / 46, 1.7B 512 43 / 36.
-bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap) {
+bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap, GemmChoice& c) {
   if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * BLK_NW || a.m_hint <= MID_MOST_ROWS || a.grouped != GROUP_NONE || kind == SEPI_STORE_F32) return false;
   if ((long long)a.NT * a.KT * 1024 >= 1LL << 32 || (long long)(m_cap + 15) / 16 * a.KT * 1024 >= 1LL << 32) return false;   // (32-bit offsets)
   const BlkPick p = blk_pick(kind, a, m_cap);
-  return p.rb > 0 && 1.1 * p.us < gemm_tile_us(kind, a, (m_cap + 127) / 128);
+  if (p.rb == 0 || 1.1 * p.us >= gemm_tile_us(kind, a, (m_cap + 127) / 128)) return false;
+  c = {GEMM_BLOCK, p.rb, p.ta, p.KS, blk_stream(kind, p, a.m_hint)};
+  return true;
 }
 
-int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
+int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c) {
   switch (kind) {
-    case SEPI_QKV_ROPE: return launch_blk_kind<SEPI_QKV_ROPE>(st, a, m_cap);
-    case SEPI_ADD_F32: return launch_blk_kind<SEPI_ADD_F32>(st, a, m_cap);
-    case SEPI_SWIGLU: return launch_blk_kind<SEPI_SWIGLU>(st, a, m_cap);
+    case SEPI_QKV_ROPE: return launch_blk_kind<SEPI_QKV_ROPE>(st, a, c, m_cap);
+    case SEPI_ADD_F32: return launch_blk_kind<SEPI_ADD_F32>(st, a, c, m_cap);
+    case SEPI_SWIGLU: return launch_blk_kind<SEPI_SWIGLU>(st, a, c, m_cap);
   }
   return 0;
 }

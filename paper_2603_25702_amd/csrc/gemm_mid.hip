@@ -290,12 +290,14 @@ __global__ __launch_bounds__(MID_NW * 64, 2) void gemm_mid_kernel(const GemmStre
 }
 
 // The lines against the neighbours (us per launch, weights from memory; this kernel / the other one):
-//   16 rows and fewer stay with the streaming kernel: 1.7B-shaped layer 37 / 32 (QKV, output, gate / up, down added up)
+//   16 rows and fewer, where no more than 32 are possible, stay with the streaming kernel: 1.7B-shaped layer 37 / 32 (QKV, output, gate / up, down added up)
 //   32 rows: 55 / 84 against two row tiles of the streaming kernel, 4B-shaped layer
 //   48 rows: 66 / 64 (4B), 41 / 41 (1.7B), 97 / 97 (8B) against gemm_block.hip, 64 rows: 76 / 68, 46 / 44, 116 / 100
 //   unembedding, against the tiled kernel: 4B 184 / 182 at 64 rows, 224 / 198 at 96
-bool gemm_mid_takes(int kind, const GemmStreamArgs& a) {
-  if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * MID_NW || a.m_hint <= 16) return false;
+//   at most 16 rows expected, but room for more than the streaming kernel takes (a right-shifted verifier of 11 to 16 masked
+//   positions; whole forwards of 12 rows, this / the streaming / the tiled kernel): 1.7B 1467 / 1439 / 3115, 4B 2423 / 2660 / 4607, 8B 3566 / 3535 / 5880
+bool gemm_mid_takes(int kind, const GemmStreamArgs& a, int m_cap) {
+  if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * MID_NW || a.m_hint < 1 || (a.m_hint <= 16 && m_cap <= STREAM_MOST_ROWS)) return false;
   return kind != SEPI_STORE_F32 ? a.m_hint <= MID_MOST_ROWS : a.m_hint <= 64 && (a.NT > 8 || a.gather);   // (a matrix of a few feature tiles: see the streaming kernel's launcher)
 }
 

@@ -393,7 +393,21 @@ static void launch_pair(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
   S2D2_LAUNCH((gemm_stream_kernel<SEPI_ADD_F32, SPRO_BF16, NW, 1, U, OPM, true>), grid, block, lds, st, a);
 }
 
-static constexpr int STREAM_MOST_ROWS = 32;   // two row tiles
+// Wide windows: the LDS-tiled kernel reads the weights once per 128 rows instead of once per 16.  Not for a matrix
+// of a few feature tiles (the MoE router, 64 experts): its weights stay in L2, a 256-column tile would be mostly
+// empty, and a row tile of 16 per workgroup spreads the rows over the whole chip.
+GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap) {
+  GemmChoice c{GEMM_STREAM, 0, 0, 1, false};
+  if (gemm_block_takes(kind, a, m_cap, c)) return c;
+  if (gemm_mid_takes(kind, a, m_cap)) return {GEMM_MID, 0, 0, 1, false};
+  // The streaming kernel takes half operands in fragment order only, except the ones that a store reads: a forward
+  // lays them out so whenever it expects at most MID_MOST_ROWS rows, and a caller that did not is sent to the tiled
+  // kernel, which takes rows too.
+  static_assert(MID_MOST_ROWS >= STREAM_MOST_ROWS, "windows of the streaming kernel are laid out in fragment order");
+  const bool half_rows = a.x_lo == LO_F16 && kind != SEPI_STORE_F32;
+  if ((m_cap > STREAM_MOST_ROWS || half_rows) && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) c.kernel = GEMM_TILE;
+  return c;
+}
 
 // Launch shapes (wavefronts per workgroup, feature tiles per workgroup, loads in flight per wavefront), tuned on the
 // 1.7B shape: the layer matrices want >= 256 workgroups; with the sliding-window K loop the step time moved by less
@@ -403,22 +417,13 @@ static constexpr int STREAM_MOST_ROWS = 32;   // two row tiles
 // workgroups (256 workgroups: 9.6 us per launch against 13.0 us with 128 workgroups of 16 wavefronts, which
 // streamed at half the rate of the other layer GEMMs).
 int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
-  // wide windows: the LDS-tiled kernel reads the weights once per 128 rows instead of once per 16.  Not for a matrix
-  // of a few feature tiles (the MoE router, 64 experts): its weights stay in L2, a 256-column tile would be mostly
-  // empty, and a row tile of 16 per workgroup spreads the rows over the whole chip.
-  if (gemm_block_takes(kind, a, m_cap)) {
-    return launch_gemm_block(st, kind, a, m_cap);
-  }
-  if (gemm_mid_takes(kind, a)) {
+  const GemmChoice c = gemm_choice(kind, a, m_cap);
+  if (c.kernel == GEMM_BLOCK) return launch_gemm_block(st, kind, a, m_cap, c);
+  if (c.kernel == GEMM_MID) {
     launch_gemm_mid(st, kind, a, m_cap);
     return a.NT;
   }
-  // The streaming kernel below takes half operands in fragment order only, except the ones that a store reads: a forward
-  // lays them out so whenever it expects at most MID_MOST_ROWS rows, and a caller that did not is sent to the tiled
-  // kernel, which takes rows too.
-  static_assert(MID_MOST_ROWS >= STREAM_MOST_ROWS, "windows of the streaming kernel are laid out in fragment order");
-  const bool half_rows = a.x_lo == LO_F16 && kind != SEPI_STORE_F32;
-  if ((m_cap > STREAM_MOST_ROWS || half_rows) && !(kind == SEPI_STORE_F32 && a.NT <= 8 && !a.gather)) {
+  if (c.kernel == GEMM_TILE) {
     launch_gemm_tile(st, kind, kind == SEPI_ADD_F32 ? SPRO_BF16 : SPRO_BF16S, a, (m_cap + 127) / 128);
     return a.NT;
   }

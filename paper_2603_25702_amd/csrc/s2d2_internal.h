@@ -299,15 +299,21 @@ void launch_rope_table(hipStream_t st, const Plan& p, int rows_cap, int D, float
 void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, int rows_cap, const float* gain,
                        float* h, void* xg, int xg_ld, int xg_lo, float* ss, int ss_stride,
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
+// Kernel of a GEMM on packed weights and, of gemm_block.hip, its block (rb x ta units of 16 x 16), workgroups that share K and kind of
+// weight loads.  By the matrix, the operands, the rows expected (m_hint) and at most (m_cap).
+enum GemmKernel { GEMM_STREAM = 0, GEMM_MID = 1, GEMM_BLOCK = 2, GEMM_TILE = 3 };
+struct GemmChoice { GemmKernel kernel; int rb, ta, KS; bool stream; };
+GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap);
 // (a residual add returns the number of partial sums of squares it leaves per row)
 int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+constexpr int STREAM_MOST_ROWS = 32;   // of a window that the streaming kernel takes: two row tiles
 // gemm_mid.hip : windows of 17 to 48 rows (unembedding: 64), half operands in fragment order
 constexpr int MID_MOST_ROWS = 48;
-bool gemm_mid_takes(int kind, const GemmStreamArgs& a);
+bool gemm_mid_takes(int kind, const GemmStreamArgs& a, int m_cap);
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
 // gemm_block.hip : wider windows, half operands in fragment order
-bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap);
-int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap, GemmChoice& c);
+int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c);
 // gemm_tile.hip : 128 x 256 LDS-tiled kernel on the same packed weights and argument block
 void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a, int row_tiles);
 double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // estimate

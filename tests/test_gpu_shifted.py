@@ -51,6 +51,15 @@ def test_small_bf16_ragged_batch_narrow_and_wide_windows():
     assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
 
 
+@pytest.mark.parametrize("N,B", [(1, 11), (2, 8), (1, 16)])
+def test_windows_of_11_to_16_masked_positions(N, B):
+    """Verifiers of at most 16 rows when fresh, with room for more than the streaming GEMM takes; later steps carry tokens."""
+    case = H.make_case(shifted(SMALL_BF16), N, B, [100, 257][:N], seed=13, synthetic_kv=True, page_size=16, room=96, norm_jitter=0.1)
+    run, rep = run_steps(case, 4)
+    print("shifted, few rows:", N, B, rep)
+    assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
+
+
 def test_sampling_mode_and_moe():
     case = H.make_case(shifted(SMALL_BF16), 2, 8, [64, 90], seed=4, synthetic_kv=True, page_size=16, room=64)
     run, rep = run_steps(case, 3, prm_kw=dict(mode=1, temperature=0.5))
