@@ -1,7 +1,7 @@
-"""GPU parity of the GEMM for windows of 17 to about 256 rows, at the edges of its range: row blocks of 16 that are full
-and that hold one row, one and two passes over the rows (windows that carry more rows than a fresh block gives), K
-shared by several workgroups, feature tiles that do not divide into groups, and a K its batches do not divide (the
-tiled kernel takes that one matrix)."""
+"""GPU parity of the GEMMs for windows of 17 to 256 rows (the mid-size kernel up to 48 of a layer's rows and 64 logit rows, then blocks and
+tiles) at the edges of row counts: row blocks of 16 that are full and that hold one row, one and two passes over the rows (windows that
+carry more rows than a fresh block gives), K shared by several workgroups, feature tiles that do not divide into groups, and a K the
+batches do not divide (the tiled kernel takes that one matrix)."""
 import pytest
 
 import s2d2_inputs as I
