@@ -66,6 +66,23 @@ int main() {
   nanm.rope_theta = 0.0f / 0.0f * 0.0f;
   EXPECT(s2d2_workspace_bytes(&nanm, 1, 4) == S2D2_EINVAL);
   EXPECT(s2d2_workspace_bytes(nullptr, 1, 4) == S2D2_EINVAL && s2d2_packed_bytes(nullptr) == S2D2_EINVAL);
+  int32_t pick[5];
+  for (size_t f = 0; f < n_fields; ++f)
+    for (int32_t v : extremes)
+      for (int32_t matrix = 4; matrix <= 8; ++matrix) {
+        s2d2_model_desc m = shapes[3];
+        (&m.n_layers)[f] = v;
+        const int32_t rc = s2d2_gemm_choice(&m, 1, 1024, S2D2_MAX_BLOCK, 256, matrix, pick);
+        EXPECT(rc != S2D2_OK || (pick[0] >= 0 && pick[0] <= 3 && pick[3] >= 1));
+      }
+  for (int32_t v : extremes) {
+    EXPECT(s2d2_gemm_choice(&shapes[3], 0, v, 4, 256, 4, pick) == (v >= 1 && v <= 1024 ? S2D2_OK : S2D2_EINVAL));
+    EXPECT(s2d2_gemm_choice(&shapes[3], 2, 4, v, 256, 5, pick) == (v >= 1 && v <= 3 * S2D2_MAX_BLOCK ? S2D2_OK : S2D2_EINVAL));
+    EXPECT(s2d2_gemm_choice(&shapes[3], 0, 4, 4, v, 6, pick) == (v >= 1 && v <= 4096 ? S2D2_OK : S2D2_EINVAL));
+    EXPECT(s2d2_gemm_choice(&shapes[3], v, 4, 4, 256, 7, pick) == (v >= 0 && v <= 2 ? S2D2_OK : S2D2_EINVAL));
+    EXPECT(s2d2_gemm_choice(&shapes[3], 0, 4, 4, 256, v, pick) == S2D2_EINVAL);
+  }
+  EXPECT(s2d2_gemm_choice(nullptr, 0, 1, 4, 256, 4, pick) == S2D2_EINVAL && s2d2_gemm_choice(&shapes[3], 0, 1, 4, 256, 4, nullptr) == S2D2_EINVAL);
 
   // ---- s2d2_create refuses bad arguments before it looks for a device ----
   s2d2_ctx* ctx = (s2d2_ctx*)(uintptr_t)1;
