@@ -399,8 +399,12 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   const int ld_o = P * HqD, lo_o = lo_of(HqD);
   const int ld_f = P * d.d_ffn, lo_f = lo_of(d.d_ffn);
   const int ld_e = P * d.d_expert;
+  // (the kernels of the matrices, once for all layers: a choice goes through up to 36 block shapes, about 0.5 us)
+  GemmChoice pick[9];
+  if (fused)
+    for (int which = 4; which <= 8; ++which)
+      if (which == 8 ? LR > 0 : which < 6 || d.n_experts == 0) pick[which] = choice_of(d, which, lo_of(matrix_of(d, which).K), sz, env);
   // queries stay bf16 (the attention kernels multiply them with the cache's bf16 keys): hi + lo planes unless the
-  // model asked for single bf16 planes
   // model asked for single bf16 planes; the kernel for wide windows takes them as half values in the half mode
   // (it converts the keys and values on their way into LDS)
   const bool q_f16 = fused && wide && opm == OPM_F16;
@@ -423,7 +427,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       a.row_seq = c->plan.row_seq; a.seq_row0 = c->plan.seq_row0;
       if (q_f16) { a.k16_out = (bf16_t*)c->kwin16; a.win_f16 = 1; }
       ProfScope ps(c, 0, (double)qkv_n * d.d_model * es, fr * qkv_n * d.d_model, 4);
-      sk(a); launch_gemm_stream(st, SEPI_QKV_ROPE, a, R);
+      sk(a); launch_gemm_stream(st, SEPI_QKV_ROPE, a, R, pick[4]);
     } else {
       { ProfScope ps(c, 3, 0.0); launch_rmsnorm(st, dt, c->h, L.norm1, d.d_model, d.rms_eps, n_rows, nullptr, R, c->a); }
       { ProfScope ps(c, 0, (double)qkv_n * d.d_model * es, fr * qkv_n * d.d_model, 4); launch_gemm(st, dt, EPI_STORE_F32, c->a, d.d_model, L.wqkv, d.d_model, qkv_n, n_rows, R, c->qkv, qkv_n); }
@@ -455,7 +459,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       a.Wp = c->pk[l].wo; a.NT = d.d_model / 16; a.KT = HqD / 32; a.N = d.d_model; a.K = HqD;
       a.X = (const bf16_t*)c->obuf; a.ldx = ld_o; a.x_lo = lo_o; a.out = c->h; a.ldo = d.d_model;
       a.xg_out = (bf16_t*)c->a; a.xg_ld = ld_a; a.xg_lo = d.n_experts ? lo_row(d.d_model) : lo_a; a.gain_next = L.norm2; a.ss_out = c->ss; a.ss_stride = ss_stride;
-      { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); sk(a); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, a, R); }
+      { ProfScope ps(c, 0, (double)d.d_model * HqD * es, fr * d.d_model * HqD, 5); sk(a); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, a, R, pick[5]); }
       const float* gain_after = l + 1 < d.n_layers ? c->layers[l + 1].norm1 : c->w.norm_f;
       if (d.n_experts == 0) {
         GemmStreamArgs b{};
@@ -463,13 +467,13 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         b.Wp = c->pk[l].wg; b.Wp2 = c->pk[l].wu; b.NT = d.d_ffn / 16; b.KT = d.d_model / 32; b.N = d.d_ffn; b.K = d.d_model;
         b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_a; b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
         b.eps = d.rms_eps; b.out = c->ffn; b.ldo = ld_f; b.out_lo = lo_f;
-        { ProfScope ps(c, 0, 2.0 * d.d_ffn * d.d_model * es, fr * 2.0 * d.d_ffn * d.d_model, 6); sk(b); launch_gemm_stream(st, SEPI_SWIGLU, b, R); }
+        { ProfScope ps(c, 0, 2.0 * d.d_ffn * d.d_model * es, fr * 2.0 * d.d_ffn * d.d_model, 6); sk(b); launch_gemm_stream(st, SEPI_SWIGLU, b, R, pick[6]); }
         GemmStreamArgs e{};
         e.m_count = n_rows;
         e.Wp = c->pk[l].wdown; e.NT = d.d_model / 16; e.KT = d.d_ffn / 32; e.N = d.d_model; e.K = d.d_ffn;
         e.X = (const bf16_t*)c->ffn; e.ldx = ld_f; e.x_lo = lo_f; e.out = c->h; e.ldo = d.d_model;
         e.xg_out = (bf16_t*)c->a; e.xg_ld = ld_a; e.xg_lo = lo_a; e.gain_next = gain_after; e.ss_out = c->ss; e.ss_stride = ss_stride;
-        { ProfScope ps(c, 0, (double)d.d_model * d.d_ffn * es, fr * d.d_model * d.d_ffn, 7); sk(e); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, e, R); }
+        { ProfScope ps(c, 0, (double)d.d_model * d.d_ffn * es, fr * d.d_model * d.d_ffn, 7); sk(e); ss_count = launch_gemm_stream(st, SEPI_ADD_F32, e, R, pick[7]); }
       } else {
         // MoE FFN: router -> top-k -> group by expert -> grouped gate/up + SwiGLU -> grouped down -> combine
         const int E = d.n_experts, Fe = d.d_expert, tk = d.top_k;
@@ -479,7 +483,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         r.Wp = c->pk[l].router; r.NT = (E + 15) / 16; r.KT = d.d_model / 32; r.N = E; r.K = d.d_model;
         r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_row(d.d_model); r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_count;
         r.eps = d.rms_eps; r.out = c->router_logits; r.ldo = E;
-        { ProfScope ps(c, 0, (double)E * d.d_model * es, fr * E * d.d_model); sk(r); launch_gemm_stream(st, SEPI_STORE_F32, r, R); }
+        { ProfScope ps(c, 0, (double)E * d.d_model * es, fr * E * d.d_model); sk(r); launch_gemm_stream(st, SEPI_STORE_F32, r, R, gemm_choice(SEPI_STORE_F32, r, R)); }
         { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w); }
         { ProfScope ps(c, 3, 0.0); launch_moe_group(st, E, tk, n_rows, choice, c->moe_sorted, c->moe_tile_expert,
                                                      c->moe_tile_row0, c->moe_tile_rows, c->moe_n_tiles, c->moe_tile_cap); }
@@ -516,7 +520,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     a.ss_part = c->ss; a.ss_stride = ss_stride; a.ss_count = ss_count; a.eps = d.rms_eps;
     a.out = logits; a.ldo = d.vocab;
     ProfScope ps(c, 0, (double)d.vocab * d.d_model * es, fl * d.vocab * d.d_model, 8);
-    sk(a); launch_gemm_stream(st, SEPI_STORE_F32, a, LR);
+    sk(a); launch_gemm_stream(st, SEPI_STORE_F32, a, LR, pick[8]);
   } else {
     { ProfScope ps(c, 3, 0.0); launch_rmsnorm(st, dt, c->h, c->w.norm_f, d.d_model, d.rms_eps, n_logit, c->plan.logit_src, LR, c->af); }
     { ProfScope ps(c, 0, (double)d.vocab * d.d_model * es, fl * d.vocab * d.d_model, 8); launch_gemm(st, dt, EPI_STORE_F32, c->af, d.d_model, c->w.unembed, d.d_model, d.vocab, n_logit, LR, logits, d.vocab); }

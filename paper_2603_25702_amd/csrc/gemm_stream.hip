@@ -416,8 +416,7 @@ GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap) {
 // The down projection has only d_model / 16 feature tiles (128 for the 1.7B shape): there K is shared by pairs of
 // workgroups (256 workgroups: 9.6 us per launch against 13.0 us with 128 workgroups of 16 wavefronts, which
 // streamed at half the rate of the other layer GEMMs).
-int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap) {
-  const GemmChoice c = gemm_choice(kind, a, m_cap);
+int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c) {
   if (c.kernel == GEMM_BLOCK) return launch_gemm_block(st, kind, a, m_cap, c);
   if (c.kernel == GEMM_MID) {
     launch_gemm_mid(st, kind, a, m_cap);

@@ -305,7 +305,7 @@ enum GemmKernel { GEMM_STREAM = 0, GEMM_MID = 1, GEMM_BLOCK = 2, GEMM_TILE = 3 }
 struct GemmChoice { GemmKernel kernel; int rb, ta, KS; bool stream; };
 GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap);
 // (a residual add returns the number of partial sums of squares it leaves per row)
-int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
+int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c);
 constexpr int STREAM_MOST_ROWS = 32;   // of a window that the streaming kernel takes: two row tiles
 // gemm_mid.hip : windows of 17 to 48 rows (unembedding: 64), half operands in fragment order
 constexpr int MID_MOST_ROWS = 48;
