@@ -18,9 +18,9 @@ namespace s2d2 {
 // rows of 40000 (10 each) 64 rows 6.0 / 8.1, 1024 29.3 / 34.6.
 static constexpr int VT = 4;
 
-// Workgroups that share the draw of a row: as many as there are compute units for, at most eight.  One / two / four / eight /
-// sixteen, us per launch, rows of 151936 logits: 4 rows 32.4 / 21.9 / 16.4 / 11.7 / 11.2, 16 33.0 / 22.0 / 16.7 / 12.5 / 13.6, 64
-// 39.1 / 26.6 / 20.2 / 22.8 / 36.7, 128 41.1 / 29.5 / 36.2, 256 44.5 / 53.6.
+// Workgroups that share the draw of a row: as many as there are compute units for (256; the workspace is sized without a device to ask),
+// at most eight.  One / two / four / eight / sixteen, us per launch, rows of 151936 logits: 4 rows 32.4 / 21.9 / 16.4 / 11.7 / 11.2, 16
+// 33.0 / 22.0 / 16.7 / 12.5 / 13.6, 64 39.1 / 26.6 / 20.2 / 22.8 / 36.7, 128 41.1 / 29.5 / 36.2, 256 44.5 / 53.6.
 static int sample_share(int rows) { return std::max(1, std::min(8, 256 / rows)); }
 int sample_rows_shared(int rows) { return std::min(rows, 128); }   // most rows with more than one
 
