@@ -41,10 +41,14 @@ static constexpr int FW_VROW = 80;                // bytes per V^T row in LDS: 3
 static constexpr int FW_KBUF = 32 * FW_KROW;
 static constexpr int FW_BUF = FW_KBUF + 128 * FW_VROW;
 static constexpr int FW_RING = 2;
-// Tiles up to which four wavefronts fetch for four (see the header).  us per launch with the merge, fetching / two key groups: 5 tiles 4B
-// draft 2 x 32 behind 1000 16.3 / 18.5 (two planes 20.3 / 21.8), MoE 4 x 16 17.1 / 20.0, 8 tiles 4B 21.6 / 23.6, 17 tiles 8B 16 x 16
-// 31.0 / 34.5, 25 tiles 8B 16 x 16 37.0 / 39.1, 8 x 16 36.6 / 36.2, 33 tiles 8 x 16 41.5 / 41.4, 129 tiles 16 x 16 126 / 115.
+// Tiles up to which four of eight wavefronts fetch for the others (see the header).  us per launch with the merge, fetching / two key
+// groups: 5 tiles 4B draft 2 x 32 behind 1000 16.3 / 18.5 (two planes 20.3 / 21.8), MoE 4 x 16 17.1 / 20.0, 8 tiles 4B 21.6 / 23.6, 17 tiles 8B
+// 16 x 16 31.0 / 34.5, 25 tiles 8B 16 x 16 37.0 / 39.1, 8 x 16 36.6 / 36.2, 33 tiles 8 x 16 41.5 / 41.4, 129 tiles 16 x 16 126 / 115.
 static constexpr int FW_SHORT = 24;
+// Tiles up to which workgroups of four wavefronts load past no cache.  Plain / streaming loads: 4 tiles 8B verification 1 x 5 behind 6000 20.6 /
+// 22.8, 1.7B 5 x 7 behind 300 to 1900 18.8 / 20.9, 4B draft 4 x 16 behind 1000 17.3 / 18.1, 6 tiles 23.9 / 25.6, 12 tiles 32.2 / 33.0, 16 tiles 8B
+// 16 x 16 40.2 / 39.3, 4B 8 x 8 34.8 / 33.3, 24 tiles 4 x 16 49.3 / 47.4, 64 tiles 8B 16 x 16 110 / 99.5.
+static constexpr int FW_SHORT4 = 8;
 
 size_t attention_wide_lds_bytes(int pt_cap, int tiles) { return (size_t)FW_RING * tiles * FW_BUF + (size_t)pt_cap * 4; }
 
@@ -63,7 +67,7 @@ __device__ __forceinline__ uint4 fw_mask(uint4 v, int nv) {
 }
 
 // (Every byte of the cache is read once per launch.  STREAM: past the caches, 7.0 TB/s for the 6.1 of plain loads in a long walk; a short one
-// ends sooner with plain loads, 4B draft 2 x 32 behind 1000 16.4 / 17.2 us.)
+// ends sooner with plain loads, see FW_SHORT4.)
 template <bool STREAM>
 __device__ __forceinline__ uint4 ld_kv(uint64_t at) {
   if (!STREAM) return __builtin_bit_cast(uint4, *(const __attribute__((address_space(1))) u32x4_t*)at);
@@ -377,7 +381,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   // values (K row idx / 16, 16-byte piece idx % 16; V^T row idx / 4, keys 8 (idx % 4) .. + 8), one tile in flight, in forms
   // compiled for full cached tiles (FAST) and for all.  Walked two tiles at a time like eight wavefronts, launches of short splits
   // took 1 to 4 us longer (1.7B shape, four tiles a split, with the merge 25 for 19) and long ones were as fast.
-  auto walk4 = [&]() __attribute__((always_inline)) {
+  auto walk4 = [&](auto stream_tag) __attribute__((always_inline)) {
+    constexpr bool STREAM = decltype(stream_tag)::value;
     constexpr std::true_type FT_{};
     constexpr std::false_type GT_{};
     const size_t pstride = (size_t)Hkv * ps * D;   // elements of a page
@@ -389,8 +394,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
         const int key = (t0 + i) * 32 + kk, kv0 = (t0 + i) * 32 + vko;
         const int pk = s_pt[min((key >> ps_shift) - pb0, pt_cap - 1)];
         const int pv = s_pt[min((kv0 >> ps_shift) - pb0, pt_cap - 1)];
-        kr = ld_kv<true>((uint64_t)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D));
-        vr = ld_kv<true>((uint64_t)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1))));
+        kr = ld_kv<STREAM>((uint64_t)(k_pages + ((size_t)kvh * ps * D + kch * 8) + (size_t)pk * pstride + (key & (ps - 1)) * D));
+        vr = ld_kv<STREAM>((uint64_t)(v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1))));
         return;
       }
       const FwTile t = tile_of(i);
@@ -404,8 +409,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
       const bf16_t* vp_c = v_pages + ((size_t)kvh * D + vd) * ps + (size_t)pv * pstride + (kv0 & (ps - 1));
       const bf16_t* kp_w = k_win + ((size_t)row0 * Hkv + kvh) * D + kch * 8 + (size_t)key * (Hkv * D);
       const bf16_t* vp_w = vT_win + ((size_t)(n * Hkv + kvh) * D + vd) * wpad + min(key0, wpad - 8);
-      kr = ld_kv<true>((uint64_t)(t.win ? kp_w : kp_c));
-      vr = ld_kv<true>((uint64_t)(t.win ? vp_w : vp_c));
+      kr = ld_kv<STREAM>((uint64_t)(t.win ? kp_w : kp_c));
+      vr = ld_kv<STREAM>((uint64_t)(t.win ? vp_w : vp_c));
     };
     auto stash1 = [=](auto fast, int u, int i, int b, uint4 kr, uint4 vr) __attribute__((always_inline)) {
       constexpr bool FAST = decltype(fast)::value;
@@ -439,7 +444,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     for (; i < n_it; ++i) pass(GT_, i);
   };
   if (n_it > 0) {
-    if constexpr (NW == 4) walk4();
+    if constexpr (NW == 4) {
+      if (n_it > FW_SHORT4) walk4(std::true_type{});
+      else walk4(std::false_type{});
+    }
     else if (two) walk(std::integral_constant<int, 2>{}, std::integral_constant<int, NW>{});
     else if (half_live) walk(std::integral_constant<int, 1>{}, std::integral_constant<int, NW / 2>{});
     else walk(std::integral_constant<int, 1>{}, std::integral_constant<int, NW>{});
