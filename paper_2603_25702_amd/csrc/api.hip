@@ -437,7 +437,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;
     const void* vp = (const uint8_t*)kv->v_pages + l * page_layer;
     if (wide) {
-      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, ws.tiles, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
+      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, ws.tiles, c->n_cus, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
       if (Z > 1) { ProfScope ps(c, 1, 0.0); launch_attention_wide_merge(st, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
     } else if (flash) {
       // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the

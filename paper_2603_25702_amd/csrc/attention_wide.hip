@@ -45,9 +45,12 @@ static constexpr int FW_RING = 2;
 // groups: 5 tiles 4B draft 2 x 32 behind 1000 16.3 / 18.5 (two planes 20.3 / 21.8), MoE 4 x 16 17.1 / 20.0, 8 tiles 4B 21.6 / 23.6, 17 tiles 8B
 // 16 x 16 31.0 / 34.5, 25 tiles 8B 16 x 16 37.0 / 39.1, 8 x 16 36.6 / 36.2, 33 tiles 8 x 16 41.5 / 41.4, 129 tiles 16 x 16 126 / 115.
 static constexpr int FW_SHORT = 24;
-// Tiles up to which workgroups of four wavefronts load past no cache.  Plain / streaming loads: 4 tiles 8B verification 1 x 5 behind 6000 20.6 /
-// 22.8, 1.7B 5 x 7 behind 300 to 1900 18.8 / 20.9, 4B draft 4 x 16 behind 1000 17.3 / 18.1, 6 tiles 23.9 / 25.6, 12 tiles 32.2 / 33.0, 16 tiles 8B
-// 16 x 16 40.2 / 39.3, 4B 8 x 8 34.8 / 33.3, 24 tiles 4 x 16 49.3 / 47.4, 64 tiles 8B 16 x 16 110 / 99.5.
+// Tiles up to which workgroups of four wavefronts load past no cache, in launches of more workgroups than compute units.  Launches, plain /
+// streaming loads, us with the merge: 4 tiles 8B verification 1 x 5 behind 6000 20.6 / 22.8, 1.7B 5 x 7 behind 300 to 1900 18.8 / 20.9, 4B draft
+// 4 x 16 behind 1000 17.3 / 18.1, 6 tiles 23.9 / 25.6, 12 tiles 32.2 / 33.0, 16 tiles 8B 16 x 16 40.2 / 39.3, 4B 8 x 8 34.8 / 33.3, 24 tiles 4 x 16
+// 49.3 / 47.4, 64 tiles 8B 16 x 16 110 / 99.5.  Whole forwards, streaming / plain: 376 workgroups (the 8B one) 3909 / 3866, 360 (the 1.7B one)
+// 1976 / 1964, 384 4B 2 x 9 behind 3000 3394 / 3396, 8B 3 x 5 behind 2000 4224 / 4230; but 136 1.7B 3 x 10 behind 700 1883 / 1933, 64 1.7B
+// 2 x 10 behind 320 1629 / 1637.
 static constexpr int FW_SHORT4 = 8;
 
 size_t attention_wide_lds_bytes(int pt_cap, int tiles) { return (size_t)FW_RING * tiles * FW_BUF + (size_t)pt_cap * 4; }
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
     const bf16_t* __restrict__ q, int q_ld, int q_lo, const bf16_t* __restrict__ k_win, const bf16_t* __restrict__ vT_win,
     const bf16_t* __restrict__ k_pages, const bf16_t* __restrict__ v_pages, KvGeom g, Plan p, int Hq, int Z,
     int wpad, float scale_log2e, bf16_t* __restrict__ o, int o_ld, int o_lo, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles /* there is LDS for */) {
+    float* __restrict__ part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles /* there is LDS for */, int cus) {
   constexpr int D = FA_D, T = NW * 64;
   constexpr bool SPLIT = QM == OPM_BF16X2, F16 = QM == OPM_F16;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -103,7 +106,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   // other (the hardware deals workgroups out in turn, whether they leave at once or not): 125 -> 167 us.
   const int qgrp = blockIdx.y;
   const int4 so = p.split_of[2 * blockIdx.z], sq = p.split_of[2 * blockIdx.z + 1];   // (one round trip for all of a split's description)
-  if ((int)blockIdx.z >= p.counts[2]) return;
+  const int n_splits = p.counts[2];
+  if ((int)blockIdx.z >= n_splits) return;
   const int n = so.x, z = so.y, t0 = so.z, t1 = so.w, Zn = sq.x, S = sq.y, row0 = sq.z, nw = sq.w;
   const int Hkv = g.n_kv_heads, ps = g.page_size;
   const int kvh = blockIdx.x, item = n * Hkv + kvh;
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_flash_wide_kernel(
   };
   if (n_it > 0) {
     if constexpr (NW == 4) {
-      if (n_it > FW_SHORT4) walk4(std::true_type{});
+      if (n_it > FW_SHORT4 || n_splits * (int)gridDim.x <= cus) walk4(std::true_type{});
       else walk4(std::false_type{});
     }
     else if (two) walk(std::integral_constant<int, 2>{}, std::integral_constant<int, NW>{});
@@ -573,10 +577,10 @@ template <int NW>
 static void launch_wide(hipStream_t st, int qm, dim3 grid, size_t lds, const bf16_t* q, int q_ld, int q_lo,
                         const bf16_t* k_win, const bf16_t* vT_win, const bf16_t* kp, const bf16_t* vp, const KvGeom& g,
                         const Plan& p, int Hq, int Z, int wpad, float scale_log2e, bf16_t* o, int o_ld, int o_lo,
-                        float* part_o, float* part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles) {
+                        float* part_o, float* part_ml, int q_tiles, int per, int pt_cap, int ps_shift, int tiles, int cus) {
 #define S2D2_WIDE_QM(QMV)                                                                                                    \
   S2D2_LAUNCH((attn_flash_wide_kernel<NW, QMV>), grid, dim3(NW * 64), lds, st, q, q_ld, q_lo, k_win, vT_win, kp, vp, g, p, \
-              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles)
+              Hq, Z, wpad, scale_log2e, o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles, cus)
   if (qm == OPM_F16) S2D2_WIDE_QM(OPM_F16);
   else if (qm == OPM_BF16X2) S2D2_WIDE_QM(OPM_BF16X2);
   else S2D2_WIDE_QM(OPM_BF16);
@@ -614,7 +618,7 @@ int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
 
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int target, int tiles, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           int Hq, int q_tiles, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)g.head_dim);
   const int qgroups = (q_tiles + 7) / 8, per = (q_tiles + qgroups - 1) / qgroups;   // tiles per workgroup, balanced
@@ -629,7 +633,7 @@ void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, co
 #define S2D2_WIDE(NWV)                                                                                                  \
   launch_wide<NWV>(st, operand_mode(q_lo), grid, lds, (const bf16_t*)q, q_ld, q_lo, (const bf16_t*)k_win, (const bf16_t*)vT_win, \
                    (const bf16_t*)k_pages_layer, (const bf16_t*)v_pages_layer, g, p, Hq, Z, wpad, scale_log2e,          \
-                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles)
+                   (bf16_t*)o, o_ld, o_lo, part_o, part_ml, q_tiles, per, pt_cap, ps_shift, tiles, cus)
   if (nw == 4) S2D2_WIDE(4);
   else S2D2_WIDE(8);
 #undef S2D2_WIDE

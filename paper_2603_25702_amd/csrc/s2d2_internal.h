@@ -348,7 +348,7 @@ int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target);
 size_t attention_wide_lds_bytes(int pt_cap, int tiles /* walked at a time: 1, or up to 2 by eight wavefronts */);
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int target, int tiles, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           int Hq, int q_tiles, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries);
 // with Z > 1, behind it: the sums of the sequences that were split
 void launch_attention_wide_merge(hipStream_t st, const KvGeom& g, const Plan& p, int N, int Hq, int q_tiles, int Z, void* o, int o_ld,

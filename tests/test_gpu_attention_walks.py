@@ -1,6 +1,7 @@
 """GPU: the walks of the wide attention kernel over pages of 8, 32 and 64 tokens (four pages to a tile, one, and half a one; other tests
 have pages of 16).  Eight wavefronts: four that fetch for four in short splits, two key groups in splits of more than 24 tiles of 32 keys,
-one group where more than half of the wavefronts have query rows.  Four wavefronts: plain loads up to 8 tiles, streaming loads behind."""
+one group where more than half of the wavefronts have query rows.  Four wavefronts: plain loads in splits of up to 8 tiles of launches of
+more than 256 workgroups, else streaming loads."""
 import pytest
 import torch
 
@@ -23,7 +24,8 @@ CFG = I.ModelCfg("walks", 2, 512, 32, 16, 128, 1536, 2048)   # 16 KV heads: 16 s
     (32, [6490, 6420]),    # 203 and 201 tiles: splits of 26 and 25, of 25 and 26, the last one with the window's two tiles
     (33, [333, 95]),       # five query tiles of seven
     (33, [3251, 41]),      # 102 tiles in splits of 6 or 7, and one split
-    (16, [130, 333]),      # three query tiles, four wavefronts
+    (16, [130, 333]),      # three query tiles, four wavefronts; four splits of 16 heads: streaming loads
+    (16, [1303, 1010]),    # 41 and 32 tiles in splits of four: 304 workgroups, plain loads
     (16, [6490, 6420]),    # 32 splits of 12 and 13 tiles
 ])
 @pytest.mark.parametrize("page_size,act_planes", [(8, 0), (32, 2), (64, 0)])
