@@ -28,12 +28,12 @@ HEADLINE, OTHERS = 4, (2, 3, 5)
 # step, from the FETCH_SIZE / WRITE_SIZE counter runs summarised under profiles/ (rocprofv3 --pmc on this file with
 # the default operand mode; a plain copy of 1 GiB reads FETCH_SIZE = 524300 KiB and WRITE_SIZE = 1048576 KiB, so
 # bytes = FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024).  Averages over all GEMM launches of two steps.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31339827, 3: 68681421, 4: 174737203, 5: 332358349}
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31341466, 3: 68667904, 4: 176668058, 5: 332862362}
 STEP_TRAFFIC_BYTES = {   # all kernels of a step: (FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024) summed over the step's launches
-    2: 5199544.2 * 2048 + 58835.1 * 1024,
-    3: 13416653.5 * 2048 + 2069251.8 * 1024,
-    4: 42893975.0 * 2048 + 5729362.2 * 1024,
-    5: 36337021.9 * 2048 + 8573698.4 * 1024,
+    2: 5124087.0 * 2048 + 102235.0 * 1024,
+    3: 13411563.4 * 2048 + 2069252.6 * 1024,
+    4: 43162695.2 * 2048 + 5729250.4 * 1024,
+    5: 36385626.8 * 2048 + 8573887.3 * 1024,
 }
 # The kernel with most of a configuration's GEMM time (config 3: all but the unembedding, 5.7 of 6.0 ms; config 4: gate / up and the
 # draft's down projection, 10.1 of 17.0 ms)
