@@ -70,6 +70,7 @@ struct s2d2_ctx {
   int32_t* moe_sorted;    // [rows_cap * top_k]
   int32_t *moe_tile_expert, *moe_tile_row0, *moe_tile_rows, *moe_n_tiles;
   int32_t moe_tile_cap;
+  float* moe_row_rs;      // [rows_cap] 1/rms of the rows ahead of the experts
   void* moe_act;          // [rows_cap * top_k, d_expert]
   float* moe_y;           // [rows_cap * top_k, d_model]
   PackedLayer* pk;
@@ -208,9 +209,10 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
     c->moe_w = cv.take<float>(RK);
     c->moe_sorted = cv.take<int32_t>(RK);
     c->moe_tile_cap = (int32_t)(RK / 128 + d.n_experts + 1);
-    c->moe_tile_expert = cv.take<int32_t>(c->moe_tile_cap);
-    c->moe_tile_row0 = cv.take<int32_t>(c->moe_tile_cap);
-    c->moe_tile_rows = cv.take<int32_t>(c->moe_tile_cap);
+    c->moe_tile_expert = cv.take<int32_t>(8 * (size_t)c->moe_tile_cap);   // (a list per XCD)
+    c->moe_tile_row0 = cv.take<int32_t>(8 * (size_t)c->moe_tile_cap);
+    c->moe_tile_rows = cv.take<int32_t>(8 * (size_t)c->moe_tile_cap);
+    c->moe_row_rs = cv.take<float>(R);
     c->moe_n_tiles = cv.take<int32_t>(8);
     c->moe_act = cv.take<uint8_t>(act_rows(RK) * (size_t)d.d_expert * es);
     c->moe_y = cv.take<float>(RK * (size_t)d.d_model);
@@ -477,6 +479,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       } else {
         // MoE FFN: router -> top-k -> group by expert -> grouped gate/up + SwiGLU -> grouped down -> combine
         const int E = d.n_experts, Fe = d.d_expert, tk = d.top_k;
+        const bool experts = gemm_expert_takes(d.d_model, Fe, R, tk, lo_row(d.d_model));
         int32_t* choice = c->moe_choice + (size_t)l * c->rows_cap * tk;
         GemmStreamArgs r{};
         r.m_count = n_rows;
@@ -484,10 +487,10 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         r.X = (const bf16_t*)c->a; r.ldx = ld_a; r.x_lo = lo_row(d.d_model); r.ss_part = c->ss; r.ss_stride = ss_stride; r.ss_count = ss_count;
         r.eps = d.rms_eps; r.out = c->router_logits; r.ldo = E;
         { ProfScope ps(c, 0, (double)E * d.d_model * es, fr * E * d.d_model); sk(r); launch_gemm_stream(st, SEPI_STORE_F32, r, R, gemm_choice(SEPI_STORE_F32, r, R)); }
-        { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w); }
-        { ProfScope ps(c, 3, 0.0); launch_moe_group(st, E, tk, n_rows, choice, c->moe_sorted, c->moe_tile_expert,
-                                                     c->moe_tile_row0, c->moe_tile_rows, c->moe_n_tiles, c->moe_tile_cap); }
+        { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w, c->ss, ss_stride, ss_count, d.d_model, d.rms_eps, experts ? c->moe_row_rs : nullptr); }
         const int tile_cap = std::min(c->moe_tile_cap, R * tk / 128 + E + 1);
+        { ProfScope ps(c, 3, 0.0); launch_moe_group(st, E, tk, n_rows, choice, c->moe_sorted, c->moe_tile_expert,
+                                                     c->moe_tile_row0, c->moe_tile_rows, c->moe_n_tiles, tile_cap, experts); }
         GemmStreamArgs b{};
         b.grouped = GROUP_GATHER; b.top_k = tk; b.n_tiles = c->moe_n_tiles; b.tile_expert = c->moe_tile_expert;
         b.tile_row0 = c->moe_tile_row0; b.tile_rows = c->moe_tile_rows; b.sorted = c->moe_sorted; b.route_w = c->moe_w;
@@ -495,14 +498,16 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         b.Wp = c->pk[l].eg; b.Wp2 = c->pk[l].eu; b.NT = Fe / 16; b.KT = d.d_model / 32; b.N = Fe; b.K = d.d_model;
         b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_row(d.d_model); b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
         b.eps = d.rms_eps; b.out = c->moe_act; b.ldo = ld_e; b.out_lo = lo_row(d.d_expert);
-        { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); launch_gemm_tile(st, SEPI_SWIGLU, SPRO_BF16S, b, tile_cap); }
+        { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); b.tile_list = tile_cap; b.row_rs = c->moe_row_rs; b.coop_wgs = c->n_cus;
+          if (experts) launch_gemm_expert(st, SEPI_SWIGLU, b, R); else launch_gemm_tile(st, SEPI_SWIGLU, SPRO_BF16S, b, tile_cap); }
         GemmStreamArgs e{};
         e.grouped = GROUP_SCATTER; e.top_k = tk; e.n_tiles = c->moe_n_tiles; e.tile_expert = c->moe_tile_expert;
         e.tile_row0 = c->moe_tile_row0; e.tile_rows = c->moe_tile_rows; e.sorted = c->moe_sorted; e.route_w = c->moe_w;
         e.expert_stride = packed_weight_bytes(d.d_model, Fe) / 16;
         e.Wp = c->pk[l].ed; e.NT = d.d_model / 16; e.KT = Fe / 32; e.N = d.d_model; e.K = Fe;
         e.X = (const bf16_t*)c->moe_act; e.ldx = ld_e; e.x_lo = lo_row(d.d_expert); e.out = c->moe_y; e.ldo = d.d_model;
-        { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); launch_gemm_tile(st, SEPI_STORE_F32, SPRO_BF16, e, tile_cap); }
+        { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); e.tile_list = tile_cap; e.coop_wgs = c->n_cus;
+          if (experts) launch_gemm_expert(st, SEPI_STORE_F32, e, R * tk); else launch_gemm_tile(st, SEPI_STORE_F32, SPRO_BF16, e, tile_cap); }
         { ProfScope ps(c, 3, 0.0); launch_moe_combine(st, c->moe_y, d.d_model, tk, n_rows, R, c->h, c->a, ld_a, lo_a, gain_after, c->ss, ss_stride); ss_count = 1; }
       }
     } else {

@@ -1,0 +1,305 @@
+// Expert GEMMs of the MoE FFN on the packed weights, both operands through LDS:
+//   Y[m, n] = sum_k X[m, k] W[n, k]   for the rows of one expert, half operands, X in rows.
+//
+// A workgroup of eight wavefronts takes up to 256 rows of an expert x 256 features (128 of gate and up each) and all of K: most experts
+// are one row tile, so their weights are requested once.  Both operands go from memory into LDS without a register on the way (a wavefront's
+// request is 1 KB; rows are gathered by the lanes' addresses), and every wavefront multiplies half of the row blocks with a quarter of the
+// features.  The reads of the next 32 columns and the requests to come are issued one by one between the matrix instructions (left to the
+// compiler all reads of a step come first: 92 us for 73 of a dense product of 256 rows, K 4096).
+//
+// What bounds it: a compute unit's requests are answered in order, about 400 lines a microsecond while the weights come from memory, whatever is in
+// flight; and all weights together at 6 to 7 TB/s.  (Bringing lines into L2 ahead of time takes the same places in that order: slower.)
+// The tiled kernel asks for 1.5 times the lines, and for the weights of an expert with 130 rows twice.  64 experts of 2048 x 1024, us per launch, tiled
+// kernel / this one: gate / up, 18 rows an expert on average 103 / 81 (6.6 TB/s), 64 rows 110 / 89, 128 rows 131 / 110, the most chosen with
+// 700 144 / 135; down 72 / 47, 89 / 56, 108 / 68, 108 / 80.
+//
+// One workgroup per compute unit takes tile after tile: XCD x those of the experts that moe_group_kernel gave it, the largest first and in
+// alternating order, so that a workgroup's tiles add up to about the same rows.  The first requests of a workgroup's next tile are made ahead of
+// the stores of the present one (in launches of a workgroup per tile 129 and 76 us for 122 and 70 at 128 rows).
+#include "gemm_epilogue.h"
+#include "../../include/s2d2.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace s2d2 {
+
+static constexpr int LDS_NW = 8, LDS_THREADS = LDS_NW * 64;
+static constexpr int LDS_WR = 2, LDS_WC = LDS_NW / LDS_WR, LDS_TW = 4, LDS_TA = LDS_WC * LDS_TW;   // wavefronts along rows and features; feature tiles of a wavefront and of the workgroup
+static constexpr uint32_t LDS_NOWHERE = 0xfffff000u;   // lane offset out of range of any operand: an instruction, no memory access
+// LDS holds a ring of the rows' 64 columns (XS places) and one of the weights' 32 (WS): by row blocks per wavefront, what fits.
+constexpr int lds_xs(int RBL) { return RBL <= 2 ? 4 : RBL <= 4 ? 3 : 2; }
+constexpr int lds_ws(int RBL) { return RBL <= 6 ? 6 : 5; }
+static constexpr unsigned LDS_BYTES = 144 * 1024;
+// Order of a wavefront's requests, by K step s of 32 columns: WL of the weights of step s + WS, and in odd steps XL of the rows of the steps
+// s + 2 XS - 1 and + 2 XS.  How many of them come behind the ones that step k + 1 needs, when step k looks (by whether k is odd).
+constexpr int lds_behind(int odd, int WS, int XS, int WL, int XL) {
+  const int k = 64 + odd, w = k + 1 - WS, x = odd ? k + 1 - 2 * XS + 1 : -1;   // the steps that requested them
+  int last = 0, at = 0;
+  for (int s = 0; s < k; ++s) {
+    at += WL;
+    if (s == w) last = at;
+    if (s & 1) {
+      at += XL;
+      if (s == x) last = at > last ? at : last;
+    }
+  }
+  return at - last;
+}
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void lds_each(const F& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    lds_each<I + 1, N>(f);
+  }
+}
+// A value that is the same in all lanes, in a scalar register for certain (a request's operands have to be).
+__device__ __forceinline__ uint32_t lds_uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+// 64 lanes x 16 bytes from memory to LDS at `at` + 16 lane
+template <bool STREAM>
+__device__ __forceinline__ void lds_request(const __amdgpu_buffer_rsrc_t& rs, uint32_t voff, uint32_t soff, uint32_t at) {
+  if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
+  else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");   // (the compiler keeps nothing in m0 here)
+}
+// at most N of this wavefront's requests outstanding, its LDS reads done; then the workgroup's barrier
+template <int N>
+__device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
+
+struct LdsItem { int m0, rows, expert, grp; };
+// A tile's operands: buffers, and the places of this wavefront's units (1 KB each) of a stage
+struct LdsPlaces {
+  uint64_t w;       // weights of the expert (gate and up: a wavefront requests units of one of the two)
+  uint32_t wo[2];   // weights: scalar offset of the unit
+  uint32_t xv[4];   // rows: a lane's offset
+};
+
+struct LdsBuffers {
+  __amdgpu_buffer_rsrc_t w, x;
+  uint32_t wo[2];
+  __device__ __forceinline__ LdsBuffers(const GemmStreamArgs& a, const LdsPlaces& p, uint32_t xbytes) {
+    w = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)lds_uniform((uint32_t)(p.w >> 32)) << 32 | lds_uniform((uint32_t)p.w)), 0, (uint32_t)a.NT * (uint32_t)a.KT * 1024u, 0x00020000);
+    x = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, xbytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) wo[i] = lds_uniform(p.wo[i]);
+  }
+};
+
+template <int EPI>
+struct LdsTile {
+  static constexpr int NACC = EPI == SEPI_SWIGLU ? 2 : 1, TPW = LDS_TA / NACC, TWP = LDS_TW / NACC;
+  static constexpr int WL = LDS_TA / LDS_NW;                             // units of a wavefront: weights (32 columns)
+  static constexpr int xl(int RBL) { return 2 * LDS_WR * RBL / LDS_NW; }   // rows (8 of them, 64 columns)
+  static constexpr uint32_t xplace(int RBL) { return 2 * LDS_WR * RBL * 1024u; }
+  static constexpr uint32_t WPLACE = LDS_TA * 1024u;
+  static constexpr uint32_t wring(int RBL) { return lds_xs(RBL) * xplace(RBL); }
+
+  static __device__ __forceinline__ void request_w(const LdsBuffers& b, uint32_t lds0, int wave, uint32_t lane16, int i, int k, uint32_t place, bool there) {
+    lds_request<true>(b.w, there ? lane16 : LDS_NOWHERE, b.wo[i] + (uint32_t)k * 1024u, lds0 + place + (wave + LDS_NW * i) * 1024u);
+  }
+  // Eight rows' 128 bytes each, whole lines (16 rows x 64 bytes are twice as many line requests: gate / up at 64 rows an expert 95 us for 88).
+  // A row's 16-byte pieces are stored in the order piece ^ (row % 8), which lets the operand reads (16 rows, one piece each) hit all banks.
+  static __device__ __forceinline__ void request_x(const LdsBuffers& b, const uint32_t (&xv)[4], uint32_t lds0, int wave, int i, int k2, uint32_t place, bool there) {
+    lds_request<false>(b.x, there ? xv[i] : LDS_NOWHERE, (uint32_t)k2 * 128u, lds0 + place + (wave + LDS_NW * i) * 1024u);
+  }
+  template <int RBL>
+  static __device__ __forceinline__ void request_first(const GemmStreamArgs& a, LdsPlaces& p, const LdsBuffers& b, const LdsItem& it, const int* s_src, uint32_t lds0, int wave, int lane, int n) {
+    constexpr int XL = xl(RBL), XS = lds_xs(RBL), WS = lds_ws(RBL);
+    static_assert(XL >= 1 && XL <= 4 && XL * LDS_NW == 2 * LDS_WR * RBL && WL == 2 && wring(RBL) + WS * WPLACE <= LDS_BYTES, "whole units per wavefront");
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int t = wave + LDS_NW * i, r = (t >> 1) * 16 + (t & 1) * 8 + (lane >> 3);
+      p.xv[i] = (t >> 1) * 16 < it.rows ? (uint32_t)s_src[r] * (uint32_t)a.ldx * 2u + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u : LDS_NOWHERE;
+    }
+#pragma unroll
+    for (int s = -(WS > 2 * XS ? WS : 2 * XS); s < 0; ++s) {
+      const int kw = s + WS, kx = s + 2 * XS - 1;   // (rows: of the steps kx and kx + 1)
+      if (kw >= 0)
+#pragma unroll
+        for (int i = 0; i < WL; ++i) request_w(b, lds0, wave, lane * 16u, i, min(kw, n - 1), wring(RBL) + kw * WPLACE, kw < n);
+      if ((s & 1) && kx >= 0)
+#pragma unroll
+        for (int i = 0; i < XL; ++i) request_x(b, p.xv, lds0, wave, i, min(kx, n - 2) >> 1, (kx >> 1) * xplace(RBL), kx < n);
+    }
+  }
+  static __device__ __forceinline__ void first(const GemmStreamArgs& a, LdsPlaces& p, uint32_t xbytes, const LdsItem& it, const int* s_src, uint32_t lds0, int wave, int lane) {
+    const int KT = a.KT;
+    static_assert(LDS_NW % 2 == 0, "a wavefront's units are all of gate or all of up");
+    p.w = (uint64_t)((NACC == 2 && (wave & 1) ? a.Wp2 : a.Wp) + (size_t)it.expert * a.expert_stride);
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int t = wave + LDS_NW * i;
+      p.wo[i] = (uint32_t)min(it.grp * TPW + t / NACC, a.NT - 1) * (uint32_t)KT * 1024u;
+    }
+    const LdsBuffers b(a, p, xbytes);
+    if (it.rows <= 64) request_first<2>(a, p, b, it, s_src, lds0, wave, lane, KT);
+    else if (it.rows <= 128) request_first<4>(a, p, b, it, s_src, lds0, wave, lane, KT);
+    else if (it.rows <= 192) request_first<6>(a, p, b, it, s_src, lds0, wave, lane, KT);
+    else request_first<8>(a, p, b, it, s_src, lds0, wave, lane, KT);
+  }
+
+  // All of K of one tile whose first stages are requested; `between` runs when the tile's operands are no longer needed, ahead of the stores.
+  template <int RBL, typename F>
+  static __device__ __forceinline__ void multiply(const GemmStreamArgs& a, const LdsPlaces& p, uint32_t xbytes, const LdsItem& it, uint8_t* smem, uint32_t lds0, const float* s_rs, const int* s_orow,
+                                                  int wave, int lane, const F& between) {
+    constexpr int XL = xl(RBL), XS = lds_xs(RBL), WS = lds_ws(RBL), NR = LDS_TW + RBL, NM = RBL * LDS_TW;
+    constexpr uint32_t XP = xplace(RBL), WR0 = wring(RBL), WR1 = WR0 + WS * WPLACE;
+    const int wr = wave % LDS_WR, wc = wave / LDS_WR, g = lane >> 4, f = lane & 15, n = a.KT;
+    const uint32_t lane16 = lane * 16;
+    const LdsBuffers b(a, p, xbytes);
+    f32x4_t acc[RBL][LDS_TW];
+#pragma unroll
+    for (int rb = 0; rb < RBL; ++rb)
+#pragma unroll
+      for (int t = 0; t < LDS_TW; ++t) acc[rb][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t fx[2][RBL], fw[2][LDS_TW];
+    // (row blocks go to the wavefronts in turn, so that those past the rows are shared out)
+    const uint8_t* xb[2];
+    xb[0] = smem + wr * 2048 + (f >> 3) * 1024 + (f & 7) * 128 + (g ^ (f & 7)) * 16;
+    xb[1] = smem + wr * 2048 + (f >> 3) * 1024 + (f & 7) * 128 + ((4 + g) ^ (f & 7)) * 16;
+    const uint8_t* wb = smem + wc * LDS_TW * 1024 + lane16;
+    auto read = [&](auto st_, auto qt, uint32_t xp, uint32_t wp) __attribute__((always_inline)) {   // operand q (weights first) of an even / odd step
+      constexpr int S = decltype(st_)::value, q = decltype(qt)::value;
+      if constexpr (q < LDS_TW) fw[S][q] = *(const u32x4_t*)(wb + wp + q * 1024);
+      else fx[S][q - LDS_TW] = *(const u32x4_t*)(xb[S] + xp + LDS_WR * (q - LDS_TW) * 2048);
+    };
+    lds_wait_barrier<lds_behind(1, WS, XS, WL, XL)>();   // (stores of the tile before count too: then this waits for more)
+    lds_each<0, NR>([&](auto q) __attribute__((always_inline)) { read(std::integral_constant<int, 0>{}, q, 0, WR0); });
+    uint32_t xp = 0, xn = XS > 1 ? XP : 0, wp = WR0, wn = WR0 + WPLACE;   // places of this step's operands and of the next one's
+    // A step's products, out of registers.  Between them the operands of step k + 1 have landed everywhere and nobody reads those of step k any more
+    // (barrier): the reads of step k + 1, and the requests that take the places of what is done with.
+    auto step = [&](auto st_, int k) __attribute__((always_inline)) {
+      constexpr int S = decltype(st_)::value, PB = NM / 8, NQ = WL + (S ? XL : 0), NO = NQ + NR;
+      const int kw = k + WS, kx = k + 2 * XS - 1;
+      lds_each<0, NM>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_)::value, rb = i / LDS_TW, t = i % LDS_TW;
+        acc[rb][t] = mfma_16x16x32<OPM_F16>(fw[S][t], fx[S][rb], acc[rb][t]);
+        if constexpr (i == PB) {
+          __builtin_amdgcn_sched_barrier(0);
+          lds_wait_barrier<lds_behind(S, WS, XS, WL, XL)>();
+        }
+        if constexpr (i >= PB)
+          lds_each<(i - PB) * NO / (NM - PB), (i - PB + 1) * NO / (NM - PB)>([&](auto j_) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_)::value, d0 = j * NQ / NO, d1 = (j + 1) * NQ / NO;
+            if constexpr (d1 > d0) {
+              if constexpr (d0 < WL) request_w(b, lds0, wave, lane16, d0, min(kw, n - 1), wp, kw < n);
+              else request_x(b, p.xv, lds0, wave, d0 - WL, min(kx, n - 2) >> 1, xp, kx < n);
+            } else read(std::integral_constant<int, 1 - S>{}, std::integral_constant<int, j - d0>{}, S ? xn : xp, wn);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      wp = wn;
+      wn = wn + WPLACE == WR1 ? WR0 : wn + WPLACE;
+      if (S) {
+        xp = xn;
+        xn = xn + XP == WR0 ? 0 : xn + XP;
+      }
+    };
+    for (int k = 0; k < n; k += 2) {   // (an even number)
+      step(std::integral_constant<int, 0>{}, k);
+      step(std::integral_constant<int, 1>{}, k + 1);
+    }
+    lds_wait_barrier<0>();
+    between();
+#pragma unroll
+    for (int rb = 0; rb < RBL; ++rb) {
+      const int blk = wr + LDS_WR * rb, r = blk * 16 + f;
+      if (blk * 16 >= it.rows) continue;   // uniform over the wavefront
+      const float rs = s_rs[r];
+      const int orow = s_orow[r];
+#pragma unroll
+      for (int t = 0; t < TWP; ++t)
+        gemm_epi_unit<EPI, false>(a, r < it.rows, orow, rs, it.grp * TPW + wc * TWP + t, g, acc[rb][t * NACC], acc[rb][t * NACC + NACC - 1], nullptr);
+    }
+  }
+};
+
+// cols: groups of features.  GATHER (gate / up): rows of X by token, the result in the experts' order, scaled by row_rs of the token; SCATTER (down): rows in
+// the experts' order, the result to the (token, slot) row, scaled by its routing weight.
+template <int EPI>
+__global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmStreamArgs a, const uint32_t xbytes, const int cols) {
+  using T = LdsTile<EPI>;
+  extern __shared__ __align__(16) uint8_t smem[];
+  __shared__ float s_rs[2][256];
+  __shared__ int s_orow[2][256], s_src[256];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (opaque: what depends on the lane alone is otherwise computed for all row counts ahead of the choice)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = tid & 255;
+  const int xcd = blockIdx.x & 7, wg = (int)blockIdx.x >> 3, wgs = (int)gridDim.x >> 3;
+  const int items = (int)lds_uniform(a.n_tiles[xcd]) * cols, first_tile = xcd * a.tile_list;
+  auto item = [&](int q, LdsItem& it) __attribute__((always_inline)) {
+    const int j = q * wgs + (q & 1 ? wgs - 1 - wg : wg);
+    if (j >= items) return false;
+    const int t = first_tile + j / cols;
+    it.m0 = (int)lds_uniform(a.tile_row0[t]); it.rows = (int)lds_uniform(a.tile_rows[t]); it.expert = (int)lds_uniform(a.tile_expert[t]); it.grp = j % cols;
+    return true;
+  };
+  auto sorted_of = [&](const LdsItem& it) __attribute__((always_inline)) { return a.sorted[it.m0 + min(row, it.rows - 1)]; };
+  auto put_rows = [&](const LdsItem& it, int sv, int b, float& rs) __attribute__((always_inline)) {   // source and destination rows; the row's factor is requested
+    if (EPI == SEPI_SWIGLU) {
+      const int token = sv / a.top_k;
+      if (tid < 256) { s_src[row] = token; s_orow[b][row] = it.m0 + row; }
+      rs = a.row_rs[token];
+    } else {
+      if (tid < 256) { s_src[row] = it.m0 + min(row, it.rows - 1); s_orow[b][row] = sv; }
+      rs = a.route_w[sv];
+    }
+  };
+  LdsItem it;
+  if (!item(0, it)) return;
+  LdsPlaces p;
+  {
+    float rs;
+    put_rows(it, sorted_of(it), 0, rs);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    T::first(a, p, xbytes, it, s_src, lds0, wave, lane);
+    if (tid < 256) s_rs[0][row] = rs;
+  }
+  for (int q = 0;; ++q) {
+    LdsItem nx;
+    const bool more = item(q + 1, nx);
+    int sv = 0;
+    if (more) sv = sorted_of(nx);
+    const int b = q & 1;
+    float rs = 0.f;
+    auto between = [&]() __attribute__((always_inline)) {   // the next tile's first stages, ahead of this one's stores
+      if (!more) return;
+      put_rows(nx, sv, b ^ 1, rs);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      T::first(a, p, xbytes, nx, s_src, lds0, wave, lane);
+    };
+    if (it.rows <= 64) T::template multiply<2>(a, p, xbytes, it, smem, lds0, s_rs[b], s_orow[b], wave, lane, between);
+    else if (it.rows <= 128) T::template multiply<4>(a, p, xbytes, it, smem, lds0, s_rs[b], s_orow[b], wave, lane, between);
+    else if (it.rows <= 192) T::template multiply<6>(a, p, xbytes, it, smem, lds0, s_rs[b], s_orow[b], wave, lane, between);
+    else T::template multiply<8>(a, p, xbytes, it, smem, lds0, s_rs[b], s_orow[b], wave, lane, between);
+    if (!more) break;
+    if (tid < 256) s_rs[b ^ 1][row] = rs;   // (the K loop's barriers lie between this and its readers)
+    it = nx;
+  }
+}
+
+template <int EPI>
+static void launch_expert(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
+  static bool lds_set[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  if (dev >= 0 && dev < 64 && !lds_set[dev] &&
+      hipFuncSetAttribute((const void*)gemm_expert_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES) == hipSuccess)
+    lds_set[dev] = true;   // on failure the launch below fails too, and the entry point reports that error
+  const int wgs = std::max(1, a.coop_wgs / 8) * 8;
+  S2D2_LAUNCH((gemm_expert_kernel<EPI>), dim3(wgs), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes, (a.NT + LdsTile<EPI>::TPW - 1) / LdsTile<EPI>::TPW);
+}
+
+// Half operands in rows, whole stages of 64 columns, 32-bit offsets.
+bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo) {
+  const long long most = std::max((long long)rows * d_model, (long long)rows * top_k * d_expert) * 2;
+  return x_lo == LO_F16 && d_model % 64 == 0 && d_expert % 64 == 0 && most < 0xfffff000LL && (long long)((d_expert + 15) / 16) * d_model * 32 < 0xfffff000LL;
+}
+void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows) {
+  const uint32_t xbytes = (uint32_t)x_rows * (uint32_t)a.ldx * 2u;
+  if (kind == SEPI_SWIGLU) launch_expert<SEPI_SWIGLU>(st, a, xbytes);
+  else launch_expert<SEPI_STORE_F32>(st, a, xbytes);
+}
+
+}  // namespace s2d2

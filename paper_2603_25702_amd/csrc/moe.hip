@@ -19,9 +19,14 @@ static constexpr int MOE_MAX_E = 256;   // experts per lane <= 4
 // One wavefront per row.
 __global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict__ logits, int E, int top_k,
                                                         const int32_t* __restrict__ m_count,
-                                                        int32_t* __restrict__ choice, float* __restrict__ route_w) {
+                                                        int32_t* __restrict__ choice, float* __restrict__ route_w,
+                                                        const float* __restrict__ ss, int ss_stride, int ss_count, float d, float eps,
+                                                        float* __restrict__ row_rs) {
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= *m_count) return;
+  float sq = 0.f;   // the row's sum of squares, for the expert GEMM
+  if (row_rs)
+    for (int i = lane; i < ss_count; i += 64) sq += ss[(size_t)row * ss_stride + i];
   float v[4];
   float m = -INFINITY;
 #pragma unroll
@@ -70,9 +75,14 @@ __global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict_
     choice[o] = esel;
     route_w[o] = wsel / wsum;
   }
+  if (row_rs) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+    if (lane == 0) row_rs[row] = 1.0f / sqrtf(sq / d + eps);
+  }
 }
 
-// One workgroup: group offsets, the list of 128-row tiles, the expert-sorted slot list; re-arms the counters.
+// One workgroup: group offsets, the list of row tiles, the expert-sorted slot list; re-arms the counters.
 // A thread keeps its slots' choices in registers between the two passes and requests them eight at a time (read one
 // per loop iteration, 16 K slots cost 32 dependent L2 round trips per thread); the tile list is written by one thread
 // per expert after a scan that touches LDS only.
@@ -80,7 +90,8 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
                                                          const int32_t* __restrict__ choice,
                                                          int32_t* __restrict__ sorted, int32_t* __restrict__ tile_expert,
                                                          int32_t* __restrict__ tile_row0, int32_t* __restrict__ tile_rows,
-                                                         int32_t* __restrict__ n_tiles, int tile_cap) {
+                                                         int32_t* __restrict__ n_tiles, int tile_cap, bool xcd_lists) {
+  __shared__ int s_class[64], s_nt[MOE_MAX_E + 8];
   __shared__ int s_off[MOE_MAX_E], s_tile0[MOE_MAX_E];
   __shared__ int s_cnt[MOE_MAX_E], s_fill[MOE_MAX_E];
   const int tid = threadIdx.x;
@@ -93,6 +104,7 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
     for (int j = j0; j < j0 + 8; ++j) mine[j] = (tid + j * 1024 < total) ? choice[tid + j * 1024] : -1;
   }
   for (int e = tid; e < E; e += 1024) { s_cnt[e] = 0; s_fill[e] = 0; }
+  if (tid < 64) s_class[tid] = 0;
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < KEEP; ++j)
@@ -122,16 +134,58 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
         run += c[j];
         t += (c[j] + 127) >> 7;
       }
-    if (tid == 63) *n_tiles = min(ti, tile_cap);
+    if (tid == 63 && !xcd_lists) *n_tiles = min(ti, tile_cap);
   }
   __syncthreads();
-  for (int e = tid; e < E; e += 1024) {
-    const int c = s_cnt[e], run = s_off[e];
-    int t = s_tile0[e];
-    for (int r0 = 0; r0 < c && t < tile_cap; r0 += 128, ++t) {
-      tile_expert[t] = e;
-      tile_row0[t] = run + r0;
-      tile_rows[t] = min(128, c - r0);
+  if (xcd_lists) {
+    // Experts by falling row count (in classes of 16 rows; in which order within one does not matter) to the XCDs 0 .. 7, 7 .. 0, 0 .. 7: about as
+    // many rows each, an expert's tiles next to each other on one of them.  Tiles of up to 256 rows, an expert's all alike.
+    const int c = tid < E ? s_cnt[tid] : 0, cls = 63 - min(63, c >> 4);
+    int nt = (c + 255) >> 8;
+    const int per = nt > 0 ? ((c + nt - 1) / nt + 15) & ~15 : 16;
+    nt = (c + per - 1) / per;
+    if (tid < E) atomicAdd(&s_class[cls], 1);
+    __syncthreads();
+    if (tid < 64) {   // experts in the classes ahead
+      const int k = s_class[tid];
+      int at = k;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(at, off, 64);
+        if (tid >= off) at += o;
+      }
+      s_class[tid] = at - k;
+    }
+    __syncthreads();
+    const int rank = tid < E ? atomicAdd(&s_class[cls], 1) : 0, turn = rank >> 3;
+    const int xcd = turn & 1 ? 7 - (rank & 7) : rank & 7;
+    if (tid < E) s_nt[rank] = nt;
+    __syncthreads();
+    if (tid < E) {
+      int t = xcd * tile_cap;
+      for (int k = 0; k < turn; ++k) t += s_nt[8 * k + (k & 1 ? 7 - xcd : xcd)];
+      for (int i = 0; i < nt && t < (xcd + 1) * tile_cap; ++i, ++t) {
+        tile_expert[t] = tid;
+        tile_row0[t] = s_off[tid] + i * per;
+        tile_rows[t] = min(per, c - i * per);
+      }
+    }
+    if (tid < 8) {
+      int t = 0;
+      for (int k = 0; 8 * k < E; ++k) {
+        const int r = 8 * k + (k & 1 ? 7 - tid : tid);
+        t += r < E ? s_nt[r] : 0;
+      }
+      n_tiles[tid] = min(t, tile_cap);
+    }
+  } else {
+    for (int e = tid; e < E; e += 1024) {
+      const int c = s_cnt[e], run = s_off[e];
+      int t = s_tile0[e];
+      for (int r0 = 0; r0 < c && t < tile_cap; r0 += 128, ++t) {
+        tile_expert[t] = e;
+        tile_row0[t] = run + r0;
+        tile_rows[t] = min(128, c - r0);
+      }
     }
   }
 #pragma unroll
@@ -186,16 +240,17 @@ __global__ void moe_copy_choices_kernel(const int32_t* __restrict__ src, int32_t
 }
 
 void launch_moe_route(hipStream_t st, const float* logits, int E, int top_k, const int32_t* m_count, int rows_cap,
-                      int32_t* choice, float* route_w) {
+                      int32_t* choice, float* route_w, const float* ss, int ss_stride, int ss_count, int d, float eps,
+                      float* row_rs) {
   S2D2_LAUNCH(moe_route_kernel, dim3((rows_cap + 3) / 4), dim3(256), 0, st, logits, E, top_k, m_count, choice,
-                     route_w);
+                     route_w, ss, ss_stride, ss_count, (float)d, eps, row_rs);
 }
 
 void launch_moe_group(hipStream_t st, int E, int top_k, const int32_t* m_count, const int32_t* choice,
                       int32_t* sorted, int32_t* tile_expert, int32_t* tile_row0, int32_t* tile_rows, int32_t* n_tiles,
-                      int tile_cap) {
+                      int tile_cap, bool xcd_lists) {
   S2D2_LAUNCH(moe_group_kernel, dim3(1), dim3(1024), 0, st, E, top_k, m_count, choice, sorted,
-                     tile_expert, tile_row0, tile_rows, n_tiles, tile_cap);
+                     tile_expert, tile_row0, tile_rows, n_tiles, tile_cap, xcd_lists);
 }
 
 void launch_moe_combine(hipStream_t st, const float* y, int d, int top_k, const int32_t* m_count, int rows_cap,

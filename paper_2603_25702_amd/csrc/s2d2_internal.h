@@ -271,12 +271,14 @@ struct GemmStreamArgs {
   // tile_expert[t]; sorted[s] = token * top_k + slot.  GROUP_GATHER reads X row sorted[s] / top_k and writes
   // row s; GROUP_SCATTER reads X row s and writes row sorted[s], scaled by route_w[sorted[s]].
   int32_t grouped, top_k;
-  const int32_t* n_tiles;
+  const int32_t* n_tiles;   // (gemm_lds.hip: of each of the 8 XCDs, whose tiles start tile_list entries apart)
   const int32_t* tile_expert;
   const int32_t* tile_row0;
   const int32_t* tile_rows;
   const int32_t* sorted;
   const float* route_w;
+  int32_t tile_list;
+  const float* row_rs;      // gemm_lds.hip, GROUP_GATHER: 1/rms of the rows
   size_t expert_stride;     // uint4 elements between the packed matrices of consecutive experts
   // split K of the tile kernel: fp32 partials (64 KB per workgroup) and one arrival counter per tile
   float* tile_partials;
@@ -317,13 +319,17 @@ int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_c
 // gemm_tile.hip : 128 x 256 LDS-tiled kernel on the same packed weights and argument block
 void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a, int row_tiles);
 double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // estimate
+// gemm_lds.hip : expert GEMMs, half operands in rows
+bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo);
+void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows /* X has at most */);
 
 // moe.hip
 void launch_moe_route(hipStream_t st, const float* logits, int E, int top_k, const int32_t* m_count, int rows_cap,
-                      int32_t* choice, float* route_w);
+                      int32_t* choice, float* route_w, const float* ss, int ss_stride, int ss_count, int d, float eps,
+                      float* row_rs /* 1/rms of the rows from their partial sums of squares, may be NULL */);
 void launch_moe_group(hipStream_t st, int E, int top_k, const int32_t* m_count, const int32_t* choice,
                       int32_t* sorted, int32_t* tile_expert, int32_t* tile_row0, int32_t* tile_rows, int32_t* n_tiles,
-                      int tile_cap);
+                      int tile_cap, bool xcd_lists /* tiles for gemm_lds.hip: of up to 256 rows, a list per XCD, tile_cap entries apart */);
 void launch_moe_combine(hipStream_t st, const float* y, int d, int top_k, const int32_t* m_count, int rows_cap,
                         float* h, void* xg, int xg_ld, int xg_lo, const float* gain_next, float* ss, int ss_stride);
 void launch_moe_copy_choices(hipStream_t st, const int32_t* src, int32_t* dst, int layers, int per_layer_src,
