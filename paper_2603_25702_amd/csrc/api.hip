@@ -340,7 +340,7 @@ GemmChoice choice_of(const s2d2_model_desc& d, int which, int lo, const FwdSize&
   const GemmMatrix m = matrix_of(d, which);
   GemmStreamArgs x{};
   x.NT = (m.N + 15) / 16; x.KT = m.K / 32; x.N = m.N; x.K = m.K; x.x_lo = lo;
-  if (which == 8) x.gather = env.tile_counters;   // (any: the unembedding has one)
+  if (which == 8) x.gather = env.tile_counters, x.x_rows = sz.R;   // (any: the unembedding has one)
   env.put(x, which == 8 ? sz.LR : sz.hint);
   return gemm_choice(m.kind, x, which == 8 ? sz.LR : sz.R);
 }
@@ -521,7 +521,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   if (fused) {
     GemmStreamArgs a{};
     a.Wp = c->pk_unembed; a.NT = (d.vocab + 15) / 16; a.KT = d.d_model / 32; a.N = d.vocab; a.K = d.d_model;
-    a.m_count = n_logit; a.X = (const bf16_t*)c->a; a.ldx = ld_a; a.x_lo = lo_a; a.gather = c->plan.logit_src;
+    a.m_count = n_logit; a.X = (const bf16_t*)c->a; a.ldx = ld_a; a.x_lo = lo_a; a.gather = c->plan.logit_src; a.x_rows = R;
     a.ss_part = c->ss; a.ss_stride = ss_stride; a.ss_count = ss_count; a.eps = d.rms_eps;
     a.out = logits; a.ldo = d.vocab;
     ProfScope ps(c, 0, (double)d.vocab * d.d_model * es, fl * d.vocab * d.d_model, 8);
@@ -897,7 +897,8 @@ int32_t s2d2_gemm_choice(const s2d2_model_desc* desc, int32_t forward, int32_t N
   const GemmMatrix m = matrix_of(*desc, matrix);
   const int lo = opm == OPM_F16 ? (fragment_order(*desc, opm, sz, env) ? LO_F16P : LO_F16) : opm == OPM_BF16X2 ? m.K : 0;
   const GemmChoice c = choice_of(*desc, matrix, lo, sz, env);
-  out[0] = c.kernel; out[1] = c.rb; out[2] = c.ta; out[3] = c.KS; out[4] = c.stream;
+  out[0] = c.kernel == GEMM_LDS ? (int32_t)GEMM_TILE : (int32_t)c.kernel;   // (both: through LDS)
+  out[1] = c.rb; out[2] = c.ta; out[3] = c.KS; out[4] = c.stream;
   return S2D2_OK;
 }
 

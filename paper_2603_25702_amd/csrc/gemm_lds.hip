@@ -1,8 +1,8 @@
-// Expert GEMMs of the MoE FFN on the packed weights, both operands through LDS:
-//   Y[m, n] = sum_k X[m, k] W[n, k]   for the rows of one expert, half operands, X in rows.
+// GEMMs on the packed weights with both operands through LDS, half operands:
+//   Y[m, n] = sum_k X[m, k] W[n, k]   for the unembedding of more than 16 rows, and for the rows of one expert of the MoE FFN (X in rows).
 //
-// A workgroup of eight wavefronts takes up to 256 rows of an expert x 256 features (128 of gate and up each) and all of K: most experts
-// are one row tile, so their weights are requested once.  Both operands go from memory into LDS without a register on the way (a wavefront's
+// A workgroup of eight wavefronts takes up to 256 rows x 256 features (128 of gate and up each) and all of K: up to 256 rows, and for most experts,
+// the weights are requested once.  Both operands go from memory into LDS without a register on the way (a wavefront's
 // request is 1 KB; rows are gathered by the lanes' addresses), and every wavefront multiplies half of the row blocks with a quarter of the
 // features.  The reads of the next 32 columns and the requests to come are issued one by one between the matrix instructions (left to the
 // compiler all reads of a step come first: 92 us for 73 of a dense product of 256 rows, K 4096).
@@ -27,9 +27,11 @@ namespace s2d2 {
 static constexpr int LDS_NW = 8, LDS_THREADS = LDS_NW * 64;
 static constexpr int LDS_WR = 2, LDS_WC = LDS_NW / LDS_WR, LDS_TW = 4, LDS_TA = LDS_WC * LDS_TW;   // wavefronts along rows and features; feature tiles of a wavefront and of the workgroup
 static constexpr uint32_t LDS_NOWHERE = 0xfffff000u;   // lane offset out of range of any operand: an instruction, no memory access
-// LDS holds a ring of the rows' 64 columns (XS places) and one of the weights' 32 (WS): by row blocks per wavefront, what fits.
-constexpr int lds_xs(int RBL) { return RBL <= 2 ? 4 : RBL <= 4 ? 3 : 2; }
-constexpr int lds_ws(int RBL) { return RBL <= 6 ? 6 : 5; }
+// LDS holds a ring of the rows' 64 columns (XS places) and one of the weights' 32 (WS): by row blocks per wavefront, what fits.  Requests are answered in
+// order, so either operand's lead has to cover all lines that are asked for ahead of it: rows two steps ahead behind weights that are five
+// ahead take 1.17 us a step where their lines take 0.64 (256 rows).
+constexpr int lds_xs(int RBL) { return RBL <= 4 ? 4 : 3; }
+constexpr int lds_ws(int RBL) { return RBL <= 2 ? 6 : RBL <= 4 ? 5 : RBL <= 6 ? 4 : 3; }
 static constexpr unsigned LDS_BYTES = 144 * 1024;
 // Order of a wavefront's requests, by K step s of 32 columns: WL of the weights of step s + WS, and in odd steps XL of the rows of the steps
 // s + 2 XS - 1 and + 2 XS.  How many of them come behind the ones that step k + 1 needs, when step k looks (by whether k is odd).
@@ -66,26 +68,31 @@ __device__ __forceinline__ void lds_request(const __amdgpu_buffer_rsrc_t& rs, ui
 template <int N>
 __device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
 
-struct LdsItem { int m0, rows, expert, grp; };
+struct LdsItem { int m0, rows, expert, nt0, tiles; };   // nt0: first feature tile (of either matrix), tiles: how many
 // A tile's operands: buffers, and the places of this wavefront's units (1 KB each) of a stage
 struct LdsPlaces {
-  uint64_t w;       // weights of the expert (gate and up: a wavefront requests units of one of the two)
-  uint32_t wo[2];   // weights: scalar offset of the unit
+  uint64_t w;       // weights of the tile's features (gate and up: a wavefront requests units of one of the two)
+  uint32_t wbytes;
+  uint32_t wo[2], wv[2];   // weights: scalar offset of the unit; LDS_NOWHERE if it does not exist
   uint32_t xv[4];   // rows: a lane's offset
 };
 
 struct LdsBuffers {
   __amdgpu_buffer_rsrc_t w, x;
-  uint32_t wo[2];
+  uint32_t wo[2], wv[2];
   __device__ __forceinline__ LdsBuffers(const GemmStreamArgs& a, const LdsPlaces& p, uint32_t xbytes) {
-    w = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)lds_uniform((uint32_t)(p.w >> 32)) << 32 | lds_uniform((uint32_t)p.w)), 0, (uint32_t)a.NT * (uint32_t)a.KT * 1024u, 0x00020000);
+    w = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)lds_uniform((uint32_t)(p.w >> 32)) << 32 | lds_uniform((uint32_t)p.w)), 0, lds_uniform(p.wbytes), 0x00020000);
     x = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, xbytes, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) wo[i] = lds_uniform(p.wo[i]);
+    for (int i = 0; i < 2; ++i) {
+      wo[i] = lds_uniform(p.wo[i]);
+      wv[i] = lds_uniform(p.wv[i]);
+    }
   }
 };
 
-template <int EPI>
+// ROWS: X in rows, else in fragment order.  STREAM: weights past the caches.
+template <int EPI, bool ROWS, bool STREAM>
 struct LdsTile {
   static constexpr int NACC = EPI == SEPI_SWIGLU ? 2 : 1, TPW = LDS_TA / NACC, TWP = LDS_TW / NACC;
   static constexpr int WL = LDS_TA / LDS_NW;                             // units of a wavefront: weights (32 columns)
@@ -95,12 +102,13 @@ struct LdsTile {
   static constexpr uint32_t wring(int RBL) { return lds_xs(RBL) * xplace(RBL); }
 
   static __device__ __forceinline__ void request_w(const LdsBuffers& b, uint32_t lds0, int wave, uint32_t lane16, int i, int k, uint32_t place, bool there) {
-    lds_request<true>(b.w, there ? lane16 : LDS_NOWHERE, b.wo[i] + (uint32_t)k * 1024u, lds0 + place + (wave + LDS_NW * i) * 1024u);
+    lds_request<STREAM>(b.w, there ? lane16 | b.wv[i] : LDS_NOWHERE, b.wo[i] + (uint32_t)k * 1024u, lds0 + place + (wave + LDS_NW * i) * 1024u);
   }
-  // Eight rows' 128 bytes each, whole lines (16 rows x 64 bytes are twice as many line requests: gate / up at 64 rows an expert 95 us for 88).
-  // A row's 16-byte pieces are stored in the order piece ^ (row % 8), which lets the operand reads (16 rows, one piece each) hit all banks.
+  // X in rows: eight rows' 128 bytes each, whole lines (16 rows x 64 bytes are twice as many line requests: gate / up at 64 rows an expert 95 us for 88).
+  // A row's 16-byte pieces are stored in the order piece ^ (row % 8), which lets the operand reads (16 rows, one piece each) hit all banks.  In fragment order a unit is 16 rows x 32 columns as
+  // the matrix instruction takes them.
   static __device__ __forceinline__ void request_x(const LdsBuffers& b, const uint32_t (&xv)[4], uint32_t lds0, int wave, int i, int k2, uint32_t place, bool there) {
-    lds_request<false>(b.x, there ? xv[i] : LDS_NOWHERE, (uint32_t)k2 * 128u, lds0 + place + (wave + LDS_NW * i) * 1024u);
+    lds_request<false>(b.x, there ? xv[i] : LDS_NOWHERE, (uint32_t)k2 * (ROWS ? 128u : 2048u), lds0 + place + (wave + LDS_NW * i) * 1024u);
   }
   template <int RBL>
   static __device__ __forceinline__ void request_first(const GemmStreamArgs& a, LdsPlaces& p, const LdsBuffers& b, const LdsItem& it, const int* s_src, uint32_t lds0, int wave, int lane, int n) {
@@ -108,8 +116,10 @@ struct LdsTile {
     static_assert(XL >= 1 && XL <= 4 && XL * LDS_NW == 2 * LDS_WR * RBL && WL == 2 && wring(RBL) + WS * WPLACE <= LDS_BYTES, "whole units per wavefront");
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
-      const int t = wave + LDS_NW * i, r = (t >> 1) * 16 + (t & 1) * 8 + (lane >> 3);
-      p.xv[i] = (t >> 1) * 16 < it.rows ? (uint32_t)s_src[r] * (uint32_t)a.ldx * 2u + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u : LDS_NOWHERE;
+      const int t = wave + LDS_NW * i;
+      if (ROWS) p.xv[i] = (uint32_t)s_src[(t >> 1) * 16 + (t & 1) * 8 + (lane >> 3)] * (uint32_t)a.ldx * 2u + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
+      else p.xv[i] = 2u * (uint32_t)frag_offset(s_src[(t >> 1) * 16 + (lane & 15)], 8 * (lane >> 4), a.K) + (t & 1) * 1024u;
+      if ((t >> 1) * 16 >= it.rows) p.xv[i] = LDS_NOWHERE;
     }
 #pragma unroll
     for (int s = -(WS > 2 * XS ? WS : 2 * XS); s < 0; ++s) {
@@ -125,11 +135,14 @@ struct LdsTile {
   static __device__ __forceinline__ void first(const GemmStreamArgs& a, LdsPlaces& p, uint32_t xbytes, const LdsItem& it, const int* s_src, uint32_t lds0, int wave, int lane) {
     const int KT = a.KT;
     static_assert(LDS_NW % 2 == 0, "a wavefront's units are all of gate or all of up");
-    p.w = (uint64_t)((NACC == 2 && (wave & 1) ? a.Wp2 : a.Wp) + (size_t)it.expert * a.expert_stride);
+    p.w = (uint64_t)((NACC == 2 && (wave & 1) ? a.Wp2 : a.Wp) + (size_t)it.expert * a.expert_stride + (size_t)it.nt0 * KT * 64);
+    p.wbytes = (uint32_t)it.tiles * (uint32_t)KT * 1024u;
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
       const int t = wave + LDS_NW * i;
-      p.wo[i] = (uint32_t)min(it.grp * TPW + t / NACC, a.NT - 1) * (uint32_t)KT * 1024u;
+      const bool ok = t / NACC < it.tiles;
+      p.wo[i] = (uint32_t)(ok ? t / NACC : 0) * (uint32_t)KT * 1024u;
+      p.wv[i] = ok ? 0u : LDS_NOWHERE;
     }
     const LdsBuffers b(a, p, xbytes);
     if (it.rows <= 64) request_first<2>(a, p, b, it, s_src, lds0, wave, lane, KT);
@@ -155,8 +168,8 @@ struct LdsTile {
     u32x4_t fx[2][RBL], fw[2][LDS_TW];
     // (row blocks go to the wavefronts in turn, so that those past the rows are shared out)
     const uint8_t* xb[2];
-    xb[0] = smem + wr * 2048 + (f >> 3) * 1024 + (f & 7) * 128 + (g ^ (f & 7)) * 16;
-    xb[1] = smem + wr * 2048 + (f >> 3) * 1024 + (f & 7) * 128 + ((4 + g) ^ (f & 7)) * 16;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) xb[u] = smem + wr * 2048 + (ROWS ? (f >> 3) * 1024 + (f & 7) * 128 + ((4 * u + g) ^ (f & 7)) * 16 : u * 1024 + (int)lane16);
     const uint8_t* wb = smem + wc * LDS_TW * 1024 + lane16;
     auto read = [&](auto st_, auto qt, uint32_t xp, uint32_t wp) __attribute__((always_inline)) {   // operand q (weights first) of an even / odd step
       constexpr int S = decltype(st_)::value, q = decltype(qt)::value;
@@ -209,7 +222,7 @@ struct LdsTile {
       const int orow = s_orow[r];
 #pragma unroll
       for (int t = 0; t < TWP; ++t)
-        gemm_epi_unit<EPI, false>(a, r < it.rows, orow, rs, it.grp * TPW + wc * TWP + t, g, acc[rb][t * NACC], acc[rb][t * NACC + NACC - 1], nullptr);
+        if (wc * TWP + t < it.tiles) gemm_epi_unit<EPI, !ROWS>(a, r < it.rows, orow, rs, it.nt0 + wc * TWP + t, g, acc[rb][t * NACC], acc[rb][t * NACC + NACC - 1], nullptr);
     }
   }
 };
@@ -218,7 +231,7 @@ struct LdsTile {
 // the experts' order, the result to the (token, slot) row, scaled by its routing weight.
 template <int EPI>
 __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmStreamArgs a, const uint32_t xbytes, const int cols) {
-  using T = LdsTile<EPI>;
+  using T = LdsTile<EPI, true, true>;
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ float s_rs[2][256];
   __shared__ int s_orow[2][256], s_src[256];
@@ -232,7 +245,7 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmS
     const int j = q * wgs + (q & 1 ? wgs - 1 - wg : wg);
     if (j >= items) return false;
     const int t = first_tile + j / cols;
-    it.m0 = (int)lds_uniform(a.tile_row0[t]); it.rows = (int)lds_uniform(a.tile_rows[t]); it.expert = (int)lds_uniform(a.tile_expert[t]); it.grp = j % cols;
+    it.m0 = (int)lds_uniform(a.tile_row0[t]); it.rows = (int)lds_uniform(a.tile_rows[t]); it.expert = (int)lds_uniform(a.tile_expert[t]); it.nt0 = j % cols * T::TPW; it.tiles = min(T::TPW, a.NT - it.nt0);
     return true;
   };
   auto sorted_of = [&](const LdsItem& it) __attribute__((always_inline)) { return a.sorted[it.m0 + min(row, it.rows - 1)]; };
@@ -279,6 +292,102 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmS
   }
 }
 
+// The unembedding.  The row count is on the device.  XCD x has ranges of feature tiles x, x + 8, ..; the row tiles (of up to 256 rows, about alike) of a
+// range sit next to each other on one XCD, so that its weights come in from memory once.  A workgroup's rows stay the same, its range is cut into groups of
+// TPW tiles.  us per launch, gemm_mid.hip (up to 64 rows) or the tiled kernel / this one: 1.7B 17 rows 119 / 106, 35 130 / 114, 96 183 / 130, 512
+// 501 / 380; 4B 64 191 / 150 (5.4 TB/s with what is stored), 128 209 / 171, 256 285 / 265; 8B 32 247 / 219, 256 444 / 424, 512 817 / 708.  Up to 16 rows
+// the streaming kernel is the faster one (1.7B, 12 rows, 95 / 103).  From 256 rows on the matrix pipes at the board's power limit bound it: without its
+// requests, 256 rows of 8B take 309 us, without its products 297, without its stores 347.
+template <int EPI, bool ROWS, bool STREAM>
+__global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_kernel(const GemmStreamArgs a, const uint32_t xbytes) {
+  using T = LdsTile<EPI, ROWS, STREAM>;
+  extern __shared__ __align__(16) uint8_t smem[];
+  __shared__ float s_rs[256];
+  __shared__ int s_orow[256], s_src[256];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = (int)lds_uniform(*a.m_count), blocks = (M + 15) >> 4;
+  if (M <= 0) return;
+  const int xcd = blockIdx.x & 7, wg = (int)blockIdx.x >> 3, wgs = (int)gridDim.x >> 3;
+  const int row_tiles = (blocks + 15) >> 4, per = (blocks + row_tiles - 1) / row_tiles, side = min(row_tiles, wgs), ranges = wgs / side;
+  if (wg >= ranges * side) return;
+  const int range = (wg / side) * 8 + xcd, nt_lo = (int)((long long)range * a.NT / (8 * ranges)), nt_hi = (int)((long long)(range + 1) * a.NT / (8 * ranges));
+  if (nt_lo >= nt_hi) return;
+  for (int rt = wg % side; rt * per < blocks; rt += side) {
+    LdsItem it;
+    it.m0 = rt * per * 16; it.rows = min(per * 16, M - it.m0); it.expert = 0; it.nt0 = nt_lo; it.tiles = min(T::TPW, nt_hi - nt_lo);
+    // ---- the rows: sources and 1/rms from the producer's partial sums of squares ----
+    {
+      const int r = tid >> 1, sub = tid & 1, s = it.m0 + min(r, it.rows - 1), src = a.gather ? a.gather[s] : s;
+      if (sub == 0) { s_src[r] = src; s_orow[r] = s; }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      LdsPlaces p;
+      T::first(a, p, xbytes, it, s_src, lds0, wave, lane);
+      const float* pp = a.ss_part + (size_t)src * a.ss_stride;
+      float v = 0.f;
+      if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
+        const int n4 = a.ss_count >> 2;
+        for (int i0 = sub; i0 < n4; i0 += 16) {
+          float4 t[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) t[j] = ((const float4*)pp)[min(i0 + 2 * j, n4 - 1)];   // clamped duplicates are skipped when summing
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (i0 + 2 * j < n4) v += (t[j].x + t[j].y) + (t[j].z + t[j].w);
+        }
+      } else {
+        for (int i = sub; i < a.ss_count; i += 2) v += pp[i];
+      }
+      v += __shfl_xor(v, 1, 64);
+      if (sub == 0) s_rs[r] = 1.0f / sqrtf(v / (float)a.K + a.eps);   // (read behind the K loop's barriers)
+      for (;;) {
+        LdsItem nx = it;
+        nx.nt0 += T::TPW;
+        nx.tiles = min(T::TPW, nt_hi - nx.nt0);
+        const bool more = nx.tiles > 0;
+        LdsPlaces np = p;
+        auto between = [&]() __attribute__((always_inline)) {
+          if (more) T::first(a, np, xbytes, nx, s_src, lds0, wave, lane);
+        };
+        if (it.rows <= 64) T::template multiply<2>(a, p, xbytes, it, smem, lds0, s_rs, s_orow, wave, lane, between);
+        else if (it.rows <= 128) T::template multiply<4>(a, p, xbytes, it, smem, lds0, s_rs, s_orow, wave, lane, between);
+        else if (it.rows <= 192) T::template multiply<6>(a, p, xbytes, it, smem, lds0, s_rs, s_orow, wave, lane, between);
+        else T::template multiply<8>(a, p, xbytes, it, smem, lds0, s_rs, s_orow, wave, lane, between);
+        if (!more) break;
+        it = nx;
+        p = np;
+      }
+    }
+    __syncthreads();   // the next rows take the same LDS
+  }
+}
+
+template <int EPI, bool ROWS, bool STREAM>
+static void launch_lds(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
+  static bool lds_set[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  if (dev >= 0 && dev < 64 && !lds_set[dev] &&
+      hipFuncSetAttribute((const void*)gemm_lds_kernel<EPI, ROWS, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES) == hipSuccess)
+    lds_set[dev] = true;
+  S2D2_LAUNCH((gemm_lds_kernel<EPI, ROWS, STREAM>), dim3(std::max(1, a.coop_wgs / 8) * 8), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes);
+}
+// Half operands, whole steps of 64 columns, 32-bit offsets into the rows.
+bool gemm_lds_takes(int kind, const GemmStreamArgs& a) {
+  if ((a.x_lo != LO_F16 && a.x_lo != LO_F16P) || a.coop_wgs < 1 || a.KT % 2 || a.grouped != GROUP_NONE || (long long)((a.x_rows + 15) / 16) * a.KT * 1024 >= 0xfffff000LL) return false;
+  return kind == SEPI_STORE_F32 && a.gather && a.m_hint > 16;
+}
+void launch_gemm_lds(hipStream_t st, int kind, const GemmStreamArgs& a) {
+  const uint32_t xbytes = (uint32_t)((a.x_rows + 15) / 16) * (uint32_t)a.KT * 1024u;   // (in rows: at least as many)
+  const bool stream = a.m_hint <= 256;   // one row tile: every weight is requested once
+  auto go = [&](auto rows_, auto stream_) { launch_lds<SEPI_STORE_F32, decltype(rows_)::value, decltype(stream_)::value>(st, a, xbytes); };
+  auto rows = [&](auto rows_) { if (stream) go(rows_, std::true_type{}); else go(rows_, std::false_type{}); };
+  if (a.x_lo == LO_F16) rows(std::true_type{});
+  else rows(std::false_type{});
+}
+
 template <int EPI>
 static void launch_expert(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
   static bool lds_set[64];
@@ -288,7 +397,7 @@ static void launch_expert(hipStream_t st, const GemmStreamArgs& a, uint32_t xbyt
       hipFuncSetAttribute((const void*)gemm_expert_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES) == hipSuccess)
     lds_set[dev] = true;   // on failure the launch below fails too, and the entry point reports that error
   const int wgs = std::max(1, a.coop_wgs / 8) * 8;
-  S2D2_LAUNCH((gemm_expert_kernel<EPI>), dim3(wgs), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes, (a.NT + LdsTile<EPI>::TPW - 1) / LdsTile<EPI>::TPW);
+  S2D2_LAUNCH((gemm_expert_kernel<EPI>), dim3(wgs), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes, (a.NT + LdsTile<EPI, true, true>::TPW - 1) / LdsTile<EPI, true, true>::TPW);
 }
 
 // Half operands in rows, whole stages of 64 columns, 32-bit offsets.

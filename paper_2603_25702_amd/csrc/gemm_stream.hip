@@ -398,6 +398,7 @@ static void launch_pair(hipStream_t st, const GemmStreamArgs& a, int m_cap) {
 // empty, and a row tile of 16 per workgroup spreads the rows over the whole chip.
 GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap) {
   GemmChoice c{GEMM_STREAM, 0, 0, 1, false};
+  if (gemm_lds_takes(kind, a)) return {GEMM_LDS, 0, 0, 1, false};
   if (gemm_block_takes(kind, a, m_cap, c)) return c;
   if (gemm_mid_takes(kind, a, m_cap)) return {GEMM_MID, 0, 0, 1, false};
   // The streaming kernel takes half operands in fragment order only, except the ones that a store reads: a forward
@@ -418,6 +419,10 @@ GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap) {
 // streamed at half the rate of the other layer GEMMs).
 int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c) {
   if (c.kernel == GEMM_BLOCK) return launch_gemm_block(st, kind, a, m_cap, c);
+  if (c.kernel == GEMM_LDS) {
+    launch_gemm_lds(st, kind, a);
+    return a.NT;
+  }
   if (c.kernel == GEMM_MID) {
     launch_gemm_mid(st, kind, a, m_cap);
     return a.NT;

@@ -241,6 +241,7 @@ struct GemmStreamArgs {
   int32_t m_hint;           // host: rows the caller expects (0 = unknown); only steers the choice of launch shape
   const bf16_t* X;          // activations [*, ldx] (for SPRO_BF16S: h * gain, not yet divided by the rms)
   int32_t ldx;
+  int32_t x_rows;           // unembedding: rows of X at most
   int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16 / LO_F16P: half values in rows / in fragment order)
   const int32_t* gather;    // optional row indices into X / ss_part
   const float* ss_part;     // SPRO_BF16S: [*, ss_stride] partial sums of squares of the residual rows
@@ -303,13 +304,13 @@ void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, 
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
 // Kernel of a GEMM on packed weights and, of gemm_block.hip, its block (rb x ta units of 16 x 16), workgroups that share K and kind of
 // weight loads.  By the matrix, the operands, the rows expected (m_hint) and at most (m_cap).
-enum GemmKernel { GEMM_STREAM = 0, GEMM_MID = 1, GEMM_BLOCK = 2, GEMM_TILE = 3 };
+enum GemmKernel { GEMM_STREAM = 0, GEMM_MID = 1, GEMM_BLOCK = 2, GEMM_TILE = 3, GEMM_LDS = 4 };
 struct GemmChoice { GemmKernel kernel; int rb, ta, KS; bool stream; };
 GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap);
 // (a residual add returns the number of partial sums of squares it leaves per row)
 int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c);
 constexpr int STREAM_MOST_ROWS = 32;   // of a window that the streaming kernel takes: two row tiles
-// gemm_mid.hip : windows of 17 to 48 rows (unembedding: 64), half operands in fragment order
+// gemm_mid.hip : windows of 17 to 48 rows, half operands in fragment order
 constexpr int MID_MOST_ROWS = 48;
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a, int m_cap);
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);
@@ -319,7 +320,9 @@ int launch_gemm_block(hipStream_t st, int kind, const GemmStreamArgs& a, int m_c
 // gemm_tile.hip : 128 x 256 LDS-tiled kernel on the same packed weights and argument block
 void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a, int row_tiles);
 double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // estimate
-// gemm_lds.hip : expert GEMMs, half operands in rows
+// gemm_lds.hip : both operands through LDS, half operands; products of many rows and the expert GEMMs (operands in rows)
+bool gemm_lds_takes(int kind, const GemmStreamArgs& a);
+void launch_gemm_lds(hipStream_t st, int kind, const GemmStreamArgs& a);
 bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo);
 void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows /* X has at most */);
 

@@ -1,0 +1,27 @@
+"""GPU parity of the unembedding of more than 16 rows: the edges of its row tiles (64, 128, 192, 256 rows, one more and one less, several tiles), fewer
+feature tiles than workgroups, ranges of one group of 16 and of several with a part of one, a vocabulary that is no multiple of 16,
+rows and fragment order, a width whose K is no multiple of 64 (the tiled kernel's)."""
+import pytest
+
+import s2d2_inputs as I
+from paper_2603_25702_amd import Params
+from paper_2603_25702_amd.binding import s2d2_gemm_choice
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,vocab,N,B", [
+    (512, 2048, 1, 17), (512, 70007, 1, 64), (512, 2041, 5, 13), (512, 4096, 8, 16), (512, 2048, 3, 43), (256, 70007, 3, 64), (256, 2048, 1, 64),
+    (512, 2041, 4, 64), (512, 70007, 9, 29), (256, 2048, 11, 47), (288, 2048, 3, 43), (576, 2048, 2, 9),
+])
+def test_rows_of_the_unembedding(d, vocab, N, B):
+    cfg = I.ModelCfg("unembed-rows", 1, d, 8, 4, 128, 512, vocab)
+    for forward in ("draft", "verify"):
+        assert s2d2_gemm_choice(cfg, forward, N, B, "unembed")[0] == "tile"   # (through LDS)
+    case = H.make_case(cfg, N, B, [20 + 13 * (n % 5) for n in range(N)], seed=53, synthetic_kv=True, page_size=16, room=4 * B + 16)
+    run, rep, prm = H.DeviceRun(case), H.Report(), Params(seed=77)
+    run.step(prm, advance=False)
+    H.check_step(case, run, run.fetch(), prm, rep=rep, seqs=sorted({0, N // 2, N - 1}))
+    print("unembedding rows:", d, vocab, N, B, rep)
+    assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
