@@ -340,7 +340,8 @@ GemmChoice choice_of(const s2d2_model_desc& d, int which, int lo, const FwdSize&
   const GemmMatrix m = matrix_of(d, which);
   GemmStreamArgs x{};
   x.NT = (m.N + 15) / 16; x.KT = m.K / 32; x.N = m.N; x.K = m.K; x.x_lo = lo;
-  if (which == 8) x.gather = env.tile_counters, x.x_rows = sz.R;   // (any: the unembedding has one)
+  x.x_rows = sz.R;
+  if (which == 8) x.gather = env.tile_counters;   // (any: the unembedding has one)
   env.put(x, which == 8 ? sz.LR : sz.hint);
   return gemm_choice(m.kind, x, which == 8 ? sz.LR : sz.R);
 }
@@ -468,7 +469,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         b.m_count = n_rows;
         b.Wp = c->pk[l].wg; b.Wp2 = c->pk[l].wu; b.NT = d.d_ffn / 16; b.KT = d.d_model / 32; b.N = d.d_ffn; b.K = d.d_model;
         b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_a; b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
-        b.eps = d.rms_eps; b.out = c->ffn; b.ldo = ld_f; b.out_lo = lo_f;
+        b.eps = d.rms_eps; b.out = c->ffn; b.ldo = ld_f; b.out_lo = lo_f; b.x_rows = R;
         { ProfScope ps(c, 0, 2.0 * d.d_ffn * d.d_model * es, fr * 2.0 * d.d_ffn * d.d_model, 6); sk(b); launch_gemm_stream(st, SEPI_SWIGLU, b, R, pick[6]); }
         GemmStreamArgs e{};
         e.m_count = n_rows;

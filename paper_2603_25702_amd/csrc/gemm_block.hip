@@ -459,7 +459,7 @@ bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap, GemmChoice& 
   if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * BLK_NW || a.m_hint <= MID_MOST_ROWS || a.grouped != GROUP_NONE || kind == SEPI_STORE_F32) return false;
   if ((long long)a.NT * a.KT * 1024 >= 1LL << 32 || (long long)(m_cap + 15) / 16 * a.KT * 1024 >= 1LL << 32) return false;   // (32-bit offsets)
   const BlkPick p = blk_pick(kind, a, m_cap);
-  if (p.rb == 0 || 1.1 * p.us >= gemm_tile_us(kind, a, (m_cap + 127) / 128)) return false;
+  if (p.rb == 0 || 1.1 * p.us >= gemm_tile_us(kind, a, (m_cap + 127) / 128) || (kind == SEPI_SWIGLU && 1.1 * p.us >= gemm_lds_gateup_us(a))) return false;
   c = {GEMM_BLOCK, p.rb, p.ta, p.KS, blk_stream(kind, p, a.m_hint)};
   return true;
 }

@@ -298,9 +298,9 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmS
 // 501 / 380; 4B 64 191 / 150 (5.4 TB/s with what is stored), 128 209 / 171, 256 285 / 265; 8B 32 247 / 219, 256 444 / 424, 512 817 / 708.  Up to 16 rows
 // the streaming kernel is the faster one (1.7B, 12 rows, 95 / 103).  From 256 rows on the matrix pipes at the board's power limit bound it: without its
 // requests, 256 rows of 8B take 309 us, without its products 297, without its stores 347.
-template <int EPI, bool ROWS, bool STREAM>
+template <bool ROWS, bool STREAM>
 __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_kernel(const GemmStreamArgs a, const uint32_t xbytes) {
-  using T = LdsTile<EPI, ROWS, STREAM>;
+  using T = LdsTile<SEPI_STORE_F32, ROWS, STREAM>;
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ float s_rs[256];
   __shared__ int s_orow[256], s_src[256];
@@ -364,38 +364,208 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_kernel(const GemmStre
   }
 }
 
-template <int EPI, bool ROWS, bool STREAM>
-static void launch_lds(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
-  static bool lds_set[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-  if (dev >= 0 && dev < 64 && !lds_set[dev] &&
-      hipFuncSetAttribute((const void*)gemm_lds_kernel<EPI, ROWS, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES) == hipSuccess)
-    lds_set[dev] = true;
-  S2D2_LAUNCH((gemm_lds_kernel<EPI, ROWS, STREAM>), dim3(std::max(1, a.coop_wgs / 8) * 8), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes);
+// ---- gate / up of many rows ----
+// Tiles of 64 RBW rows x 192 features (96 of gate and up each): with eight wavefronts 4 x 2, each RBW row blocks x 6 feature tiles, a step of 32 columns takes
+// 0.58 KB of lines per product where the 128 x 128 pairs of the tiled kernel take 0.75, and the chip is filled without sharing K.  Both operands in fragment order,
+// five to eight stages of 32 columns.  The row count is on the device: P row tiles expected, whose height follows it.
+constexpr int LDS_GU_WR = 4, LDS_GU_WC = 2, LDS_GU_TW = 6, LDS_GU_TA = LDS_GU_WC * LDS_GU_TW, LDS_GU_TPW = LDS_GU_TA / 2;   // (TPW: pairs of a workgroup)
+constexpr int lds_gu_stages(int RBW) { return RBW == 4 ? 5 : RBW == 3 ? 6 : RBW == 2 ? 7 : 8; }
+constexpr int lds_gu_stage(int RBW) { return (LDS_GU_WR * RBW + LDS_GU_TA) * 1024; }
+constexpr int LDS_GU_DUMP = 144 * 1024;   // where units that do not exist go
+static_assert(5 * lds_gu_stage(4) <= LDS_GU_DUMP && 6 * lds_gu_stage(3) <= LDS_GU_DUMP && 7 * lds_gu_stage(2) <= LDS_GU_DUMP && 8 * lds_gu_stage(1) <= LDS_GU_DUMP, "LDS");
+
+template <int RBW>
+__device__ __forceinline__ void lds_gateup_body(const GemmStreamArgs& a, const int groups, const int P, const int M, const uint32_t xbytes, uint8_t* smem, float* s_rs) {
+  constexpr int NW = LDS_NW, WR = LDS_GU_WR, TW = LDS_GU_TW, TPW = LDS_GU_TPW, RB = WR * RBW, XU = RB, WU = LDS_GU_TA;
+  constexpr int XL = (XU + NW - 1) / NW, WL = (WU + NW - 1) / NW, L = XL + WL, ST = lds_gu_stages(RBW), NR = RBW + TW, NM = RBW * TW;
+  constexpr uint32_t STAGE = lds_gu_stage(RBW);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (opaque: what depends on the lane alone is otherwise computed for all heights ahead of the choice)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave % WR, wc = wave / WR, g = lane >> 4, f = lane & 15;
+  const int KT = a.KT, blocks = (M + 15) >> 4, tiles = min(P, (blocks + RB - 1) / RB);
+  // XCD i % 8 has the groups of features c % 8 == i % 8, all row tiles of one next to each other: its weights come in from memory once
+  const int s_ = (int)blockIdx.x >> 3, grp = (s_ / tiles) * 8 + (blockIdx.x & 7);
+  if (grp >= groups) return;
+  const uint32_t wbytes = (uint32_t)min(TPW, a.NT - grp * TPW) * (uint32_t)KT * 1024u;
+  // (a wavefront requests units of gate or of up only)
+  const uint64_t matrix = (uint64_t)((wave & 1 ? a.Wp2 : a.Wp) + (size_t)grp * TPW * KT * 64);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)lds_uniform((uint32_t)(matrix >> 32)) << 32 | lds_uniform((uint32_t)matrix)), 0, wbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, xbytes, 0x00020000);
+  const uint32_t lane16 = lane * 16;
+  uint32_t wo[WL], wv[WL], xo[XL], xv[XL];
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {
+    const int t = wave + NW * i;
+    const bool ok = t < WU && grp * TPW + (t >> 1) < a.NT;
+    wo[i] = (ok ? (uint32_t)(t >> 1) : 0u) * (uint32_t)KT * 1024u;
+    wv[i] = ok ? 0u : LDS_NOWHERE;
+  }
+  auto request = [&](auto i_, int k, uint32_t buf) __attribute__((always_inline)) {   // weights first
+    constexpr int i = decltype(i_)::value;
+    const uint32_t ko = (uint32_t)min(k, KT - 1) * 1024u, lanes = k < KT ? lane16 : LDS_NOWHERE;
+    if constexpr (i < WL) {
+      const int t = wave + NW * i;
+      lds_request<false>(rw, lanes | wv[i], wo[i] + ko, lds0 + (WU % NW == 0 || t < WU ? buf + (XU + t) * 1024u : LDS_GU_DUMP));
+    } else {
+      const int t = wave + NW * (i - WL);
+      lds_request<false>(rx, lanes | xv[i - WL], xo[i - WL] + ko, lds0 + (XU % NW == 0 || t < XU ? buf + t * 1024u : LDS_GU_DUMP));
+    }
+  };
+  for (int pass = s_ % tiles; pass * RB < blocks; pass += tiles) {
+    const int m0 = pass * RB * 16, Mloc = min(RB * 16, M - m0);
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int t = wave + NW * i;
+      const bool ok = t < XU && t * 16 < Mloc;
+      xo[i] = (uint32_t)((m0 >> 4) + (ok ? t : 0)) * (uint32_t)KT * 1024u;
+      xv[i] = ok ? 0u : LDS_NOWHERE;
+    }
+    lds_each<0, ST>([&](auto s) __attribute__((always_inline)) {
+      lds_each<0, L>([&](auto i) __attribute__((always_inline)) { request(i, decltype(s)::value, decltype(s)::value * STAGE); });
+    });
+    {   // 1/rms of the rows from the producer's partial sums of squares
+      const int r = tid >> 1, sub = tid & 1;
+      const float* pp = a.ss_part + (size_t)min(m0 + r, M - 1) * a.ss_stride;
+      float v = 0.f;
+      if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
+        const int n4 = a.ss_count >> 2;
+        for (int i0 = sub; i0 < n4; i0 += 16) {
+          float4 t[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) t[j] = ((const float4*)pp)[min(i0 + 2 * j, n4 - 1)];   // clamped duplicates are skipped when summing
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (i0 + 2 * j < n4) v += (t[j].x + t[j].y) + (t[j].z + t[j].w);
+        }
+      } else {
+        for (int i = sub; i < a.ss_count; i += 2) v += pp[i];
+      }
+      v += __shfl_xor(v, 1, 64);
+      if (r < RB * 16 && sub == 0) s_rs[r] = 1.0f / sqrtf(v / (float)a.K + a.eps);
+    }
+    f32x4_t acc[RBW][TW];
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+      for (int t = 0; t < TW; ++t) acc[rb][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t fx[2][RBW], fw[2][TW];
+    const uint8_t* xb = smem + wr * 1024 + lane16;   // (row blocks go to the wavefronts in turn)
+    const uint8_t* wb = smem + (XU + wc * TW) * 1024 + lane16;
+    auto read = [&](auto st_, auto j_, uint32_t buf) __attribute__((always_inline)) {
+      constexpr int S = decltype(st_)::value, j = decltype(j_)::value;
+      if constexpr (j < TW) fw[S][j] = *(const u32x4_t*)(wb + buf + j * 1024);
+      else fx[S][j - TW] = *(const u32x4_t*)(xb + buf + WR * (j - TW) * 1024);
+    };
+    lds_wait_barrier<L * (ST - 1)>();
+    lds_each<0, NR>([&](auto j) __attribute__((always_inline)) { read(std::integral_constant<int, 0>{}, j, 0); });
+    uint32_t buf = 0, nbuf = STAGE;
+    // (as in multiply() above: stage k + 1 lands, the reads of it and the requests of stage k + ST between the products of stage k)
+    auto step = [&](auto st_, int k) __attribute__((always_inline)) {
+      constexpr int S = decltype(st_)::value, PB = NM / 8, NO = L + NR;
+      lds_each<0, NM>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_)::value, rb = i / TW, t = i % TW;
+        acc[rb][t] = mfma_16x16x32<OPM_F16>(fw[S][t], fx[S][rb], acc[rb][t]);
+        if constexpr (i == PB) {
+          __builtin_amdgcn_sched_barrier(0);
+          lds_wait_barrier<L * (ST - 2)>();
+        }
+        if constexpr (i >= PB)
+          lds_each<(i - PB) * NO / (NM - PB), (i - PB + 1) * NO / (NM - PB)>([&](auto j_) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_)::value, d0 = j * L / NO, d1 = (j + 1) * L / NO;
+            if constexpr (d1 > d0) request(std::integral_constant<int, d0>{}, k + ST, buf);
+            else read(std::integral_constant<int, 1 - S>{}, std::integral_constant<int, j - d0>{}, nbuf);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      buf = nbuf;
+      nbuf = nbuf + STAGE == ST * STAGE ? 0 : nbuf + STAGE;
+    };
+    for (int k = 0; k < KT; k += 2) {   // (an even number)
+      step(std::integral_constant<int, 0>{}, k);
+      step(std::integral_constant<int, 1>{}, k + 1);
+    }
+    lds_wait_barrier<0>();
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb) {
+      const int blk = wr + WR * rb, r = blk * 16 + f;
+      if (blk * 16 >= Mloc) continue;   // uniform over the wavefront
+      const float rs = s_rs[r];
+#pragma unroll
+      for (int t = 0; t < TW / 2; ++t)
+        gemm_epi_unit<SEPI_SWIGLU, true>(a, r < Mloc, m0 + min(r, Mloc - 1), rs, grp * TPW + wc * (TW / 2) + t, g, acc[rb][2 * t], acc[rb][2 * t + 1], nullptr);
+    }
+    __syncthreads();   // rows beyond the expected ones take the same LDS
+  }
 }
-// Half operands, whole steps of 64 columns, 32-bit offsets into the rows.
+
+__global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_gateup_kernel(const GemmStreamArgs a, const int P, const int groups, const uint32_t xbytes) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  __shared__ float s_rs[256];
+  const int M = (int)lds_uniform(*a.m_count), blocks = (M + 15) >> 4;
+  if (M <= 0) return;
+  const int rbw = ((blocks + P - 1) / P + LDS_GU_WR - 1) / LDS_GU_WR;   // heights by the rows there are
+  if (rbw <= 1) lds_gateup_body<1>(a, groups, P, M, xbytes, smem, s_rs);
+  else if (rbw == 2) lds_gateup_body<2>(a, groups, P, M, xbytes, smem, s_rs);
+  else if (rbw == 3) lds_gateup_body<3>(a, groups, P, M, xbytes, smem, s_rs);
+  else lds_gateup_body<4>(a, groups, P, M, xbytes, smem, s_rs);
+}
+
+// Row tiles and time of a launch: rounds of workgroups, each KT steps and its ends (measured with KT 64, 80 and 128, one round and two).
+struct LdsGateup { int P; double us; };
+static LdsGateup lds_gateup(const GemmStreamArgs& a) {
+  constexpr double per_kt[5] = {0, 0, .44, .58, .65}, ends[5] = {0, 0, 6.0, 8.0, 11.0};
+  LdsGateup best{0, 1e30};
+  const int groups = (a.NT + LDS_GU_TPW - 1) / LDS_GU_TPW;
+  for (int rbw = 2; rbw <= 4; ++rbw) {
+    const int P = (a.m_hint + 64 * rbw - 1) / (64 * rbw);
+    const double us = std::ceil((groups + 7) / 8 * P / (a.coop_wgs / 8.0)) * (a.KT * per_kt[rbw] + ends[rbw]);
+    if (us < best.us) best = {P, us};
+  }
+  return best;
+}
+double gemm_lds_gateup_us(const GemmStreamArgs& a) {
+  if (a.KT < 64 || (long long)a.NT * a.KT < 24576) return 1e30;   // (matrices of 48 MB together: below, the estimate has not been measured)
+  if (a.x_lo != LO_F16P || a.coop_wgs < 8 || a.KT % 2 || a.grouped != GROUP_NONE || (long long)((a.x_rows + 15) / 16) * a.KT * 1024 >= 0xfffff000LL) return 1e30;
+  return lds_gateup(a).us;
+}
+
+// The unembedding: half operands, whole steps of 64 columns, 32-bit offsets into the rows.
 bool gemm_lds_takes(int kind, const GemmStreamArgs& a) {
   if ((a.x_lo != LO_F16 && a.x_lo != LO_F16P) || a.coop_wgs < 1 || a.KT % 2 || a.grouped != GROUP_NONE || (long long)((a.x_rows + 15) / 16) * a.KT * 1024 >= 0xfffff000LL) return false;
   return kind == SEPI_STORE_F32 && a.gather && a.m_hint > 16;
 }
+static void lds_attribute(const void* fn, unsigned bytes, bool (&done)[64]) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
+  if (!done[dev] && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess) done[dev] = true;   // on failure the launch fails too, and the entry point reports that error
+}
+template <bool ROWS, bool STREAM>
+static void launch_lds(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
+  static bool lds_set[64];
+  lds_attribute((const void*)gemm_lds_kernel<ROWS, STREAM>, LDS_BYTES, lds_set);
+  S2D2_LAUNCH((gemm_lds_kernel<ROWS, STREAM>), dim3(std::max(1, a.coop_wgs / 8) * 8), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes);
+}
 void launch_gemm_lds(hipStream_t st, int kind, const GemmStreamArgs& a) {
   const uint32_t xbytes = (uint32_t)((a.x_rows + 15) / 16) * (uint32_t)a.KT * 1024u;   // (in rows: at least as many)
-  const bool stream = a.m_hint <= 256;   // one row tile: every weight is requested once
-  auto go = [&](auto rows_, auto stream_) { launch_lds<SEPI_STORE_F32, decltype(rows_)::value, decltype(stream_)::value>(st, a, xbytes); };
-  auto rows = [&](auto rows_) { if (stream) go(rows_, std::true_type{}); else go(rows_, std::false_type{}); };
-  if (a.x_lo == LO_F16) rows(std::true_type{});
-  else rows(std::false_type{});
+  if (kind == SEPI_SWIGLU) {
+    static bool lds_set[64];
+    lds_attribute((const void*)gemm_lds_gateup_kernel, LDS_GU_DUMP + 1024, lds_set);
+    const int P = lds_gateup(a).P, groups = (a.NT + LDS_GU_TPW - 1) / LDS_GU_TPW;
+    S2D2_LAUNCH(gemm_lds_gateup_kernel, dim3((groups + 7) / 8 * 8 * P), dim3(LDS_THREADS), LDS_GU_DUMP + 1024, st, a, P, groups, xbytes);
+    return;
+  }
+  const bool rows = a.x_lo == LO_F16, stream = a.m_hint <= 256;   // stream: one row tile, every weight is requested once
+  if (rows && stream) launch_lds<true, true>(st, a, xbytes);
+  else if (rows) launch_lds<true, false>(st, a, xbytes);
+  else if (stream) launch_lds<false, true>(st, a, xbytes);
+  else launch_lds<false, false>(st, a, xbytes);
 }
 
 template <int EPI>
 static void launch_expert(hipStream_t st, const GemmStreamArgs& a, uint32_t xbytes) {
   static bool lds_set[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-  if (dev >= 0 && dev < 64 && !lds_set[dev] &&
-      hipFuncSetAttribute((const void*)gemm_expert_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES) == hipSuccess)
-    lds_set[dev] = true;   // on failure the launch below fails too, and the entry point reports that error
+  lds_attribute((const void*)gemm_expert_kernel<EPI>, LDS_BYTES, lds_set);
   const int wgs = std::max(1, a.coop_wgs / 8) * 8;
   S2D2_LAUNCH((gemm_expert_kernel<EPI>), dim3(wgs), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes, (a.NT + LdsTile<EPI, true, true>::TPW - 1) / LdsTile<EPI, true, true>::TPW);
 }

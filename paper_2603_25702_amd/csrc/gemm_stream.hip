@@ -401,6 +401,7 @@ GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap) {
   if (gemm_lds_takes(kind, a)) return {GEMM_LDS, 0, 0, 1, false};
   if (gemm_block_takes(kind, a, m_cap, c)) return c;
   if (gemm_mid_takes(kind, a, m_cap)) return {GEMM_MID, 0, 0, 1, false};
+  if (kind == SEPI_SWIGLU && a.m_hint > MID_MOST_ROWS && gemm_lds_gateup_us(a) < gemm_tile_us(kind, a, (m_cap + 127) / 128)) return {GEMM_LDS, 0, 0, 1, false};
   // The streaming kernel takes half operands in fragment order only, except the ones that a store reads: a forward
   // lays them out so whenever it expects at most MID_MOST_ROWS rows, and a caller that did not is sent to the tiled
   // kernel, which takes rows too.

@@ -241,7 +241,7 @@ struct GemmStreamArgs {
   int32_t m_hint;           // host: rows the caller expects (0 = unknown); only steers the choice of launch shape
   const bf16_t* X;          // activations [*, ldx] (for SPRO_BF16S: h * gain, not yet divided by the rms)
   int32_t ldx;
-  int32_t x_rows;           // unembedding: rows of X at most
+  int32_t x_rows;           // unembedding, gate / up: rows of X at most
   int32_t x_lo;             // low-plane offset of X's rows (0: one bf16 plane, > 0: two planes, LO_F16 / LO_F16P: half values in rows / in fragment order)
   const int32_t* gather;    // optional row indices into X / ss_part
   const float* ss_part;     // SPRO_BF16S: [*, ss_stride] partial sums of squares of the residual rows
@@ -322,6 +322,7 @@ void launch_gemm_tile(hipStream_t st, int kind, int pro, const GemmStreamArgs& a
 double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // estimate
 // gemm_lds.hip : both operands through LDS, half operands; products of many rows and the expert GEMMs (operands in rows)
 bool gemm_lds_takes(int kind, const GemmStreamArgs& a);
+double gemm_lds_gateup_us(const GemmStreamArgs& a);   // estimate for gate / up, 1e30 where it cannot run
 void launch_gemm_lds(hipStream_t st, int kind, const GemmStreamArgs& a);
 bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo);
 void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows /* X has at most */);
