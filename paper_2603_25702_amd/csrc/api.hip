@@ -285,9 +285,9 @@ KvGeom geom(const s2d2_ctx* c, const s2d2_kv_view* kv) {
 }
 
 // Shape of the wide attention launch: q_tiles 32-row query tiles per window; target key splits of all sequences together,
-// per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence; LDS for
+// per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence and run tiles in one; LDS for
 // `tiles` key tiles at a time beside a split's share of the page table, 0 if that is too long.
-struct WideShape { int q_tiles, target, Z, tiles; };
+struct WideShape { int q_tiles, target, Z, tiles, run; };
 WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) {
   WideShape w;
   const KvGeom g = geom(c, kv);
@@ -297,6 +297,7 @@ WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) 
   for (int fill : {nw == 8 ? c->wide_wgs / 2 : c->wide_wgs, c->wide_wgs}) {
     w.target = std::max(1, std::min((fill + wg - 1) / wg, WIDE_MAX_TARGET));
     w.Z = attention_wide_splits(g, N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
+    w.run = attention_wide_run_most(g, N, w.Z, w.target);
     for (w.tiles = nw == 8 ? 2 : 1; w.tiles > 0; --w.tiles)
       if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, w.Z, w.target), w.tiles) <= 160 * 1024) return w;
   }
@@ -732,7 +733,7 @@ int32_t s2d2_draft(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state* 
   const WideShape ws = wide_shape(c, kv, N, draft_size(N, B).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 0, d.right_shifted, N, B, d.mask_id, prm->ar_mask, kv->seq_len, st->block_pos0, st->block_tokens,
               st->carry_tokens, nullptr, c->plan, out->logit_row_of, out->span_start, out->span_len, nullptr, nullptr, nullptr, kv->status,
-              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
   if ((rc = forward(c, kv, N, draft_size(N, B), nullptr, nullptr, out->logits))) return rc;
   { ProfScope ps(c, 2, 0.0); launch_vocab_draft(c->stream, out->logits, d.vocab, c->plan.counts + 1, N * B, c->vws, c->plan.logit_seq,
                      c->plan.logit_idx, B, out->xhat, out->p, out->lse, out->margin, out->entropy_n,
@@ -752,7 +753,7 @@ int32_t s2d2_verify(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state*
   const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, d.right_shifted).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 1, d.right_shifted, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               draft->xhat, c->plan, out->logit_row_of, nullptr, nullptr, out->stage_row0, out->stage_lead, prm->active, kv->status,
-              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, out->q, out->lse_ver); }
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run, out->q, out->lse_ver); }
   if ((rc = forward(c, kv, N, verify_size(N, B, d.right_shifted), out->k_stage, out->v_stage, out->logits_ver))) return rc;
   { ProfScope ps(c, 2, 0.0); launch_vocab_score(c->stream, out->logits_ver, d.vocab, c->plan.counts + 1, N * B, c->vws, c->plan.logit_seq,
                      c->plan.logit_idx, B, draft->xhat, out->q, out->lse_ver, inv_temperature(prm)); }
@@ -820,7 +821,7 @@ int32_t s2d2_block_complete(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_bloc
   const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, 0).win);
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, causal ? 3 : 2, 0, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               nullptr, c->plan, scratch->logit_row_of, nullptr, nullptr, scratch->stage_row0, scratch->stage_lead, nullptr, nullptr,
-              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
   if ((rc = forward(c, kv, N, verify_size(N, B, 0), scratch->k_stage, scratch->v_stage, scratch->logits_ver))) return rc;
   const KvGeom g = geom(c, kv);
   // every staged row is appended: lead = rows, accepted = 0 (the zero array stands in for n_accept and span_len)
@@ -843,7 +844,7 @@ int32_t s2d2_prefill(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t T, 
   const FwdSize sz = prefill_size(N, T);
   const WideShape ws = wide_shape(c, kv, N, sz.win);
   { ProfScope ps(c, 3, 0.0); launch_plan_prefill(c->stream, N, T, d.mask_id, kv->seq_len, tokens, ld, n_tokens, c->plan,
-              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z); }
+              kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
   if ((rc = forward(c, kv, N, sz, k_stage, v_stage, nullptr))) return rc;
   const KvGeom g = geom(c, kv);
   { ProfScope ps(c, 3, 0.0); launch_kv_append(c->stream, d.dtype, d.n_layers, N, c->rows_cap, g, kv->k_pages, kv->v_pages,

@@ -608,12 +608,14 @@ int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_e
   return Z;
 }
 
-// Page-table entries a split can touch (plus slack for the ragged ends): N sequences of the cache's capacity share the
-// target's splits, a single one has at most Z.
-int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
+// Tiles of a split at most: N sequences of the cache's capacity share the target's splits, a single one has at most Z.
+int attention_wide_run_most(const KvGeom& g, int N, int Z, int target) {
   const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32;
-  const long long per_split = std::max((long long)std::max((cap_tiles + Z - 1) / Z, WIDE_MIN_TILES), ((long long)N * cap_tiles + target - 1) / target) + 1;
-  return (int)std::min((long long)g.max_pages_per_seq, per_split * 32 / g.page_size + 2);
+  return (int)std::max((long long)std::max((cap_tiles + Z - 1) / Z, WIDE_MIN_TILES), ((long long)N * cap_tiles + target - 1) / target);
+}
+// Page-table entries a split can touch (plus slack for the ragged ends).
+int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
+  return (int)std::min((long long)g.max_pages_per_seq, ((long long)attention_wide_run_most(g, N, Z, target) + 1) * 32 / g.page_size + 2);
 }
 
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,

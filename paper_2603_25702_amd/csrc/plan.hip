@@ -17,15 +17,49 @@ namespace s2d2 {
 // embedding row outside the table.
 __device__ __forceinline__ int in_vocab(int tok, int vocab, int mask_id) { return (unsigned)tok < (unsigned)vocab ? tok : mask_id; }
 
+// Key splits of sequence n (n < N; others 0): runs of the length that gives split_target of them if all tiles were one sequence's, or of up to half as much
+// more if then all splits of the batch are resident at once: the part of a run at the end of every sequence otherwise makes a few more than the
+// target, and the workgroups left over start when the first ones are done.  Forwards, us, without / with: 4B draft of eight sequences of
+// 1024 to 4096 tokens 4251 / 3871 (67 splits for 64), 4B verification of 20 9375 / 8788, 8B of 16 blocks behind 300 to 6000 12957 / 12284, MoE draft of 20
+// 5797 / 5449.  All threads of the workgroup.
+constexpr int RUNS = 16;
+__device__ __forceinline__ int splits_of(int total, int tiles, int n, int N, int split_target, int split_most, int run_most, int32_t* s_runs /* [RUNS], zero */) {
+  const int least = max(WIDE_MIN_TILES, (total + split_target - 1) / split_target);
+  auto run = [&](int i) { return least + (least * i + 2 * RUNS - 3) / (2 * RUNS - 2); };   // least .. least * 3 / 2
+  auto splits = [&](int i) { return max(1, min(split_most, (tiles + run(i) - 1) / run(i))); };
+  int first = n < N ? splits(0) : 0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) first += __shfl_xor(first, off, 64);
+  if ((n & 63) == 0) atomicAdd(&s_runs[0], first);
+  __syncthreads();
+  int pick = 0;
+  if (s_runs[0] > split_target) {   // uniform
+    int v[RUNS];
+#pragma unroll
+    for (int i = 1; i < RUNS; ++i) v[i] = n < N ? splits(i) : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int i = 1; i < RUNS; ++i) v[i] += __shfl_xor(v[i], off, 64);
+    if ((n & 63) == 0)
+#pragma unroll
+      for (int i = 1; i < RUNS; ++i) atomicAdd(&s_runs[i], v[i]);
+    __syncthreads();
+    for (int i = RUNS - 1; i > 0; --i)
+      if (s_runs[i] <= split_target && run(i) <= run_most) pick = i;
+  }
+  return n < N ? splits(pick) : 0;
+}
+
 __global__ __launch_bounds__(1024) void plan_kernel(
     int verify, int shifted, int N, int B, int mask_id, int ar_mask, const int32_t* __restrict__ seq_len,
     const int32_t* __restrict__ pos0, const int32_t* __restrict__ block,
     const int32_t* __restrict__ carry, const int32_t* __restrict__ xhat, Plan p,
     int32_t* __restrict__ logit_row_of, int32_t* __restrict__ span_start,
     int32_t* __restrict__ span_len, int32_t* __restrict__ stage_row0, int32_t* __restrict__ stage_lead,
-    const int32_t* __restrict__ active, int32_t* __restrict__ status, int seq_cap, int split_target, int split_most, float* __restrict__ clear_a,
+    const int32_t* __restrict__ active, int32_t* __restrict__ status, int seq_cap, int split_target, int split_most, int run_most, float* __restrict__ clear_a,
     float* __restrict__ clear_b) {
-  __shared__ int32_t s_tiles, s_splits[1024];
+  __shared__ int32_t s_tiles, s_splits[1024], s_runs[RUNS];
   __shared__ int32_t s_rows[1024];
   __shared__ int32_t s_lrows[1024];
   const int n = threadIdx.x;
@@ -60,6 +94,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(
     else        { rows = nc + (B - c); lrows = bad ? 0 : n_masked; }
   }
   if (n == 0) s_tiles = 0;
+  if (n < RUNS) s_runs[n] = 0;
   s_rows[n] = rows;
   s_lrows[n] = lrows;
   __syncthreads();
@@ -67,8 +102,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(
   const int tiles = rows > 0 ? (max(0, min(S, seq_cap)) + 31) >> 5 : 0;
   if (tiles) atomicAdd(&s_tiles, tiles);
   __syncthreads();
-  const int run = max(WIDE_MIN_TILES, (s_tiles + split_target - 1) / split_target);
-  const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
+  const int splits = splits_of(s_tiles, tiles, n, N, split_target, split_most, run_most, s_runs);
   s_splits[n] = splits;
   __syncthreads();
   // inclusive Hillis-Steele scan over the sequences
@@ -183,10 +217,10 @@ void launch_plan(hipStream_t st, int verify, int shifted, int N, int B, int mask
                  const int32_t* seq_len, const int32_t* pos0, const int32_t* block,
                  const int32_t* carry, const int32_t* xhat, const Plan& p, int32_t* logit_row_of,
                  int32_t* span_start, int32_t* span_len, int32_t* stage_row0, int32_t* stage_lead,
-                 const int32_t* active, int32_t* status, int seq_cap, int split_target, int split_most, float* clear_a, float* clear_b) {
+                 const int32_t* active, int32_t* status, int seq_cap, int split_target, int split_most, int run_most, float* clear_a, float* clear_b) {
   S2D2_LAUNCH(plan_kernel, dim3(1), dim3((N + 63) / 64 * 64), 0, st, verify, shifted, N, B, mask_id, ar_mask,
                      seq_len, pos0, block, carry, xhat, p, logit_row_of, span_start, span_len,
-                     stage_row0, stage_lead, active, status, seq_cap, split_target, split_most, clear_a, clear_b);
+                     stage_row0, stage_lead, active, status, seq_cap, split_target, split_most, run_most, clear_a, clear_b);
 }
 
 // Prompt tokens pushed into the cache: n_tokens[n] causal rows of sequence n behind its cached ones, no logits.  A
@@ -194,18 +228,18 @@ void launch_plan(hipStream_t st, int verify, int shifted, int N, int B, int mask
 __global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int mask_id, const int32_t* __restrict__ seq_len,
                                                             const int32_t* __restrict__ tokens, int ld,
                                                             const int32_t* __restrict__ n_tokens, Plan p, int seq_cap,
-                                                            int split_target, int split_most) {
-  __shared__ int32_t s_tiles, s_rows[1024], s_splits[1024];
+                                                            int split_target, int split_most, int run_most) {
+  __shared__ int32_t s_tiles, s_rows[1024], s_splits[1024], s_runs[RUNS];
   const int n = threadIdx.x;
   const int S = n < N ? seq_len[n] : 0, rows = n < N ? max(0, min(T, n_tokens[n])) : 0;
   if (n == 0) s_tiles = 0;
+  if (n < RUNS) s_runs[n] = 0;
   s_rows[n] = rows;
   __syncthreads();
   const int tiles = rows > 0 ? (max(0, min(S, seq_cap)) + 31) >> 5 : 0;
   if (tiles) atomicAdd(&s_tiles, tiles);
   __syncthreads();
-  const int run = max(WIDE_MIN_TILES, (s_tiles + split_target - 1) / split_target);
-  const int splits = n < N ? max(1, min(split_most, (tiles + run - 1) / run)) : 0;
+  const int splits = splits_of(s_tiles, tiles, n, N, split_target, split_most, run_most, s_runs);
   s_splits[n] = splits;
   __syncthreads();
   for (int off = 1; off < N; off <<= 1) {
@@ -237,9 +271,9 @@ __global__ __launch_bounds__(1024) void plan_prefill_kernel(int N, int T, int ma
 }
 
 void launch_plan_prefill(hipStream_t st, int N, int T, int mask_id, const int32_t* seq_len, const int32_t* tokens, int ld,
-                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most) {
+                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most, int run_most) {
   S2D2_LAUNCH(plan_prefill_kernel, dim3(1), dim3(1024), 0, st, N, T, mask_id, seq_len, tokens, ld, n_tokens, p, seq_cap,
-              split_target, split_most);
+              split_target, split_most, run_most);
 }
 
 // ---------------------------------------------------------------------------------------------

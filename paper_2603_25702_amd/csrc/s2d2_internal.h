@@ -203,10 +203,10 @@ void launch_plan(hipStream_t st, int verify /* 0 draft, 1 verifier, 2 block comp
                  int32_t* span_start, int32_t* span_len, int32_t* stage_row0, int32_t* stage_lead,
                  const int32_t* active, int32_t* status,
                  int seq_cap, int split_target /* wide attention: key splits of all sequences together, per KV head */,
-                 int split_most /* and of one sequence */,
+                 int split_most /* and of one sequence */, int run_most /* tiles of one at most, for more than the target's share */,
                  float* clear_a = nullptr, float* clear_b = nullptr /* verifier: [N, B] outputs zeroed for every position */);
 void launch_plan_prefill(hipStream_t st, int N, int T, int mask_id, const int32_t* seq_len, const int32_t* tokens, int ld,
-                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most);
+                         const int32_t* n_tokens, const Plan& p, int seq_cap, int split_target, int split_most, int run_most);
 void launch_kv_append(hipStream_t st, int dtype, int n_layers, int N, int rows_cap, const KvGeom& g,
                       void* k_pages, void* v_pages, const void* k_stage, const void* v_stage,
                       const int32_t* stage_row0, const int32_t* stage_lead, const int32_t* span_len,
@@ -354,6 +354,7 @@ int attention_wide_init();
 int attention_wide_nw(int q_tiles);
 constexpr int WIDE_MIN_TILES = 4;   // key tiles (of 32) a split of the wide kernel keeps at least
 int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target);
+int attention_wide_run_most(const KvGeom& g, int N, int Z, int target);
 int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target);
 size_t attention_wide_lds_bytes(int pt_cap, int tiles /* walked at a time: 1, or up to 2 by eight wavefronts */);
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
