@@ -28,7 +28,7 @@ static constexpr int BLK_ROW_LDS = 512 + 48 * 64;   // per-row and per-unit data
 // K tiles in flight per wavefront: what fits next to the accumulators (two workgroups per compute unit, 256 registers;
 // one with 512 from 36 units on).  More than two changed nothing (see above); the small blocks' loops are shorter with four.
 constexpr int blk_u(int RB, int TA) { return RB * TA <= 16 ? 4 : 2; }
-constexpr bool blk_shares(int RB, int TA) { return RB * TA != 32; }   // may share K (8 x 4 has no registers for it)
+constexpr bool blk_shares(int RB, int TA) { return RB * TA != 32 && RB != 6; }   // may share K (8 x 4 has no registers for it; six row blocks are taken where they fill the chip without)
 constexpr int blk_wgs(int RB, int TA) { return RB * TA > 32 ? 1 : 2; }   // workgroups per compute unit
 
 // LDS accesses of this wavefront done, then the workgroup's barrier; global loads stay in flight.
@@ -179,8 +179,12 @@ __device__ __forceinline__ void gemm_block_body(const GemmStreamArgs& a, const B
       gemm_epi_request<EPI>(a, r, nt, gm, n_.e);
       if (EPI == SEPI_ADD_F32) n_.h = *(const float4*)((const float*)a.out + (size_t)r * a.ldo + nt * 16 + 4 * gm);
     };
-    Ahead next;
-    if (!SHARED) request(unit(0), next);
+    constexpr int DEP = EPI == SEPI_SWIGLU ? 1 : 3;   // units requested ahead
+    Ahead next[DEP];
+    if (!SHARED) {
+#pragma unroll
+      for (int i = 0; i < DEP; ++i) request(unit(i), next[i]);
+    }
     blk_barrier();
     auto unit_sum = [&](int u, f32x4_t (&sum)[NACC]) __attribute__((always_inline)) {
 #pragma unroll
@@ -202,14 +206,17 @@ __device__ __forceinline__ void gemm_block_body(const GemmStreamArgs& a, const B
     // (Loops over units are not unrolled: that is 10-20 KB of instructions that every workgroup would fetch once.)
     if (!SHARED) {
 #pragma unroll 1
-      for (int q = 0; q < UPW; ++q) {
-        const int u = unit(q);
-        Ahead at = next;
-        request(unit(q + 1), next);
-        if (!unit_ok(u)) continue;
-        f32x4_t sum[NACC];
-        unit_sum(u, sum);
-        finish(u, sum, at);
+      for (int q0 = 0; q0 < UPW; q0 += DEP) {
+#pragma unroll
+        for (int i = 0; i < DEP; ++i) {
+          const int u = unit(q0 + i);
+          if (unit_ok(u)) {
+            f32x4_t sum[NACC];
+            unit_sum(u, sum);
+            finish(u, sum, next[i]);
+          }
+          request(unit(q0 + i + DEP), next[i]);
+        }
       }
     } else {
       // K shared by KS workgroups: the shares 1 .. KS - 1 (first in dispatch order; they never wait) hand their sums over as
@@ -372,8 +379,14 @@ __global__ __launch_bounds__(BLK_THREADS, blk_wgs(RB, TA)) void gemm_block_kerne
 // compute unit.
 struct BlkShape { int rb, ta; double per_kt, ends; };
 static constexpr BlkShape BLK_SHAPES[] = {{2, 2, .066, 3.0}, {4, 2, .092, 3.2}, {4, 3, .104, 3.6}, {4, 4, .115, 3.9}, {4, 6, .141, 4.9}, {6, 4, .146, 4.9},
-                                          {8, 4, .168, 5.3}, {6, 6, .185, 8.0}, {8, 6, .205, 9.0}};
+                                          {8, 4, .168, 5.3}, {6, 6, .185, 8.0}, {8, 6, .205, 9.0}, {6, 8, .205, 9.0}};
 struct BlkPick { int rb, ta, KS; double us; };
+// Six row blocks: 768 rows of the 1.7B shape are 256 blocks of 6 x 4 in the output and down projection (192 of 8 x 4: 56 -> 47 us for the
+// two, with the requests of the epilogue) and of 6 x 8 in QKV (768 of 4 x 4, two or three on a compute unit: 32.8 -> 28.8).  With fewer than 64 K tiles the difference
+// between two shapes is less than the estimates below are off by, and those of before stay.
+constexpr bool blk_compiled(int kind, int RB, int TA) {
+  return kind == SEPI_SWIGLU ? TA != 3 && TA != 8 : RB == 6 ? TA == 8 || (TA == 4 && kind == SEPI_ADD_F32) : true;
+}
 
 // A launch takes the longer of what its busiest compute unit and what the chip needs: rounds of workgroups times the times
 // above (where two workgroups share a compute unit and there are several rounds, most of a workgroup's ends is hidden), and the weights from memory at 6.3 TB/s, then the rest of the operands from L2 at 25, behind 3 us; activations that do not stay in an XCD's L2 are
@@ -385,7 +398,7 @@ static BlkPick blk_pick(int kind, const GemmStreamArgs& a, int m_cap) {
   const int nacc = kind == SEPI_SWIGLU ? 2 : 1;
   const double kt_mb = 1.024e-3;   // MB of a unit's operand per K tile
   for (const BlkShape& s : BLK_SHAPES) {
-    if (s.ta % nacc || (kind != SEPI_SWIGLU && s.rb == 6)) continue;
+    if (s.ta % nacc || !blk_compiled(kind, s.rb, s.ta) || (kind != SEPI_SWIGLU && s.rb == 6 && a.KT < 64)) continue;
     const int tpw = s.ta / nacc, groups = (a.NT + tpw - 1) / tpw, tiles = (a.m_hint + 16 * s.rb - 1) / (16 * s.rb), caps = (m_cap + 16 * s.rb - 1) / (16 * s.rb);
     const int u = blk_u(s.rb, s.ta);
     for (int ks = 1; ks <= 4; ++ks) {
@@ -444,7 +457,7 @@ static int launch_blk_kind(hipStream_t st, const GemmStreamArgs& a, const GemmCh
 #define S2D2_BLK(RB, TA) if (c.rb == RB && c.ta == TA) return launch_blk_shape<EPI, RB, TA>(st, a, c, m_cap)
   S2D2_BLK(2, 2); S2D2_BLK(4, 2); S2D2_BLK(4, 4); S2D2_BLK(4, 6); S2D2_BLK(8, 4); S2D2_BLK(8, 6);
   if constexpr (EPI == SEPI_SWIGLU) { S2D2_BLK(6, 4); S2D2_BLK(6, 6); }
-  else { S2D2_BLK(4, 3); }
+  else { S2D2_BLK(4, 3); S2D2_BLK(6, 8); if constexpr (EPI == SEPI_ADD_F32) { S2D2_BLK(6, 4); } }
 #undef S2D2_BLK
   return 0;   // (the pick is one of these)
 }
