@@ -269,7 +269,7 @@ int32_t s2d2_accept(s2d2_ctx* ctx, const s2d2_block_state* st, int32_t N, int32_
  * tight serving loops, harnesses that forbid hipMalloc.  Same inputs, outputs and results as s2d2_accept (bit for
  * bit), but no context and no workspace: the scratch of the residual draw (tile sums that the workgroups of a
  * sequence hand to each other, 4 bytes per 256 vocabulary entries and sequence, and one arrival counter per
- * sequence) lives in a device array inside the library, 512.5 KB on every GPU the library runs on, held until the
+ * sequence) lives in a device array inside the library, 544 KB on every GPU the library runs on, held until the
  * process ends.  Limits: N <= 128, vocab <= 262144 (2^18), B <= S2D2_MAX_BLOCK; beyond them the call returns
  * S2D2_ENOSPC and launches nothing.  `stream` is a hipStream_t (NULL: the default stream), `vocab` the width of
  * the logit rows; st->block_pos0 and st->carry_tokens are not read.  The call enqueues two kernels (a fill that

@@ -40,7 +40,6 @@ struct s2d2_ctx {
   size_t ws_bytes;
   // carved workspace
   Plan plan;
-  int32_t* tmp_count;
   float* h;
   void* a;
   float* qkv;
@@ -159,7 +158,6 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   const size_t es = elt_size(d.dtype);
   c->plan.counts = cv.take<int32_t>(8);
   c->plan.vocab = d.vocab;
-  c->tmp_count = cv.take<int32_t>(8);
   c->plan.row_token = cv.take<int32_t>(R);
   c->plan.row_pos = cv.take<int32_t>(R);
   c->plan.row_seq = cv.take<int32_t>(R);
@@ -227,9 +225,10 @@ size_t carve(s2d2_ctx* c, uint8_t* base) {
   c->vws.chunks = vocab_chunks(d.vocab);
   c->vws.part = cv.take<float>(LR * (size_t)c->vws.chunks * 8);
   c->accept_tiles = cv.take<float>(tile_sum_floats(c->max_batch, d.vocab));
-  c->accept_arrive = cv.take<int32_t>(c->max_batch);
+  c->accept_arrive = cv.take<int32_t>((size_t)c->max_batch * ARRIVE_STRIDE);
   c->vws.sample_tiles = cv.take<float>(tile_sum_floats(sample_rows_shared((int)LR), d.vocab));
-  c->vws.sample_arrive = cv.take<int32_t>(sample_rows_shared((int)LR));
+  c->vws.sample_arrive = cv.take<int32_t>((size_t)sample_rows_shared((int)LR) * ARRIVE_STRIDE);
+  c->vws.arrive = cv.take<int32_t>(LR * ARRIVE_STRIDE);
   return (cv.off + 255) & ~(size_t)255;
 }
 
@@ -535,8 +534,6 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   return check_launch("forward");
 }
 
-__global__ void set_i32_kernel(int32_t* p, int32_t v) { *p = v; }
-
 }  // namespace
 
 extern "C" {
@@ -668,8 +665,9 @@ int32_t s2d2_create(const s2d2_model_desc* desc, const s2d2_weights* weights, in
   launch_fill_i32(c->stream, c->dev_status, 64, 0);
   launch_fill_i32(c->stream, c->attn_counters, c->attn_groups, 0);
   launch_fill_i32(c->stream, c->zeros_i32, c->max_batch, 0);
-  launch_fill_i32(c->stream, c->accept_arrive, c->max_batch, 0);
-  launch_fill_i32(c->stream, c->vws.sample_arrive, sample_rows_shared(c->logit_cap), 0);
+  launch_fill_i32(c->stream, c->accept_arrive, c->max_batch * ARRIVE_STRIDE, 0);
+  launch_fill_i32(c->stream, c->vws.arrive, c->logit_cap * ARRIVE_STRIDE, 0);
+  launch_fill_i32(c->stream, c->vws.sample_arrive, sample_rows_shared(c->logit_cap) * ARRIVE_STRIDE, 0);
   if (c->tile_counters) launch_fill_i32(c->stream, c->tile_counters, TILE_COUNTER_CAP, 0);
   if (c->pair_buf) launch_fill_i32(c->stream, (int32_t*)c->pair_buf, PAIR_CAP * 256 * 2, 0);
   if (accept_static_scratch(nullptr, nullptr)) { (void)hipGetLastError(); free(c->pk); free(c->layers); free(c); return fail(S2D2_ELAUNCH, "could not look up the device address of the library's scratch array"); }
@@ -789,7 +787,7 @@ int32_t s2d2_accept_static(void* stream, int32_t vocab, const s2d2_block_state* 
   if (accept_static_scratch(&tiles, &arrivals)) return fail(S2D2_ELAUNCH, "s2d2_accept_static: could not look up the device address of the library's scratch array");
   hipStream_t s = (hipStream_t)stream;
   // the array keeps what the last call left: the arrival counters must start at zero (a fill kernel, no memset node)
-  launch_fill_i32(s, arrivals, N, 0);
+  launch_fill_i32(s, arrivals, N * ARRIVE_STRIDE, 0);
   launch_accept(s, N, B, vocab, prm->seed, prm->step, prm->step_dev, prm->gamma, prm->resample, inv_temperature(prm),
                 draft->span_start, draft->span_len, draft->logits, draft->logit_row_of, ver->logits_ver, ver->logit_row_of,
                 draft->xhat, draft->p, draft->lse, ver->q, ver->lse_ver, st->block_tokens, out->n_accept, out->n_commit,
@@ -977,8 +975,7 @@ int32_t s2d2_vocab_draft_stats(s2d2_ctx* c, const float* logits, int32_t rows, i
   if (!logits || !xhat || !p || !lse || !margin || !entropy_n) return fail(S2D2_EINVAL, "NULL argument");
   if ((uintptr_t)logits & 15) return fail(S2D2_EINVAL, "logits must be 16-byte aligned");
   if (rows == 0) return S2D2_OK;
-  S2D2_LAUNCH(set_i32_kernel, dim3(1), dim3(1), 0, c->stream, c->tmp_count, rows);
-  launch_vocab_draft(c->stream, logits, c->desc.vocab, c->tmp_count, rows, c->vws, nullptr, nullptr, 0, xhat, p, lse,
+  launch_vocab_draft(c->stream, logits, c->desc.vocab, nullptr, rows, c->vws, nullptr, nullptr, 0, xhat, p, lse,
                      margin, entropy_n, VocabSample{false, 1.0f, 0, 0, nullptr});
   return check_launch("s2d2_vocab_draft_stats");
 }
@@ -989,8 +986,7 @@ int32_t s2d2_vocab_score(s2d2_ctx* c, const float* logits_ver, int32_t rows, con
   if (!logits_ver || !token || !q || !lse) return fail(S2D2_EINVAL, "NULL argument");
   if ((uintptr_t)logits_ver & 15) return fail(S2D2_EINVAL, "logits must be 16-byte aligned");
   if (rows == 0) return S2D2_OK;
-  S2D2_LAUNCH(set_i32_kernel, dim3(1), dim3(1), 0, c->stream, c->tmp_count, rows);
-  launch_vocab_score(c->stream, logits_ver, c->desc.vocab, c->tmp_count, rows, c->vws, nullptr, nullptr, 0, token, q, lse, 1.0f);
+  launch_vocab_score(c->stream, logits_ver, c->desc.vocab, nullptr, rows, c->vws, nullptr, nullptr, 0, token, q, lse, 1.0f);
   return check_launch("s2d2_vocab_score");
 }
 

@@ -372,9 +372,12 @@ void launch_stream_ts_copy(hipStream_t st, void* out); // timing build only
 size_t attention_generic_lds_bytes(const KvGeom& g, int max_window_rows);
 
 // vocab.hip
+// Words between two arrival counters: one each to a memory channel's stretch of addresses (next to each other all arrivals of a launch are counted by one channel).
+constexpr int ARRIVE_STRIDE = 64;
 struct VocabWs {
   float* part;       // [rows_cap_logits, chunks, 8] partial statistics
   int32_t chunks;    // chunks per row
+  int32_t* arrive;   // [rows_cap_logits] arrival counters of the rows' chunks, zero between launches
   float* sample_tiles;      // [sample_rows_shared, vocabulary tiles] tile sums of the rows whose draw several workgroups share
   int32_t* sample_arrive;   // [sample_rows_shared] their arrival counters, zero between launches
 };

@@ -24,6 +24,11 @@ static constexpr int VT = 4;
 static int sample_share(int rows) { return std::max(1, std::min(8, 256 / rows)); }
 int sample_rows_shared(int rows) { return std::min(rows, 128); }   // most rows with more than one
 
+// Workgroups of the statistics, and with them chunks per workgroup, up to one per lane of the wavefront that merges them: four for each of 256 compute
+// units, all resident.  768 / 1024 / 1280 / 2048 / 2560, us, rows of 151936 logits: 64 rows 13.6 / 13.5 / 14.9 / 15.0 / 23.1, 256 31.8 / 32.9 / 31.8 / 32.0 / 32.4,
+// 1024 104.6 / 105.5 / 106.1 / 107.3 / 106.8.
+static constexpr int STATS_WGS = 1024, STATS_MOST = 64;
+
 int vocab_chunks(int V) { return (V + 1024 * VT - 1) / (1024 * VT); }
 
 struct Stat {
@@ -73,135 +78,159 @@ __device__ __forceinline__ float wave_all(float v, const F& op) {
   return op(v, __shfl_xor(v, 32, 64));
 }
 
-// part[row][chunk][8] = {m, z, e, m2, arg}
+// What becomes of a row's statistics: outputs at [sequence of the row][block index], or [row] without logit_seq.
+struct VocabOut {
+  const int32_t *logit_seq, *logit_idx;
+  int B;
+  const int32_t* token;                      // scores: the token of each place
+  int32_t* xhat;                             // proposals and their statistics
+  float *p, *lse, *margin, *entropy_n, *q;   // (q and lse: scores)
+};
+__device__ __forceinline__ int vocab_place(const VocabOut& f, int row) { return f.logit_seq ? f.logit_seq[row] * f.B + f.logit_idx[row] : row; }
+
+// SampleFromLogits (greedy): x_hat = arg-max, p = softmax probability of it, plus lse, margin, H/ln V.
+// ScoreFromLogits: q = softmax(logits_ver)[token], lse.  tok, x: the token and its logit.
+template <bool SCORE>
+__device__ __forceinline__ void vocab_finish(const Stat& s, const VocabOut& f, int o, int V, int tok, float x) {
+  const float l = s.m + logf(s.z);
+  f.lse[o] = l;
+  if (SCORE) {
+    f.q[o] = (tok >= 0 && tok < V) ? expf(x - l) : 0.f;
+  } else {
+    const float inv = 1.0f / s.z;
+    f.xhat[o] = s.arg < V ? s.arg : 0;   // no comparable logit in the row (all NaN): the first index, as an arg-max over NaNs gives
+    f.p[o] = inv;
+    f.margin[o] = inv - expf(s.m2 - s.m) * inv;
+    f.entropy_n[o] = fmaxf(0.f, logf(s.z) - s.e * inv) / logf((float)V);
+  }
+}
+
+// part[row][chunk][8] = {m, z, e, m2, arg}; the workgroup of a row that counts its arrival last merges the row's chunks and finishes it
+// (arrive: a counter per row, zero between launches): a lane per chunk, then a butterfly over the lanes, a fixed order (stat_merge is
+// symmetric, ties go to the lower index).  Nobody waits for another workgroup.
 // inv_t: 1 / temperature (1 in greedy mode: the multiplication is then exact); all statistics are those of
 // softmax(logits * inv_t).
 //
 // Bound: reading the logits, with the vector ALU close behind (ten instructions and an exponential a logit).  The exponentials
 // are taken against the wavefront's maximum, so that only sums are left to reduce over its lanes; with each lane's own maximum
-// and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions:
-// rows of 151936 logits, us per launch before / now: 4 rows 5.6 / 4.9, 64 13.4 / 11.3, 256 33.4 / 28.2 (4.7 / 5.5 TB/s), 1024
-// (eight float4 a lane before) 106 / 98 (6.3 TB/s).
-__global__ __launch_bounds__(256) void vocab_partial_kernel(const float* __restrict__ logits, int V,
-                                                            const int32_t* __restrict__ count, int chunks,
-                                                            float inv_t, float* __restrict__ part) {
-  __shared__ Stat s_w[4];
-  const int row = blockIdx.y, chunk = blockIdx.x;
-  if (row >= *count) return;
+// and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions.
+// A workgroup walks a run of chunks with the next one requested and arrives once.  Rows of 151936 logits, us, a workgroup per chunk and a launch
+// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.7, 64 14.9 / 12.5, 128 20.4 / 18.9, 256 32.1 / 32.2 (4.8 TB/s), 512 55.9 / 56.9, 1024 103.9 / 104.8
+// (an arrival per chunk instead: 256 rows 50, each end of a workgroup a store's way and an atomic's).
+template <bool SCORE>
+__global__ __launch_bounds__(256) void vocab_stats_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,
+                                                          int chunks, int per, float inv_t, float* __restrict__ part, int32_t* __restrict__ arrive,
+                                                          const VocabOut f) {
+  __shared__ Stat s_w[STATS_MOST][4];
+  const int row = blockIdx.y, c0 = blockIdx.x * per, mine = min(per, chunks - c0);   // chunks c0 .. c0 + mine - 1
+  if (count && row >= *count) return;
   const float* x = logits + (size_t)row * V;
-  const int base = chunk * 1024 * VT;
   const int tid = threadIdx.x;
-  float v[4 * VT];
-  const bool vec_ok = (V & 3) == 0;
+  auto load = [&](int c, f32x4_t (&v)[VT], auto vec) __attribute__((always_inline)) {
 #pragma unroll
-  for (int t = 0; t < VT; ++t) {
-    const int i = base + t * 1024 + tid * 4;
-    if (vec_ok && i + 3 < V) {
-      const f32x4_t f = ld_stream((const f32x4_t*)(x + i));
-      v[4 * t] = f[0] * inv_t; v[4 * t + 1] = f[1] * inv_t; v[4 * t + 2] = f[2] * inv_t; v[4 * t + 3] = f[3] * inv_t;
-    } else {
+    for (int t = 0; t < VT; ++t) {
+      const int i = (c0 + c) * 1024 * VT + t * 1024 + tid * 4;
+      if (decltype(vec)::value) v[t] = ld_stream((const f32x4_t*)(x + min(i, V - 4)));   // (past the end: not looked at)
+      else
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * t + e] = (i + e < V) ? x[i + e] * inv_t : -INFINITY;
+        for (int e = 0; e < 4; ++e) v[t][e] = x[min(i + e, V - 1)];
     }
-  }
-  float lm = -INFINITY, lm2 = -INFINITY;   // this lane's largest and second largest logit; the place of the first largest
-  int at = 0;
+  };
+  // statistics of one chunk's logits, over the wavefront
+  auto reduce = [&](int c, const f32x4_t (&r)[VT]) __attribute__((always_inline)) {
+    const int base = (c0 + c) * 1024 * VT;
+    float v[4 * VT];
 #pragma unroll
-  for (int t = 0; t < 4 * VT; ++t) {
-    at = v[t] > lm ? t : at;
-    lm2 = __builtin_amdgcn_fmed3f(v[t], lm, lm2);
-    lm = fmaxf(lm, v[t]);
-  }
-  auto larger = [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); };
-  auto sum = [](float a, float b) __attribute__((always_inline)) { return a + b; };
-  Stat s = stat_empty();
-  s.m = wave_all(lm, larger);
-  const bool own = lm > -INFINITY;   // (a lane without a comparable logit adds nothing)
-  float z = 0.f, e = 0.f;
-  if (own) {
+    for (int t = 0; t < 4 * VT; ++t) v[t] = base + (t >> 2) * 1024 + tid * 4 + (t & 3) < V ? r[t >> 2][t & 3] * inv_t : -INFINITY;
+    float lm = -INFINITY, lm2 = -INFINITY;   // this lane's largest and second largest logit; the place of the first largest
+    int at = 0;
 #pragma unroll
     for (int t = 0; t < 4 * VT; ++t) {
-      const float d = v[t] - s.m;
-      const float ex = __expf(d);          // exp(-inf) = 0 for padded slots
-      z += ex;
-      e = __builtin_fmaf(ex, fmaxf(d, -200.f), e);   // (-inf would make 0 * -inf; exp is 0 well above -200)
+      at = v[t] > lm ? t : at;
+      lm2 = __builtin_amdgcn_fmed3f(v[t], lm, lm2);
+      lm = fmaxf(lm, v[t]);
+    }
+    auto larger = [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); };
+    auto sum = [](float a, float b) __attribute__((always_inline)) { return a + b; };
+    Stat s = stat_empty();
+    s.m = wave_all(lm, larger);
+    const bool own = lm > -INFINITY;   // (a lane without a comparable logit adds nothing)
+    float z = 0.f, e = 0.f;
+    if (own) {
+#pragma unroll
+      for (int t = 0; t < 4 * VT; ++t) {
+        const float d = v[t] - s.m;
+        const float ex = __expf(d);          // exp(-inf) = 0 for padded slots
+        z += ex;
+        e = __builtin_fmaf(ex, fmaxf(d, -200.f), e);   // (-inf would make 0 * -inf; exp is 0 well above -200)
+      }
+    }
+    s.z = wave_all(z, sum);
+    s.e = wave_all(e, sum);
+    const unsigned long long top = __ballot(own && lm == s.m);   // the lanes that hold the maximum
+    const bool one = __popcll(top) == 1;
+    s.m2 = wave_all(one && lm == s.m ? lm2 : lm, larger);
+    if (top) {
+      const int i = base + (at >> 2) * 1024 + tid * 4 + (at & 3);
+      s.arg = __builtin_amdgcn_readlane(i, __ffsll((long long)top) - 1);
+      if (!one)
+        for (unsigned long long rest = top & (top - 1); rest; rest &= rest - 1) s.arg = min(s.arg, __builtin_amdgcn_readlane(i, __ffsll((long long)rest) - 1));
+    }
+    if ((tid & 63) == 0) s_w[c][tid >> 6] = s;
+  };
+  auto walk = [&](auto vec) __attribute__((always_inline)) {   // a chunk is requested ahead of the one before it being reduced
+    f32x4_t a[VT], b[VT];
+    load(0, a, vec);
+    for (int c = 0; c < mine; c += 2) {
+      if (c + 1 < mine) load(c + 1, b, vec);
+      reduce(c, a);
+      if (c + 1 < mine) {
+        if (c + 2 < mine) load(c + 2, a, vec);
+        reduce(c + 1, b);
+      }
+    }
+  };
+  if ((V & 3) == 0) walk(std::true_type{});
+  else walk(std::false_type{});
+  const int o = vocab_place(f, row);
+  int tok = 0;
+  float xt = 0.f;
+  if (SCORE) {
+    tok = f.token[o];
+    xt = x[tok >= 0 && tok < V ? tok : 0] * inv_t;
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  Stat r = stat_empty();
+  if (tid < mine) r = stat_merge(stat_merge(s_w[tid][0], s_w[tid][1]), stat_merge(s_w[tid][2], s_w[tid][3]));
+  if (gridDim.x > 1) {
+    if (tid < mine) {
+      float* po = part + ((size_t)row * chunks + c0 + tid) * 8;
+      st16f_coh(po, r.m, r.z, r.e, r.m2);
+      st4f_coh(po + 4, __int_as_float(r.arg));
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // the write-through stores have completed before the arrival is counted
+    int last = 0;
+    if (tid == 0) {
+      last = __hip_atomic_fetch_add(&arrive[row * ARRIVE_STRIDE], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+      if (last) __hip_atomic_store(&arrive[row * ARRIVE_STRIDE], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    r = stat_empty();
+    for (int c = tid; c < chunks; c += 64) {
+      const float* pc = part + ((size_t)row * chunks + c) * 8;
+      r = stat_merge(r, Stat{ld4f_coh(pc), ld4f_coh(pc + 1), ld4f_coh(pc + 2), ld4f_coh(pc + 3), __float_as_int(ld4f_coh(pc + 4))});
     }
   }
-  s.z = wave_all(z, sum);
-  s.e = wave_all(e, sum);
-  const unsigned long long top = __ballot(own && lm == s.m);   // the lanes that hold the maximum
-  const bool one = __popcll(top) == 1;
-  s.m2 = wave_all(one && lm == s.m ? lm2 : lm, larger);
-  if (top) {
-    const int i = base + (at >> 2) * 1024 + tid * 4 + (at & 3);
-    s.arg = __builtin_amdgcn_readlane(i, __ffsll((long long)top) - 1);
-    if (!one)
-      for (unsigned long long rest = top & (top - 1); rest; rest &= rest - 1) s.arg = min(s.arg, __builtin_amdgcn_readlane(i, __ffsll((long long)rest) - 1));
-  }
-  if ((tid & 63) == 0) s_w[tid >> 6] = s;
-  __syncthreads();
-  if (tid == 0) {
-    Stat r = stat_merge(stat_merge(s_w[0], s_w[1]), stat_merge(s_w[2], s_w[3]));
-    float* o = part + ((size_t)row * chunks + chunk) * 8;
-    o[0] = r.m; o[1] = r.z; o[2] = r.e; o[3] = r.m2; o[4] = __int_as_float(r.arg);
-  }
-}
-
-static void launch_partial(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t) {
-  S2D2_LAUNCH(vocab_partial_kernel, dim3(ws.chunks, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, inv_t, ws.part);
-}
-
-// Chunk partials of one row, merged by one wavefront: lane c takes chunks c, c + 64, ..., then a butterfly over the
-// lanes (a fixed order; stat_merge is symmetric, ties go to the lower index).  One thread walking the 38 chunks of a
-// 152k vocabulary one after the other took 8-10 us per launch.  Lane 0's result is the one that is used.
-__device__ __forceinline__ Stat merge_chunks(const float* part, int row, int chunks) {
-  Stat r = stat_empty();
-  for (int c = threadIdx.x & 63; c < chunks; c += 64) {
-    const float* o = part + ((size_t)row * chunks + c) * 8;
-    Stat s{o[0], o[1], o[2], o[3], __float_as_int(o[4])};
-    r = stat_merge(r, s);
-  }
   for (int off = 1; off < 64; off <<= 1) r = stat_merge(r, stat_shfl_xor(r, off));
-  return r;
+  if (tid == 0) vocab_finish<SCORE>(r, f, o, V, tok, xt);
 }
 
-// SampleFromLogits (greedy): x_hat = arg-max, p = softmax probability of it, plus lse, margin, H/ln V.
-__global__ void vocab_draft_final_kernel(const float* __restrict__ part, int chunks, int V,
-                                         const int32_t* __restrict__ count,
-                                         const int32_t* __restrict__ logit_seq,
-                                         const int32_t* __restrict__ logit_idx, int B,
-                                         int32_t* __restrict__ xhat, float* __restrict__ p,
-                                         float* __restrict__ lse, float* __restrict__ margin,
-                                         float* __restrict__ entropy_n) {
-  const int row = blockIdx.x;   // one wavefront per logit row
-  if (row >= *count) return;
-  const Stat s = merge_chunks(part, row, chunks);
-  if (threadIdx.x != 0) return;
-  const int o = logit_seq ? logit_seq[row] * B + logit_idx[row] : row;
-  const float inv = 1.0f / s.z;
-  xhat[o] = s.arg < V ? s.arg : 0;   // no comparable logit in the row (all NaN): the first index, as an arg-max over NaNs gives
-  p[o] = inv;
-  lse[o] = s.m + logf(s.z);
-  margin[o] = inv - expf(s.m2 - s.m) * inv;
-  entropy_n[o] = fmaxf(0.f, logf(s.z) - s.e * inv) / logf((float)V);
-}
-
-// ScoreFromLogits: q = softmax(logits_ver)[token], lse.
-__global__ void vocab_score_final_kernel(const float* __restrict__ part, int chunks, int V,
-                                         const float* __restrict__ logits, const int32_t* __restrict__ count,
-                                         const int32_t* __restrict__ logit_seq,
-                                         const int32_t* __restrict__ logit_idx, int B,
-                                         const int32_t* __restrict__ token, float inv_t, float* __restrict__ q,
-                                         float* __restrict__ lse) {
-  const int row = blockIdx.x;   // one wavefront per logit row
-  if (row >= *count) return;
-  const Stat s = merge_chunks(part, row, chunks);
-  if (threadIdx.x != 0) return;
-  const int o = logit_seq ? logit_seq[row] * B + logit_idx[row] : row;
-  const float l = s.m + logf(s.z);
-  const int tok = token[o];
-  lse[o] = l;
-  q[o] = (tok >= 0 && tok < V) ? expf(logits[(size_t)row * V + tok] * inv_t - l) : 0.f;
+template <bool SCORE>
+static void launch_stats(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap, const VocabWs& ws, float inv_t, const VocabOut& f) {
+  const int wgs = std::max(1, STATS_WGS / rows_cap), per = std::min((ws.chunks + wgs - 1) / wgs, STATS_MOST);
+  S2D2_LAUNCH((vocab_stats_kernel<SCORE>), dim3((ws.chunks + per - 1) / per, rows_cap), dim3(256), 0, st, logits, V, count, ws.chunks, per, inv_t, ws.part,
+              ws.arrive, f);
 }
 
 __global__ void vocab_sample_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,
@@ -214,9 +243,7 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         int32_t* xhat, float* p, float* lse, float* margin, float* entropy_n, const VocabSample& sm) {
   const float inv_t = sm.sample ? 1.0f / sm.temperature : 1.0f;
-  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_draft_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
-                     count, logit_seq, logit_idx, B, xhat, p, lse, margin, entropy_n);
+  launch_stats<false>(st, logits, V, count, rows_cap, ws, inv_t, VocabOut{logit_seq, logit_idx, B, nullptr, xhat, p, lse, margin, entropy_n, nullptr});
   if (sm.sample)
     S2D2_LAUNCH(vocab_sample_kernel, dim3(rows_cap, sample_share(rows_cap)), dim3(1024), 0, st, logits, V, count, logit_seq, logit_idx, B,
                 sm.seed, sm.step, sm.step_dev, inv_t, lse, xhat, p, ws.sample_tiles, ws.sample_arrive);
@@ -225,9 +252,7 @@ void launch_vocab_draft(hipStream_t st, const float* logits, int V, const int32_
 void launch_vocab_score(hipStream_t st, const float* logits, int V, const int32_t* count, int rows_cap,
                         const VocabWs& ws, const int32_t* logit_seq, const int32_t* logit_idx, int B,
                         const int32_t* token, float* q, float* lse, float inv_t) {
-  launch_partial(st, logits, V, count, rows_cap, ws, inv_t);
-  S2D2_LAUNCH(vocab_score_final_kernel, dim3(rows_cap), dim3(64), 0, st, ws.part, ws.chunks, V,
-                     logits, count, logit_seq, logit_idx, B, token, inv_t, q, lse);
+  launch_stats<true>(st, logits, V, count, rows_cap, ws, inv_t, VocabOut{logit_seq, logit_idx, B, token, nullptr, nullptr, lse, nullptr, nullptr, q});
 }
 
 // Per sequence: defaults for committed positions, threshold set S = {i in M: p_i > tau} U {argmax p}.
@@ -477,7 +502,7 @@ __global__ __launch_bounds__(1024) void vocab_sample_kernel(
   if (gridDim.y == 1) {
     token = inverse_cdf_block(prob4, V, u, s_tile, s_w, &s_tile_sel, &s_before);
   } else {
-    if (!share_tile_sums(prob4, V, blockIdx.y, gridDim.y, tile_scratch + (size_t)row * ((V + RTILE - 1) / RTILE), &arrivals[row], s_tile, &s_last)) return;
+    if (!share_tile_sums(prob4, V, blockIdx.y, gridDim.y, tile_scratch + (size_t)row * ((V + RTILE - 1) / RTILE), &arrivals[row * ARRIVE_STRIDE], s_tile, &s_last)) return;
     token = inverse_cdf_finish(prob4, V, u, s_tile, s_w, &s_tile_sel, &s_before);
   }
   if (threadIdx.x == 0 && token >= 0) {   // (no mass cannot happen for a softmax; the arg-max proposal would stay)
@@ -558,7 +583,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(
   if (G == 1) {
     token = inverse_cdf_block(residual4, V, u2, s_tile, s_w, &s_tile_sel, &s_before);
   } else {
-    if (!share_tile_sums(residual4, V, g, G, tile_scratch + (size_t)n * ((V + RTILE - 1) / RTILE), &arrivals[n], s_tile, &s_last)) return;
+    if (!share_tile_sums(residual4, V, g, G, tile_scratch + (size_t)n * ((V + RTILE - 1) / RTILE), &arrivals[n * ARRIVE_STRIDE], s_tile, &s_last)) return;
     token = inverse_cdf_finish(residual4, V, u2, s_tile, s_w, &s_tile_sel, &s_before);
   }
   if (tid == 0) {
@@ -593,8 +618,8 @@ size_t tile_sum_floats(int rows, int V) { return (size_t)rows * ((V + RTILE - 1)
 // is looked up once per device and only that pointer is ever passed to a kernel.
 // ---------------------------------------------------------------------------------------------
 static constexpr size_t STATIC_TILE_FLOATS = (size_t)ACCEPT_STATIC_MAX_BATCH * (ACCEPT_STATIC_MAX_VOCAB / RTILE);
-static constexpr size_t STATIC_SCRATCH_BYTES = STATIC_TILE_FLOATS * sizeof(float) + ACCEPT_STATIC_MAX_BATCH * sizeof(int32_t);
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];   // 512.5 KB per GPU, held until the process ends
+static constexpr size_t STATIC_SCRATCH_BYTES = STATIC_TILE_FLOATS * sizeof(float) + ACCEPT_STATIC_MAX_BATCH * ARRIVE_STRIDE * sizeof(int32_t);
+static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];   // 544 KB per GPU, held until the process ends
 
 static constexpr int STATIC_MAX_DEVICES = 64;
 static std::mutex g_scratch_mutex;
