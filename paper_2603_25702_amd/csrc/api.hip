@@ -414,7 +414,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   const int PQ = fused && flash && opm != OPM_BF16 && !q_f16 ? 2 : 1;
   const int ld_q = PQ * HqD, lo_q = q_f16 ? LO_F16 : (PQ == 2 ? HqD : 0);
   if (fused) { ProfScope ps(c, 3, 0.0); launch_embed_norm(st, c->w.embed, d.d_model, c->plan, R, c->layers[0].norm1, c->h, c->a, ld_a, lo_a, c->ss, ss_stride, c->rope_cs, d.head_dim, d.rope_theta); }
-  else { ProfScope ps(c, 3, 0.0); launch_embed(st, dt, c->w.embed, d.d_model, c->plan, R, c->h); }
+  else { ProfScope ps(c, 3, 0.0); launch_embed_rmsnorm(st, dt, c->w.embed, d.d_model, c->plan, R, c->layers[0].norm1, d.rms_eps, d.head_dim, d.rope_theta, c->h, c->a, c->rope_cs); }
   int ss_count = 1;   // partial sums of squares per residual row that the last producer left
   for (int l = 0; l < d.n_layers; ++l) {
     const s2d2_layer_weights& L = c->layers[l];
@@ -432,9 +432,9 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       ProfScope ps(c, 0, (double)qkv_n * d.d_model * es, fr * qkv_n * d.d_model, 4);
       sk(a); launch_gemm_stream(st, SEPI_QKV_ROPE, a, R, pick[4]);
     } else {
-      { ProfScope ps(c, 3, 0.0); launch_rmsnorm(st, dt, c->h, L.norm1, d.d_model, d.rms_eps, n_rows, nullptr, R, c->a); }
+      if (l > 0) { ProfScope ps(c, 3, 0.0); launch_rmsnorm(st, dt, c->h, L.norm1, d.d_model, d.rms_eps, n_rows, nullptr, R, c->a); }
       { ProfScope ps(c, 0, (double)qkv_n * d.d_model * es, fr * qkv_n * d.d_model, 4); launch_gemm(st, dt, EPI_STORE_F32, c->a, d.d_model, L.wqkv, d.d_model, qkv_n, n_rows, R, c->qkv, qkv_n); }
-      { ProfScope ps(c, 3, 0.0); launch_rope_split(st, dt, c->qkv, c->plan, R, d.n_q_heads, d.n_kv_heads, d.head_dim, d.rope_theta, c->qbuf, kw, vw, flash ? c->vT_win : nullptr, c->wpad); }
+      { ProfScope ps(c, 3, 0.0); launch_rope_split(st, dt, c->qkv, c->plan, R, d.n_q_heads, d.n_kv_heads, d.head_dim, c->rope_cs, c->qbuf, kw, vw, flash ? c->vT_win : nullptr, c->wpad); }
     }
     if (LR == 0 && l == d.n_layers - 1) return check_launch("forward");
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;

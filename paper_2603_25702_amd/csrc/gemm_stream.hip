@@ -58,23 +58,6 @@ void launch_pack_weight(hipStream_t st, const void* W, int N, int K, int rope_pa
                      K, NT, KT, rope_pairs, D, (uint4*)out, to_f16);
 }
 
-// cos / sin of pos * theta^(-2i/D) for every window row (fp64 phase), [rows, D/2] float2
-__global__ void rope_table_kernel(Plan p, int half, int D, float theta, float2* __restrict__ cs) {
-  const int r = blockIdx.x;
-  if (r >= p.counts[0]) return;
-  const double pos = (double)p.row_pos[r];
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const double inv = exp2(-2.0 * (double)i / (double)D * log2((double)theta));
-    double s, c;
-    sincos(pos * inv, &s, &c);
-    cs[(size_t)r * half + i] = make_float2((float)c, (float)s);
-  }
-}
-
-void launch_rope_table(hipStream_t st, const Plan& p, int rows_cap, int D, float theta, void* cs) {
-  S2D2_LAUNCH(rope_table_kernel, dim3(rows_cap), dim3(64), 0, st, p, D / 2, D, theta, (float2*)cs);
-}
-
 // ---------------------------------------------------------------------------------------------
 // Latency matters as much as bandwidth here (a layer's matrices are 8-50 MB, a few microseconds
 // of HBM time each), so every global load of a wavefront is in flight at once: its weight
@@ -470,7 +453,7 @@ int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_
 }
 
 // First norm of the forward: xg = bf16(h * gain), one partial sum of squares per row; and the row's RoPE table
-// (cos / sin of pos * theta^(-2i/D), fp64 phase) when cs is given, which saves the launch of rope_table_kernel.
+// (cos / sin of pos * theta^(-2i/D), fp64 phase) when cs is given, which saves a launch.
 __global__ __launch_bounds__(256) void embed_norm_kernel(const bf16_t* __restrict__ embed, int d, Plan p,
                                                          const float* __restrict__ gain, float* __restrict__ h,
                                                          bf16_t* __restrict__ xg, int xg_ld, int xg_lo,

@@ -218,12 +218,14 @@ void launch_commit_threshold(hipStream_t st, int N, int B, int32_t* block, const
                              const uint64_t* unmask);
 
 // elementwise.hip
-void launch_embed(hipStream_t st, int dtype, const void* embed, int d, const Plan& p, int rows_cap, float* h);
+// h = the rows' embeddings, out = their rmsnorm * gain as `dtype`, cs[row, D/2] = cos / sin of the rows' rotations
+void launch_embed_rmsnorm(hipStream_t st, int dtype, const void* embed, int d, const Plan& p, int rows_cap, const float* gain, float eps, int D, float theta,
+                          float* h, void* out, void* cs);
 // out[r] = rmsnorm(h[src(r)]) * gain as `dtype`; src = gather[r] if gather else r; rows from *count.
 void launch_rmsnorm(hipStream_t st, int dtype, const float* h, const float* gain, int d, float eps,
                     const int32_t* count, const int32_t* gather, int rows_cap, void* out);
 void launch_rope_split(hipStream_t st, int dtype, const float* qkv, const Plan& p, int rows_cap, int Hq,
-                       int Hkv, int D, float theta, void* q_out, void* k_out, void* v_out, void* vT_out, int wpad);
+                       int Hkv, int D, const void* cs, void* q_out, void* k_out, void* v_out, void* vT_out, int wpad);
 
 // gemm.hip : Y[m, n] = sum_k X[m, k] * W[n, k], X and W in `dtype`, fp32 accumulation.
 void launch_gemm(hipStream_t st, int dtype, GemmEpilogue epi, const void* X, int ldx, const void* W, int K,
@@ -298,7 +300,6 @@ struct GemmStreamArgs {
 };
 size_t packed_weight_bytes(int N, int K);
 void launch_pack_weight(hipStream_t st, const void* W, int N, int K, int rope_pairs, int D, void* out, int to_f16 /* convert bf16 -> half */);
-void launch_rope_table(hipStream_t st, const Plan& p, int rows_cap, int D, float theta, void* cs);
 void launch_embed_norm(hipStream_t st, const void* embed, int d, const Plan& p, int rows_cap, const float* gain,
                        float* h, void* xg, int xg_ld, int xg_lo, float* ss, int ss_stride,
                        void* rope_cs /* [rows, D/2] (cos, sin), may be NULL */, int D, float theta);
