@@ -60,17 +60,25 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   // pages of the first V values, the key, the V values.  Behind the query's store to LDS only those are in flight.
   const float q0 = tid < D ? to_f32(q[((size_t)r * Hq + hq) * D + tid]) : 0.f;
   const int part = tid & 3, quarter = tid >> 8, t8 = tid & 255, d = t8 % D, sl = t8 / D;
-  // (a load under a condition is waited for before the next one: without cached keys the first page is looked up all the same)
+  // Places in the cache: division by a page size that is a power of two is a shift (thirteen divisions per thread are a fifth of the launch's instructions), and
+  // a block's number (n_pages Hkv) fits 32 bits, as a block is 128 bytes or more.
+  const bool p2 = (ps & (ps - 1)) == 0;
+  const int sh = 31 - __builtin_clz(ps);
+  const uint32_t block = (uint32_t)ps * D;
+  auto cached_at = [&](int s) __attribute__((always_inline)) { return max(min(s, S - 1), 0); };   // (without cached keys the first page is looked up all the same: a load under a condition is waited for before the next one)
   auto place = [&](int s, int& page, int& slot) __attribute__((always_inline)) {
-    const int c = max(min(s, S - 1), 0), i = c / ps;
+    const int c = cached_at(s);
+    int i;
+    if (p2) i = c >> sh;
+    else i = c / ps;
     page = pt[i];
     slot = c - i * ps;
   };
-  auto page0 = [&](int page) __attribute__((always_inline)) { return (size_t)min(max(page, 0), g.n_pages - 1) * Hkv + kvh; };
-  auto win0 = [&](int s) __attribute__((always_inline)) { return (size_t)(row0 + max(s - S, 0)) * Hkv + kvh; };
+  auto page0 = [&](int page) __attribute__((always_inline)) { return (uint64_t)((uint32_t)min(max(page, 0), g.n_pages - 1) * (uint32_t)Hkv + kvh) * block; };
+  auto win0 = [&](int s) __attribute__((always_inline)) { return (uint64_t)((uint32_t)(row0 + max(s - S, 0)) * (uint32_t)Hkv + kvh) * (uint32_t)D; };
   auto key_row = [&](int s, int page, int slot) __attribute__((always_inline)) {
-    const T* cached = k_pages + (page0(page) * ps + slot) * D;
-    const T* own = k_win + win0(s) * D;
+    const T* cached = k_pages + page0(page) + (uint32_t)slot * (uint32_t)D;
+    const T* own = k_win + win0(s);
     return s < S ? cached : own;
   };
   uint4 kv[CB];   // pieces of the key's row that this lane adds next
@@ -83,15 +91,25 @@ __global__ __launch_bounds__(1024) void attn_generic_kernel(
   int vpage[VB], vslot[VB];
   auto key_of = [&](int e0, int u) __attribute__((always_inline)) { return sl + (e0 + quarter * VB + u) * NS; };
   auto find_v = [&](int e0) __attribute__((always_inline)) {
+    if (p2) {
 #pragma unroll
-    for (int u = 0; u < VB; ++u) place(key_of(e0, u), vpage[u], vslot[u]);
+      for (int u = 0; u < VB; ++u) vpage[u] = cached_at(key_of(e0, u)) >> sh;
+    } else {
+#pragma unroll
+      for (int u = 0; u < VB; ++u) vpage[u] = cached_at(key_of(e0, u)) / ps;
+    }
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+      vslot[u] = cached_at(key_of(e0, u)) - vpage[u] * ps;
+      vpage[u] = pt[vpage[u]];
+    }
   };
   auto load_v = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
       const int s = min(key_of(e0, u), total - 1);
-      const T* cached = v_pages + (page0(vpage[u]) * D + d) * ps + vslot[u];   // cache V is stored [D, page_size]
-      const T* own = v_win + win0(s) * D + d;
+      const T* cached = v_pages + page0(vpage[u]) + (uint32_t)(d * ps + vslot[u]);   // cache V is stored [D, page_size]
+      const T* own = v_win + win0(s) + (uint32_t)d;
       val[u] = *(s < S ? cached : own);
     }
   };
