@@ -283,19 +283,23 @@ KvGeom geom(const s2d2_ctx* c, const s2d2_kv_view* kv) {
                 c->desc.n_kv_heads, c->desc.head_dim};
 }
 
+struct FwdSize { int win, R, LR, hint; };
 // Shape of the wide attention launch: q_tiles 32-row query tiles per window; target key splits of all sequences together,
 // per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence and run tiles in one; LDS for
 // `tiles` key tiles at a time beside a split's share of the page table, 0 if that is too long.
-struct WideShape { int q_tiles, target, Z, tiles, run; };
-WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) {
+struct WideShape { int q_tiles, per, nw, target, Z, tiles, run; };
+WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, const FwdSize& sz) {
   WideShape w;
   const KvGeom g = geom(c, kv);
-  w.q_tiles = (win * (c->desc.n_q_heads / c->desc.n_kv_heads) + 31) / 32;
-  const int wg = c->desc.n_kv_heads * ((w.q_tiles + 7) / 8), nw = attention_wide_nw(w.q_tiles);
+  w.q_tiles = (sz.win * (c->desc.n_q_heads / c->desc.n_kv_heads) + 31) / 32;
+  const int Hkv = c->desc.n_kv_heads, expected = ((sz.hint + N - 1) / N * (c->desc.n_q_heads / Hkv) + 31) / 32;
+  w.per = attention_wide_per(w.q_tiles, expected);
+  w.nw = attention_wide_nw(w.per, N * Hkv * ((expected + w.per - 1) / w.per));
+  const int groups = (w.q_tiles + w.per - 1) / w.per, wg = Hkv * groups, nw = w.nw;
   // One workgroup of eight wavefronts per compute unit, two of four; where the page table is too long for that, more and shorter splits.
   for (int fill : {nw == 8 ? c->wide_wgs / 2 : c->wide_wgs, c->wide_wgs}) {
     w.target = std::max(1, std::min((fill + wg - 1) / wg, WIDE_MAX_TARGET));
-    w.Z = attention_wide_splits(g, N * c->desc.n_kv_heads, w.q_tiles, c->attn_part_entries, w.target);
+    w.Z = attention_wide_splits(g, N * Hkv, w.q_tiles, groups, c->attn_part_entries, w.target);
     w.run = attention_wide_run_most(g, N, w.Z, w.target);
     for (w.tiles = nw == 8 ? 2 : 1; w.tiles > 0; --w.tiles)
       if (attention_wide_lds_bytes(attention_wide_pt_cap(g, N, w.Z, w.target), w.tiles) <= 160 * 1024) return w;
@@ -306,7 +310,6 @@ WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, int win) 
 // One forward over the planned window rows; K/V of every window row go to k_stage/v_stage
 // ([n_layers, rows_cap, Hkv, D]) if given, else to a one-layer scratch.
 // Bounds of a forward: rows of one window, rows, logit rows of all windows, and the rows the caller expects.
-struct FwdSize { int win, R, LR, hint; };
 FwdSize draft_size(int N, int B) { return {2 * B, 2 * N * B, N * B, N * B}; }        // carry + block; a fresh block has B rows
 // carry + 2L; a fresh block has 2 B (more only with carried or pending committed tokens), of a right-shifted model lead + L - 1
 FwdSize verify_size(int N, int B, int shifted) { return {3 * B, 3 * N * B, N * B, (shifted ? 1 : 2) * N * B}; }
@@ -362,7 +365,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
   const KvGeom g = geom(c, kv);
   // MFMA flash attention for bf16 / head_dim 128 / pages that hold whole 8-key groups; else the generic kernel
   const bool flash = dt == S2D2_BF16 && d.head_dim == 128 && kv->page_size % 8 == 0;
-  const WideShape ws = wide_shape(c, kv, N, sz.win);
+  const WideShape ws = wide_shape(c, kv, N, sz);
   const int q_tiles = ws.q_tiles;   // 32-row query tiles of this call's windows
   int Z = 1;
   // several query tiles per (sequence, KV head): the kernel that shares K / V tiles among them
@@ -440,7 +443,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
     const void* kp = (const uint8_t*)kv->k_pages + l * page_layer;
     const void* vp = (const uint8_t*)kv->v_pages + l * page_layer;
     if (wide) {
-      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, Z, ws.target, ws.tiles, c->n_cus, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
+      { ProfScope ps(c, 1, 0.0); launch_attention_wide(st, c->qbuf, fused ? ld_q : HqD, fused ? lo_q : 0, q_f16 ? c->kwin16 : kw, c->vT_win, kp, vp, g, c->plan, N, d.n_q_heads, q_tiles, ws.per, ws.nw, Z, ws.target, ws.tiles, c->n_cus, c->wpad, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
       if (Z > 1) { ProfScope ps(c, 1, 0.0); launch_attention_wide_merge(st, g, c->plan, N, d.n_q_heads, q_tiles, Z, c->obuf, ld_o, lo_o, c->attn_part, c->attn_part_entries); }
     } else if (flash) {
       // Narrow windows of a few sequences: the launch is a chain of dependent round trips on a fraction of the
@@ -728,7 +731,7 @@ int32_t s2d2_draft(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state* 
   int32_t rc;
   if ((rc = check_state(c, st, N, B)) || (rc = check_kv(c, kv)) || (rc = check_params(prm)) || (rc = check_draft_out(out))) return rc;
   const s2d2_model_desc& d = c->desc;
-  const WideShape ws = wide_shape(c, kv, N, draft_size(N, B).win);
+  const WideShape ws = wide_shape(c, kv, N, draft_size(N, B));
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 0, d.right_shifted, N, B, d.mask_id, prm->ar_mask, kv->seq_len, st->block_pos0, st->block_tokens,
               st->carry_tokens, nullptr, c->plan, out->logit_row_of, out->span_start, out->span_len, nullptr, nullptr, nullptr, kv->status,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
@@ -748,7 +751,7 @@ int32_t s2d2_verify(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_block_state*
       (rc = check_draft_out(draft)) || (rc = check_verify_out(out)))
     return rc;
   const s2d2_model_desc& d = c->desc;
-  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, d.right_shifted).win);
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, d.right_shifted));
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, 1, d.right_shifted, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               draft->xhat, c->plan, out->logit_row_of, nullptr, nullptr, out->stage_row0, out->stage_lead, prm->active, kv->status,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run, out->q, out->lse_ver); }
@@ -816,7 +819,7 @@ int32_t s2d2_block_complete(s2d2_ctx* c, const s2d2_kv_view* kv, const s2d2_bloc
   const s2d2_model_desc& d = c->desc;
   if (d.right_shifted) return fail(S2D2_EINVAL, "s2d2_block_complete is not defined for right-shifted models (their cache lags one token)");
   if (causal != 0 && causal != 1) return fail(S2D2_EINVAL, "causal must be 0 or 1");
-  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, 0).win);
+  const WideShape ws = wide_shape(c, kv, N, verify_size(N, B, 0));
   { ProfScope ps(c, 3, 0.0); launch_plan(c->stream, causal ? 3 : 2, 0, N, B, d.mask_id, 1, kv->seq_len, st->block_pos0, st->block_tokens, st->carry_tokens,
               nullptr, c->plan, scratch->logit_row_of, nullptr, nullptr, scratch->stage_row0, scratch->stage_lead, nullptr, nullptr,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
@@ -840,7 +843,7 @@ int32_t s2d2_prefill(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, int32_t T, 
   if ((rc = check_kv(c, kv))) return rc;
   const s2d2_model_desc& d = c->desc;
   const FwdSize sz = prefill_size(N, T);
-  const WideShape ws = wide_shape(c, kv, N, sz.win);
+  const WideShape ws = wide_shape(c, kv, N, sz);
   { ProfScope ps(c, 3, 0.0); launch_plan_prefill(c->stream, N, T, d.mask_id, kv->seq_len, tokens, ld, n_tokens, c->plan,
               kv->max_pages_per_seq * kv->page_size, ws.target, ws.Z, ws.run); }
   if ((rc = forward(c, kv, N, sz, k_stage, v_stage, nullptr))) return rc;

@@ -587,12 +587,25 @@ static void launch_wide(hipStream_t st, int qm, dim3 grid, size_t lds, const bf1
 #undef S2D2_WIDE_QM
 }
 
-// Wavefronts per workgroup for q_tiles query tiles: as few query groups as 8-wavefront workgroups allow,
-// then the smallest supported workgroup that covers a group.
-int attention_wide_nw(int q_tiles) {
-  const int groups = (q_tiles + 7) / 8, need = (q_tiles + groups - 1) / groups;
-  return need <= 4 ? 4 : 8;   // (two wavefronts for two tiles measured slower: four share the fetch work, 3.76 -> 3.27 ms of attention per step on the 4B shape)
+// Query tiles of a workgroup, of q_tiles that there is room for and `expected` ones that have rows.  Up to five expected: one workgroup for up to
+// eight tiles, so that a tile of keys is fetched once (where at most four have rows its eight wavefronts stand in two key groups).  More: up to four
+// tiles, as many in every workgroup that has rows: cut by the room, half as much again for a verifier, one
+// workgroup had all rows but those of a tile or two.  Forwards, us, by the room in eights / expected in fours / expected in eights: 8B verification
+// of 16 sequences behind 2000 to 4000, 5 expected of 8 15317 / 15419 / 17404, 6 of 9 18923 / 16695 / 18751, 7 of 11 21599 / 20342 / 21436, 8 of 12 22561 / 21358 /
+// 22477; 4B 3 sequences 6 of 8 4566 / 4480 / 4478, 4 sequences 7 of 11 5488 / 5413 / 5468; MoE 6 sequences 8 of 12 5046 / 4991 / 5080; 1.7B prefill 12 of 12 15964 / 15723
+// / 15929.
+int attention_wide_per(int q_tiles, int expected) {
+  const int most = expected > 5 ? 4 : 8, over = expected > 5 ? expected : q_tiles, groups = (over + most - 1) / most;
+  return (over + groups - 1) / groups;
 }
+
+// Wavefronts of a workgroup: eight for more than four tiles, and for up to four where sequences, heads and groups are at most 128 workgroups ahead of the
+// key splits: four multiply every other tile each, or four fetch.  With more of them a launch has few splits to even out ragged caches with, and twice as
+// many workgroups of four are worth more.  (Two wavefronts for two tiles: slower, four share the fetch work.)  Forwards, us, four / eight wavefronts:
+// workgroups 40 1.7B verification in mid-block 1821 / 1717, 48 4B 6 tiles 4551 / 4351, 64 4B verification 4816 / 4732, 96 1.7B prefill 15824 / 15399, 96 4B draft behind
+// 4000 to 8000 5588 / 5510, 128 8B draft behind 8192 10777 / 10537, MoE verification 5232 / 5186, 192 8B draft behind 500 to 3000 8736 / 8932, 256 4B draft
+// 7064 / 7116, 8B verification of 6 tiles 16847 / 17866.
+int attention_wide_nw(int per, int wgs) { return per > 4 || wgs <= 128 ? 8 : 4; }
 
 // Most splits of a sequence: a split keeps at least four key tiles, the partials fit their buffer.  One, and so no merge
 // launch, where the cache holds so few tiles that cutting them saves less than that launch costs (2-3 us when nothing was
@@ -600,8 +613,8 @@ int attention_wide_nw(int q_tiles) {
 // uncut against cut, us: 32 sequences of block 8, 4B (256 workgroups) 6 tiles 6460 / 6700, 8 6614 / 6795, 10 6666 / 6916, 13
 // 6740 / 6846; 21 sequences, two planes (168) 6 tiles 7800 / 7943, 8 7916 / 8039, 10 7972 / 7999, 13 8153 / 8082; 16
 // sequences (128) 6 tiles 4762 / 4823, 8 4868 / 4839; one sequence (8) 6 tiles 1593 / 1574.
-int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target) {
-  const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32, wgs = items * ((q_tiles + 7) / 8);
+int attention_wide_splits(const KvGeom& g, int items, int q_tiles, int groups, size_t part_entries, int target) {
+  const int cap_tiles = (g.max_pages_per_seq * g.page_size + 31) / 32, wgs = items * groups;
   if (cap_tiles <= (wgs >= 256 ? 18 : wgs >= 128 ? 7 : WIDE_MIN_TILES)) return 1;
   int Z = std::max(1, std::min(std::min((cap_tiles + WIDE_MIN_TILES - 1) / WIDE_MIN_TILES, 64), target + 1));
   while (Z > 1 && (size_t)Z * items * q_tiles > part_entries) --Z;
@@ -620,11 +633,10 @@ int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target) {
 
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           int Hq, int q_tiles, int per, int nw, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)g.head_dim);
-  const int qgroups = (q_tiles + 7) / 8, per = (q_tiles + qgroups - 1) / qgroups;   // tiles per workgroup, balanced
-  const int nw = attention_wide_nw(q_tiles);
+  const int qgroups = (q_tiles + per - 1) / per;
   const int pt_cap = attention_wide_pt_cap(g, N, Z, target);
   float* part_o = part;
   float* part_ml = part + part_entries * 32 * FA_D;

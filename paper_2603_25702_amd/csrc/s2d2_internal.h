@@ -352,15 +352,16 @@ void launch_attention_flash(hipStream_t st, const void* q, int q_ld, int q_lo, c
                             int32_t* counters, const void* prefetch, size_t prefetch_bytes, int prefetch_wgs);
 // Several query tiles per (sequence, KV head): one workgroup shares each K / V tile among them.
 int attention_wide_init();
-int attention_wide_nw(int q_tiles);
+int attention_wide_per(int q_tiles, int expected);   // query tiles of a workgroup
+int attention_wide_nw(int per, int wgs /* sequences x KV heads x groups of tiles with rows */);
 constexpr int WIDE_MIN_TILES = 4;   // key tiles (of 32) a split of the wide kernel keeps at least
-int attention_wide_splits(const KvGeom& g, int items, int q_tiles, size_t part_entries, int target);
+int attention_wide_splits(const KvGeom& g, int items, int q_tiles, int groups, size_t part_entries, int target);
 int attention_wide_run_most(const KvGeom& g, int N, int Z, int target);
 int attention_wide_pt_cap(const KvGeom& g, int N, int Z, int target);
 size_t attention_wide_lds_bytes(int pt_cap, int tiles /* walked at a time: 1, or up to 2 by eight wavefronts */);
 void launch_attention_wide(hipStream_t st, const void* q, int q_ld, int q_lo, const void* k_win, const void* vT_win,
                            const void* k_pages_layer, const void* v_pages_layer, const KvGeom& g, const Plan& p, int N,
-                           int Hq, int q_tiles, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
+                           int Hq, int q_tiles, int per, int nw, int Z, int target, int tiles, int cus, int wpad, void* o, int o_ld, int o_lo, float* part,
                            size_t part_entries);
 // with Z > 1, behind it: the sums of the sequences that were split
 void launch_attention_wide_merge(hipStream_t st, const KvGeom& g, const Plan& p, int N, int Hq, int q_tiles, int Z, void* o, int o_ld,
