@@ -115,8 +115,8 @@ __device__ __forceinline__ void vocab_finish(const Stat& s, const VocabOut& f, i
 // are taken against the wavefront's maximum, so that only sums are left to reduce over its lanes; with each lane's own maximum
 // and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions.
 // A workgroup walks a run of chunks with the next one requested and arrives once.  Rows of 151936 logits, us, a workgroup per chunk and a launch
-// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.7, 64 14.9 / 12.5, 128 20.4 / 18.9, 256 32.1 / 32.2 (4.8 TB/s), 512 55.9 / 56.9, 1024 103.9 / 104.8
-// (an arrival per chunk instead: 256 rows 50, each end of a workgroup a store's way and an atomic's).
+// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.6, 64 14.9 / 12.3, 128 20.4 / 18.5, 256 32.1 / 32.6 (4.8 TB/s), 512 55.9 / 56.1, 1024 103.9 / 103.7
+// (an arrival per chunk instead: 256 rows 50, each end of a workgroup a store's way and an atomic's; the end of the row looked for in every chunk: 1024 rows 104.8).
 template <bool SCORE>
 __global__ __launch_bounds__(256) void vocab_stats_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,
                                                           int chunks, int per, float inv_t, float* __restrict__ part, int32_t* __restrict__ arrive,
@@ -141,7 +141,11 @@ __global__ __launch_bounds__(256) void vocab_stats_kernel(const float* __restric
     const int base = (c0 + c) * 1024 * VT;
     float v[4 * VT];
 #pragma unroll
-    for (int t = 0; t < 4 * VT; ++t) v[t] = base + (t >> 2) * 1024 + tid * 4 + (t & 3) < V ? r[t >> 2][t & 3] * inv_t : -INFINITY;
+    for (int t = 0; t < 4 * VT; ++t) v[t] = r[t >> 2][t & 3] * inv_t;
+    if (base + 1024 * VT > V) {   // (the last chunk of a row)
+#pragma unroll
+      for (int t = 0; t < 4 * VT; ++t) v[t] = base + (t >> 2) * 1024 + tid * 4 + (t & 3) < V ? v[t] : -INFINITY;
+    }
     float lm = -INFINITY, lm2 = -INFINITY;   // this lane's largest and second largest logit; the place of the first largest
     int at = 0;
 #pragma unroll
