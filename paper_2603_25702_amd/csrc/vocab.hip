@@ -24,10 +24,10 @@ static constexpr int VT = 4;
 static int sample_share(int rows) { return std::max(1, std::min(8, 256 / rows)); }
 int sample_rows_shared(int rows) { return std::min(rows, 128); }   // most rows with more than one
 
-// Workgroups of the statistics, and with them chunks per workgroup, up to one per lane of the wavefront that merges them: four for each of 256 compute
-// units, all resident.  768 / 1024 / 1280 / 2048 / 2560, us, rows of 151936 logits: 64 rows 13.6 / 13.5 / 14.9 / 15.0 / 23.1, 256 31.8 / 32.9 / 31.8 / 32.0 / 32.4,
-// 1024 104.6 / 105.5 / 106.1 / 107.3 / 106.8.
-static constexpr int STATS_WGS = 1024, STATS_MOST = 64;
+// Workgroups of the statistics, and with them chunks per workgroup, up to one per lane of the wavefront that merges them.  1024 / 4096 / 8192 / 16384 / one
+// a chunk, us, rows of 151936 logits: 4 rows 5.6 in all, 64 12.2 / 10.8 / 10.8 / 10.8 / 10.9, 256 31.5 / 28.5 / 28.7 / 30.3 / 30.8, 512 55.8 / 54.4 / 52.4 / 52.5 /
+// 58.9, 1024 103.3 / 105.8 / 102.3 / 99.2 / 112.1; behind the forward of 1024 rows 127 / 123 / 118 / - / 118.
+static constexpr int STATS_WGS = 8192, STATS_MOST = 64;
 
 int vocab_chunks(int V) { return (V + 1024 * VT - 1) / (1024 * VT); }
 
@@ -115,8 +115,8 @@ __device__ __forceinline__ void vocab_finish(const Stat& s, const VocabOut& f, i
 // are taken against the wavefront's maximum, so that only sums are left to reduce over its lanes; with each lane's own maximum
 // and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions.
 // A workgroup walks a run of chunks with the next one requested and arrives once.  Rows of 151936 logits, us, a workgroup per chunk and a launch
-// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.6, 64 14.9 / 12.3, 128 20.4 / 18.5, 256 32.1 / 32.6 (4.8 TB/s), 512 55.9 / 56.1, 1024 103.9 / 103.7
-// (an arrival per chunk instead: 256 rows 50, each end of a workgroup a store's way and an atomic's; the end of the row looked for in every chunk: 1024 rows 104.8).
+// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.6, 64 14.9 / 10.8, 128 20.4 / 16.4, 256 32.1 / 28.7 (5.4 TB/s), 512 55.9 / 52.4, 1024 103.9 / 102.3 (6.1 TB/s)
+// (with the arrival counters of all rows in one stretch of memory and an arrival per chunk: 256 rows 50).
 template <bool SCORE>
 __global__ __launch_bounds__(256) void vocab_stats_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,
                                                           int chunks, int per, float inv_t, float* __restrict__ part, int32_t* __restrict__ arrive,
