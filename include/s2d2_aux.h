@@ -20,7 +20,8 @@ extern "C" {
 int32_t s2d2_moe_choices(s2d2_ctx* ctx, int32_t rows, int32_t* out /* device */);
 
 /* Debugging aid: device address of an internal activation buffer of the most recent forward
- * ("h" fp32 residual rows [rows, d]; "a" operand of the next norm; "q", "o", "ffn", "kwin", "vwin", "ss").
+ * ("h" fp32 residual rows [rows, d]; "a" operand of the next norm; "q", "o", "ffn", "kwin", "vwin", "ss"; of MoE
+ * models "moe_tiles", int32 [8]: row tiles of the experts on each XCD).
  * Contents are those of the last layer that ran; layouts are internal and may change. */
 int32_t s2d2_debug_buffer(s2d2_ctx* ctx, const char* name, void** ptr);
 
