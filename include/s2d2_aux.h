@@ -28,8 +28,8 @@ int32_t s2d2_debug_buffer(s2d2_ctx* ctx, const char* name, void** ptr);
 /* Which GEMM kernel a forward of N sequences and block size B runs on a matrix (host only, nothing is launched).
  *   forward  0 draft, 1 verifier, 2 prefill of B tokens per sequence;  cus: compute units of the device
  *   matrix   4 QKV, 5 output, 6 gate / up, 7 down projection (dense models), 8 unembedding
- *   out      host [5]: kernel (0 streaming, 1 mid-size, 2 blocks, 3 tiled or through LDS), and of a block: row blocks and feature tiles of 16,
- *            workgroups that share K, 1 for streaming weight loads
+ *   out      host [5]: kernel (0 streaming, 1 mid-size, 2 blocks, 3 tiled, 4 both operands through LDS), and of a block: row blocks and
+ *            feature tiles of 16, workgroups that share K, 1 for streaming weight loads
  * For a bf16 model with packed weights and pages of whole groups of 8 keys. */
 int32_t s2d2_gemm_choice(const s2d2_model_desc* desc, int32_t forward, int32_t N, int32_t B, int32_t cus, int32_t matrix,
                          int32_t* out);

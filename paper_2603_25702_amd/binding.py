@@ -175,12 +175,12 @@ def model_desc(cfg, act_planes: int = 0) -> ModelDesc:
 
 def s2d2_gemm_choice(cfg, forward: str, N: int, B: int, matrix: str, cus: int = 256, act_planes: int = 0):
     """The GEMM kernel that a forward ("draft", "verify", "prefill") runs on a matrix ("qkv", "o", "gateup", "down", "unembed"):
-    ("stream" | "mid" | "block" | "tile", row blocks, feature tiles, workgroups that share K, streaming loads)."""
+    ("stream" | "mid" | "block" | "tile" | "lds", row blocks, feature tiles, workgroups that share K, streaming loads)."""
     lib = load_library()
     out = (C.c_int32 * 5)()
     _check(lib, lib.s2d2_gemm_choice(C.byref(model_desc(cfg, act_planes)), ("draft", "verify", "prefill").index(forward), N, B, cus,
                                      4 + ("qkv", "o", "gateup", "down", "unembed").index(matrix), out))
-    return (("stream", "mid", "block", "tile")[out[0]], out[1], out[2], out[3], bool(out[4]))
+    return (("stream", "mid", "block", "tile", "lds")[out[0]], out[1], out[2], out[3], bool(out[4]))
 
 
 @dataclass

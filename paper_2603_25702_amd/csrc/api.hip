@@ -900,8 +900,7 @@ int32_t s2d2_gemm_choice(const s2d2_model_desc* desc, int32_t forward, int32_t N
   const GemmMatrix m = matrix_of(*desc, matrix);
   const int lo = opm == OPM_F16 ? (fragment_order(*desc, opm, sz, env) ? LO_F16P : LO_F16) : opm == OPM_BF16X2 ? m.K : 0;
   const GemmChoice c = choice_of(*desc, matrix, lo, sz, env);
-  out[0] = c.kernel == GEMM_LDS ? (int32_t)GEMM_TILE : (int32_t)c.kernel;   // (both: through LDS)
-  out[1] = c.rb; out[2] = c.ta; out[3] = c.KS; out[4] = c.stream;
+  out[0] = c.kernel; out[1] = c.rb; out[2] = c.ta; out[3] = c.KS; out[4] = c.stream;
   return S2D2_OK;
 }
 

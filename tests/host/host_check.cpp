@@ -73,7 +73,7 @@ int main() {
         s2d2_model_desc m = shapes[3];
         (&m.n_layers)[f] = v;
         const int32_t rc = s2d2_gemm_choice(&m, 1, 1024, S2D2_MAX_BLOCK, 256, matrix, pick);
-        EXPECT(rc != S2D2_OK || (pick[0] >= 0 && pick[0] <= 3 && pick[3] >= 1));
+        EXPECT(rc != S2D2_OK || (pick[0] >= 0 && pick[0] <= 4 && pick[3] >= 1));
       }
   for (int32_t v : extremes) {
     EXPECT(s2d2_gemm_choice(&shapes[3], 0, v, 4, 256, 4, pick) == (v >= 1 && v <= 1024 ? S2D2_OK : S2D2_EINVAL));

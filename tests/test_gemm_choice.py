@@ -25,6 +25,30 @@ def test_windows_of_few_rows_do_not_pay_for_tiles_of_128(cfg, shifted):
                         assert s2d2_gemm_choice(cfg, forward, N, B, m)[0] in ("stream", "mid"), (N, B, forward, m)
 
 
+@pytest.mark.parametrize("cfg", DENSE + [I.CONFIGS[5].cfg], ids=lambda c: c.name)
+def test_unembedding_of_more_than_16_rows_goes_through_lds(cfg):
+    for N, B in ((1, 4), (1, 16), (4, 4), (1, 17), (5, 7), (16, 16), (32, 32)):
+        for forward in ("draft", "verify"):
+            assert s2d2_gemm_choice(cfg, forward, N, B, "unembed")[0] == ("lds" if N * B > 16 else "stream"), (N, B, forward)
+
+
+@pytest.mark.parametrize("d,kernel", [(256, "lds"), (288, "tile"), (320, "lds"), (352, "tile")])
+def test_unembedding_whose_columns_are_no_multiple_of_64_is_tiled(d, kernel):
+    cfg = I.ModelCfg("columns", 1, d, 8, 4, 128, 512, 2048)
+    assert s2d2_gemm_choice(cfg, "draft", 3, 43, "unembed")[0] == kernel
+    assert s2d2_gemm_choice(cfg, "draft", 3, 43, "unembed", act_planes=2)[0] == "tile"   # (two planes: 16-bit halves only)
+
+
+def test_gate_up_through_lds_for_large_matrices_of_many_rows():
+    """Which of the kernels has gate / up is seen from outside: the one through LDS is not reported as the tiled one."""
+    for cfg, forward, N, B, kernel in ((DENSE[2], "draft", 16, 16, "lds"), (DENSE[2], "verify", 16, 16, "lds"), (DENSE[0], "prefill", 4, 192, "lds"),
+                                       (DENSE[2], "draft", 4, 16, "block"), (DENSE[1], "verify", 8, 8, "block"), (DENSE[0], "draft", 1, 4, "stream")):
+        assert s2d2_gemm_choice(cfg, forward, N, B, "gateup")[0] == kernel, (cfg.name, forward, N, B)
+    for d, f in ((1984, 12288), (2048, 6112), (2080, 6144), (1024, 65536)):   # K short of 2048 or no multiple of 64, matrices of less than 48 MB
+        for rows in range(1, 65):
+            assert s2d2_gemm_choice(I.ModelCfg("small", 1, d, 8, 4, 128, f, 2048), "draft", 16, rows, "gateup")[0] != "lds", (d, f, rows)
+
+
 def test_arguments_are_checked():
     cfg = DENSE[0]
     for args in (("draft", 0, 4, "qkv"), ("verify", 1, 65, "o"), ("prefill", 1, 193, "o"), ("prefill", 4, 60, "unembed")):

@@ -1,5 +1,5 @@
-"""GPU parity of gate / up of many rows through LDS: row tiles of 128, 192 and 256 rows, one row more and one less than they hold, feature tiles that do not
-fill the last group, windows of fewer rows than expected (mid-block: the tiles shrink) and of more (carried tokens: the workgroups walk on)."""
+"""GPU parity of gate / up of many rows through LDS: row tiles of 128, 192 and 256 rows, one row more than one or three of them hold (129, 385 rows: a last tile of
+one row) and one less than four (767, 1023), feature tiles that do not fill the last group, the kernel that each forward runs, windows of fewer rows than expected (mid-block: the tiles shrink) and of more (carried tokens: the workgroups walk on)."""
 import pytest
 
 import s2d2_inputs as I
@@ -10,12 +10,14 @@ from tests.test_gpu_parity import run_steps
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,d_ffn,N,B,steps", [
-    (2048, 6144, 16, 20, 2), (2048, 6176, 11, 35, 1), (2048, 6144, 12, 32, 1), (2560, 6176, 8, 24, 2), (2048, 6144, 19, 27, 1), (4096, 12288, 4, 41, 2), (4096, 12320, 16, 32, 1),
+@pytest.mark.parametrize("d,d_ffn,N,B,steps,draft,verify", [
+    (2048, 6144, 16, 20, 2, "lds", "tile"), (2048, 6176, 11, 35, 1, "tile", "lds"), (2048, 6144, 12, 32, 1, "lds", "lds"), (2560, 6176, 8, 24, 2, "block", "lds"),
+    (2560, 9728, 3, 43, 2, "lds", "tile"), (2048, 6144, 7, 55, 1, "lds", "lds"), (2048, 6144, 13, 59, 1, "lds", "lds"), (2048, 6144, 31, 33, 1, "lds", "lds"),
+    (4096, 12288, 4, 41, 2, "lds", "lds"), (4096, 12320, 16, 32, 1, "tile", "lds"),
 ])
-def test_gate_up_of_many_rows(d, d_ffn, N, B, steps):
+def test_gate_up_of_many_rows(d, d_ffn, N, B, steps, draft, verify):
     cfg = I.ModelCfg("gateup-rows", 1, d, 8, 4, 128, d_ffn, 2048)
-    assert "tile" in [s2d2_gemm_choice(cfg, f, N, B, "gateup")[0] for f in ("draft", "verify")]   # (through LDS)
+    assert [s2d2_gemm_choice(cfg, f, N, B, "gateup")[0] for f in ("draft", "verify")] == [draft, verify]
     case = H.make_case(cfg, N, B, [20 + 13 * (i % 5) for i in range(N)], seed=59, synthetic_kv=True, page_size=16, room=4 * B + 16, norm_jitter=0.1)
     run, rep = run_steps(case, steps, seqs=sorted({0, N // 2, N - 1}))
     print("gate / up rows:", d, d_ffn, N, B, rep)

@@ -11,14 +11,14 @@ from tests import harness as H
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,vocab,N,B", [
-    (512, 2048, 1, 17), (512, 70007, 1, 64), (512, 2041, 5, 13), (512, 4096, 8, 16), (512, 2048, 3, 43), (256, 70007, 3, 64), (256, 2048, 1, 64),
-    (512, 2041, 4, 64), (512, 70007, 9, 29), (256, 2048, 11, 47), (288, 2048, 3, 43), (576, 2048, 2, 9),
+@pytest.mark.parametrize("d,vocab,N,B,kernel", [
+    (512, 2048, 1, 17, "lds"), (512, 70007, 1, 64, "lds"), (512, 2041, 5, 13, "lds"), (512, 4096, 8, 16, "lds"), (512, 2048, 3, 43, "lds"), (256, 70007, 3, 64, "lds"), (256, 2048, 1, 64, "lds"),
+    (512, 2041, 4, 64, "lds"), (512, 70007, 9, 29, "lds"), (256, 2048, 11, 47, "lds"), (288, 2048, 3, 43, "tile"), (576, 2048, 2, 9, "lds"),
 ])
-def test_rows_of_the_unembedding(d, vocab, N, B):
+def test_rows_of_the_unembedding(d, vocab, N, B, kernel):
     cfg = I.ModelCfg("unembed-rows", 1, d, 8, 4, 128, 512, vocab)
     for forward in ("draft", "verify"):
-        assert s2d2_gemm_choice(cfg, forward, N, B, "unembed")[0] == "tile"   # (through LDS)
+        assert s2d2_gemm_choice(cfg, forward, N, B, "unembed")[0] == kernel
     case = H.make_case(cfg, N, B, [20 + 13 * (n % 5) for n in range(N)], seed=53, synthetic_kv=True, page_size=16, room=4 * B + 16)
     run, rep, prm = H.DeviceRun(case), H.Report(), Params(seed=77)
     run.step(prm, advance=False)
