@@ -348,11 +348,16 @@ GemmChoice choice_of(const s2d2_model_desc& d, int which, int lo, const FwdSize&
   env.put(x, which == 8 ? sz.LR : sz.hint);
   return gemm_choice(m.kind, x, which == 8 ? sz.LR : sz.R);
 }
-// Half operands go in fragment order where a kernel that wants it takes one of the matrices.
+// Half operands go in fragment order where a kernel that wants it takes one of the matrices; the tiled kernel, which then has the others, takes either.
+// Forwards of six layers that have only gate / up of these, us, in rows (gate / up tiled) / in fragment order: 8B verification of 16 x 28 3275 / 3170, 16 x 32 3454 / 3321,
+// 32 x 32 6307 / 6051, draft of 32 x 32 4038 / 3944, 4B verification of 24 x 48 5731 / 5530, 1.7B of 40 x 48 4747 / 4463.
 bool fragment_order(const s2d2_model_desc& d, int opm, const FwdSize& sz, const GemmEnv& env) {
   if (opm != OPM_F16) return false;
   bool frag = sz.hint <= MID_MOST_ROWS;
-  for (int which = 4; which <= (d.n_experts == 0 ? 7 : 5) && !frag; ++which) frag = choice_of(d, which, LO_F16P, sz, env).kernel == GEMM_BLOCK;
+  for (int which = 4; which <= (d.n_experts == 0 ? 7 : 5) && !frag; ++which) {
+    const GemmKernel k = choice_of(d, which, LO_F16P, sz, env).kernel;
+    frag = k == GEMM_BLOCK || k == GEMM_LDS;
+  }
   return frag;
 }
 

@@ -49,6 +49,18 @@ def test_gate_up_through_lds_for_large_matrices_of_many_rows():
             assert s2d2_gemm_choice(I.ModelCfg("small", 1, d, 8, 4, 128, f, 2048), "draft", 16, rows, "gateup")[0] != "lds", (d, f, rows)
 
 
+@pytest.mark.parametrize("cfg", DENSE, ids=lambda c: c.name)
+def test_gate_up_has_its_kernel_whatever_the_other_matrices_have(cfg):
+    """The kernel through LDS wants its operands in fragment order: they come so where it is the only one that does (8B, 832 rows and more:
+    the other three matrices are tiled).  Fewer heads leave gate / up the same and give the others to other kernels."""
+    few = dataclasses.replace(cfg, n_q_heads=8, n_kv_heads=4)
+    for N in (1, 5, 8, 13, 16, 22, 26, 28, 32, 40, 48):
+        for B in range(1, 65):
+            for forward in ("draft", "verify"):
+                if N * B * (2 if forward == "verify" else 1) > 48:
+                    assert s2d2_gemm_choice(cfg, forward, N, B, "gateup") == s2d2_gemm_choice(few, forward, N, B, "gateup"), (N, B, forward)
+
+
 def test_arguments_are_checked():
     cfg = DENSE[0]
     for args in (("draft", 0, 4, "qkv"), ("verify", 1, 65, "o"), ("prefill", 1, 193, "o"), ("prefill", 4, 60, "unembed")):

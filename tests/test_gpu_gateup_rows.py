@@ -22,3 +22,13 @@ def test_gate_up_of_many_rows(d, d_ffn, N, B, steps, draft, verify):
     run, rep = run_steps(case, steps, seqs=sorted({0, N // 2, N - 1}))
     print("gate / up rows:", d, d_ffn, N, B, rep)
     assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
+
+
+@pytest.mark.parametrize("cfg,N,B", [(I.ModelCfg("gateup-alone", 1, 4096, 32, 8, 128, 12288, 2048), 13, 32), (I.ModelCfg("gateup-alone", 1, 4096, 32, 8, 128, 12288, 2048), 16, 32)])
+def test_gate_up_through_lds_between_tiled_matrices(cfg, N, B):
+    kernels = [s2d2_gemm_choice(cfg, "verify", N, B, m)[0] for m in ("qkv", "o", "gateup", "down")]
+    assert kernels == ["tile", "tile", "lds", "tile"]
+    case = H.make_case(cfg, N, B, [20 + 13 * (i % 5) for i in range(N)], seed=61, synthetic_kv=True, page_size=16, room=4 * B + 16, norm_jitter=0.1)
+    run, rep = run_steps(case, 1, seqs=sorted({0, N // 2, N - 1}))
+    print("gate / up alone:", N, B, rep)
+    assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
