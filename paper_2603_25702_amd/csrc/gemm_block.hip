@@ -382,8 +382,9 @@ static constexpr BlkShape BLK_SHAPES[] = {{2, 2, .066, 3.0}, {4, 2, .092, 3.2}, 
                                           {8, 4, .168, 5.3}, {6, 6, .185, 8.0}, {8, 6, .205, 9.0}, {6, 8, .205, 9.0}};
 struct BlkPick { int rb, ta, KS; double us; };
 // Six row blocks: 768 rows of the 1.7B shape are 256 blocks of 6 x 4 in the output and down projection (192 of 8 x 4: 56 -> 47 us for the
-// two, with the requests of the epilogue) and of 6 x 8 in QKV (768 of 4 x 4, two or three on a compute unit: 32.8 -> 28.8).  With fewer than 64 K tiles the difference
-// between two shapes is less than the estimates below are off by, and those of before stay.
+// two, with the requests of the epilogue) and of 6 x 8 in QKV (768 of 4 x 4, two or three on a compute unit: 32.8 -> 28.8).  From 56 K tiles on: forwards of four layers of
+// 704 to 1536 rows without / with them 1792 columns 983 / 951 to 678 / 663 us, 1920 686 / 673; at 1536 columns the difference is less than the estimates below are off by (0.993 to
+// 1.011 of the time), and the other shapes stay.
 constexpr bool blk_compiled(int kind, int RB, int TA) {
   return kind == SEPI_SWIGLU ? TA != 3 && TA != 8 : RB == 6 ? TA == 8 || (TA == 4 && kind == SEPI_ADD_F32) : true;
 }
@@ -398,7 +399,7 @@ static BlkPick blk_pick(int kind, const GemmStreamArgs& a, int m_cap) {
   const int nacc = kind == SEPI_SWIGLU ? 2 : 1;
   const double kt_mb = 1.024e-3;   // MB of a unit's operand per K tile
   for (const BlkShape& s : BLK_SHAPES) {
-    if (s.ta % nacc || !blk_compiled(kind, s.rb, s.ta) || (kind != SEPI_SWIGLU && s.rb == 6 && a.KT < 64)) continue;
+    if (s.ta % nacc || !blk_compiled(kind, s.rb, s.ta) || (kind != SEPI_SWIGLU && s.rb == 6 && a.KT < 56)) continue;
     const int tpw = s.ta / nacc, groups = (a.NT + tpw - 1) / tpw, tiles = (a.m_hint + 16 * s.rb - 1) / (16 * s.rb), caps = (m_cap + 16 * s.rb - 1) / (16 * s.rb);
     const int u = blk_u(s.rb, s.ta);
     for (int ks = 1; ks <= 4; ++ks) {

@@ -511,7 +511,12 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_gateup_kernel(const G
   else lds_gateup_body<4>(a, groups, P, M, xbytes, smem, s_rs);
 }
 
-// Row tiles and time of a launch: rounds of workgroups, each KT steps and its ends (measured with KT 64, 80 and 128, one round and two).
+// Row tiles and time of a launch: rounds of workgroups, each KT steps and its ends (fitted with KT 64, 80 and 128, one round and two).
+// How far the choice between this kernel, the tiled one and the blocks is from the fastest of them, us per layer on average over 128 to 1024 rows
+// in steps of 64, in brackets without this kernel: 4096 x 12288 0.8 (18), 2560 x 9728 1.1 (8), 2048 x 11008 0.6 (11), 2048 x 6144 0.2 (8), 3072 x 8192 0.9 (3).
+// Matrices of less than 48 MB together, or of less than 2048 columns, are given to it where it is 1.15 times faster than the others by the estimates:
+// of 255 forwards of four layers (17 matrices from 512 x 8192 to 4096 x 2048, 128 to 1536 rows) it then has 48, of which the least improved takes 0.99 of the time
+// without it, the most 0.88; by the bare estimates it has 93, and ten of them take 1.02 to 1.03 times as long.
 struct LdsGateup { int P; double us; };
 static LdsGateup lds_gateup(const GemmStreamArgs& a) {
   constexpr double per_kt[5] = {0, 0, .44, .58, .65}, ends[5] = {0, 0, 6.0, 8.0, 11.0};
@@ -525,9 +530,9 @@ static LdsGateup lds_gateup(const GemmStreamArgs& a) {
   return best;
 }
 double gemm_lds_gateup_us(const GemmStreamArgs& a) {
-  if (a.KT < 64 || (long long)a.NT * a.KT < 24576) return 1e30;   // (matrices of 48 MB together: below, the estimate has not been measured)
+  if (a.KT < 24 || (long long)a.NT * a.KT < 8192) return 1e30;   // (matrices of less than 16 MB together, or of less than 768 columns: little to gain, 2048 x 2048 0.2 us a layer)
   if (a.x_lo != LO_F16P || a.coop_wgs < 8 || a.KT % 2 || a.grouped != GROUP_NONE || (long long)((a.x_rows + 15) / 16) * a.KT * 1024 >= 0xfffff000LL) return 1e30;
-  return lds_gateup(a).us;
+  return lds_gateup(a).us * (a.KT < 64 || (long long)a.NT * a.KT < 24576 ? 1.15 : 1.0);   // (see lds_gateup)
 }
 
 // The unembedding: half operands, whole steps of 64 columns, 32-bit offsets into the rows.

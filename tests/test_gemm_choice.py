@@ -44,9 +44,11 @@ def test_gate_up_through_lds_for_large_matrices_of_many_rows():
     for cfg, forward, N, B, kernel in ((DENSE[2], "draft", 16, 16, "lds"), (DENSE[2], "verify", 16, 16, "lds"), (DENSE[0], "prefill", 4, 192, "lds"),
                                        (DENSE[2], "draft", 4, 16, "block"), (DENSE[1], "verify", 8, 8, "block"), (DENSE[0], "draft", 1, 4, "stream")):
         assert s2d2_gemm_choice(cfg, forward, N, B, "gateup")[0] == kernel, (cfg.name, forward, N, B)
-    for d, f in ((1984, 12288), (2048, 6112), (2080, 6144), (1024, 65536)):   # K short of 2048 or no multiple of 64, matrices of less than 48 MB
+    for d, f in ((736, 65536), (704, 12288), (2080, 6144), (2048, 2016), (1024, 4064)):   # fewer than 768 columns or no multiple of 64, matrices of less than 16 MB
         for rows in range(1, 65):
             assert s2d2_gemm_choice(I.ModelCfg("small", 1, d, 8, 4, 128, f, 2048), "draft", 16, rows, "gateup")[0] != "lds", (d, f, rows)
+    for d, f, N, B in ((768, 6144, 13, 59), (1024, 4096, 41, 25), (1536, 4608, 31, 33)):
+        assert s2d2_gemm_choice(I.ModelCfg("mid", 1, d, 8, 4, 128, f, 2048), "draft", N, B, "gateup")[0] == "lds", (d, f)
 
 
 @pytest.mark.parametrize("cfg", DENSE, ids=lambda c: c.name)

@@ -22,3 +22,13 @@ def test_six_row_blocks(d, d_ffn, N, B, steps, draft, verify):
     run, rep = run_steps(case, steps, seqs=sorted({0, N // 2, N - 1}))
     print("six row blocks:", d, d_ffn, N, B, rep)
     assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
+
+
+@pytest.mark.parametrize("N,B,draft,verify", [(12, 31, "4x4 4x3 4x6 4x3", "8x4 6x4 8x6 6x4"), (24, 32, "8x4 6x4 8x6 6x4", "8x4 6x8 tile 6x8")])
+def test_six_row_blocks_of_the_fewest_columns(N, B, draft, verify):
+    cfg = I.ModelCfg("block-six-rows", 2, 1792, 14, 2, 128, 1792, 2048)   # 56 K tiles
+    assert blocks(cfg, "draft", N, B) == draft and blocks(cfg, "verify", N, B) == verify
+    case = H.make_case(cfg, N, B, [20 + 13 * (i % 5) for i in range(N)], seed=47, synthetic_kv=True, page_size=16, room=4 * B + 16, norm_jitter=0.1)
+    run, rep = run_steps(case, 2, seqs=sorted({0, N // 2, N - 1}))
+    print("six row blocks, 56 K tiles:", N, B, rep)
+    assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL

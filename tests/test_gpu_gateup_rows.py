@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     (2048, 6144, 16, 20, 2, "lds", "tile"), (2048, 6176, 11, 35, 1, "tile", "lds"), (2048, 6144, 12, 32, 1, "lds", "lds"), (2560, 6176, 8, 24, 2, "block", "lds"),
     (2560, 9728, 3, 43, 2, "lds", "tile"), (2048, 6144, 7, 55, 1, "lds", "lds"), (2048, 6144, 13, 59, 1, "lds", "lds"), (2048, 6144, 31, 33, 1, "lds", "lds"),
     (4096, 12288, 4, 41, 2, "lds", "lds"), (4096, 12320, 16, 32, 1, "tile", "lds"),
+    (768, 6144, 7, 55, 1, "tile", "lds"), (768, 6144, 13, 59, 2, "lds", "lds"), (1024, 4096, 41, 25, 1, "lds", "tile"), (1536, 4608, 31, 33, 1, "lds", "lds"),   # (the fewest steps, the smallest matrices)
 ])
 def test_gate_up_of_many_rows(d, d_ffn, N, B, steps, draft, verify):
     cfg = I.ModelCfg("gateup-rows", 1, d, 8, 4, 128, d_ffn, 2048)
