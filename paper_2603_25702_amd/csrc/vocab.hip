@@ -24,10 +24,12 @@ static constexpr int VT = 4;
 static int sample_share(int rows) { return std::max(1, std::min(8, 256 / rows)); }
 int sample_rows_shared(int rows) { return std::min(rows, 128); }   // most rows with more than one
 
-// Workgroups of the statistics, and with them chunks per workgroup, up to one per lane of the wavefront that merges them.  1024 / 4096 / 8192 / 16384 / one
-// a chunk, us, rows of 151936 logits: 4 rows 5.6 in all, 64 12.2 / 10.8 / 10.8 / 10.8 / 10.9, 256 31.5 / 28.5 / 28.7 / 30.3 / 30.8, 512 55.8 / 54.4 / 52.4 / 52.5 /
-// 58.9, 1024 103.3 / 105.8 / 102.3 / 99.2 / 112.1; behind the forward of 1024 rows 127 / 123 / 118 / - / 118.
-static constexpr int STATS_WGS = 8192, STATS_MOST = 64;
+// Workgroups of the statistics, and most chunks that one walks.  1024 / 4096 / 8192 / 16384 workgroups / one a
+// chunk, us, rows of 151936 logits: 4 rows 5.6 in all, 64 12.2 / 10.8 / 10.8 / 10.8 / 10.9, 256 31.5 / 28.5 / 28.7 / 30.3 / 30.8, 512 55.8 / 54.4 / 52.4 / 52.5 /
+// 58.9, 1024 (runs of 38, 10, 5, 3 and 1 chunks) 103.3 / 105.8 / 102.3 / 99.2 / 112.1.  Behind a forward, that is with the logits' last quarter in the memory-side
+// cache, runs of 5 / 3 / 2 / 1 chunks, in brackets a workgroup per chunk and a launch for the merge: 1024 rows of the MoE shape 115 / 112 / 113 / 116 (113), of the 1.7B
+// one 112 / 109 / 108 / 115 (109), 4B verification 109 / 104 / 104 / 111 (111); 768 rows of 8B, 4 / 3 / 2 / 1 84 / 80 / 81 / 88 (88), 512, 3 / 2 / 1 54 / 57 / 62 (60).
+static constexpr int STATS_WGS = 8192, STATS_MOST = 3;
 
 int vocab_chunks(int V) { return (V + 1024 * VT - 1) / (1024 * VT); }
 
@@ -115,7 +117,7 @@ __device__ __forceinline__ void vocab_finish(const Stat& s, const VocabOut& f, i
 // are taken against the wavefront's maximum, so that only sums are left to reduce over its lanes; with each lane's own maximum
 // and a merge of whole statistics (five exchanges, two exponentials, six times over) the merge was half of the instructions.
 // A workgroup walks a run of chunks with the next one requested and arrives once.  Rows of 151936 logits, us, a workgroup per chunk and a launch
-// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.6, 64 14.9 / 10.8, 128 20.4 / 16.4, 256 32.1 / 28.7 (5.4 TB/s), 512 55.9 / 52.4, 1024 103.9 / 102.3 (6.1 TB/s)
+// behind it for the merge / now: 4 rows 4.9 + 4.5 / 5.6, 64 14.9 / 10.8, 128 20.4 / 16.4, 256 32.1 / 28.7 (5.4 TB/s), 512 55.9 / 52.4, 1024 103.9 / 99.2 (6.3 TB/s)
 // (with the arrival counters of all rows in one stretch of memory and an arrival per chunk: 256 rows 50).
 template <bool SCORE>
 __global__ __launch_bounds__(256) void vocab_stats_kernel(const float* __restrict__ logits, int V, const int32_t* __restrict__ count,

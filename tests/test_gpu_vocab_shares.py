@@ -1,5 +1,5 @@
-"""GPU: vocabulary statistics of rows that one to all workgroups of their chunks share, against 64 bits: a chunk per workgroup, odd runs of chunks, a whole
-row in one workgroup, more chunks than lanes; called again and again (the arrival counters are back at zero)."""
+"""GPU: vocabulary statistics of rows that one to all workgroups of their chunks share, against 64 bits: a chunk per workgroup, runs of two and of three chunks (the
+most) with a shorter last one, a whole row in one workgroup, more chunks than lanes; called again and again (the arrival counters are back at zero)."""
 import math
 
 import pytest
@@ -11,7 +11,7 @@ from paper_2603_25702_amd import Engine
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V,counts", [(266245, [17, 1]), (45003, [1100, 300, 3]), (45004, [1152]), (12292, [1152]), (4096, [5]), (5, [2])])
+@pytest.mark.parametrize("V,counts", [(266245, [17, 1]), (45003, [1100, 300, 3]), (45004, [1152]), (77003, [1152]), (77004, [1152, 900]), (12292, [1152]), (4096, [5]), (5, [2])])
 def test_rows_shared_by_workgroups(V, counts):
     cfg = I.shrink(I.CONFIGS[2].cfg, n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
     eng = Engine(cfg, I.gen_weights(cfg, 0), 18, 64)
