@@ -17,3 +17,17 @@ def test_groups(B, lens):
     run, rep = run_steps(case, 3)
     print("groups:", B, lens, rep)
     assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
+
+
+@pytest.mark.parametrize("B,lens", [
+    (24, [300 + 41 * (n % 5) for n in range(17)]),                # verification: 6 tiles in room for 9 make 3 groups of 3, 2 of them with rows: 136 workgroups of four wavefronts
+    (32, [33 + 190 * (n % 4) for n in range(16)] + [1100]),       # 8 in room for 12, 3 groups of 4
+    (28, [640] * 30 + [31, 97, 5]),                               # 7 in room for 11, 3 groups of 4, more sequences than a wavefront's half
+])
+def test_groups_of_four_wavefronts(B, lens):
+    """More than 128 workgroups ahead of the key splits and several groups of query tiles: workgroups of four wavefronts, the last group with
+    rows in part or without any."""
+    case = H.make_case(CFG, len(lens), B, lens, seed=79, synthetic_kv=True, page_size=16, room=4 * B + 16)
+    run, rep = run_steps(case, 3, seqs=sorted({0, len(lens) // 2, len(lens) - 1}))
+    print("groups of four wavefronts:", B, lens[:5], rep)
+    assert rep.max_logit_err_draft <= H.LOGIT_RTOL and rep.max_logit_err_verify <= H.LOGIT_RTOL
