@@ -535,10 +535,20 @@ double gemm_lds_gateup_us(const GemmStreamArgs& a) {
   return lds_gateup(a).us * (a.KT < 64 || (long long)a.NT * a.KT < 24576 ? 1.15 : 1.0);   // (see lds_gateup)
 }
 
-// The unembedding: half operands, whole steps of 64 columns, 32-bit offsets into the rows.
+// The unembedding: half operands, whole steps of 64 columns, 32-bit offsets into the rows, and enough feature tiles for each of the kernel's ranges.  A workgroup's K loop
+// takes as long for one feature tile as for 16, so a small vocabulary wants the kernels that cut K or take fewer features a workgroup (mid-size, streaming, tiled).  us per launch, this
+// kernel / the one that the others' rules pick, as the difference, at 2048 columns: 8192 features (2 tiles a range of one row tile) 32 rows +9, 64 +7, 128 -12, 256 +17, 512 +14; 16384 +3,
+// -3, -6, +14, +8; 24576 +2, -3, -1, +11, -15; 36864 +1, -7, 0, -16, -16; 50304 -17, -19, -3, -26, -38; at 4096 columns 8192 features +14, +11, +12, +41, +20; 24576 +3, -14,
+// -17, -9, -21; at 1024 columns 8192 features +7, +6, -6, +3, +4.  257 to 384 rows with 17 to 20 tiles a range (the second group of 16 nearly empty), 4096 columns +18 to +26.  Over 780 such cases
+// (512 to 8192 columns, 2048 to 65536 features, 17 to 1024 rows) the rule is 0.3 us from the faster one on average; this kernel everywhere 4.2, nowhere 15.
 bool gemm_lds_takes(int kind, const GemmStreamArgs& a) {
   if ((a.x_lo != LO_F16 && a.x_lo != LO_F16P) || a.coop_wgs < 1 || a.KT % 2 || a.grouped != GROUP_NONE || (long long)((a.x_rows + 15) / 16) * a.KT * 1024 >= 0xfffff000LL) return false;
-  return kind == SEPI_STORE_F32 && a.gather && a.m_hint > 16;
+  if (kind != SEPI_STORE_F32 || !a.gather || a.m_hint <= 16) return false;
+  const int rows = a.m_hint, row_tiles = (rows + 255) / 256, wgs = std::max(1, a.coop_wgs / 8);
+  const double per = a.NT / (8.0 * (wgs / std::min(row_tiles, wgs)));   // feature tiles of a range
+  if (rows > 256 && rows <= 384 && per > 16.0 && per < 21.0) return false;
+  const int least = rows <= 32 ? 7 : rows <= 64 && a.x_lo == LO_F16P ? 6 : rows <= 128 ? std::min(a.KT / 32, 4) : rows <= 192 && a.KT <= 32 ? 0 : rows <= 256 && a.KT >= 128 ? 5 : 9;
+  return per >= least;
 }
 static void lds_attribute(const void* fn, unsigned bytes, bool (&done)[64]) {
   int dev = 0;

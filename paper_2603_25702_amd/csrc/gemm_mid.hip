@@ -1,5 +1,5 @@
 // GEMM on the packed weights for windows between the streaming kernel's 16 rows and the blocks of gemm_block.hip:
-//   Y[m, n] = sum_k X[m, k] W[n, k],  17 to 48 rows, half operands, X in fragment order (LO_F16P).
+//   Y[m, n] = sum_k X[m, k] W[n, k],  17 to 48 rows (unembedding of small vocabularies: 64), half operands, X in fragment order (LO_F16P).
 //
 // At these sizes a launch is bound by reading the weights once, and on the way there by everything that is not the
 // K loop: the tiled kernel pads the rows to 128, splits K over compute units to fill the chip, and pays row maps,
@@ -48,12 +48,14 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
   float* s_rs = (float*)smem;                       // [128] 1/rms of the rows
   f32x4_t* s_red = (f32x4_t*)(smem + 512);          // [wavefront of a half][unit][accumulator][lane]
 
-  // Every load is 64 lanes x 16 contiguous bytes: scalar tile address + 16 lane.
+  // Every load is 64 lanes x 16 contiguous bytes: scalar tile address + 16 lane (gathered rows: + an offset per lane).
+  const int32_t* gather = EPI == SEPI_STORE_F32 ? a.gather : nullptr;
   uint32_t xo[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int r0 = m0 + min(rb * 16, (Mloc - 1) & ~15);   // blocks past the rows read the last one again; never stored
-    xo[rb] = (uint32_t)(r0 >> 4) * (uint32_t)KT * 1024u;
+    if (EPI == SEPI_STORE_F32) xo[rb] = 2u * (uint32_t)(gather ? frag_offset(gather[min(r0 + f, M - 1)], 8 * g, a.K) : frag_offset(r0 + f, 8 * g, a.K));
+    else xo[rb] = (uint32_t)(r0 >> 4) * (uint32_t)KT * 1024u;
   }
   const uint32_t lane16 = lane * 16;
   u32x4_t x[RB][U];
@@ -73,7 +75,7 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
   auto load_x = [&](int u, int kt) __attribute__((always_inline)) {
     const uint8_t* xk = (const uint8_t*)a.X + (size_t)kt * 1024;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) x[rb][u] = *(const u32x4_t*)(xk + xo[rb] + lane16);
+    for (int rb = 0; rb < RB; ++rb) x[rb][u] = EPI == SEPI_STORE_F32 ? *(const u32x4_t*)(xk + xo[rb]) : *(const u32x4_t*)(xk + xo[rb] + lane16);
   };
   int grp = set;
   point(grp);
@@ -88,7 +90,7 @@ __device__ __forceinline__ void gemm_mid_body(const GemmStreamArgs& a, u32x4_t (
     constexpr int SSV = 64 / TPR;                           // float4 per thread and round
     const int ss_row = tid / TPR, ss_sub = tid % TPR;
     const int rr = min(m0 + ss_row, M - 1);   // rows past the count read a valid row; their 1/rms is never used
-    const float* pp = a.ss_part + (size_t)rr * a.ss_stride;
+    const float* pp = a.ss_part + (size_t)(gather ? gather[rr] : rr) * a.ss_stride;
     float v = 0.f;
     if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
       const int n4 = a.ss_count >> 2;
@@ -291,11 +293,12 @@ __global__ __launch_bounds__(MID_NW * 64, 2) void gemm_mid_kernel(const GemmStre
 //   16 rows and fewer, where no more than 32 are possible, stay with the streaming kernel: 1.7B-shaped layer 37 / 32 (QKV, output, gate / up, down added up)
 //   32 rows: 55 / 84 against two row tiles of the streaming kernel, 4B-shaped layer
 //   48 rows: 66 / 64 (4B), 41 / 41 (1.7B), 97 / 97 (8B) against gemm_block.hip, 64 rows: 76 / 68, 46 / 44, 116 / 100
+//   unembedding of the vocabularies that gemm_lds.hip leaves, 64 rows, less than the tiled kernel takes: 8192 features of 2048 columns 21, of 1024 14, 4096 of 2048 10
 //   at most 16 rows expected, but room for more than the streaming kernel takes (a right-shifted verifier of 11 to 16 masked
 //   positions; whole forwards of 12 rows, this / the streaming / the tiled kernel): 1.7B 1467 / 1439 / 3115, 4B 2423 / 2660 / 4607, 8B 3566 / 3535 / 5880
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a, int m_cap) {
   if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * MID_NW || a.m_hint < 1 || (a.m_hint <= 16 && m_cap <= STREAM_MOST_ROWS)) return false;
-  return kind != SEPI_STORE_F32 && a.m_hint <= MID_MOST_ROWS;
+  return kind != SEPI_STORE_F32 ? a.m_hint <= MID_MOST_ROWS : a.m_hint <= 64 && (a.NT > 8 || a.gather);   // (a matrix of a few feature tiles: see the streaming kernel's launcher)
 }
 
 template <int EPI, int TPW, bool SHARED>
@@ -313,7 +316,8 @@ static void launch_mid_as(hipStream_t st, const GemmStreamArgs& a, int wgs, int 
 template <int EPI, int TPW>
 static void launch_mid(hipStream_t st, const GemmStreamArgs& a, int passes, int KS) {
   const int groups = (a.NT + TPW - 1) / TPW;
-  if (KS > 1) return launch_mid_as<EPI, TPW, true>(st, a, groups * KS, passes, KS);
+  if constexpr (EPI != SEPI_STORE_F32)
+    if (KS > 1) return launch_mid_as<EPI, TPW, true>(st, a, groups * KS, passes, KS);
   launch_mid_as<EPI, TPW, false>(st, a, std::min(groups, a.coop_wgs), passes, 1);
 }
 
@@ -324,13 +328,13 @@ static void launch_mid(hipStream_t st, const GemmStreamArgs& a, int passes, int 
 static void mid_shape(int kind, const GemmStreamArgs& a, int passes, int& tpw, int& KS) {
   const int nacc = kind == SEPI_SWIGLU ? 2 : 1, rb = std::min(MID_RB, (a.m_hint + 15) / 16);
   // (what the accumulators and two tiles of operands in flight leave of 256 registers)
-  const int most = 3;
+  const int most = kind == SEPI_STORE_F32 ? 4 : 3;
   double best = 1e30;
   tpw = KS = 1;
   for (int t = 1; t <= most; ++t)
     for (int k = 1; k <= 4; ++k) {
       const int groups = (a.NT + t - 1) / t, ta = t * nacc;
-      if (k > 1 && (groups * k > a.coop_wgs || a.KT < 4 * MID_NW * k || !a.pair_buf ||
+      if (k > 1 && (kind == SEPI_STORE_F32 || groups * k > a.coop_wgs || a.KT < 4 * MID_NW * k || !a.pair_buf ||
                     (long long)groups * passes * 3 * MID_RB * ta > a.pair_cap)) break;
       const double rounds = (groups * k + a.coop_wgs - 1) / a.coop_wgs, w = ta * a.KT * 1.024e-3, x = rb * a.KT * 1.024e-3;   // MB of a group
       const double us = std::max(groups * (w / 6.0 + x / 20.0), rounds / k * (w * 1e3 / 30.0 + x * 1e3 / 100.0)) + rounds * 0.12 * rb * ta + (k > 1 ? 2.5 : 0.0);
@@ -343,6 +347,7 @@ static void launch_mid_kind(hipStream_t st, const GemmStreamArgs& a, int m_cap) 
   const int passes = (m_cap + 16 * MID_RB - 1) / (16 * MID_RB);
   int tpw, KS;
   mid_shape(EPI, a, passes, tpw, KS);
+  if constexpr (EPI == SEPI_STORE_F32) { if (tpw == 4) return launch_mid<EPI, 4>(st, a, passes, KS); }
   if (tpw == 3) return launch_mid<EPI, 3>(st, a, passes, KS);
   if (tpw == 2) return launch_mid<EPI, 2>(st, a, passes, KS);
   launch_mid<EPI, 1>(st, a, passes, KS);
@@ -353,6 +358,7 @@ void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_ca
     case SEPI_QKV_ROPE: launch_mid_kind<SEPI_QKV_ROPE>(st, a, m_cap); break;
     case SEPI_ADD_F32: launch_mid_kind<SEPI_ADD_F32>(st, a, m_cap); break;
     case SEPI_SWIGLU: launch_mid_kind<SEPI_SWIGLU>(st, a, m_cap); break;
+    case SEPI_STORE_F32: launch_mid_kind<SEPI_STORE_F32>(st, a, m_cap); break;
   }
 }
 

@@ -311,7 +311,7 @@ GemmChoice gemm_choice(int kind, const GemmStreamArgs& a, int m_cap);
 // (a residual add returns the number of partial sums of squares it leaves per row)
 int launch_gemm_stream(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap, const GemmChoice& c);
 constexpr int STREAM_MOST_ROWS = 32;   // of a window that the streaming kernel takes: two row tiles
-// gemm_mid.hip : windows of 17 to 48 rows, half operands in fragment order
+// gemm_mid.hip : windows of 17 to 48 rows (unembedding of small vocabularies: 64), half operands in fragment order
 constexpr int MID_MOST_ROWS = 48;
 bool gemm_mid_takes(int kind, const GemmStreamArgs& a, int m_cap);
 void launch_gemm_mid(hipStream_t st, int kind, const GemmStreamArgs& a, int m_cap);

@@ -39,6 +39,15 @@ def test_unembedding_whose_columns_are_no_multiple_of_64_is_tiled(d, kernel):
     assert s2d2_gemm_choice(cfg, "draft", 3, 43, "unembed", act_planes=2)[0] == "tile"   # (two planes: 16-bit halves only)
 
 
+@pytest.mark.parametrize("d,vocab,rows,kernel", [
+    (2048, 8192, 32, "mid"), (2048, 8192, 64, "mid"), (2048, 8192, 128, "lds"), (2048, 8192, 256, "tile"), (2048, 16384, 512, "tile"), (4096, 8192, 128, "tile"),
+    (2048, 32000, 32, "lds"), (2048, 24576, 64, "lds"), (2048, 36864, 256, "lds"), (4096, 20480, 256, "lds"), (2048, 20480, 512, "lds"), (4096, 36864, 320, "tile"),
+])
+def test_unembedding_of_small_vocabularies_leaves_the_kernel_through_lds(d, vocab, rows, kernel):
+    """Its workgroups take as long for one feature tile as for 16: two tiles a workgroup, 8192 features of 2048 columns and 256 rows, took 17 us longer."""
+    assert s2d2_gemm_choice(I.ModelCfg("vocab", 1, d, 16, 8, 128, 1024, vocab), "draft", rows // 16, 16, "unembed")[0] == kernel
+
+
 def test_gate_up_through_lds_for_large_matrices_of_many_rows():
     """Which of the kernels has gate / up is seen from outside: the one through LDS is not reported as the tiled one."""
     for cfg, forward, N, B, kernel in ((DENSE[2], "draft", 16, 16, "lds"), (DENSE[2], "verify", 16, 16, "lds"), (DENSE[0], "prefill", 4, 192, "lds"),

@@ -1,6 +1,6 @@
 """GPU parity of the unembedding of more than 16 rows: the edges of its row tiles (64, 128, 192, 256 rows, one more and one less, several tiles), fewer
 feature tiles than workgroups, ranges of one group of 16 and of several with a part of one, a vocabulary that is no multiple of 16,
-rows and fragment order, a width whose K is no multiple of 64 (the tiled kernel's)."""
+rows and fragment order; vocabularies too small for it, and a width whose K is no multiple of 64 (the other kernels')."""
 import pytest
 
 import s2d2_inputs as I
@@ -12,8 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,vocab,N,B,kernel", [
-    (512, 2048, 1, 17, "lds"), (512, 70007, 1, 64, "lds"), (512, 2041, 5, 13, "lds"), (512, 4096, 8, 16, "lds"), (512, 2048, 3, 43, "lds"), (256, 70007, 3, 64, "lds"), (256, 2048, 1, 64, "lds"),
-    (512, 2041, 4, 64, "lds"), (512, 70007, 9, 29, "lds"), (256, 2048, 11, 47, "lds"), (288, 2048, 3, 43, "tile"), (576, 2048, 2, 9, "lds"),
+    (512, 28673, 1, 17, "lds"), (512, 70007, 1, 64, "lds"), (512, 2041, 5, 13, "lds"), (512, 4096, 8, 16, "lds"), (512, 2048, 3, 43, "lds"), (256, 70007, 3, 64, "lds"),
+    (256, 2048, 3, 64, "lds"), (512, 40007, 4, 64, "lds"), (512, 70007, 9, 29, "lds"), (256, 20483, 11, 47, "lds"), (576, 28680, 2, 9, "lds"), (1024, 24583, 2, 24, "lds"),
+    (512, 2048, 1, 17, "stream"), (1024, 8199, 2, 24, "mid"), (1024, 2041, 1, 64, "mid"), (256, 2048, 1, 64, "tile"), (512, 2041, 4, 64, "tile"), (288, 2048, 3, 43, "tile"),   # (small vocabularies, columns)
 ])
 def test_rows_of_the_unembedding(d, vocab, N, B, kernel):
     cfg = I.ModelCfg("unembed-rows", 1, d, 8, 4, 128, 512, vocab)
