@@ -488,7 +488,8 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
       } else {
         // MoE FFN: router -> top-k -> group by expert -> grouped gate/up + SwiGLU -> grouped down -> combine
         const int E = d.n_experts, Fe = d.d_expert, tk = d.top_k;
-        const bool experts = gemm_expert_takes(d.d_model, Fe, R, tk, lo_row(d.d_model));
+        const bool experts = gemm_expert_takes(E, d.d_model, Fe, R, sz.hint, tk, lo_row(d.d_model), c->n_cus);
+        const int slices = gemm_expert_slices(E, d.d_model, Fe);
         int32_t* choice = c->moe_choice + (size_t)l * c->rows_cap * tk;
         GemmStreamArgs r{};
         r.m_count = n_rows;
@@ -499,7 +500,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         { ProfScope ps(c, 3, 0.0); launch_moe_route(st, c->router_logits, E, tk, n_rows, R, choice, c->moe_w, c->ss, ss_stride, ss_count, d.d_model, d.rms_eps, experts ? c->moe_row_rs : nullptr); }
         const int tile_cap = std::min(c->moe_tile_cap, R * tk / 128 + E + 1);
         { ProfScope ps(c, 3, 0.0); launch_moe_group(st, E, tk, n_rows, choice, c->moe_sorted, c->moe_tile_expert,
-                                                     c->moe_tile_row0, c->moe_tile_rows, c->moe_n_tiles, tile_cap, experts); }
+                                                     c->moe_tile_row0, c->moe_tile_rows, c->moe_n_tiles, tile_cap, experts ? 8 / slices : 0); }
         GemmStreamArgs b{};
         b.grouped = GROUP_GATHER; b.top_k = tk; b.n_tiles = c->moe_n_tiles; b.tile_expert = c->moe_tile_expert;
         b.tile_row0 = c->moe_tile_row0; b.tile_rows = c->moe_tile_rows; b.sorted = c->moe_sorted; b.route_w = c->moe_w;
@@ -507,7 +508,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         b.Wp = c->pk[l].eg; b.Wp2 = c->pk[l].eu; b.NT = Fe / 16; b.KT = d.d_model / 32; b.N = Fe; b.K = d.d_model;
         b.X = (const bf16_t*)c->a; b.ldx = ld_a; b.x_lo = lo_row(d.d_model); b.ss_part = c->ss; b.ss_stride = ss_stride; b.ss_count = ss_count;
         b.eps = d.rms_eps; b.out = c->moe_act; b.ldo = ld_e; b.out_lo = lo_row(d.d_expert);
-        { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); b.tile_list = tile_cap; b.row_rs = c->moe_row_rs; b.coop_wgs = c->n_cus;
+        { ProfScope ps(c, 0, 2.0 * E * (double)Fe * d.d_model * es, fr * tk * 2.0 * Fe * d.d_model, 6); b.tile_list = tile_cap; b.tile_slices = slices; b.row_rs = c->moe_row_rs; b.coop_wgs = c->n_cus;
           if (experts) launch_gemm_expert(st, SEPI_SWIGLU, b, R); else launch_gemm_tile(st, SEPI_SWIGLU, SPRO_BF16S, b, tile_cap); }
         GemmStreamArgs e{};
         e.grouped = GROUP_SCATTER; e.top_k = tk; e.n_tiles = c->moe_n_tiles; e.tile_expert = c->moe_tile_expert;
@@ -515,7 +516,7 @@ int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& s
         e.expert_stride = packed_weight_bytes(d.d_model, Fe) / 16;
         e.Wp = c->pk[l].ed; e.NT = d.d_model / 16; e.KT = Fe / 32; e.N = d.d_model; e.K = Fe;
         e.X = (const bf16_t*)c->moe_act; e.ldx = ld_e; e.x_lo = lo_row(d.d_expert); e.out = c->moe_y; e.ldo = d.d_model;
-        { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); e.tile_list = tile_cap; e.coop_wgs = c->n_cus;
+        { ProfScope ps(c, 0, (double)E * d.d_model * Fe * es, fr * tk * (double)d.d_model * Fe, 7); e.tile_list = tile_cap; e.tile_slices = slices; e.coop_wgs = c->n_cus;
           if (experts) launch_gemm_expert(st, SEPI_STORE_F32, e, R * tk); else launch_gemm_tile(st, SEPI_STORE_F32, SPRO_BF16, e, tile_cap); }
         { ProfScope ps(c, 3, 0.0); launch_moe_combine(st, c->moe_y, d.d_model, tk, n_rows, R, c->h, c->a, ld_a, lo_a, gain_after, c->ss, ss_stride); ss_count = 1; }
       }

@@ -13,8 +13,8 @@
 // kernel / this one: gate / up, 18 rows an expert on average 103 / 81 (6.6 TB/s), 64 rows 110 / 89, 128 rows 131 / 110, the most chosen with
 // 700 144 / 135; down 72 / 47, 89 / 56, 108 / 68, 108 / 80.
 //
-// One workgroup per compute unit takes tile after tile: XCD x those of the experts that moe_group_kernel gave it, the largest first and in
-// alternating order, so that a workgroup's tiles add up to about the same rows.  The first requests of a workgroup's next tile are made ahead of
+// One workgroup per compute unit takes tile after tile: XCD x those of the experts that moe_group_kernel gave it (of a slice of their features, where there are few experts), the largest
+// first and in alternating order, so that a workgroup's tiles add up to about the same rows.  The first requests of a workgroup's next tile are made ahead of
 // the stores of the present one (in launches of a workgroup per tile 129 and 76 us for 122 and 70 at 128 rows).
 #include "gemm_epilogue.h"
 #include "../../include/s2d2.h"
@@ -240,12 +240,13 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmS
   asm volatile("" : "+v"(tid));   // (opaque: what depends on the lane alone is otherwise computed for all row counts ahead of the choice)
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = tid & 255;
   const int xcd = blockIdx.x & 7, wg = (int)blockIdx.x >> 3, wgs = (int)gridDim.x >> 3;
-  const int items = (int)lds_uniform(a.n_tiles[xcd]) * cols, first_tile = xcd * a.tile_list;
+  const int list = xcd / a.tile_slices, slice = xcd % a.tile_slices, c0 = slice * cols / a.tile_slices, mine = (slice + 1) * cols / a.tile_slices - c0;   // (at least one: see gemm_expert_slices)
+  const int items = (int)lds_uniform(a.n_tiles[list]) * mine, first_tile = list * a.tile_list;
   auto item = [&](int q, LdsItem& it) __attribute__((always_inline)) {
     const int j = q * wgs + (q & 1 ? wgs - 1 - wg : wg);
     if (j >= items) return false;
-    const int t = first_tile + j / cols;
-    it.m0 = (int)lds_uniform(a.tile_row0[t]); it.rows = (int)lds_uniform(a.tile_rows[t]); it.expert = (int)lds_uniform(a.tile_expert[t]); it.nt0 = j % cols * T::TPW; it.tiles = min(T::TPW, a.NT - it.nt0);
+    const int t = first_tile + j / mine;
+    it.m0 = (int)lds_uniform(a.tile_row0[t]); it.rows = (int)lds_uniform(a.tile_rows[t]); it.expert = (int)lds_uniform(a.tile_expert[t]); it.nt0 = (c0 + j % mine) * T::TPW; it.tiles = min(T::TPW, a.NT - it.nt0);
     return true;
   };
   auto sorted_of = [&](const LdsItem& it) __attribute__((always_inline)) { return a.sorted[it.m0 + min(row, it.rows - 1)]; };
@@ -585,10 +586,25 @@ static void launch_expert(hipStream_t st, const GemmStreamArgs& a, uint32_t xbyt
   S2D2_LAUNCH((gemm_expert_kernel<EPI>), dim3(wgs), dim3(LDS_THREADS), LDS_BYTES, st, a, xbytes, (a.NT + LdsTile<EPI, true, true>::TPW - 1) / LdsTile<EPI, true, true>::TPW);
 }
 
-// Half operands in rows, whole stages of 64 columns, 32-bit offsets.
-bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo) {
+static int expert_groups(int features, int per) { return (features / 16 + per - 1) / per; }   // of features, a workgroup's tile each
+// Half operands in rows, whole stages of 64 columns, 32-bit offsets.  Few experts of small matrices and many rows: tiles of 256 x 256 leave most compute units
+// without one.  Drafts of two layers, us, tiled kernel / this one: 2 experts of 2048 x 2048, both chosen, 128 rows 294 / 305, 256 316 / 383, 512 357 / 418; 8 of 1024 x 1024, 2 chosen, 512 rows
+// 292 / 317, 1024 349 / 369; but 8 of 2048 x 2048 256 rows 364 / 362, 1024 527 / 485, and few rows of 2 experts 229 / 217, of 8 195 / 182.  (Where the two are
+// close the tiled kernel is ahead here and there: 32 of 1024 x 1024, 4 chosen, 512 rows 313 / 331, 4 of 2048 x 4096, 1 chosen, up to 8 rows 239 / 248.)
+bool gemm_expert_takes(int experts, int d_model, int d_expert, int rows, int rows_expected, int top_k, int x_lo, int cus) {
   const long long most = std::max((long long)rows * d_model, (long long)rows * top_k * d_expert) * 2;
+  if (experts * expert_groups(d_expert, LdsTile<SEPI_SWIGLU, true, true>::TPW) * 2 < cus && rows_expected * top_k >= 64 * experts) return false;
   return x_lo == LO_F16 && d_model % 64 == 0 && d_expert % 64 == 0 && most < 0xfffff000LL && (long long)((d_expert + 15) / 16) * d_model * 32 < 0xfffff000LL;
+}
+// Slices of the features that the XCDs of a list have between them.  Of few experts, or of the two that one row chooses, whole ones leave XCDs with nothing
+// to do or with twice as much as others.  Drafts of two layers, us, tiled kernel / one slice / four: 4 experts of 4096 x 8192, 2 chosen, 1 row 448 / 518 / 413, 1024 rows 1479 / 2498 / 1275;
+// 8 of 4096 x 14336 1 row 611 / 841 / 582, 512 rows 1722 / 2009 / 1637; 8 of 2048 x 4096 1024 rows 664 / 852 / 650; 12 of 2048 x 1408 482 / 549 / 458.  16 experts and more by the
+// expert: its rows are read on one XCD (64 of 2048 x 1024, four layers, 9 rows 549 / 543, 256 rows 1036 / 1041, verification of 144 rows 844 / 867).
+int gemm_expert_slices(int experts, int d_model, int d_expert) {
+  const int groups = std::min(expert_groups(d_expert, LdsTile<SEPI_SWIGLU, true, true>::TPW), expert_groups(d_model, LdsTile<SEPI_STORE_F32, true, true>::TPW));
+  int s = experts < 16 ? 4 : 1;
+  while (s > groups) s >>= 1;
+  return s;
 }
 void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows) {
   const uint32_t xbytes = (uint32_t)x_rows * (uint32_t)a.ldx * 2u;

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
                                                          const int32_t* __restrict__ choice,
                                                          int32_t* __restrict__ sorted, int32_t* __restrict__ tile_expert,
                                                          int32_t* __restrict__ tile_row0, int32_t* __restrict__ tile_rows,
-                                                         int32_t* __restrict__ n_tiles, int tile_cap, bool xcd_lists) {
+                                                         int32_t* __restrict__ n_tiles, int tile_cap, int lists) {
   __shared__ int s_class[64], s_nt[MOE_MAX_E + 8];
   __shared__ int s_off[MOE_MAX_E], s_tile0[MOE_MAX_E];
   __shared__ int s_cnt[MOE_MAX_E], s_fill[MOE_MAX_E];
@@ -134,11 +134,11 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
         run += c[j];
         t += (c[j] + 127) >> 7;
       }
-    if (tid == 63 && !xcd_lists) *n_tiles = min(ti, tile_cap);
+    if (tid == 63 && lists == 0) *n_tiles = min(ti, tile_cap);
   }
   __syncthreads();
-  if (xcd_lists) {
-    // Experts by falling row count (in classes of 16 rows; in which order within one does not matter) to the XCDs 0 .. 7, 7 .. 0, 0 .. 7: about as
+  if (lists > 0) {
+    // Experts by falling row count (in classes of 16 rows; in which order within one does not matter) to the lists 0 .. L - 1, L - 1 .. 0, 0 .. L - 1: about as
     // many rows each, an expert's tiles next to each other on one of them.  Tiles of up to 256 rows, an expert's all alike.
     // Experts without a row come last, in a class of their own: dealt out among those of up to 15 rows they leave one XCD with five experts where
     // another has one, and a launch takes as long as the fullest.  9 rows (19 to 26 of 64 experts), us a launch, among / behind them: gate / up
@@ -159,14 +159,14 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
       s_class[tid] = at - k;
     }
     __syncthreads();
-    const int rank = tid < E ? atomicAdd(&s_class[cls], 1) : 0, turn = rank >> 3;
-    const int xcd = turn & 1 ? 7 - (rank & 7) : rank & 7;
+    const int rank = tid < E ? atomicAdd(&s_class[cls], 1) : 0, last = lists - 1, turn = rank / lists;   // (lists: a power of two)
+    const int list = turn & 1 ? last - (rank & last) : rank & last;
     if (tid < E) s_nt[rank] = nt;
     __syncthreads();
     if (tid < E) {
-      int t = xcd * tile_cap;
-      for (int k = 0; k < turn; ++k) t += s_nt[8 * k + (k & 1 ? 7 - xcd : xcd)];
-      for (int i = 0; i < nt && t < (xcd + 1) * tile_cap; ++i, ++t) {
+      int t = list * tile_cap;
+      for (int k = 0; k < turn; ++k) t += s_nt[lists * k + (k & 1 ? last - list : list)];
+      for (int i = 0; i < nt && t < (list + 1) * tile_cap; ++i, ++t) {
         tile_expert[t] = tid;
         tile_row0[t] = s_off[tid] + i * per;
         tile_rows[t] = min(per, c - i * per);
@@ -174,11 +174,11 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(int E, int top_k, const
     }
     if (tid < 8) {
       int t = 0;
-      for (int k = 0; 8 * k < E; ++k) {
-        const int r = 8 * k + (k & 1 ? 7 - tid : tid);
+      for (int k = 0; tid < lists && lists * k < E; ++k) {
+        const int r = lists * k + (k & 1 ? last - tid : tid);
         t += r < E ? s_nt[r] : 0;
       }
-      n_tiles[tid] = min(t, tile_cap);
+      n_tiles[tid] = min(t, tile_cap);   // (lists that there are not: none)
     }
   } else {
     for (int e = tid; e < E; e += 1024) {
@@ -251,9 +251,9 @@ void launch_moe_route(hipStream_t st, const float* logits, int E, int top_k, con
 
 void launch_moe_group(hipStream_t st, int E, int top_k, const int32_t* m_count, const int32_t* choice,
                       int32_t* sorted, int32_t* tile_expert, int32_t* tile_row0, int32_t* tile_rows, int32_t* n_tiles,
-                      int tile_cap, bool xcd_lists) {
+                      int tile_cap, int lists) {
   S2D2_LAUNCH(moe_group_kernel, dim3(1), dim3(1024), 0, st, E, top_k, m_count, choice, sorted,
-                     tile_expert, tile_row0, tile_rows, n_tiles, tile_cap, xcd_lists);
+                     tile_expert, tile_row0, tile_rows, n_tiles, tile_cap, lists);
 }
 
 void launch_moe_combine(hipStream_t st, const float* y, int d, int top_k, const int32_t* m_count, int rows_cap,

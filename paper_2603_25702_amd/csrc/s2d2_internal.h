@@ -274,13 +274,13 @@ struct GemmStreamArgs {
   // tile_expert[t]; sorted[s] = token * top_k + slot.  GROUP_GATHER reads X row sorted[s] / top_k and writes
   // row s; GROUP_SCATTER reads X row s and writes row sorted[s], scaled by route_w[sorted[s]].
   int32_t grouped, top_k;
-  const int32_t* n_tiles;   // (gemm_lds.hip: of each of the 8 XCDs, whose tiles start tile_list entries apart)
+  const int32_t* n_tiles;   // (gemm_lds.hip: of each of the 8 / tile_slices lists, whose tiles start tile_list entries apart)
   const int32_t* tile_expert;
   const int32_t* tile_row0;
   const int32_t* tile_rows;
   const int32_t* sorted;
   const float* route_w;
-  int32_t tile_list;
+  int32_t tile_list, tile_slices;   // gemm_lds.hip: XCD x has slice x % tile_slices of the features of list x / tile_slices
   const float* row_rs;      // gemm_lds.hip, GROUP_GATHER: 1/rms of the rows
   size_t expert_stride;     // uint4 elements between the packed matrices of consecutive experts
   // split K of the tile kernel: fp32 partials (64 KB per workgroup) and one arrival counter per tile
@@ -325,7 +325,8 @@ double gemm_tile_us(int kind, const GemmStreamArgs& a, int row_tiles);   // esti
 bool gemm_lds_takes(int kind, const GemmStreamArgs& a);
 double gemm_lds_gateup_us(const GemmStreamArgs& a);   // estimate for gate / up, 1e30 where it cannot run
 void launch_gemm_lds(hipStream_t st, int kind, const GemmStreamArgs& a);
-bool gemm_expert_takes(int d_model, int d_expert, int rows, int top_k, int x_lo);
+bool gemm_expert_takes(int experts, int d_model, int d_expert, int rows, int rows_expected, int top_k, int x_lo, int cus);
+int gemm_expert_slices(int experts, int d_model, int d_expert);   // of the features, by XCD
 void launch_gemm_expert(hipStream_t st, int kind, const GemmStreamArgs& a, int x_rows /* X has at most */);
 
 // moe.hip
@@ -334,7 +335,7 @@ void launch_moe_route(hipStream_t st, const float* logits, int E, int top_k, con
                       float* row_rs /* 1/rms of the rows from their partial sums of squares, may be NULL */);
 void launch_moe_group(hipStream_t st, int E, int top_k, const int32_t* m_count, const int32_t* choice,
                       int32_t* sorted, int32_t* tile_expert, int32_t* tile_row0, int32_t* tile_rows, int32_t* n_tiles,
-                      int tile_cap, bool xcd_lists /* tiles for gemm_lds.hip: of up to 256 rows, a list per XCD, tile_cap entries apart */);
+                      int tile_cap, int lists /* 0: one of tiles of 128 rows; else tiles for gemm_lds.hip, of up to 256 rows, in this many lists tile_cap entries apart */);
 void launch_moe_combine(hipStream_t st, const float* y, int d, int top_k, const int32_t* m_count, int rows_cap,
                         float* h, void* xg, int xg_ld, int xg_lo, const float* gain_next, float* ss, int ss_stride);
 void launch_moe_copy_choices(hipStream_t st, const int32_t* src, int32_t* dst, int layers, int per_layer_src,
