@@ -283,6 +283,7 @@ KvGeom geom(const s2d2_ctx* c, const s2d2_kv_view* kv) {
                 c->desc.n_kv_heads, c->desc.head_dim};
 }
 
+// Bounds of a forward: rows of one window, rows, logit rows of all windows, and the rows the caller expects.
 struct FwdSize { int win, R, LR, hint; };
 // Shape of the wide attention launch: q_tiles 32-row query tiles per window; target key splits of all sequences together,
 // per KV head, fill the chip with workgroups (one per KV head, group of query tiles and split); at most Z of one sequence and run tiles in one; LDS for
@@ -307,9 +308,6 @@ WideShape wide_shape(const s2d2_ctx* c, const s2d2_kv_view* kv, int N, const Fwd
   return w;
 }
 
-// One forward over the planned window rows; K/V of every window row go to k_stage/v_stage
-// ([n_layers, rows_cap, Hkv, D]) if given, else to a one-layer scratch.
-// Bounds of a forward: rows of one window, rows, logit rows of all windows, and the rows the caller expects.
 FwdSize draft_size(int N, int B) { return {2 * B, 2 * N * B, N * B, N * B}; }        // carry + block; a fresh block has B rows
 // carry + 2L; a fresh block has 2 B (more only with carried or pending committed tokens), of a right-shifted model lead + L - 1
 FwdSize verify_size(int N, int B, int shifted) { return {3 * B, 3 * N * B, N * B, (shifted ? 1 : 2) * N * B}; }
@@ -361,7 +359,8 @@ bool fragment_order(const s2d2_model_desc& d, int opm, const FwdSize& sz, const 
   return frag;
 }
 
-// Without logit rows (LR = 0) the forward ends with the K/V of the last layer.
+// One forward over the planned window rows; K/V of every window row go to k_stage/v_stage
+// ([n_layers, rows_cap, Hkv, D]) if given, else to a one-layer scratch.  Without logit rows (LR = 0) it ends with the K/V of the last layer.
 int32_t forward(s2d2_ctx* c, const s2d2_kv_view* kv, int32_t N, const FwdSize& sz, void* k_stage, void* v_stage, float* logits) {
   const s2d2_model_desc& d = c->desc;
   const int dt = d.dtype, R = sz.R, LR = sz.LR, es = elt_size(dt);

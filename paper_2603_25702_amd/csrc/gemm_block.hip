@@ -468,7 +468,8 @@ static int launch_blk_kind(hipStream_t st, const GemmStreamArgs& a, const GemmCh
 // has just written count as well).  Inside forwards, us per launch, this kernel / the tiled one: QKV 8B 256 rows 32 / 44, 512
 // 48 / 54, 4B 22 / 35, 35 / 43, 1.7B 512 rows 22 / 35, MoE 1024 rows 32 / 40; output 8B 23 / 35, 34 / 39, 4B 18 / 29, 27 / 45, 1.7B
 // 14 / 28, MoE 21 / 35; down 8B 56 / 69, 4B 37 / 43, 51 / 68, 1.7B 29 / 35; gate / up 4B 512 rows 71 / 85, 128 rows 34 / 45, 1.7B 128
-// rows 18 / 26, 8B 96 rows 46 / 58, and left to the tiled kernel 8B 256 rows 82 / 73, 512 141 / 109, 4B 256 53 / 46, 1.7B 512 43 / 36.
+// rows 18 / 26, 8B 96 rows 46 / 58, and left to others 8B 256 rows 82 / 73, 512 141 / 109, 4B 256 53 / 46, 1.7B 512 43 / 36 (gate / up of so many rows goes through LDS
+// now, see gemm_lds.hip).
 bool gemm_block_takes(int kind, const GemmStreamArgs& a, int m_cap, GemmChoice& c) {
   if (a.x_lo != LO_F16P || a.coop_wgs < 1 || a.KT % 4 || a.KT < 4 * BLK_NW || a.m_hint <= MID_MOST_ROWS || a.grouped != GROUP_NONE || kind == SEPI_STORE_F32) return false;
   if ((long long)a.NT * a.KT * 1024 >= 1LL << 32 || (long long)(m_cap + 15) / 16 * a.KT * 1024 >= 1LL << 32) return false;   // (32-bit offsets)

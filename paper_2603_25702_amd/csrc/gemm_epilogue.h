@@ -1,5 +1,5 @@
-// Epilogue of the packed-weight GEMMs on one 16 x 16 accumulator in MFMA register order, shared by the tiled and the
-// mid-size kernel.
+// Epilogue of the packed-weight GEMMs on one 16 x 16 accumulator in MFMA register order, shared by the tiled, the
+// mid-size and the block kernels and those through LDS.
 #pragma once
 #include "s2d2_internal.h"
 

@@ -56,6 +56,25 @@ __device__ __forceinline__ void lds_each(const F& f) {
     lds_each<I + 1, N>(f);
   }
 }
+// Sum of squares of a row from its producer's partial sums, by the two lanes sub = 0 and 1.
+__device__ __forceinline__ float lds_row_squares(const GemmStreamArgs& a, int row, int sub) {
+  const float* pp = a.ss_part + (size_t)row * a.ss_stride;
+  float v = 0.f;
+  if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
+    const int n4 = a.ss_count >> 2;
+    for (int i0 = sub; i0 < n4; i0 += 16) {
+      float4 t[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = ((const float4*)pp)[min(i0 + 2 * j, n4 - 1)];   // clamped duplicates are skipped when summing
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (i0 + 2 * j < n4) v += (t[j].x + t[j].y) + (t[j].z + t[j].w);
+    }
+  } else {
+    for (int i = sub; i < a.ss_count; i += 2) v += pp[i];
+  }
+  return v + __shfl_xor(v, 1, 64);
+}
 // A value that is the same in all lanes, in a scalar register for certain (a request's operands have to be).
 __device__ __forceinline__ uint32_t lds_uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 // 64 lanes x 16 bytes from memory to LDS at `at` + 16 lane
@@ -326,22 +345,7 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_kernel(const GemmStre
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       LdsPlaces p;
       T::first(a, p, xbytes, it, s_src, lds0, wave, lane);
-      const float* pp = a.ss_part + (size_t)src * a.ss_stride;
-      float v = 0.f;
-      if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
-        const int n4 = a.ss_count >> 2;
-        for (int i0 = sub; i0 < n4; i0 += 16) {
-          float4 t[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) t[j] = ((const float4*)pp)[min(i0 + 2 * j, n4 - 1)];   // clamped duplicates are skipped when summing
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (i0 + 2 * j < n4) v += (t[j].x + t[j].y) + (t[j].z + t[j].w);
-        }
-      } else {
-        for (int i = sub; i < a.ss_count; i += 2) v += pp[i];
-      }
-      v += __shfl_xor(v, 1, 64);
+      const float v = lds_row_squares(a, src, sub);
       if (sub == 0) s_rs[r] = 1.0f / sqrtf(v / (float)a.K + a.eps);   // (read behind the K loop's barriers)
       for (;;) {
         LdsItem nx = it;
@@ -427,22 +431,7 @@ __device__ __forceinline__ void lds_gateup_body(const GemmStreamArgs& a, const i
     });
     {   // 1/rms of the rows from the producer's partial sums of squares
       const int r = tid >> 1, sub = tid & 1;
-      const float* pp = a.ss_part + (size_t)min(m0 + r, M - 1) * a.ss_stride;
-      float v = 0.f;
-      if ((a.ss_count & 3) == 0 && (a.ss_stride & 3) == 0) {
-        const int n4 = a.ss_count >> 2;
-        for (int i0 = sub; i0 < n4; i0 += 16) {
-          float4 t[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) t[j] = ((const float4*)pp)[min(i0 + 2 * j, n4 - 1)];   // clamped duplicates are skipped when summing
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (i0 + 2 * j < n4) v += (t[j].x + t[j].y) + (t[j].z + t[j].w);
-        }
-      } else {
-        for (int i = sub; i < a.ss_count; i += 2) v += pp[i];
-      }
-      v += __shfl_xor(v, 1, 64);
+      const float v = lds_row_squares(a, min(m0 + r, M - 1), sub);
       if (r < RB * 16 && sub == 0) s_rs[r] = 1.0f / sqrtf(v / (float)a.K + a.eps);
     }
     f32x4_t acc[RBW][TW];
