@@ -28,16 +28,16 @@ HEADLINE, OTHERS = 4, (2, 3, 5)
 # step, from the FETCH_SIZE / WRITE_SIZE counter runs summarised under profiles/ (rocprofv3 --pmc on this file with
 # the default operand mode; a plain copy of 1 GiB reads FETCH_SIZE = 524300 KiB and WRITE_SIZE = 1048576 KiB, so
 # bytes = FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024).  Averages over all GEMM launches of two steps.
-GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31341466, 3: 68667904, 4: 176668058, 5: 332862362}
+GEMM_TRAFFIC_BYTES_PER_LAUNCH = {2: 31341261, 3: 68674458, 4: 157912883, 5: 260249395}
 STEP_TRAFFIC_BYTES = {   # all kernels of a step: (FETCH_SIZE KiB * 2048 + WRITE_SIZE KiB * 1024) summed over the step's launches
-    2: 5124087.0 * 2048 + 102235.0 * 1024,
-    3: 13411563.4 * 2048 + 2069252.6 * 1024,
-    4: 43162695.2 * 2048 + 5729250.4 * 1024,
-    5: 36385626.8 * 2048 + 8573887.3 * 1024,
+    2: 5124189.2 * 2048 + 102260.0 * 1024,
+    3: 12858390.1 * 2048 + 1635548.6 * 1024,
+    4: 40559979.8 * 2048 + 4853581.2 * 1024,
+    5: 29883139.8 * 2048 + 9234378.9 * 1024,
 }
-# The kernel with most of a configuration's GEMM time (config 3: all but the unembedding, 5.7 of 6.0 ms; config 4: gate / up and the
-# draft's down projection, 10.1 of 17.0 ms)
-GEMM_KERNEL = {2: "gemm_stream_kernel", 3: "gemm_block_kernel", 4: "gemm_tile_kernel", 5: "gemm_tile_kernel"}
+# The kernel with most of a configuration's GEMM time (config 3: all but the unembedding, 5.7 of 6.0 ms; config 4: QKV, output and the draft's
+# down projection, 7.0 of 15.9 ms, with 5.6 of gate / up in gemm_lds_gateup_kernel; config 5: 8.4 of 12.5)
+GEMM_KERNEL = {2: "gemm_stream_kernel", 3: "gemm_block_kernel", 4: "gemm_block_kernel", 5: "gemm_expert_kernel"}
 
 
 def log(*a):

@@ -9,13 +9,13 @@
 //
 // What bounds it: a compute unit's requests are answered in order, about 400 lines a microsecond while the weights come from memory, whatever is in
 // flight; and all weights together at 6 to 7 TB/s.  (Bringing lines into L2 ahead of time takes the same places in that order: slower.)
-// The tiled kernel asks for 1.5 times the lines, and for the weights of an expert with 130 rows twice.  64 experts of 2048 x 1024, us per launch, tiled
+// The tiled kernel asks for 1.5 times the lines, and for the weights of an expert with 130 rows twice.  64 experts of 2048 x 1024, launches alone, us, tiled
 // kernel / this one: gate / up, 18 rows an expert on average 103 / 81 (6.6 TB/s), 64 rows 110 / 89, 128 rows 131 / 110, the most chosen with
-// 700 144 / 135; down 72 / 47, 89 / 56, 108 / 68, 108 / 80.
+// 700 144 / 135; down 72 / 47, 89 / 56, 108 / 68, 108 / 80.  Inside the draft of 32 sequences of 32, 128 rows an expert on average, this kernel takes 121 to 126 and 76 to 78.
 //
 // One workgroup per compute unit takes tile after tile: XCD x those of the experts that moe_group_kernel gave it (of a slice of their features, where there are few experts), the largest
 // first and in alternating order, so that a workgroup's tiles add up to about the same rows.  The first requests of a workgroup's next tile are made ahead of
-// the stores of the present one (in launches of a workgroup per tile 129 and 76 us for 122 and 70 at 128 rows).
+// the stores of the present one (launches of a workgroup per tile take 6 to 7 us longer at 128 rows).
 #include "gemm_epilogue.h"
 #include "../../include/s2d2.h"
 
@@ -317,7 +317,8 @@ __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_expert_kernel(const GemmS
 // TPW tiles.  us per launch, gemm_mid.hip (up to 64 rows) or the tiled kernel / this one: 1.7B 17 rows 119 / 106, 35 130 / 114, 96 183 / 130, 512
 // 501 / 380; 4B 64 191 / 150 (5.4 TB/s with what is stored), 128 209 / 171, 256 285 / 265; 8B 32 247 / 219, 256 444 / 424, 512 817 / 708.  Up to 16 rows
 // the streaming kernel is the faster one (1.7B, 12 rows, 95 / 103).  From 256 rows on the matrix pipes at the board's power limit bound it: without its
-// requests, 256 rows of 8B take 309 us, without its products 297, without its stores 347.
+// requests, 256 rows of 8B take 309 us, without its products 297, without its stores 347.  (X in rows, for models too small for fragment order: two or three registers a lane go to scratch;
+// forwards of one layer, before this kernel / now: 512 columns, 151936 features, 64 rows 123 / 106, 512 350 / 297, 256 columns, 32000 features, 64 rows 96 / 89.)
 template <bool ROWS, bool STREAM>
 __global__ __launch_bounds__(LDS_THREADS, 2) void gemm_lds_kernel(const GemmStreamArgs a, const uint32_t xbytes) {
   using T = LdsTile<SEPI_STORE_F32, ROWS, STREAM>;
